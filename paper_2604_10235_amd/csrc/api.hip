@@ -165,6 +165,7 @@ int make_plan(const codecomp_params* p, Plan* pl) {
   // the cut; per (layer*head, request) what the parts agreed on.  The keys near the cut reuse the raw attention mass
   // (dead once the scores exist): one 32-bit word per token and layer*head, exactly its size.
   pl->sel_parts = 0;
+  pl->by_parts = max_n - p->window > kSelectMaxCandidates;
   const int max_npre = max_n - p->window;
   if (max_npre > kSelectMaxCandidates || (max_npre >= kPartMinCandidates && LH * (size_t)p->n_seqs < (size_t)kPartFewProblems)) {
     int64_t parts = 0;
@@ -181,6 +182,20 @@ int make_plan(const codecomp_params* p, Plan* pl) {
   }
   pl->ws_bytes = off;
   return CODECOMP_OK;
+}
+
+int launch_compress(const Plan& pl, const void* q, const void* k, const void* v, const float* prior, float* scores, int32_t* idx,
+                    void* k_out, void* v_out, void* workspace, hipStream_t stream) {
+  if (fused_tail(pl)) {
+    if (int rc = launch_score(pl, q, k, prior, scores, workspace, stream, CODECOMP_STAGE_ALL & ~CODECOMP_STAGE_FINISH)) return rc;
+    if (int rc = launch_finish_select(pl, prior, scores, idx, workspace, stream)) return rc;
+  } else {
+    if (int rc = launch_score(pl, q, k, prior, scores, workspace, stream)) return rc;
+    const int rc = pl.select_mode == CODECOMP_SELECT_TWO_STAGE ? launch_select_two_stage(pl, scores, prior, idx, workspace, stream)
+                                                               : launch_select(pl, scores, idx, workspace, stream);
+    if (rc) return rc;
+  }
+  return launch_gather(pl, k, v, idx, k_out, v_out, stream);
 }
 
 static int check_ws(const Plan& pl, const void* ws, size_t bytes) {
@@ -279,14 +294,7 @@ int codecomp_compress(const void* q_obs, const void* k, const void* v, const flo
   if (misaligned16(q_obs) || misaligned16(k) || misaligned16(v) || misaligned16(k_out) || misaligned16(v_out))
     return CODECOMP_EINVAL_SHAPE;
   if (int rc = check_ws(pl, workspace, workspace_bytes)) return rc;
-  hipStream_t s = (hipStream_t)hip_stream;
-  if (int rc = launch_score(pl, q_obs, k, prior, scores, workspace, s)) return rc;
-  if (pl.select_mode == CODECOMP_SELECT_TWO_STAGE) {
-    if (int rc = launch_select_two_stage(pl, scores, prior, idx, workspace, s)) return rc;
-  } else {
-    if (int rc = launch_select(pl, scores, idx, workspace, s)) return rc;
-  }
-  return launch_gather(pl, k, v, idx, k_out, v_out, s);
+  return launch_compress(pl, q_obs, k, v, prior, scores, idx, k_out, v_out, workspace, (hipStream_t)hip_stream);
 }
 
 const char* codecomp_status_string(int status) {

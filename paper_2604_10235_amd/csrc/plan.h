@@ -14,10 +14,7 @@ constexpr int kTileKeys = 64;         // keys staged through LDS per pipeline st
 constexpr int kMaxScoreGrid = 2048;   // most workgroups a score pass is launched with
 constexpr int kMinTilesPerWorkgroup = 4;
 constexpr int kLeadTiles = 4;         // a segment start (query fragments, first K tile) costs about this many tiles
-constexpr int kSelectThreads = 1024;  // one workgroup per (layer, head, request) in select, for short requests
-constexpr int kSelectSmallThreads = 256;    // ... and in batches of many requests of at most 256 x 16 candidates
-constexpr int kSelectSmallMaxItems = 16;
-constexpr int kSelectSmallProblems = 1024;  // problems from which on the small workgroups are used
+constexpr int kSelectManyProblems = 512;    // (layer, head, request) problems from which on several selection workgroups share a compute unit
 // Longer requests are selected by several workgroups each: parts of kPartChunk candidates, one 256-thread workgroup
 // per part and step (first-digit counts, the candidates near the cut, the ordered output; between the last two one
 // workgroup per request finishes the radix select on those candidates).
@@ -25,9 +22,13 @@ constexpr int kPartThreads = 256;
 constexpr int kPartItems = 32;                             // candidates a thread holds
 constexpr int kPartChunk = kPartThreads * kPartItems;      // candidates per part
 constexpr int kSelectMaxCandidates = 65536;                // most candidates one workgroup keeps in registers (64 per thread)
-constexpr int kPartMinCandidates = 16384;                  // few problems: parts are used from this many candidates on
-constexpr int kPartFewProblems = 100;                      // (layer, head, request) problems below which one workgroup each leaves the device idle
+// (Batches of few problems also get the parts' workspace from this many candidates on; they no longer use it: one workgroup
+// per problem is quicker up to kSelectMaxCandidates.)
+constexpr int kPartMinCandidates = 16384;
+constexpr int kPartFewProblems = 100;
 constexpr int kFirstDigitBins = 2048;
+constexpr int kFinishHalo = 512;      // largest supported (pool_kernel - 1) / 2
+constexpr int kSmallHalo = 32;        // ... by the 256-thread workgroups of the fused tail
 
 struct Plan {
   int L, Hq, Hkv, G, d, W, pool, n_seqs;
@@ -61,6 +62,7 @@ struct Plan {
   // workspace layout (byte offsets, each 256-byte aligned)
   size_t off_stats, off_lse, off_uraw, off_member, off_member_count, ws_bytes;
   // selection by parts (0 parts: one workgroup per request does it all)
+  bool by_parts;             // the selection runs by parts
   int sel_parts;             // sum over requests of max(1, ceil((N_r - W) / kPartChunk))
   size_t off_part_hist, off_part_sure, off_part_head, off_part_before;
 };
@@ -71,11 +73,31 @@ void assign_row_blocks(Plan* plan);
 // Validates `p` and fills `plan`.  Returns 0 or a CODECOMP_E* code.  Host only, no HIP calls.
 int make_plan(const codecomp_params* p, Plan* plan);
 
+// Tail of the score step: pooling and the prior.
+struct FinishArgs {
+  const float* uraw;
+  const float* prior;
+  const int32_t* cu_seqlens;
+  float* scores;
+  int n_seqs, T, LH, row_splits, pool;
+  int mass_trim;      // window positions at the end of every request that hold no attention mass (prefix-only softmax)
+  int pool_trim;      // window positions at the end of every request that pooling leaves out (prefix-only pooling)
+  int pool_max;       // 1: max pooling
+  float lambda, inv_pool;
+};
+FinishArgs finish_args(const Plan& pl, const float* prior, float* scores, void* workspace);
+
 int launch_score(const Plan& pl, const void* q, const void* k, const float* prior, float* scores,
                  void* workspace, hipStream_t stream, unsigned stages = CODECOMP_STAGE_ALL);
 int launch_select(const Plan& pl, const float* scores, int32_t* idx, void* workspace, hipStream_t stream);
 int launch_select_two_stage(const Plan& pl, const float* scores, const float* prior, int32_t* idx, void* workspace,
                             hipStream_t stream);
+// Score, select and gather in one go: the enqueue order behind codecomp_compress.
+int launch_compress(const Plan& pl, const void* q, const void* k, const void* v, const float* prior, float* scores, int32_t* idx,
+                    void* k_out, void* v_out, void* workspace, hipStream_t stream);
+// Pooling, prior and selection of requests that one workgroup each can take (fused_tail says whether these parameters can).
+bool fused_tail(const Plan& pl);
+int launch_finish_select(const Plan& pl, const float* prior, float* scores, int32_t* idx, void* workspace, hipStream_t stream);
 int launch_gather(const Plan& pl, const void* k, const void* v, const int32_t* idx, void* k_out, void* v_out,
                   hipStream_t stream);
 

@@ -55,20 +55,7 @@ __global__ __launch_bounds__(256) void score_merge_kernel(ScoreArgs a) {
   }
 }
 
-struct FinishArgs {
-  const float* uraw;
-  const float* prior;
-  const int32_t* cu_seqlens;
-  float* scores;
-  int n_seqs, T, LH, row_splits, pool;
-  int mass_trim;      // window positions at the end of every request that hold no attention mass (prefix-only softmax)
-  int pool_trim;      // window positions at the end of every request that pooling leaves out (prefix-only pooling)
-  int pool_max;       // 1: max pooling
-  float lambda, inv_pool;
-};
-
 constexpr int kFinishTile = 2048;     // tokens per workgroup of the finish kernel (one round of workgroups at the bench size)
-constexpr int kFinishHalo = 512;      // largest supported (pool_kernel - 1) / 2
 
 __device__ __forceinline__ int request_of(const int32_t* cu, int n_seqs, int j) {
   int lo = 0, hi = n_seqs;              // cu[lo] <= j < cu[lo+1]
@@ -166,6 +153,18 @@ __global__ __launch_bounds__(256) void score_finish_kernel(FinishArgs a) {
   }
 }
 
+FinishArgs finish_args(const Plan& pl, const float* prior, float* scores, void* workspace) {
+  FinishArgs f;
+  f.uraw = reinterpret_cast<const float*>(static_cast<char*>(workspace) + pl.off_uraw);
+  f.prior = prior; f.cu_seqlens = pl.cu_seqlens_dev; f.scores = scores;
+  f.n_seqs = pl.n_seqs; f.T = pl.T; f.LH = pl.L * pl.Hkv; f.row_splits = pl.row_splits; f.pool = pl.pool;
+  f.lambda = pl.lambda; f.inv_pool = 1.0f / (float)pl.pool;
+  f.mass_trim = pl.key_trim;
+  f.pool_trim = (pl.variant & CODECOMP_VARIANT_POOL_PREFIX) ? pl.W : 0;
+  f.pool_max = (pl.variant & CODECOMP_VARIANT_POOL_MAX) ? 1 : 0;
+  return f;
+}
+
 int launch_row_merge(const Plan& pl, const ScoreArgs& a, hipStream_t stream) {
   const bool many = (int64_t)pl.n_seqs * pl.L * pl.Hkv >= 2048;     // enough workgroups for the device as it is
   const dim3 mgrid(many ? 1 : (a.lrows + 255) / 256, pl.n_seqs, pl.L * pl.Hkv);
@@ -203,13 +202,7 @@ int launch_score(const Plan& pl, const void* q, const void* k, const float* prio
   if (rc) return rc;
   if (!(stages & CODECOMP_STAGE_FINISH)) return 0;
 
-  FinishArgs f;
-  f.uraw = a.uraw; f.prior = prior; f.cu_seqlens = pl.cu_seqlens_dev; f.scores = scores;
-  f.n_seqs = pl.n_seqs; f.T = pl.T; f.LH = pl.L * pl.Hkv; f.row_splits = pl.row_splits; f.pool = pl.pool;
-  f.lambda = pl.lambda; f.inv_pool = 1.0f / (float)pl.pool;
-  f.mass_trim = pl.key_trim;
-  f.pool_trim = (pl.variant & CODECOMP_VARIANT_POOL_PREFIX) ? pl.W : 0;
-  f.pool_max = (pl.variant & CODECOMP_VARIANT_POOL_MAX) ? 1 : 0;
+  const FinishArgs f = finish_args(pl, prior, scores, workspace);
   score_finish_kernel<<<dim3((pl.T + kFinishTile - 1) / kFinishTile, pl.L * pl.Hkv), dim3(256), 0, stream>>>(f);
   if (hipError_t e = hipGetLastError()) return (int)e;
   return 0;

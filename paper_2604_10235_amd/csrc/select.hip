@@ -2,20 +2,21 @@
 // of the prefix [0, N - W); equal scores go to the lower index; indices come out ascending
 // (section "Attention-based KV Cache Compression": the best-scored context tokens are kept until the budget is used up).
 //
-// An MSB-first radix select over order-preserving integer images of the float scores (digits of 11, 11
-// and 10 bits, LDS histograms) finds the score of the last admitted token and how many tokens tied at
-// that score are admitted; one ordered pass (prefix sums of "sure" and "tied" flags) then writes the
-// indices already sorted.  No float is ever added, nothing depends on the order in which workgroups run:
-// the result is the same bits on every call.
+// Counting rounds over order-preserving integer images of the float scores (LDS histograms) find the score of the last
+// admitted token and how many tokens tied at that score are admitted; one ordered pass (prefix sums of "sure" and
+// "tied" flags) then writes the indices already sorted.  No float is ever added, nothing depends on the order in which
+// workgroups run: the result is the same bits on every call.
 //
-// Requests of at most 65536 candidates in a batch with enough problems to occupy the device: one workgroup
-// of 1024 threads (256 threads when all requests are short and there are a thousand problems or more) owns one
-// (layer, head, request) problem; the candidates are read from memory once, all loads in flight together, and
-// stay in registers through the three digit passes and the ordered pass.
-// A batch with a longer request, or with few problems and long requests: every request is cut into parts
-// of 8192 candidates and four kernels run one 256-thread workgroup per part (the third one per request),
-// so that a problem is spread over as many compute units as it has parts and a ragged batch is not paced
-// by its longest request:
+// Requests of at most 65536 candidates: one workgroup owns one (layer, head, request) problem; the candidates are read from
+// memory once, all loads in flight together, and stay in registers until the indices are out.  In the fused call that
+// workgroup also does the tail of the score step (finish_select_kernel).
+// What bounds it is instruction issue and barriers of the one compute unit that works on a problem, so: few rounds, ballots
+// instead of shuffles, register-to-register prefix sums, 16-byte loads and stores through buffer descriptors.  Measured
+// (kernel times, the separate pooling kernel + the three-digit radix selection of 1024 threads before -> now): 2048 tokens
+// x 4 problems 17.7 -> 4.6 us; 8192 x 8: 21.4 -> 7.7; 32768 x 112: 46.6 -> 26.4; 65536 x 256: 147 -> 69; sixteen requests
+// of 8K .. 48K x 4 (by parts before): 67 -> 34; 64 requests of 128 .. 2300 x 112: 130 -> 31 us.
+// A batch with a longer request: every request is cut into parts of 8192 candidates and four kernels run one 256-thread
+// workgroup per part (the third one per request), so that a problem is spread over as many compute units as it has parts:
 //   counts  every part counts the first digit of its candidates (2048 bins) and stores the counts;
 //   near    every part adds up the counts of its request, finds the bin that holds the cut, and appends its
 //           candidates of that bin (keys only, in token order) to the request's list, at the place the
@@ -34,242 +35,293 @@
 //                binary prior is the paper's rule for an overfull protected set: its first tokens),
 //                Bp = B - W; stage 2 fills the remaining Bp - |P| slots with the best pooled-attention
 //                tokens not in P.
+#include <type_traits>
+
 #include "plan.h"
 
 namespace codecomp {
 
-// Monotone map float -> uint32 (larger float <=> larger key); -0 and +0 share a key.
+constexpr uint32_t kForced = 0xFFFFFFFFu;      // key of a candidate that is admitted whatever the cut; 0: no candidate
+
+// Monotone map float -> uint32 (larger float <=> larger key); -0 and +0 share a key.  Strictly between 0 and kForced,
+// also for NaN.
 __device__ __forceinline__ uint32_t order_key(float x) {
   x = x + 0.0f;   // -0 -> +0
   const uint32_t u = __float_as_uint(x);
-  return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
+  const uint32_t key = u ^ ((uint32_t)((int32_t)u >> 31) | 0x80000000u);      // negative: all bits flipped, else the sign bit set
+  return min(max(key, 1u), kForced - 1u);
 }
 
-constexpr int kSelTileItems = 4;    // consecutive candidates per thread inside one ordered tile
-constexpr int kHistStride = 2049;   // odd stride: equal bins of different copies sit in different banks
+// ---------------------------------------------------------------------------------------------------------
+// One workgroup per problem.
+// ---------------------------------------------------------------------------------------------------------
 
-// The one-workgroup kernels come in two sizes.  NT = 1024 threads, up to 64 candidates per thread, 8 private copies of
-// the first-digit histogram (130 KB of LDS: one workgroup per compute unit) for long requests; NT = 256 threads, up to
-// 16 candidates per thread, 2 copies (21 KB: seven workgroups per compute unit) for batches of many short requests,
-// where what counts is how many problems a compute unit works on at once (measured on 7168 problems of 14 .. 2185
-// candidates: 270 us with the large workgroups, 132 / 105 / 108 us with the small ones and 4 / 2 / 1 copies; from
-// 8192 candidates per problem on the large ones are faster).
-template <int NT> struct SelectSize {
-  static constexpr int kMaxItems = NT == kSelectThreads ? kSelectMaxCandidates / kSelectThreads : kSelectSmallMaxItems;
-  static constexpr int kCopies = NT == kSelectThreads ? 8 : 2;     // picked by lane % kCopies
-};
+constexpr int kCutBins = 2048;      // bins of one counting round
+constexpr int kCutList = 128;       // keys left to rank by comparing them with one another
 
+// Slot s of thread tid holds candidate j = (s / 4) * 4 * NT + 4 * tid + s % 4: four consecutive candidates per thread and
+// "quad" q = s / 4, the 256 candidates of a wave and quad consecutive too.
 template <int NT> struct SelectShared {
-  unsigned int hist[SelectSize<NT>::kCopies * kHistStride];
-  unsigned int prefix, need;
-  int wave_sure[NT / 64], wave_tie[NT / 64];
-  int tile_sure, tile_tie;
-  // class (0 out, 1 tied at the cut, 2 in) of every register-resident candidate, one byte each, indexed by
-  // candidate: written in the load layout, read back as runs of consecutive candidates per thread
-  unsigned int cls_words[NT * SelectSize<NT>::kMaxItems / 4];
+  alignas(16) unsigned int hist[kCutBins];
+  alignas(16) unsigned int list[kCutList];
+  unsigned int list_n;
+  unsigned int pick[3];
+  alignas(16) unsigned int wave_a[NT / 64], wave_b[NT / 64];
+  unsigned int chunk[NT / 4];       // per run of 256 consecutive candidates: admitted | tied << 16 (at most 16 quads)
 };
 
-// One candidate into the digit histogram.  CROWDED (the first digit: every candidate takes part and the scores
-// crowd into a few dozen bins): LDS atomics of one instruction that hit the same address are served one after
-// the other, so each lane adds to one of several private copies (lane % copies) and fewer lanes can collide;
-// the copies are summed when the bin is picked.  Ballot-based aggregation was tried first: its serial
-// scalar/vector control flow cost about 1000 cycles per candidate slot and workgroup.  Later digits: only the
-// few candidates that share the prefix take part, one copy.
-template <bool CROWDED, int NT>
-__device__ __forceinline__ void hist_add(SelectShared<NT>& sh, bool match, uint32_t bin) {
-  if (match) atomicAdd(&sh.hist[(CROWDED ? (threadIdx.x & (SelectSize<NT>::kCopies - 1)) * kHistStride : 0) + bin], 1u);
+// Rows are read and written through buffer descriptors: an access past `n` elements reads 0 and writes nothing, so that no
+// index is clamped or compared and all loads of a thread are in flight together.
+typedef __amdgpu_buffer_rsrc_t rsrc_t;
+template <class T>
+__device__ __forceinline__ rsrc_t row_of(const T* p, int n) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(static_cast<const void*>(p)), (short)0, max(n, 0) * (int)sizeof(T), 0x00020000);
+}
+__device__ __forceinline__ float4 row_f32x4(rsrc_t r, int lane_byte, int wave_byte) {
+  return __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(r, lane_byte, wave_byte, 0));
 }
 
-__device__ __forceinline__ int pass_shift(int pass) { return pass == 0 ? 21 : (pass == 1 ? 10 : 0); }
-__device__ __forceinline__ int pass_bins(int pass) { return pass == 2 ? 1024 : 2048; }
-__device__ __forceinline__ uint32_t pass_himask(int pass) {
-  return pass == 0 ? 0u : (0xFFFFFFFFu << (pass == 1 ? 21 : 10));
+// Prefix operations over the 64 lanes of a wave in six register-to-register steps (row shifts, then the last lane of a
+// row of 16 and of the lower half broadcast upwards).
+template <class Op>
+__device__ __forceinline__ uint32_t wave_scan(uint32_t x, Op op) {
+#define CODECOMP_DPP(CTRL, ROWS) \
+  x = op(x, (uint32_t)__builtin_amdgcn_update_dpp((int)Op::kIdentity, (int)x, CTRL, ROWS, 0xf, false));
+  CODECOMP_DPP(0x111, 0xf) CODECOMP_DPP(0x112, 0xf) CODECOMP_DPP(0x114, 0xf) CODECOMP_DPP(0x118, 0xf)
+  CODECOMP_DPP(0x142, 0xa) CODECOMP_DPP(0x143, 0xc)
+#undef CODECOMP_DPP
+  return x;                         // lane i: op over lanes 0 .. i
+}
+struct OpAdd { static constexpr uint32_t kIdentity = 0u; __device__ uint32_t operator()(uint32_t a, uint32_t b) const { return a + b; } };
+struct OpMin { static constexpr uint32_t kIdentity = ~0u; __device__ uint32_t operator()(uint32_t a, uint32_t b) const { return min(a, b); } };
+struct OpMax { static constexpr uint32_t kIdentity = 0u; __device__ uint32_t operator()(uint32_t a, uint32_t b) const { return max(a, b); } };
+__device__ __forceinline__ uint32_t last_lane(uint32_t x) { return (uint32_t)__builtin_amdgcn_readlane((int)x, 63); }
+
+// op over the values that waves first .. last - 1 left in `of`; the same in every lane.
+template <int NW, class Op>
+__device__ __forceinline__ uint32_t over_waves(const unsigned int (&of)[NW], int first, int last, Op op) {
+  uint32_t x = Op::kIdentity;
+  if constexpr (NW <= 4) {
+#pragma unroll
+    for (int w = 0; w < NW; ++w) { const uint32_t o = of[w]; x = w >= first && w < last ? op(x, o) : x; }
+    return (uint32_t)__builtin_amdgcn_readfirstlane((int)x);
+  } else {
+    const int lane = threadIdx.x & 63;
+    if (lane < NW && lane >= first && lane < last) x = of[lane];
+    return last_lane(wave_scan(x, op));
+  }
 }
 
-template <int NT>
-__device__ __forceinline__ void hist_clear(SelectShared<NT>& sh, int nbins, int copies) {
-  for (int b = threadIdx.x; b < (copies - 1) * kHistStride + nbins; b += NT) sh.hist[b] = 0;
-  __syncthreads();
-}
-
-// After a digit pass: the bin holding the `remaining`-th largest candidate; fixes that digit in `prefix`
-// and reduces `remaining` to the rank inside the bin.  All threads call it.  No step waits for an LDS
-// read that depends on the previous one: the copies are summed by all threads, wave 0 finds the lane whose
-// group of bins holds the rank (suffix sums over lanes), then the bin inside that group the same way.
-template <int NT>
-__device__ __forceinline__ void hist_pick(SelectShared<NT>& sh, int nbins, int copies, int shift, uint32_t& prefix,
-                                          uint32_t& remaining) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  __syncthreads();
-  if (copies > 1) {                    // totals of the private copies into copy 0 (a thread touches only its own bins)
-    for (int b = threadIdx.x; b < nbins; b += NT) {
-      unsigned int c = 0;
-      for (int k = 0; k < copies; ++k) c += sh.hist[k * kHistStride + b];
-      sh.hist[b] = c;
+// Runs body(s) for the slots in use, four at a time (a slot past them holds key 0, which nothing counts).
+template <int ITEMS, class Body>
+__device__ __forceinline__ void for_slots(int slots, Body body) {
+  static_assert(ITEMS % 4 == 0, "groups of four slots");
+#pragma unroll
+  for (int g = 0; g < ITEMS; g += 4)
+    if (g < slots) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) body(g + e);
     }
+}
+
+template <int NT>
+__device__ __forceinline__ void hist_clear(SelectShared<NT>& sh) {
+#pragma unroll
+  for (int b = 0; b < kCutBins; b += NT) sh.hist[b + threadIdx.x] = 0;
+}
+
+// The bin that holds the `rank`-th largest counted key, its rank inside that bin and the bin's count (0: fewer than `rank`
+// keys are counted).  Every thread sums its bins, prefix sums over lanes and waves find the one thread whose bins hold
+// the rank.  All threads call it, behind a barrier after the last count.
+template <int NT>
+__device__ __forceinline__ void pick_bin(SelectShared<NT>& sh, uint32_t rank, uint32_t& bin, uint32_t& rank_in_bin, int& count) {
+  constexpr int NW = NT / 64, PER = kCutBins / NT;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  unsigned int own[PER], mine = 0;
+#pragma unroll
+  for (int i = 0; i < PER; ++i) { own[i] = sh.hist[tid * PER + i]; mine += own[i]; }
+  const unsigned int incl = wave_scan(mine, OpAdd{}), total = last_lane(incl);
+  if (lane == 0) sh.wave_a[wave] = total;
+  if (tid == 0) sh.pick[2] = 0;                   // everyone has read the last pick: a barrier lies between
+  __syncthreads();
+  unsigned int higher = over_waves<NW>(sh.wave_a, wave + 1, NW, OpAdd{}) + total - incl;     // keys in the bins of higher waves and threads
+  if (higher < rank && rank <= higher + mine) {
+#pragma unroll
+    for (int i = PER - 1; i >= 0; --i) {
+      if (higher < rank && rank <= higher + own[i]) {
+        sh.pick[0] = (unsigned int)(tid * PER + i); sh.pick[1] = rank - higher; sh.pick[2] = own[i];
+      }
+      higher += own[i];
+    }
+  }
+  __syncthreads();
+  bin = (uint32_t)__builtin_amdgcn_readfirstlane((int)sh.pick[0]);
+  rank_in_bin = (uint32_t)__builtin_amdgcn_readfirstlane((int)sh.pick[1]);
+  count = __builtin_amdgcn_readfirstlane((int)sh.pick[2]);
+}
+
+// The `need`-th largest competing key (1 <= need <= competing) and how many keys tied at it are admitted.  A thread
+// holds keys[s], s < slots; 0 = no candidate, kForced = admitted whatever the cut, anything between competes.
+//
+// Counting rounds over the range [lo, hi] the cut is known to lie in, 2048 equal bins wide: the first range is that
+// of the keys themselves (smallest to largest), so that the bins follow the scores wherever these sit; a fixed first digit
+// (sign, exponent and two mantissa bits) put all of them into a few dozen bins, whose LDS atomics then wait for one another.
+// The bin of the cut usually holds a handful of keys after one round: at most 128 are ranked by comparing all with all.
+// From 16 candidates per thread on, the first round counts every eighth slot first and takes from that sample a bin that
+// is almost surely below the cut: of the other slots only the keys from that bin up are counted (an LDS atomic
+// costs by the number of lanes that take part).  Should the sample have misled, the rest is counted after all.
+template <int NT, int ITEMS>
+__device__ __forceinline__ void find_cut(SelectShared<NT>& sh, const uint32_t (&keys)[ITEMS], int slots, int competing, uint32_t need,
+                                         uint32_t& tau, int& ties) {
+  constexpr int NW = NT / 64;
+  constexpr int kSampleEvery = 8;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  uint32_t mn = 0xFFFFFFFFu, mx = 0u;                 // of key - 1 and key + 1: both kinds of non-competing keys drop out
+  for_slots<ITEMS>(slots, [&](int s) { mn = min(mn, keys[s] - 1u); mx = max(mx, keys[s] + 1u); });
+  mn = last_lane(wave_scan(mn, OpMin{}));
+  mx = last_lane(wave_scan(mx, OpMax{}));
+  if (lane == 0) { sh.wave_a[wave] = mn; sh.wave_b[wave] = mx; }
+  hist_clear(sh);
+  if (tid < kCutList) sh.list[tid] = 0;
+  if (tid == 0) sh.list_n = 0;
+  __syncthreads();
+  uint32_t lo = over_waves<NW>(sh.wave_a, 0, NW, OpMin{}) + 1u;
+  uint32_t hi = over_waves<NW>(sh.wave_b, 0, NW, OpMax{}) - 1u;
+  // Which slots the next counting pass takes (bit 0: every eighth, bit 1: the others), the bins it counts, and the rank
+  // that is looked up afterwards; one loop for all of them keeps the code short (it is fetched once per launch).
+  enum { kSample = 1, kOthers = 2, kAll = 3, kRest = 6 };       // kRest: the others again, below the first bound
+  int take = ITEMS >= 16 && slots > kSampleEvery ? kSample : kAll;
+  uint32_t rank = need;
+  uint32_t from = 0, span = hi - lo;             // counted: keys lo + from .. lo + from + span
+  for (;;) {
+    const uint32_t width = hi - lo;
+    const int shift = width < (uint32_t)kCutBins ? 0 : 21 - __builtin_clz(width);
+    for_slots<ITEMS>(slots, [&](int s) {
+      if ((take >> (s % kSampleEvery != 0)) & 1) {
+        const uint32_t d = keys[s] - lo;                      // 0 and kForced lie outside every range
+        if (d - from <= span) atomicAdd(&sh.hist[d >> shift], 1u);
+      }
+    });
+    __syncthreads();
+    uint32_t bin, rank_in_bin, want = rank;
+    int count;
+    if (take == kSample) {       // the cut's rank in a sample of m of the n keys is about need * m / n: a tenth and three standard deviations more
+      const float at = (float)need * (float)(((slots + kSampleEvery - 1) / kSampleEvery) * NT) / (float)competing;
+      want = (uint32_t)(1.1f * at + 3.0f * __builtin_sqrtf(at) + 8.0f);
+    }
+    pick_bin<NT>(sh, want, bin, rank_in_bin, count);
+    if (take == kSample) {
+      from = count > 0 ? bin << shift : 0u;      // no such rank: the sample is smaller
+      span = width - from;
+      take = kOthers;
+      continue;
+    }
+    if (take == kOthers && (count == 0 || (bin << shift) < from)) {             // misled: the bins below are needed after all
+      span = from - 1u;
+      from = 0;
+      take = kRest;
+      continue;
+    }
+    take = kAll;
+    lo += bin << shift;
+    rank = rank_in_bin;
+    if (shift == 0) { tau = lo; ties = (int)rank; return; }
+    hi = min(hi, lo + ((1u << shift) - 1u));
+    if (count <= kCutList) {
+      const uint32_t w = hi - lo;
+      for_slots<ITEMS>(slots, [&](int s) {
+        if (keys[s] - lo <= w) sh.list[atomicAdd(&sh.list_n, 1u)] = keys[s];     // `count` entries, in any order
+      });
+      __syncthreads();
+      if (tid < count) {
+        const uint32_t k = sh.list[tid];
+        unsigned int above = 0, equal = 0;
+        for (int i = 0; i < count; i += 4) {           // (places past the last entry hold 0, below every key)
+          const uint4 o = *reinterpret_cast<const uint4*>(&sh.list[i]);
+          above += (o.x > k) + (o.y > k) + (o.z > k) + (o.w > k);
+          equal += (o.x == k) + (o.y == k) + (o.z == k) + (o.w == k);
+        }
+        if (above < rank && rank <= above + equal) { sh.pick[0] = k; sh.pick[1] = rank - above; }   // equal keys write the same
+      }
+      __syncthreads();
+      tau = (uint32_t)__builtin_amdgcn_readfirstlane((int)sh.pick[0]);
+      ties = __builtin_amdgcn_readfirstlane((int)sh.pick[1]);
+      return;
+    }
+    from = 0;
+    span = hi - lo;
+    hist_clear(sh);
     __syncthreads();
   }
-  if (wave == 0) {
-    const int per = nbins / 64;        // lane owns bins [lane*per, lane*per+per), per <= 32
-    unsigned int mine = 0;
-    for (int i = 0; i < per; ++i) mine += sh.hist[lane * per + i];
-    unsigned int run = mine;           // inclusive suffix sum over lanes
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-      const unsigned int o = __shfl_down(run, off);
-      if (lane + off < 64) run += o;
-    }
-    const unsigned int above = run - mine;   // count in bins owned by higher lanes
-    const unsigned long long hit = __ballot(above < remaining && remaining <= above + mine);   // exactly one lane
-    const int owner = __ffsll(hit) - 1;
-    const unsigned int above_owner = __builtin_amdgcn_readlane(above, owner);
-    // the bins of the owner, one per lane
-    const unsigned int c = lane < per ? sh.hist[owner * per + lane] : 0u;
-    unsigned int suf = c;              // inclusive suffix sum over the owner's bins
-#pragma unroll
-    for (int off = 1; off < 32; off <<= 1) {
-      const unsigned int o = __shfl_down(suf, off);
-      if (lane + off < 64) suf += o;
-    }
-    const unsigned int higher = above_owner + suf - c;      // candidates in bins above this one
-    if (lane < per && higher < remaining && remaining <= higher + c) {   // exactly one lane
-      sh.prefix = prefix | ((uint32_t)(owner * per + lane) << shift);
-      sh.need = remaining - higher;    // rank inside the chosen bin
-    }
-  }
-  __syncthreads();
-  prefix = sh.prefix;
-  remaining = sh.need;
 }
 
-// Exclusive prefix counts over the workgroup for one ordered tile.  In: this thread's counts.  Out: counts
-// in lower threads of the tile, and the tile totals.  All threads call it.
-template <int NT>
-__device__ __forceinline__ void tile_scan(SelectShared<NT>& sh, int nsure, int ntie, int& before_sure, int& before_tie,
-                                          int& tot_sure, int& tot_tie) {
-  constexpr int NWV = NT / 64;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  int ss = nsure, st = ntie;
+// The ordered output.  The counts of all runs of 256 consecutive candidates (wave and quad) are prefix-summed once;
+// inside a run the lower lanes' candidates come first.  emit(j, admitted, pos) is called for the candidates, pos = number of
+// admitted candidates before j: neighbouring lanes write neighbouring places.  ALL: also for those that are not admitted.
+template <bool ALL, int NT, int ITEMS, class Emit>
+__device__ __forceinline__ void emit_in_order(SelectShared<NT>& sh, const uint32_t (&keys)[ITEMS], int slots, int npre,
+                                              uint32_t tau, int ties, Emit emit) {
+  constexpr int NW = NT / 64, QUADS = ITEMS / 4;
+  static_assert(QUADS <= 16 && QUADS * NW <= NT, "one run count per lane, one thread per run");
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  int mine = 0;
 #pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const int os = __shfl_up(ss, off), ot = __shfl_up(st, off);
-    if (lane >= off) { ss += os; st += ot; }
-  }
-  if (lane == 63) { sh.wave_sure[wave] = ss; sh.wave_tie[wave] = st; }
-  __syncthreads();
-  if (wave == 0) {
-    int ws = lane < NWV ? sh.wave_sure[lane] : 0, wt = lane < NWV ? sh.wave_tie[lane] : 0;
-    int is = ws, it = wt;
+  for (int q = 0; q < QUADS; ++q) {
+    if (4 * q >= slots) continue;
+    int in = 0, tied = 0;
 #pragma unroll
-    for (int off = 1; off < NWV; off <<= 1) {
-      const int os = __shfl_up(is, off), ot = __shfl_up(it, off);
-      if (lane >= off) { is += os; it += ot; }
+    for (int e = 0; e < 4; ++e) {
+      in += __popcll(__ballot(keys[4 * q + e] > tau));
+      tied += __popcll(__ballot(keys[4 * q + e] == tau));
     }
-    if (lane < NWV) { sh.wave_sure[lane] = is - ws; sh.wave_tie[lane] = it - wt; }
-    if (lane == NWV - 1) { sh.tile_sure = is; sh.tile_tie = it; }
+    mine = lane == q ? in | tied << 16 : mine;
+  }
+  if (lane < QUADS) sh.chunk[lane * NW + wave] = (unsigned int)mine;       // quads not in use: 0
+  __syncthreads();
+  // fewer than 65536 candidates lie above the cut, so the low half never carries; all 65536 can be tied at it only
+  // in the inclusive sum of the last run, which is not used
+  const unsigned int x = tid < QUADS * NW ? sh.chunk[tid] : 0u;
+  const unsigned int incl = wave_scan(x, OpAdd{});
+  constexpr int SCANNED = (QUADS * NW + 63) / 64;                          // waves that hold a run's count
+  if (SCANNED > 1) {
+    if (lane == 63 && wave < SCANNED) sh.wave_b[wave] = incl;
+    __syncthreads();
+  }
+  if (tid < QUADS * NW) {
+    unsigned int before = incl - x;
+#pragma unroll
+    for (int w = 0; w < SCANNED - 1; ++w) before += w < wave ? sh.wave_b[w] : 0u;
+    sh.chunk[tid] = before;
   }
   __syncthreads();
-  before_sure = sh.wave_sure[wave] + ss - nsure;
-  before_tie = sh.wave_tie[wave] + st - ntie;
-  tot_sure = sh.tile_sure;
-  tot_tie = sh.tile_tie;
-  __syncthreads();                      // wave_* / tile_* are rewritten by the next tile
-}
-
-// The selection proper.  A "candidate source" gives, for index j in [0, npre):
-//   key(j)      order-preserving integer image of its score,
-//   eligible(j) whether it competes in the radix select,
-//   forced(j)   whether it is admitted regardless (stage 2: members of the protected set).
-// The candidates are loaded once into registers, ITEMS per thread (npre <= NT * ITEMS).
-// emit(j, admitted, pos) is called for every j, pos = number of admitted candidates before j.
-template <int NT, int ITEMS, class Source, class Emit>
-__device__ __forceinline__ void select_wg(SelectShared<NT>& sh, Source src, Emit emit, int npre, int need) {
-  const int tid = threadIdx.x;
-  constexpr int kSelTile = NT * kSelTileItems;
-  static_assert(ITEMS > 0 && ITEMS % kSelTileItems == 0 && ITEMS <= SelectSize<NT>::kMaxItems, "register-resident candidates");
-  uint32_t keys[ITEMS];
-  unsigned long long elig = 0, forc = 0;       // one bit per register slot
-  // slot s of this thread holds candidate j = (s / 4) * kSelTile + tid * 4 + (s % 4): tiles in order, 4 consecutive
-  if (npre > 0) {                              // the same for every thread
-    // unconditional loads (index clamped into the row) so that all of them are in flight together
+  const int base = lane < QUADS ? (int)sh.chunk[lane * NW + wave] : 0;
 #pragma unroll
-    for (int s = 0; s < ITEMS; ++s) {
-      const int j = (s / kSelTileItems) * kSelTile + tid * kSelTileItems + (s % kSelTileItems);
-      const int jc = j < npre ? j : npre - 1;
-      const uint32_t key = src.key(jc);
-      const bool el = src.eligible(jc), fo = src.forced(jc);
-      keys[s] = j < npre ? key : 0u;
-      if (j < npre && el) elig |= 1ull << s;
-      if (j < npre && fo) forc |= 1ull << s;
+  for (int q = 0; q < QUADS; ++q) {
+    if (4 * q >= slots) continue;
+    const unsigned int b = (unsigned int)__builtin_amdgcn_readlane(base, q);
+    int pos = (int)(b & 0xFFFFu), tb = (int)(b >> 16);
+    unsigned long long any_tie = 0;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const unsigned long long m = __ballot(keys[4 * q + e] > tau);
+      pos = (int)__builtin_amdgcn_mbcnt_hi((unsigned int)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned int)m, (unsigned int)pos));
+      any_tie |= __ballot(keys[4 * q + e] == tau);
     }
-  } else {
+    if (any_tie != 0 && ties > 0) {
 #pragma unroll
-    for (int s = 0; s < ITEMS; ++s) keys[s] = 0u;
-  }
-
-  uint32_t tau = 0xFFFFFFFFu;
-  int ties = 0;                               // need == 0: only forced candidates are admitted
-  if (need > 0) {
-    uint32_t prefix = 0, remaining = (uint32_t)need;
-#pragma unroll
-    for (int pass = 0; pass < 3; ++pass) {
-      const int shift = pass_shift(pass), nbins = pass_bins(pass);
-      const uint32_t himask = pass_himask(pass);
-      const int copies = pass == 0 ? SelectSize<NT>::kCopies : 1;
-      hist_clear(sh, nbins, copies);
-#pragma unroll
-      for (int s = 0; s < ITEMS; ++s) {
-        const bool match = ((elig >> s) & 1ull) && (keys[s] & himask) == prefix;
-        if (pass == 0) hist_add<true, NT>(sh, match, (keys[s] >> shift) & (uint32_t)(nbins - 1));
-        else hist_add<false, NT>(sh, match, (keys[s] >> shift) & (uint32_t)(nbins - 1));
+      for (int e = 0; e < 4; ++e) {
+        const unsigned long long m = __ballot(keys[4 * q + e] == tau);
+        tb = (int)__builtin_amdgcn_mbcnt_hi((unsigned int)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned int)m, (unsigned int)tb));
       }
-      hist_pick(sh, nbins, copies, shift, prefix, remaining);
     }
-    tau = prefix;
-    ties = (int)remaining;
-  }
-
-  // ---- ordered pass.  The classes (0 out, 1 tied at the cut, 2 in) go through LDS so that every thread ends up
-  // with ITEMS consecutive candidates: one workgroup prefix sum, and each thread writes its admitted indices to
-  // consecutive places.
-  constexpr int T4 = ITEMS / kSelTileItems;
 #pragma unroll
-  for (int t = 0; t < T4; ++t) {
-    unsigned int word = 0;
-#pragma unroll
-    for (int e = 0; e < kSelTileItems; ++e) {
-      const int s = t * kSelTileItems + e;
-      const bool el = (elig >> s) & 1ull, fo = (forc >> s) & 1ull;
-      const unsigned int c = fo ? 2u : (el ? (keys[s] > tau ? 2u : (keys[s] == tau ? 1u : 0u)) : 0u);
-      word |= c << (8 * e);
-    }
-    sh.cls_words[t * NT + tid] = word;                   // candidates 4 * (t * NT + tid) .. + 3
-  }
-  __syncthreads();
-  unsigned int mine[T4];
-  int nsure = 0, ntie = 0;
-#pragma unroll
-  for (int t = 0; t < T4; ++t) {
-    mine[t] = sh.cls_words[tid * T4 + t];                // candidates tid * ITEMS + 4 t .. + 3
-#pragma unroll
-    for (int e = 0; e < kSelTileItems; ++e) {
-      const unsigned int c = (mine[t] >> (8 * e)) & 255u;
-      nsure += c == 2u; ntie += c == 1u;
-    }
-  }
-  int ps, pt, ts, tt;
-  tile_scan(sh, nsure, ntie, ps, pt, ts, tt);
-#pragma unroll
-  for (int t = 0; t < T4; ++t) {
-#pragma unroll
-    for (int e = 0; e < kSelTileItems; ++e) {
-      const int j = tid * ITEMS + t * kSelTileItems + e;
-      const unsigned int c = (mine[t] >> (8 * e)) & 255u;
-      if (j < npre) {
-        const bool admitted = c == 2u || (c == 1u && pt < ties);
-        emit(j, admitted, ps + min(pt, ties));
-      }
-      ps += c == 2u; pt += c == 1u;
+    for (int e = 0; e < 4; ++e) {
+      const int j = (q * NT + tid) * 4 + e;
+      const bool in = keys[4 * q + e] > tau, tied = keys[4 * q + e] == tau;
+      const bool admitted = in || (tied && tb < ties);
+      if (ALL ? j < npre : admitted) emit(j, admitted, pos + min(tb, ties));
+      pos += in;
+      tb += tied;
     }
   }
 }
@@ -307,96 +359,227 @@ struct FillSource {             // two-stage, stage 2: protected tokens are in, 
   __device__ bool forced(int j) const { return member[j] != 0; }
 };
 
-// additive rule: one selection on the fused scores
+// A row of floats into registers, all loads in flight together.
 template <int NT, int ITEMS>
+__device__ __forceinline__ void load_row(rsrc_t row, float (&x)[ITEMS]) {
+#pragma unroll
+  for (int s = 0; s < ITEMS; s += 4) {
+    const float4 v = row_f32x4(row, (int)threadIdx.x * 16, s * NT * 4);
+    x[s] = v.x; x[s + 1] = v.y; x[s + 2] = v.z; x[s + 3] = v.w;
+  }
+}
+
+// Slots that `count` candidates take per thread.
+template <int NT>
+__device__ __forceinline__ int slots_of(int count) { return (count + 4 * NT - 1) / (4 * NT) * 4; }
+
+// Keys in registers -> indices of the kept tokens at `out`: the best `need` competing ones (and the forced ones).
+template <int NT, int ITEMS>
+__device__ __forceinline__ void select_and_emit(SelectShared<NT>& sh, const uint32_t (&keys)[ITEMS], int slots, int npre, int competing,
+                                                int need, bool all, int32_t* out) {
+  uint32_t tau = all ? 0u : kForced - 1u;       // every candidate / the forced ones only
+  int ties = 0;
+  if (!all && need > 0) find_cut<NT, ITEMS>(sh, keys, slots, competing, (uint32_t)need, tau, ties);
+  emit_in_order<false, NT, ITEMS>(sh, keys, slots, npre, tau, ties, [&](int j, bool, int pos) { out[pos] = j; });
+}
+
+// additive rule: one selection on the fused scores; two-stage rule, stage 2 (FILL): attention fills what stage 1 left
+template <bool FILL, int NT, int ITEMS>
 __global__ __launch_bounds__(NT) void select_kernel(SelectArgs a) {
   __shared__ SelectShared<NT> sh;
   const int tid = threadIdx.x;
   const int seq = blockIdx.x;
   const int lz = blockIdx.y;
   const int s0 = a.cu_seqlens[seq];
-  const int n = a.cu_seqlens[seq + 1] - s0;
+  const int npre = a.cu_seqlens[seq + 1] - s0 - a.W;   // candidates
   const int o0 = a.cu_budgets[seq];
-  const int budget = a.cu_budgets[seq + 1] - o0;
-  const int npre = n - a.W;              // candidates
-  const int need = budget - a.W;         // how many of them are kept
+  const int bp = a.cu_budgets[seq + 1] - o0 - a.W;     // how many of them are kept
   int32_t* out = a.idx + (int64_t)lz * a.TB + o0;
-
-  // the observation window is always kept
-  for (int t = tid; t < a.W; t += NT) out[need + t] = npre + t;
-  if (need <= 0) return;                 // uniform
-  if (need >= npre) {                    // everything is kept
-    for (int j = tid; j < npre; j += NT) out[j] = j;
-    return;
-  }
-  if (npre > NT * ITEMS) return;         // the host picks ITEMS from the longest request: cannot happen
-  ScoreSource src = {a.scores + (int64_t)lz * a.T + s0};
-  select_wg<NT, ITEMS>(sh, src, [&](int j, bool admitted, int pos) { if (admitted) out[pos] = j; }, npre, need);
-}
-
-// two-stage rule, stage 1: once per request (the prior is shared by layers and heads)
-template <int NT, int ITEMS>
-__global__ __launch_bounds__(NT) void select_stage1_kernel(SelectArgs a) {
-  __shared__ SelectShared<NT> sh;
-  __shared__ int sh_flagged;
-  const int tid = threadIdx.x;
-  const int seq = blockIdx.x;
-  const int s0 = a.cu_seqlens[seq];
-  const int n = a.cu_seqlens[seq + 1] - s0;
-  const int budget = a.cu_budgets[seq + 1] - a.cu_budgets[seq];
-  const int npre = n - a.W;
-  const int bp = budget - a.W;           // slots of the prefix
-  const float* p = a.prior + s0;
-  uint8_t* member = a.member + s0;
-
-  for (int t = tid; t < a.W; t += NT) member[npre + t] = 0;
-  // number of structurally marked prefix tokens
-  if (tid == 0) sh_flagged = 0;
-  __syncthreads();
-  int mine = 0;
-  for (int j = tid; j < npre; j += NT) mine += p[j] > 0.f;
+  for (int t = tid; t < a.W; t += NT) out[bp + t] = npre + t;      // the observation window is always kept
+  if (bp <= 0 || npre > NT * ITEMS) return;            // the host picks ITEMS from the longest request: the latter cannot happen
+  const int slots = slots_of<NT>(npre);
+  const rsrc_t row = row_of(a.scores + (int64_t)lz * a.T + s0, npre);
+  uint32_t keys[ITEMS];
+  float x[ITEMS];
+  uint8_t member[FILL ? ITEMS : 1];
+  load_row<NT, ITEMS>(row, x);
+  if constexpr (FILL) {
+    const rsrc_t mrow = row_of(a.member + s0, npre);
 #pragma unroll
-  for (int off = 32; off > 0; off >>= 1) mine += __shfl_xor(mine, off);
-  if ((tid & 63) == 0 && mine) atomicAdd(&sh_flagged, mine);
-  __syncthreads();
-  const int flagged = sh_flagged;
-  int bspan = max(a.span_min, (int)floor((double)a.span_ratio * (double)bp));
-  bspan = min(bp, bspan);
-  const int need = min(bspan, flagged);
-  if (tid == 0) a.member_count[seq] = need;
-  if (need <= 0 || npre > NT * ITEMS) {
-    for (int j = tid; j < npre; j += NT) member[j] = 0;
-    return;
+    for (int s = 0; s < ITEMS; ++s) member[s] = __builtin_amdgcn_raw_buffer_load_b8(mrow, tid * 4 + s % 4, s / 4 * NT * 4, 0);
   }
-  PriorSource src = {p};
-  select_wg<NT, ITEMS>(sh, src, [&](int j, bool admitted, int) { member[j] = admitted ? 1 : 0; }, npre, need);
+#pragma unroll
+  for (int s = 0; s < ITEMS; ++s) {
+    keys[s] = (s / 4 * NT + tid) * 4 + s % 4 < npre ? order_key(x[s]) : 0u;
+    if constexpr (FILL) keys[s] = member[s] ? kForced : keys[s];
+  }
+  const int members = FILL ? a.member_count[seq] : 0;
+  select_and_emit<NT, ITEMS>(sh, keys, slots, npre, npre - members, bp - members, bp >= npre, out);
 }
 
-// two-stage rule, stage 2: attention fills what stage 1 left
-template <int NT, int ITEMS>
-__global__ __launch_bounds__(NT) void select_stage2_kernel(SelectArgs a) {
+// The tail of the fused call in one kernel: the attention mass of a request is pooled, the prior added, the scores stored
+// (what score_finish_kernel does, the same sums in the same order), and the selection goes on with the scores it holds in
+// registers.  The masses pass through LDS, up to 32768 tokens at a time, so that a thread finds its neighbours there.
+template <bool FILL, int NT, int ITEMS, int HALO>
+__global__ __launch_bounds__(NT) void finish_select_kernel(SelectArgs a, FinishArgs f) {
+  constexpr int BLOCK = ITEMS < 32768 / NT ? ITEMS : 32768 / NT;   // slots per LDS filling
+  constexpr int NEAR = 4;                                          // neighbours on a side that three 16-byte LDS reads cover
+  static_assert(HALO % 4 == 0 && HALO >= NEAR, "16-byte LDS accesses");
+  __shared__ __attribute__((aligned(16))) float mass[BLOCK * NT + 2 * HALO];
   __shared__ SelectShared<NT> sh;
   const int tid = threadIdx.x;
   const int seq = blockIdx.x;
   const int lz = blockIdx.y;
   const int s0 = a.cu_seqlens[seq];
   const int n = a.cu_seqlens[seq + 1] - s0;
+  const int npre = n - a.W;                            // candidates
   const int o0 = a.cu_budgets[seq];
-  const int budget = a.cu_budgets[seq + 1] - o0;
-  const int npre = n - a.W;
-  const int bp = budget - a.W;
-  const int need = bp - a.member_count[seq];   // slots left for attention (>= 0)
+  const int bp = a.cu_budgets[seq + 1] - o0 - a.W;     // how many of them are kept
   int32_t* out = a.idx + (int64_t)lz * a.TB + o0;
-
-  for (int t = tid; t < a.W; t += NT) out[bp + t] = npre + t;
+  for (int t = tid; t < a.W; t += NT) out[bp + t] = npre + t;      // the observation window is always kept
+  if (n > NT * ITEMS) return;                          // the host picks ITEMS from the longest request: cannot happen
+  const int half = (f.pool - 1) >> 1;
+  const int pooled_end = n - f.pool_trim;              // tokens from here on get no attention term
+  const int mass_end = n - max(f.mass_trim, f.pool_trim);          // tokens from here on have no mass to pool
+  const float* u = f.uraw + (int64_t)lz * f.T + s0;
+  const int64_t split_stride = (int64_t)f.LH * f.T;
+  const rsrc_t prior = row_of(f.prior + s0, n);
+  const rsrc_t scores = row_of(f.scores + (int64_t)lz * f.T + s0, n);
+  const rsrc_t members_row = row_of(a.member + s0, FILL ? npre : 0);
+  float weight[NEAR + 1];                              // 1 for the neighbours that the pooling width reaches, else 0
+#pragma unroll
+  for (int t = 0; t <= NEAR; ++t) weight[t] = t <= half ? 1.f : 0.f;
+  uint32_t keys[ITEMS];
+#pragma unroll
+  for (int s = 0; s < ITEMS; ++s) keys[s] = 0u;
+#pragma unroll
+  for (int b0 = 0; b0 < ITEMS; b0 += BLOCK) {
+    const int width = b0 + BLOCK <= ITEMS ? BLOCK : ITEMS - b0;     // slots of this filling
+    const int base = b0 * NT;
+    if (base >= n) continue;                           // the same for every thread
+    if (b0 > 0) __syncthreads();                       // the last filling has been read
+    float4 v[BLOCK / 4];
+    {
+      const rsrc_t row = row_of(u, mass_end);
+#pragma unroll
+      for (int s = 0; s < BLOCK; s += 4)
+        if (s < width) v[s / 4] = row_f32x4(row, tid * 16, (base + s * NT) * 4);
+    }
+    for (int sp = 1; sp < f.row_splits; ++sp) {        // added in the order of the splits
+      const rsrc_t row = row_of(u + sp * split_stride, mass_end);
+      float4 w[BLOCK / 4];
+#pragma unroll
+      for (int s = 0; s < BLOCK; s += 4)
+        if (s < width) w[s / 4] = row_f32x4(row, tid * 16, (base + s * NT) * 4);
+#pragma unroll
+      for (int s = 0; s < BLOCK / 4; ++s)
+        if (4 * s < width) { v[s].x += w[s].x; v[s].y += w[s].y; v[s].z += w[s].z; v[s].w += w[s].w; }
+    }
+    const int reach = max(half, NEAR);
+    for (int i = tid; i < 2 * reach; i += NT) {        // the neighbours on both sides
+      const int x = i < reach ? base - reach + i : base + width * NT + (i - reach);
+      float val = 0.f;
+      if (x >= 0 && x < mass_end)
+        for (int sp = 0; sp < f.row_splits; ++sp) val += u[sp * split_stride + x];
+      mass[HALO + x - base] = val;
+    }
+#pragma unroll
+    for (int s = 0; s < BLOCK; s += 4)
+      if (s < width) *reinterpret_cast<float4*>(&mass[HALO + (s / 4 * NT + tid) * 4]) = v[s / 4];
+    __syncthreads();
+#pragma unroll
+    for (int s = 0; s < BLOCK; s += 4) {
+      if (s >= width || base + s * NT >= n) continue;
+      const int lane_byte = tid * 16, quad_byte = (base + s * NT) * 4;
+      float acc[4] = {0.f, 0.f, 0.f, 0.f};
+      const float4 p4 = row_f32x4(prior, lane_byte, quad_byte);
+      const float p[4] = {p4.x, p4.y, p4.z, p4.w};
+      uint8_t member[4] = {0, 0, 0, 0};
+      if constexpr (FILL) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) member[e] = __builtin_amdgcn_raw_buffer_load_b8(members_row, tid * 4 + e, base + s * NT, 0);
+      }
+      const float* m = mass + HALO + (s / 4 * NT + tid) * 4;
+      if (half <= NEAR) {
+        const float4 w0 = *reinterpret_cast<const float4*>(m - 4), w1 = *reinterpret_cast<const float4*>(m), w2 = *reinterpret_cast<const float4*>(m + 4);
+        const float w[12] = {w0.x, w0.y, w0.z, w0.w, w1.x, w1.y, w1.z, w1.w, w2.x, w2.y, w2.z, w2.w};
+        if (f.pool_max) {
+#pragma unroll
+          for (int t = -NEAR; t <= NEAR; ++t)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[e] = fmaxf(acc[e], weight[t < 0 ? -t : t] * w[4 + e + t]);           // masses are >= 0
+        } else {
+#pragma unroll
+          for (int t = -NEAR; t <= NEAR; ++t)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[e] = __builtin_fmaf(weight[t < 0 ? -t : t], w[4 + e + t], acc[e]);
+        }
+      } else if (f.pool_max) {
+        for (int t = -half; t <= half; ++t)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) acc[e] = fmaxf(acc[e], m[e + t]);
+      } else {
+        for (int t = -half; t <= half; ++t)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) acc[e] += m[e + t];
+      }
+      float c[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int j = base + s * NT + tid * 4 + e;
+        const float pooled = f.pool_max ? acc[e] : acc[e] * f.inv_pool;
+        c[e] = __builtin_fmaf(f.lambda, p[e], j < pooled_end ? pooled : 0.f);
+        keys[b0 + s + e] = j < npre ? (member[e] ? kForced : order_key(c[e])) : 0u;
+      }
+      typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+      __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, make_float4(c[0], c[1], c[2], c[3])), scores, lane_byte, quad_byte, 0);
+    }
+  }
   if (bp <= 0) return;
-  if (bp >= npre) {
-    for (int j = tid; j < npre; j += NT) out[j] = j;
+  const int slots = slots_of<NT>(npre);
+  const int members = FILL ? a.member_count[seq] : 0;
+  select_and_emit<NT, ITEMS>(sh, keys, slots, npre, npre - members, bp - members, bp >= npre, out);
+}
+
+// two-stage rule, stage 1: once per request (the prior is shared by layers and heads)
+template <int NT, int ITEMS>
+__global__ __launch_bounds__(NT) void select_stage1_kernel(SelectArgs a) {
+  __shared__ SelectShared<NT> sh;
+  const int tid = threadIdx.x;
+  const int seq = blockIdx.x;
+  const int s0 = a.cu_seqlens[seq];
+  const int npre = a.cu_seqlens[seq + 1] - s0 - a.W;
+  const int bp = a.cu_budgets[seq + 1] - a.cu_budgets[seq] - a.W;           // slots of the prefix
+  uint8_t* member = a.member + s0;
+  for (int t = tid; t < a.W; t += NT) member[npre + t] = 0;
+  if (npre <= 0 || npre > NT * ITEMS) {                                     // no candidate (more than fit cannot happen, as above)
+    if (tid == 0) a.member_count[seq] = 0;
     return;
   }
-  if (npre > NT * ITEMS) return;
-  FillSource src = {a.scores + (int64_t)lz * a.T + s0, a.member + s0};
-  select_wg<NT, ITEMS>(sh, src, [&](int j, bool admitted, int pos) { if (admitted) out[pos] = j; }, npre, need);
+  const int slots = slots_of<NT>(npre);
+  const rsrc_t row = row_of(a.prior + s0, npre);
+  uint32_t keys[ITEMS];
+  float x[ITEMS];
+  load_row<NT, ITEMS>(row, x);
+#pragma unroll
+  for (int s = 0; s < ITEMS; ++s) keys[s] = x[s] > 0.f ? order_key(x[s]) : 0u;       // past the row: 0, not marked
+  // number of structurally marked prefix tokens
+  int mine = 0;
+  for_slots<ITEMS>(slots, [&](int s) { mine += __popcll(__ballot(keys[s] != 0u)); });
+  if ((tid & 63) == 0) sh.chunk[tid >> 6] = (unsigned int)mine;
+  __syncthreads();
+  int flagged = 0;
+#pragma unroll
+  for (int w = 0; w < NT / 64; ++w) flagged += (int)sh.chunk[w];
+  __syncthreads();
+  int bspan = max(a.span_min, (int)floor((double)a.span_ratio * (double)bp));
+  bspan = min(bp, bspan);
+  const int need = min(bspan, flagged);
+  if (tid == 0) a.member_count[seq] = max(need, 0);
+  uint32_t tau = kForced - 1u;
+  int ties = 0;
+  if (need > 0) find_cut<NT, ITEMS>(sh, keys, slots, flagged, (uint32_t)need, tau, ties);
+  emit_in_order<true, NT, ITEMS>(sh, keys, slots, npre, tau, ties, [&](int j, bool admitted, int) { member[j] = admitted ? 1 : 0; });
 }
 
 // ---------------------------------------------------------------------------------------------------------
@@ -415,6 +598,7 @@ struct PartArgs {
 
 enum { kModeNone = 0, kModeAll = 1, kModeSelect = 2 };   // no competing candidate admitted / all of them / a real selection
 
+constexpr int kHistStride = 2049;     // odd stride: equal bins of different copies sit in different banks
 constexpr int kPartCopies = 4;       // private copies of a histogram (lane % 4)
 constexpr int kPartHistWords = 8 * (kFirstDigitBins / 2 + 1);   // 8 packed copies of the first-digit counts, or 4 plain copies of a digit
 static_assert(kPartHistWords >= kPartCopies * kHistStride, "histogram storage of the part kernels");
@@ -954,33 +1138,24 @@ __global__ __launch_bounds__(kPartThreads) void part_emit_kernel(SelectArgs a, P
   }
 }
 
-// Which one-workgroup kernel: 256 threads when every request fits 256 x 16 candidates and the batch has enough
-// problems to keep several such workgroups on every compute unit, else 1024 threads.
-static bool small_workgroups(const Plan& pl, int64_t problems) {
-  return pl.max_n - pl.W <= kSelectSmallThreads * kSelectSmallMaxItems && problems >= kSelectSmallProblems;
-}
-// candidates kept in registers per thread, chosen from the longest request
-static int items_for(const Plan& pl, int threads) {
-  const int npre = pl.max_n - pl.W;
-  for (int items : {8, 16, 32, 48}) if (npre <= threads * items) return items;
-  return 64;
-}
-
-#define CODECOMP_DISPATCH_ITEMS(KERNEL, GRID, PROBLEMS, ARGS)                                              \
-  if (small_workgroups(pl, PROBLEMS)) {                                                                    \
-    switch (items_for(pl, kSelectSmallThreads)) {                                                          \
-      case 8: KERNEL<kSelectSmallThreads, 8><<<GRID, dim3(kSelectSmallThreads), 0, stream>>>(ARGS); break;   \
-      default: KERNEL<kSelectSmallThreads, 16><<<GRID, dim3(kSelectSmallThreads), 0, stream>>>(ARGS); break; \
-    }                                                                                                      \
-  } else {                                                                                                 \
-    switch (items_for(pl, kSelectThreads)) {                                                               \
-      case 8: KERNEL<kSelectThreads, 8><<<GRID, dim3(kSelectThreads), 0, stream>>>(ARGS); break;           \
-      case 16: KERNEL<kSelectThreads, 16><<<GRID, dim3(kSelectThreads), 0, stream>>>(ARGS); break;         \
-      case 32: KERNEL<kSelectThreads, 32><<<GRID, dim3(kSelectThreads), 0, stream>>>(ARGS); break;         \
-      case 48: KERNEL<kSelectThreads, 48><<<GRID, dim3(kSelectThreads), 0, stream>>>(ARGS); break;         \
-      default: KERNEL<kSelectThreads, 64><<<GRID, dim3(kSelectThreads), 0, stream>>>(ARGS); break;         \
-    }                                                                                                      \
+// Calls launch(threads, candidates per thread) for requests of at most `longest` candidates.  Few problems: a workgroup has
+// its compute unit to itself, and many threads with few candidates each are quickest (8192 tokens: 7.7 us with 1024 x 8 against
+// 10.5 with 512 x 16; 4093: 6.1 with 1024 x 4 against 9.4 with 256 x 16; 2048: 4.6 with 512 x 4 against 6.8 with 1024 x 8).
+// Many problems: smaller workgroups, of which several share a compute unit, spend less on barriers and on work that every
+// wave repeats (7168 problems of 128 .. 2300 tokens: 31 us with 256 x 8).
+template <class Launch>
+static void dispatch_items(int longest, int64_t problems, Launch launch) {
+  auto with = [&](auto nt, auto items) { launch(nt, items); };
+#define CODECOMP_WG(NT, ITEMS) if (longest <= NT * ITEMS) return with(std::integral_constant<int, NT>{}, std::integral_constant<int, ITEMS>{});
+  if (problems >= kSelectManyProblems) {
+    CODECOMP_WG(256, 8) CODECOMP_WG(256, 16) CODECOMP_WG(512, 16) CODECOMP_WG(512, 32)
+  } else {
+    CODECOMP_WG(256, 4) CODECOMP_WG(512, 4) CODECOMP_WG(1024, 4) CODECOMP_WG(1024, 8) CODECOMP_WG(1024, 16)
   }
+  CODECOMP_WG(1024, 32) CODECOMP_WG(1024, 48)
+  with(std::integral_constant<int, 1024>{}, std::integral_constant<int, 64>{});
+#undef CODECOMP_WG
+}
 
 static PartArgs part_args(const Plan& pl, void* workspace) {
   char* ws = static_cast<char*>(workspace);
@@ -1008,18 +1183,7 @@ static int launch_parts(const Plan& pl, const SelectArgs& a, const PartArgs& c, 
   return 0;
 }
 
-int launch_select(const Plan& pl, const float* scores, int32_t* idx, void* workspace, hipStream_t stream) {
-  SelectArgs a = {};
-  a.scores = scores; a.cu_seqlens = pl.cu_seqlens_dev; a.cu_budgets = pl.cu_budgets_dev; a.idx = idx;
-  a.n_seqs = pl.n_seqs; a.T = pl.T; a.TB = pl.TB; a.W = pl.W;
-  if (pl.sel_parts > 0) return launch_parts<RuleAdditive>(pl, a, part_args(pl, workspace), pl.L * pl.Hkv, stream);
-  CODECOMP_DISPATCH_ITEMS(select_kernel, dim3(pl.n_seqs, pl.L * pl.Hkv), (int64_t)pl.n_seqs * pl.L * pl.Hkv, a)
-  if (hipError_t e = hipGetLastError()) return (int)e;
-  return 0;
-}
-
-int launch_select_two_stage(const Plan& pl, const float* scores, const float* prior, int32_t* idx, void* workspace,
-                            hipStream_t stream) {
+static SelectArgs select_args(const Plan& pl, const float* scores, const float* prior, int32_t* idx, void* workspace) {
   char* ws = static_cast<char*>(workspace);
   SelectArgs a = {};
   a.scores = scores; a.prior = prior; a.cu_seqlens = pl.cu_seqlens_dev; a.cu_budgets = pl.cu_budgets_dev; a.idx = idx;
@@ -1027,14 +1191,57 @@ int launch_select_two_stage(const Plan& pl, const float* scores, const float* pr
   a.member_count = reinterpret_cast<int32_t*>(ws + pl.off_member_count);
   a.n_seqs = pl.n_seqs; a.T = pl.T; a.TB = pl.TB; a.W = pl.W;
   a.span_ratio = pl.span_ratio; a.span_min = pl.span_min;
-  if (pl.sel_parts > 0) {
+  return a;
+}
+
+static int launch_stage1(const Plan& pl, const SelectArgs& a, hipStream_t stream) {
+  dispatch_items(pl.max_n - pl.W, (int64_t)pl.n_seqs, [&](auto nt, auto items) {
+    select_stage1_kernel<nt(), items()><<<dim3(pl.n_seqs), dim3(nt()), 0, stream>>>(a);
+  });
+  if (hipError_t e = hipGetLastError()) return (int)e;
+  return 0;
+}
+
+// One workgroup keeps a request's scores in registers (64 per thread of the large ones).
+bool fused_tail(const Plan& pl) { return pl.max_n <= kSelectMaxCandidates; }
+
+int launch_finish_select(const Plan& pl, const float* prior, float* scores, int32_t* idx, void* workspace, hipStream_t stream) {
+  const SelectArgs a = select_args(pl, scores, prior, idx, workspace);
+  const FinishArgs f = finish_args(pl, prior, scores, workspace);
+  const bool fill = pl.select_mode == CODECOMP_SELECT_TWO_STAGE;
+  if (fill)
+    if (int rc = launch_stage1(pl, a, stream)) return rc;
+  dispatch_items(pl.max_n, (int64_t)pl.n_seqs * pl.L * pl.Hkv, [&](auto nt, auto items) {
+    const dim3 grid(pl.n_seqs, pl.L * pl.Hkv), block(nt());
+    if (fill) finish_select_kernel<true, nt(), items(), kFinishHalo><<<grid, block, 0, stream>>>(a, f);
+    else finish_select_kernel<false, nt(), items(), kFinishHalo><<<grid, block, 0, stream>>>(a, f);
+  });
+  if (hipError_t e = hipGetLastError()) return (int)e;
+  return 0;
+}
+
+int launch_select(const Plan& pl, const float* scores, int32_t* idx, void* workspace, hipStream_t stream) {
+  const SelectArgs a = select_args(pl, scores, nullptr, idx, workspace);
+  if (pl.by_parts) return launch_parts<RuleAdditive>(pl, a, part_args(pl, workspace), pl.L * pl.Hkv, stream);
+  dispatch_items(pl.max_n - pl.W, (int64_t)pl.n_seqs * pl.L * pl.Hkv, [&](auto nt, auto items) {
+    select_kernel<false, nt(), items()><<<dim3(pl.n_seqs, pl.L * pl.Hkv), dim3(nt()), 0, stream>>>(a);
+  });
+  if (hipError_t e = hipGetLastError()) return (int)e;
+  return 0;
+}
+
+int launch_select_two_stage(const Plan& pl, const float* scores, const float* prior, int32_t* idx, void* workspace,
+                            hipStream_t stream) {
+  const SelectArgs a = select_args(pl, scores, prior, idx, workspace);
+  if (pl.by_parts) {
     const PartArgs c = part_args(pl, workspace);
     if (int rc = launch_parts<RuleStage1>(pl, a, c, 1, stream)) return rc;
     return launch_parts<RuleStage2>(pl, a, c, pl.L * pl.Hkv, stream);
   }
-  CODECOMP_DISPATCH_ITEMS(select_stage1_kernel, dim3(pl.n_seqs), (int64_t)pl.n_seqs, a)
-  if (hipError_t e = hipGetLastError()) return (int)e;
-  CODECOMP_DISPATCH_ITEMS(select_stage2_kernel, dim3(pl.n_seqs, pl.L * pl.Hkv), (int64_t)pl.n_seqs * pl.L * pl.Hkv, a)
+  if (int rc = launch_stage1(pl, a, stream)) return rc;
+  dispatch_items(pl.max_n - pl.W, (int64_t)pl.n_seqs * pl.L * pl.Hkv, [&](auto nt, auto items) {
+    select_kernel<true, nt(), items()><<<dim3(pl.n_seqs, pl.L * pl.Hkv), dim3(nt()), 0, stream>>>(a);
+  });
   if (hipError_t e = hipGetLastError()) return (int)e;
   return 0;
 }

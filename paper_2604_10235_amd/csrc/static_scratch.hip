@@ -48,12 +48,5 @@ extern "C" int codecomp_compress_static(const void* q_obs, const void* k, const 
   if (pl.ws_bytes > (size_t)CODECOMP_STATIC_SCRATCH_BYTES) return CODECOMP_EINVAL_WORKSPACE;   // too large for the array
   void* ws = nullptr;
   if (int rc = scratch_of_current_device(&ws)) return rc;
-  hipStream_t s = (hipStream_t)hip_stream;
-  if (int rc = launch_score(pl, q_obs, k, prior, scores, ws, s)) return rc;
-  if (pl.select_mode == CODECOMP_SELECT_TWO_STAGE) {
-    if (int rc = launch_select_two_stage(pl, scores, prior, idx, ws, s)) return rc;
-  } else {
-    if (int rc = launch_select(pl, scores, idx, ws, s)) return rc;
-  }
-  return launch_gather(pl, k, v, idx, k_out, v_out, s);
+  return launch_compress(pl, q_obs, k, v, prior, scores, idx, k_out, v_out, ws, (hipStream_t)hip_stream);
 }

@@ -1,0 +1,56 @@
+"""The fused call pools, adds the prior and selects in one kernel where one workgroup holds a request: same bits as the
+separate calls (each of which is checked against the oracle elsewhere) at the edges of every workgroup shape."""
+import numpy as np
+import pytest
+
+from paper_2604_10235_amd import workloads as wl
+from tests import parity_util as pu
+
+pytestmark = pytest.mark.gpu
+
+W = 16
+
+
+def both(w, **kw):
+    import torch
+    from paper_2604_10235_amd import binding as b
+    q, k, v, prior = wl.make_all(w)
+    steps, fused = (b.DeviceProblem(w, q, k, v, prior, **kw) for _ in range(2))
+    steps.score(); steps.select(); steps.gather()
+    fused.workspace.fill_(0xFF)                                    # nothing may be read before it is written
+    fused.scores.fill_(float("nan")); fused.idx.fill_(-1); fused.k_out.fill_(0)
+    fused.compress()
+    torch.cuda.synchronize()
+    assert torch.equal(steps.scores.view(torch.int32), fused.scores.view(torch.int32))
+    assert torch.equal(steps.idx, fused.idx)
+    cu, cb = w.cu_seqlens(), w.cu_budgets()
+    assert np.array_equal(b.DeviceProblem.bits(fused.k_out), pu.host_gather(k, fused.idx.cpu().numpy(), cu, cb))
+    return fused
+
+
+def batch(lens, heads=2, **over):
+    budgets = [max(W, W + (n - W) * (1 + i % 3) // 7) for i, n in enumerate(lens)]
+    return wl.scaled(wl.tiny(), seqlens=lens, budgets=budgets, window=W, n_q_heads=heads, n_kv_heads=heads, **over)
+
+
+@pytest.mark.parametrize("edge", [4, 1024, 2048, 4096, 8192, 16384, 32768, 49152, 65536])
+@pytest.mark.parametrize("off", [-1, 0, 1])
+def test_edges_of_the_workgroup_shapes(edge, off):
+    n = max(W, edge + off)
+    both(batch([n, W + 5, W, W + 1]))                              # the longest request picks the shape
+    both(batch([n], prior_weight=0.0), select_mode=1, span_budget_ratio=0.5)
+
+
+@pytest.mark.parametrize("longest", [2048, 4096, 8192, 16384])
+def test_many_problems_take_the_small_workgroups(longest):
+    both(batch([longest, longest - 3, 700, W + 2], heads=128))     # 512 problems
+
+
+@pytest.mark.parametrize("pool", [1, 3, 5, 7, 9, 11, 65, 1025])
+@pytest.mark.parametrize("variant", [0, 4, 8, 16, 4 | 8 | 16])
+def test_pooling_widths_and_readings(pool, variant):
+    both(batch([5003, 300, 33041, W + 40], pool_kernel=pool), score_variant=variant)
+
+
+def test_masses_of_several_row_splits_are_added():
+    both(wl.scaled(wl.qwen7b_32k(), n_layers=1, seqlens=[2000, 600], budgets=[700, 512], window=512, n_q_heads=8, n_kv_heads=2))
