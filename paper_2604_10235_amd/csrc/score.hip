@@ -194,6 +194,7 @@ int launch_score(const Plan& pl, const void* q, const void* k, const float* prio
   a.kv_sl = pl.kv_sl; a.kv_sh = pl.kv_sh; a.kv_st = pl.kv_st;
   a.c = pl.scale * 1.4426950408889634f;
   a.inv_g = (pl.variant & CODECOMP_VARIANT_GROUP_SUM) ? 1.0f : 1.0f / (float)pl.G;
+  a.inv_w = 1.0f / (float)pl.W;
   a.key_trim = pl.key_trim;
   a.blocks_per_head = (pl.variant & CODECOMP_VARIANT_GROUP_MAX) ? pl.W / 32 : 1;
   int rc;

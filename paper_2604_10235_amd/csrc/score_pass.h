@@ -65,6 +65,7 @@ struct ScoreArgs {
   int64_t q_sl, q_ss, q_sh, q_st, kv_sl, kv_sh, kv_st;
   float c;        // softmax_scale * log2(e)
   float inv_g;
+  float inv_w;    // 1 / W
 };
 
 #define NEG_BIG (-1.0e30f)
@@ -148,6 +149,10 @@ __host__ __device__ __forceinline__ void team_of(int b, int grid, int row_splits
     split = b % row_splits;
   }
 }
+
+// row / W for a row below 65536.  (row + 0.5) / W lies at least 0.5 / W away from every integer, and the rounding of the
+// reciprocal and of the product moves it by less than 65536 / W * 2^-22 = 0.016 / W.
+__device__ __forceinline__ int row_group(int row, float inv_w) { return (int)(((float)row + 0.5f) * inv_w); }
 
 // MFMA helper: D = A * B + C on one 32x32x16 bf16 step.  PASS 1 puts the keys on the A side
 // (output lane = query row), PASS 2 the queries (output lane = key).
@@ -273,22 +278,39 @@ __global__ __launch_bounds__(NW * 64, (NW >= 3 ? 2 : 1)) void score_pass_kernel(
   // The first K tile of the segment is sent for before the query rows, so that both arrive in one round trip.
   CODECOMP_GLOAD(kstart, stage)
 
-  // ---- this wave's query rows as MFMA fragments
+  // ---- this wave's query rows as MFMA fragments.  A fragment is 16 bytes of each of 32 rows: asked for like that, every
+  // load meets 32 cache lines and the rows of a workgroup cost four times as many line lookups as they have lines (times
+  // the k-steps that share a line).  So the rows come as whole cache lines, QP consecutive lanes per row, and the wave
+  // redistributes them through its own slice of the tile buffers (free between segments), 32 rows x QP pieces a round;
+  // the 16-byte pieces of a row are XOR-swizzled with the row number, so that neither side meets bank conflicts.
   u32x4 qf[2][KS];
+  constexpr int QP = 2 * LDS_ROWS * ROWB / NW >= 32 * 8 * 16 ? 8 : 4;    // pieces of a row per round: 128 or 64 bytes
+  constexpr int QROUNDS = CH_PER_ROW / QP;
+  constexpr int QL = QP / 2;                   // loads, and k-steps, per round
+  static_assert(NW * 32 * QP * 16 <= 2 * LDS_ROWS * ROWB, "query slices fit the tile buffers");
+  u32x4 qraw[2][KS];
   {
-    const uint16_t* qb = a.q + (int64_t)layer * a.q_sl + (int64_t)seq * a.q_ss;
+    const uint16_t* qb = a.q + (int64_t)layer * a.q_sl + (int64_t)seq * a.q_ss + (int64_t)(head * a.G) * a.q_sh;
 #pragma unroll
     for (int sl = 0; sl < 2; ++sl) {
-      const int row = split_row0 + rb_of[sl] * 32 + l32;
-      const bool ok = row < a.R && (sl == 0 || halves1 != 0);
-      const int g = ok ? row / a.W : 0;
-      const int t = ok ? row - g * a.W : 0;
-      const uint16_t* p = qb + (int64_t)(head * a.G + g) * a.q_sh + (int64_t)t * a.q_st + hf * 8;
+      if (sl == 1 && halves1 == 0) {
 #pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        u32x4 v = *reinterpret_cast<const u32x4*>(p + ks * 16);     // row 0 of the group when !ok: in bounds
-        if (!ok) v = u32x4{0, 0, 0, 0};
-        qf[sl][ks] = v;
+        for (int ks = 0; ks < KS; ++ks) qraw[1][ks] = u32x4{0, 0, 0, 0};
+        continue;
+      }
+#pragma unroll
+      for (int i = 0; i < QL; ++i) {
+        const int row = split_row0 + rb_of[sl] * 32 + (lane + 64 * i) / QP;
+        const bool ok = row < a.R;
+        const int g = ok ? row_group(row, a.inv_w) : 0;
+        const int t = ok ? row - g * a.W : 0;
+        const uint16_t* p = qb + (int64_t)g * a.q_sh + (int64_t)t * a.q_st + (lane % QP) * 8;
+#pragma unroll
+        for (int rd = 0; rd < QROUNDS; ++rd) {
+          u32x4 v = *reinterpret_cast<const u32x4*>(p + rd * QP * 8);     // row 0 of the group when !ok: in bounds
+          if (!ok) v = u32x4{0, 0, 0, 0};
+          qraw[sl][rd * QL + i] = v;
+        }
       }
     }
   }
@@ -310,6 +332,32 @@ __global__ __launch_bounds__(NW * 64, (NW >= 3 ? 2 : 1)) void score_pass_kernel(
         const float x = lse[row];                 // row < lrows: in bounds; padding rows get no weight
         nl[sl][v] = row < a.R ? -x : -INFINITY;
       }
+  }
+
+  {
+    unsigned char* slice = &ktile[0][0] + wave * (32 * QP * 16);
+    auto wave_sync = [&]() __attribute__((always_inline)) {      // LDS operations of one wave run in order: only the compiler has to keep it
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    };
+#pragma unroll
+    for (int sl = 0; sl < 2; ++sl)
+#pragma unroll
+      for (int rd = 0; rd < QROUNDS; ++rd) {
+#pragma unroll
+        for (int i = 0; i < QL; ++i) {
+          const int r = (lane + 64 * i) / QP;
+          *reinterpret_cast<u32x4*>(slice + (r * QP + ((lane ^ r) % QP)) * 16) = qraw[sl][rd * QL + i];
+        }
+        wave_sync();
+#pragma unroll
+        for (int k = 0; k < QL; ++k)
+          qf[sl][rd * QL + k] = *reinterpret_cast<const u32x4*>(slice + (l32 * QP + (((2 * k + hf) ^ l32) % QP)) * 16);
+        wave_sync();
+      }
+    // the slices become tile buffers again: every wave has to be done with its own
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
   }
 
   // Sum the per-wave column partials of one finished tile and store the attention mass (pass 2).
