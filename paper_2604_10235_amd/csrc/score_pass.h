@@ -130,9 +130,21 @@ __device__ __forceinline__ void locate_first(const int32_t* cu, int n_seqs, int 
   }
 }
 
-// Team (of `wgs`) whose tile range [g*total/wgs, (g+1)*total/wgs) holds tile x.
+// First tile of team g of `wgs`: floor(g * total / wgs) in 32 bits (g <= wgs <= 2048).
+__device__ __forceinline__ int first_tile(int g, int total, int wgs) {
+  const unsigned int each = (unsigned int)total / (unsigned int)wgs, left = (unsigned int)total - each * (unsigned int)wgs;
+  return (int)((unsigned int)g * each + (unsigned int)g * left / (unsigned int)wgs);
+}
+
+// Team (of `wgs`) whose tile range [first_tile(g), first_tile(g + 1)) holds tile x: the largest g with
+// g * total < (x + 1) * wgs.  The product in floats is off by far less than one (x * wgs / total < 2048, error below
+// 2^-9), so its whole part is at most one off.
 __device__ __forceinline__ int wg_of_tile(int x, int total, int wgs) {
-  return (int)((((int64_t)x + 1) * wgs + total - 1) / total) - 1;
+  const int64_t lim = ((int64_t)x + 1) * wgs;
+  int g = (int)((float)x * ((float)wgs / (float)total));
+  if ((int64_t)g * total >= lim) --g;
+  else if ((int64_t)(g + 1) * total < lim) ++g;
+  return g;
 }
 
 // Team and row split of workgroup b in a launch of `grid` workgroups (grid = teams * row_splits).  Workgroups are
@@ -201,8 +213,8 @@ __global__ __launch_bounds__(NW * 64, (NW >= 3 ? 2 : 1)) void score_pass_kernel(
   team = __builtin_amdgcn_readfirstlane(team);
   split = __builtin_amdgcn_readfirstlane(split);
   const int teams = (int)gridDim.x / a.row_splits;
-  const int x_begin = (int)((int64_t)team * a.total_tiles / teams);
-  const int x_end = (int)((int64_t)(team + 1) * a.total_tiles / teams);
+  const int x_begin = __builtin_amdgcn_readfirstlane(first_tile(team, a.total_tiles, teams));
+  const int x_end = __builtin_amdgcn_readfirstlane(first_tile(team + 1, a.total_tiles, teams));
   // the request the walk stands in: request cur_seq of problem cur_lz, whose lead begins at position cur_acc
   int cur_lz = x_begin / a.tiles_per_problem, cur_seq = 0, cur_acc = 0;
   if (a.n_seqs > 16 && x_begin < x_end)                      // few requests: walking there from the first one is as quick
