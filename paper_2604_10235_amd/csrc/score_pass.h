@@ -300,6 +300,12 @@ __global__ __launch_bounds__(NW * 64, (NW >= 3 ? 2 : 1)) void score_pass_kernel(
   constexpr int QROUNDS = CH_PER_ROW / QP;
   constexpr int QL = QP / 2;                   // loads, and k-steps, per round
   static_assert(NW * 32 * QP * 16 <= 2 * LDS_ROWS * ROWB, "query slices fit the tile buffers");
+  // What is derived from this copy of the lane number is computed anew for every segment: carried through the tile loop, as
+  // the compiler would do it otherwise, these offsets cost registers that the loop needs (head_dim 128, pass 2: 45 spilled
+  // registers with four waves, 8 with eight; now 4 and none).
+  int qlane = lane;
+  asm volatile("" : "+v"(qlane));
+  const int ql32 = qlane & 31, qhf = qlane >> 5;
   u32x4 qraw[2][KS];
   {
     const uint16_t* qb = a.q + (int64_t)layer * a.q_sl + (int64_t)seq * a.q_ss + (int64_t)(head * a.G) * a.q_sh;
@@ -312,11 +318,11 @@ __global__ __launch_bounds__(NW * 64, (NW >= 3 ? 2 : 1)) void score_pass_kernel(
       }
 #pragma unroll
       for (int i = 0; i < QL; ++i) {
-        const int row = split_row0 + rb_of[sl] * 32 + (lane + 64 * i) / QP;
+        const int row = split_row0 + rb_of[sl] * 32 + (qlane + 64 * i) / QP;
         const bool ok = row < a.R;
         const int g = ok ? row_group(row, a.inv_w) : 0;
         const int t = ok ? row - g * a.W : 0;
-        const uint16_t* p = qb + (int64_t)g * a.q_sh + (int64_t)t * a.q_st + (lane % QP) * 8;
+        const uint16_t* p = qb + (int64_t)g * a.q_sh + (int64_t)t * a.q_st + (qlane % QP) * 8;
 #pragma unroll
         for (int rd = 0; rd < QROUNDS; ++rd) {
           u32x4 v = *reinterpret_cast<const u32x4*>(p + rd * QP * 8);     // row 0 of the group when !ok: in bounds
@@ -340,7 +346,7 @@ __global__ __launch_bounds__(NW * 64, (NW >= 3 ? 2 : 1)) void score_pass_kernel(
     for (int sl = 0; sl < 2; ++sl)
 #pragma unroll
       for (int v = 0; v < 16; ++v) {
-        const int row = split_row0 + rb_of[sl] * 32 + 8 * (v >> 2) + 4 * hf + (v & 3);
+        const int row = split_row0 + rb_of[sl] * 32 + 8 * (v >> 2) + 4 * qhf + (v & 3);
         const float x = lse[row];                 // row < lrows: in bounds; padding rows get no weight
         nl[sl][v] = row < a.R ? -x : -INFINITY;
       }
@@ -359,13 +365,13 @@ __global__ __launch_bounds__(NW * 64, (NW >= 3 ? 2 : 1)) void score_pass_kernel(
       for (int rd = 0; rd < QROUNDS; ++rd) {
 #pragma unroll
         for (int i = 0; i < QL; ++i) {
-          const int r = (lane + 64 * i) / QP;
-          *reinterpret_cast<u32x4*>(slice + (r * QP + ((lane ^ r) % QP)) * 16) = qraw[sl][rd * QL + i];
+          const int r = (qlane + 64 * i) / QP;
+          *reinterpret_cast<u32x4*>(slice + (r * QP + ((qlane ^ r) % QP)) * 16) = qraw[sl][rd * QL + i];
         }
         wave_sync();
 #pragma unroll
         for (int k = 0; k < QL; ++k)
-          qf[sl][rd * QL + k] = *reinterpret_cast<const u32x4*>(slice + (l32 * QP + (((2 * k + hf) ^ l32) % QP)) * 16);
+          qf[sl][rd * QL + k] = *reinterpret_cast<const u32x4*>(slice + (ql32 * QP + (((2 * k + qhf) ^ ql32) % QP)) * 16);
         wave_sync();
       }
     // the slices become tile buffers again: every wave has to be done with its own
