@@ -95,7 +95,7 @@ typedef struct codecomp_params {
                                   64-key tile; with more than 512 softmax rows per KV head the rows are split over
                                   teams of workgroups and n is rounded down to whole teams)          */
   int32_t score_lead_tiles;    /* weight, in 64-key tiles, given to the start of a request when the tiles are shared
-                                  out: 0 = built-in value, < 0 = none, 1..64 = that many             */
+                                  out: 0 = built-in value (none in short calls), < 0 = none, 1..64 = that many */
 } codecomp_params;
 
 /* Other readings of what the paper leaves open about the tail of the score step (section
@@ -165,7 +165,8 @@ int codecomp_score(const void* q_obs, const void* k, const float* prior, const c
  * order row statistics -> row merge -> attention mass -> pool + prior.  Meant for per-kernel
  * timing and stage-wise debugging: a later stage reads what the earlier ones left in `workspace`,
  * so the stages of one problem must be enqueued in order with the same arguments.
- * CODECOMP_STAGE_ALL is exactly codecomp_score. */
+ * CODECOMP_STAGE_ALL is exactly codecomp_score (which in short calls does the row merge inside the mass kernel: there the
+ * stages one by one differ from it by the regrouping of fp32 sums). */
 enum {
   CODECOMP_STAGE_ROW_STATS = 1,   /* pass 1: per-chunk (max, sum) of every softmax row             */
   CODECOMP_STAGE_ROW_MERGE = 2,   /* log-sum-exp of every row over the chunks of its request       */

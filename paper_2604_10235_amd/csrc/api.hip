@@ -121,13 +121,14 @@ int make_plan(const codecomp_params* p, Plan* pl) {
   if ((pl->variant & CODECOMP_VARIANT_GROUP_MAX) && (pl->W % 32 != 0 || pl->row_splits != 1)) return CODECOMP_EINVAL_MODE;
   if (p->score_workgroups < 0 || p->score_lead_tiles > 64) return CODECOMP_EINVAL_SHAPE;
   pl->grid_override = p->score_workgroups;
-  pl->lead_tiles = p->score_lead_tiles == 0 ? kLeadTiles : (p->score_lead_tiles < 0 ? 0 : p->score_lead_tiles);
   int64_t tiles = 0;
   for (int r = 0; r < p->n_seqs; ++r) {
     int n = p->cu_seqlens_host[r + 1] - p->cu_seqlens_host[r] - pl->key_trim;     // >= 0: W <= N_r was checked
     tiles += (n + kTileKeys - 1) / kTileKeys;
   }
   const int64_t problems = (int64_t)pl->L * pl->Hkv * pl->row_splits;
+  const int automatic_lead = tiles > 0 && tiles * problems <= kNoLeadTiles ? 0 : kLeadTiles;
+  pl->lead_tiles = p->score_lead_tiles == 0 ? automatic_lead : (p->score_lead_tiles < 0 ? 0 : p->score_lead_tiles);
   const int64_t positions = tiles + (int64_t)pl->lead_tiles * pl->n_seqs;
   if (positions * problems > (1 << 30)) return CODECOMP_EINVAL_SHAPE;
   pl->tiles_per_problem = (int)positions;

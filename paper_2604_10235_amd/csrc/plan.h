@@ -12,8 +12,12 @@ constexpr int kRowsPerWave = 64;      // query rows (window x group) one wavefro
 constexpr int kMaxWaves = 8;          // wavefronts per workgroup in the score kernels
 constexpr int kTileKeys = 64;         // keys staged through LDS per pipeline step
 constexpr int kMaxScoreGrid = 2048;   // most workgroups a score pass is launched with
-constexpr int kMinTilesPerWorkgroup = 4;
 constexpr int kLeadTiles = 4;         // a segment start (query fragments, first K tile) costs about this many tiles
+// Calls of up to this many (tile, row split) pairs get no leads: a workgroup then has one tile or two and nearly all of them start
+// exactly one segment, so that a lead only leaves some workgroups idle and others with twice the tiles.  With -> without leads:
+// one layer of 1000 tokens (64 pairs) 26.7 -> 24.7 us, 2048 (128) 29.3 -> 26.8, 4093 with window 128 (512) 35.0 -> 32.4; 3000
+// tokens of 8 KV heads (376) 30.3 -> 28.4; 6000 (376) 33.1 -> 33.2.
+constexpr int kNoLeadTiles = 512;
 constexpr int kSelectManyProblems = 512;    // (layer, head, request) problems from which on several selection workgroups share a compute unit
 // Longer requests are selected by several workgroups each: parts of kPartChunk candidates, one 256-thread workgroup
 // per part and step (first-digit counts, the candidates near the cut, the ordered output; between the last two one

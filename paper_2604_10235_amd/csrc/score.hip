@@ -16,7 +16,7 @@ extern template int dispatch_waves<64, true>(const Plan&, const ScoreArgs&, hipS
 // asks for four of them at once, and their sums meet in LDS.  Kernel time with one thread per row that walks the segments
 // one after the other -> now: 2 layers of 8192 tokens (33 segments a row, 16 ways) 19.0 -> 4.7 us; one layer of 4093 tokens
 // (W 128) 10.7 -> 4.2; 4 layers of 20011 tokens 11.9 -> 4; 7168 problems (one way) 38.6 -> 38.9.
-constexpr int kMergeThreads = 256, kMergeBatch = 4, kMergeMaxWays = 16;
+constexpr int kMergeThreads = 256, kMergeMaxWays = 16;
 
 __global__ __launch_bounds__(kMergeThreads) void score_merge_kernel(ScoreArgs a, int ways_log2) {
   __shared__ int part[kMergeThreads / 64];
@@ -48,7 +48,7 @@ __global__ __launch_bounds__(kMergeThreads) void score_merge_kernel(ScoreArgs a,
     if (row < a.lrows) {
       const int split = row / (a.nb * 32);
       const int rb = (row - split * a.nb * 32) >> 5;
-      const int h0 = a.rb_holder[rb][0], h1 = a.rb_holder[rb][1];
+      const int h0 = (int)(a.rb_holder[rb] & 255u), h1 = (int)(a.rb_holder[rb] >> 8);
       const int two = h1 != 255 ? 1 : 0;
       const int items = segments << two;           // (segment, holder) pairs of this row
       // the segment of team g in this problem and row split sits in slot (g + p) * row_splits + split
@@ -231,8 +231,8 @@ int launch_score(const Plan& pl, const void* q, const void* k, const float* prio
   a.row_splits = pl.row_splits; a.nb = pl.row_blocks; a.srows = pl.waves * kRowsPerWave;
   a.lrows = pl.row_splits * pl.row_blocks * 32;
   for (int w = 0; w < kMaxWaves; ++w) a.wave_desc[w] = pl.wave_desc[w];
-  for (int b = 0; b < 2 * kMaxWaves; ++b) { a.rb_holder[b][0] = pl.rb_holder[b][0]; a.rb_holder[b][1] = pl.rb_holder[b][1]; }
-  a.lead = pl.lead_tiles; a.tiles_per_problem = pl.tiles_per_problem; a.total_tiles = pl.total_tiles; a.stat_teams = 0; a.T = pl.T;
+  for (int b = 0; b < 2 * kMaxWaves; ++b) a.rb_holder[b] = (uint32_t)pl.rb_holder[b][0] | (uint32_t)pl.rb_holder[b][1] << 8;
+  a.lead = pl.lead_tiles; a.tiles_per_problem = pl.tiles_per_problem; a.total_tiles = pl.total_tiles; a.stat_teams = 0; a.merge_in_mass = 0; a.T = pl.T;
   a.LH = pl.L * pl.Hkv;
   a.q_sl = pl.q_sl; a.q_ss = pl.q_ss; a.q_sh = pl.q_sh; a.q_st = pl.q_st;
   a.kv_sl = pl.kv_sl; a.kv_sh = pl.kv_sh; a.kv_st = pl.kv_st;

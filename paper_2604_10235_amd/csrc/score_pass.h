@@ -61,7 +61,8 @@ struct ScoreArgs {
   int key_trim;                      // keys at the end of every request left out of the softmax (prefix-only variant)
   int blocks_per_head;               // largest-head-mass variant: row blocks of one query head (window / 32)
   uint32_t wave_desc[kMaxWaves];     // row block of slot 0 | row block of slot 1 << 8 | halves of slot 1 << 16 (bit 0: first, bit 1: second)
-  uint8_t rb_holder[2 * kMaxWaves][2];   // per row block: the (wave * 2 + slot) indices that hold its statistics, 255 = none
+  uint32_t rb_holder[2 * kMaxWaves];     // per row block: the (wave * 2 + slot) indices that hold its statistics, first | second << 8, 255 = none
+  int merge_in_mass;                 // 1: pass 2 folds the row statistics itself, `lse` is not used
   int64_t q_sl, q_ss, q_sh, q_st, kv_sl, kv_sh, kv_st;
   float c;        // softmax_scale * log2(e)
   float inv_g;
@@ -165,6 +166,38 @@ __host__ __device__ __forceinline__ void team_of(int b, int grid, int row_splits
 // row / W for a row below 65536.  (row + 0.5) / W lies at least 0.5 / W away from every integer, and the rounding of the
 // reciprocal and of the product moves it by less than 65536 / W * 2^-22 = 0.016 / W.
 __device__ __forceinline__ int row_group(int row, float inv_w) { return (int)(((float)row + 0.5f) * inv_w); }
+
+// log2-sum-exp of one row: its statistics are (reference, sum) pairs, one per segment (`slot` pairs apart) and holder.  Two
+// half waves share them, each asks for BATCH at once; all lanes return the whole row's value.
+constexpr int kMergeBatch = 4;
+__device__ __forceinline__ float merge_row(const float2* st, int slot, int segments, uint32_t holders, int hf) {
+  constexpr int BATCH = 2 * kMergeBatch;
+  const int h0 = (int)(holders & 255u), h1 = (int)((holders >> 8) & 255u);
+  const int two = h1 != 255 ? 1 : 0;
+  const int items = segments << two;
+  float M = NEG_BIG, L = 0.f;
+  for (int i = 0; i < items; i += 2 * BATCH) {
+    float2 s[BATCH];
+#pragma unroll
+    for (int u = 0; u < BATCH; ++u) {
+      const int at = min(i + 2 * u + hf, items - 1);
+      s[u] = st[(int64_t)(at >> two) * slot + ((at & two) ? h1 : h0) * 32];
+    }
+    float Mn = M;
+#pragma unroll
+    for (int u = 0; u < BATCH; ++u) {
+      if (i + 2 * u + hf >= items) s[u] = make_float2(NEG_BIG, 0.f);
+      Mn = fmaxf(Mn, s[u].x);
+    }
+    L *= __builtin_amdgcn_exp2f(M - Mn);
+#pragma unroll
+    for (int u = 0; u < BATCH; ++u) L += s[u].y * __builtin_amdgcn_exp2f(s[u].x - Mn);
+    M = Mn;
+  }
+  const float Mo = __shfl_xor(M, 32), Lo = __shfl_xor(L, 32);
+  const float Mn = fmaxf(M, Mo);
+  return Mn + log2f(L * __builtin_amdgcn_exp2f(M - Mn) + Lo * __builtin_amdgcn_exp2f(Mo - Mn));
+}
 
 // MFMA helper: D = A * B + C on one 32x32x16 bf16 step.  PASS 1 puts the keys on the A side
 // (output lane = query row), PASS 2 the queries (output lane = key).
@@ -340,7 +373,27 @@ __global__ __launch_bounds__(NW * 64, (NW >= 3 ? 2 : 1)) void score_pass_kernel(
   float l_run0 = 0.f, l_run1 = 0.f;
   // pass 2 state: -lse of the 2 x 16 rows this lane holds in the S tiles
   float nl[2][16];
-  if constexpr (PASS == 2) {
+  // Workgroups of up to four waves: lane i and lane i + 32 bring the normaliser of row i of the block, which is dealt out
+  // through LDS below; in short calls they fold it from the row statistics themselves (see kMergeInMassSegments).
+  constexpr bool DEAL = PASS == 2 && NW <= 4;
+  float row_lse[2] = {0.f, 0.f};
+  if constexpr (DEAL) {
+    if (a.merge_in_mass) {
+      const int x0 = lz * a.tiles_per_problem + cur_acc + a.lead;
+      const int g0 = wg_of_tile(x0, a.total_tiles, a.stat_teams);
+      const int segments = wg_of_tile(x0 + tiles_of_seq - 1, a.total_tiles, a.stat_teams) - g0 + 1;
+      const float2* st = reinterpret_cast<const float2*>(a.stats) +
+                         ((int64_t)(lz * a.n_seqs + seq + g0) * a.row_splits + split) * a.srows + ql32;
+#pragma unroll
+      for (int sl = 0; sl < 2; ++sl)
+        if (sl == 0 || halves1 != 0) row_lse[sl] = merge_row(st, a.row_splits * a.srows, segments, a.rb_holder[rb_of[sl]], qhf);
+    } else {
+      const float* lse = a.lse + ((int64_t)lz * a.n_seqs + seq) * a.lrows + split_row0 + ql32;
+#pragma unroll
+      for (int sl = 0; sl < 2; ++sl)
+        if (sl == 0 || halves1 != 0) row_lse[sl] = lse[rb_of[sl] * 32];         // row < lrows: in bounds
+    }
+  } else if constexpr (PASS == 2) {
     const float* lse = a.lse + ((int64_t)lz * a.n_seqs + seq) * a.lrows;
 #pragma unroll
     for (int sl = 0; sl < 2; ++sl)
@@ -374,6 +427,20 @@ __global__ __launch_bounds__(NW * 64, (NW >= 3 ? 2 : 1)) void score_pass_kernel(
           qf[sl][rd * QL + k] = *reinterpret_cast<const u32x4*>(slice + (ql32 * QP + (((2 * k + qhf) ^ ql32) % QP)) * 16);
         wave_sync();
       }
+    if constexpr (DEAL) {
+#pragma unroll
+      for (int sl = 0; sl < 2; ++sl) {
+        const bool ok = split_row0 + rb_of[sl] * 32 + ql32 < a.R;
+        if (qhf == 0) reinterpret_cast<float*>(slice)[ql32] = ok ? -row_lse[sl] : -INFINITY;       // padding rows get no weight
+        wave_sync();
+#pragma unroll
+        for (int v = 0; v < 16; v += 4) {
+          const float4 x = *reinterpret_cast<const float4*>(slice + (2 * v + 4 * qhf) * 4);
+          nl[sl][v] = x.x; nl[sl][v + 1] = x.y; nl[sl][v + 2] = x.z; nl[sl][v + 3] = x.w;
+        }
+        wave_sync();
+      }
+    }
     // the slices become tile buffers again: every wave has to be done with its own
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
   }
@@ -394,7 +461,7 @@ __global__ __launch_bounds__(NW * 64, (NW >= 3 ? 2 : 1)) void score_pass_kernel(
           float cur = 0.f;
           for (int rb = 0; rb < a.nb; ++rb) {
             for (int h = 0; h < 2; ++h) {
-              const int holder = a.rb_holder[rb][h];      // wave * 2 + slot
+              const int holder = (a.rb_holder[rb] >> (8 * h)) & 255;      // wave * 2 + slot
               if (holder != 255) cur += colbuf[tile & 3][holder * 2][lane] + colbuf[tile & 3][holder * 2 + 1][lane];
             }
             if ((rb + 1) % a.blocks_per_head == 0 || rb == a.nb - 1) { s = fmaxf(s, cur); cur = 0.f; }
@@ -704,6 +771,15 @@ __global__ __launch_bounds__(NW * 64, (NW >= 3 ? 2 : 1)) void score_pass_kernel(
 #undef CODECOMP_SSTORE
 }
 
+// Up to this many segments of a row, pass 2 of workgroups of up to four waves folds the row statistics in its own prologue,
+// together with the loads of the query rows, instead of a merge kernel in between (a launch of about 4 us).  Measured, merge
+// kernel -> fold: one layer of 2048 tokens, head_dim 64 (9 segments) 28.5 -> 25.1 us; 8 layers of 9000, head_dim 64 58.0 ->
+// 55.7, 49.4 -> 47.5; 4 layers of 9000, 3 waves 67.5 -> 64.7; 8 layers of 20000, 4 waves 79.7 -> 78.9; 32 of 65536: the same.
+// Eight waves keep the kernel: with the fold compiled in, 28 layers of 32768 tokens took 935 us instead of 923, 64 short
+// requests x 28 layers 3.10 ms instead of 3.04.  With more segments every workgroup repeats a long chain of loads: one layer of
+// 4300 tokens, 2 KV heads, 4 waves (68 segments) 29.3 us with the kernel, 30.2 with the fold.
+constexpr int kMergeInMassSegments = 40;
+
 // Enqueues the row merge between the two passes (defined in score.hip).
 int launch_row_merge(const Plan& pl, const ScoreArgs& a, hipStream_t stream);
 
@@ -726,13 +802,14 @@ int resident_workgroups(Kernel kernel, int threads, std::atomic<int>* cache) {
   return cus * per_cu;
 }
 
-// Teams of one launch "wave": as many workgroups as the device holds at once (row_splits of them per team), each
-// team with an equal share of the tiles (at least kMinTilesPerWorkgroup, so that small problems are not all
-// prologue), unless the caller fixed the number of workgroups (codecomp_params.score_workgroups).
+// Teams of one launch "wave": as many workgroups as the device holds at once (row_splits of them per team), each team with
+// an equal share of the tiles, unless the caller fixed the number of workgroups (codecomp_params.score_workgroups).  Short calls go
+// down to one tile per workgroup: a pass is then one segment start and one tile long, with at least four tiles (fewer
+// segments to merge) it was longer: one layer of 2048 tokens, head_dim 64 25.6 -> 20.0 us (call), 4093 with window 128
+// 39.3 -> 35.4, 1000 with 4 KV heads 34.2 -> 26.9, 2048 36.6 -> 29.3.
 inline int score_teams(const Plan& pl, int resident) {
   int g = (resident > 0 ? resident : 256) / pl.row_splits;
   if (pl.grid_override > 0) g = pl.grid_override / pl.row_splits;
-  else g = g < pl.real_tiles / kMinTilesPerWorkgroup ? g : pl.real_tiles / kMinTilesPerWorkgroup;
   if (g > pl.real_tiles) g = pl.real_tiles;
   if (g > kMaxScoreGrid / pl.row_splits) g = kMaxScoreGrid / pl.row_splits;
   return g < 1 ? 1 : g;
@@ -748,7 +825,12 @@ int launch_passes(const Plan& pl, ScoreArgs a, hipStream_t stream, unsigned stag
     score_pass_kernel<D, NW, 1, false, K8><<<dim3(a.stat_teams * pl.row_splits), block, 0, stream>>>(a);
     if (hipError_t e = hipGetLastError()) return (int)e;
   }
-  if (stages & CODECOMP_STAGE_ROW_MERGE) {
+  // segments of the longest request at most
+  const int max_tiles = (pl.max_n - pl.key_trim + kTileKeys - 1) / kTileKeys;
+  const int64_t max_segments = pl.total_tiles > 0 ? (int64_t)max_tiles * a.stat_teams / pl.total_tiles + 2 : 0;
+  constexpr unsigned kAllThree = CODECOMP_STAGE_ROW_STATS | CODECOMP_STAGE_ROW_MERGE | CODECOMP_STAGE_MASS;
+  a.merge_in_mass = NW <= 4 && (stages & kAllThree) == kAllThree && max_segments <= kMergeInMassSegments;
+  if ((stages & CODECOMP_STAGE_ROW_MERGE) && !a.merge_in_mass) {
     if (int rc = launch_row_merge(pl, a, stream)) return rc;
   }
   if ((stages & CODECOMP_STAGE_MASS) && any_tile) {

@@ -1,0 +1,35 @@
+"""Branches that short calls and crowded selections take: pass 2 folding the row statistics itself (workgroups of up to four
+waves, few segments per request) against the merge kernel, one tile per workgroup, and the cut found in lists that just fit
+and just do not fit the registers of the resolving workgroup."""
+import numpy as np
+import pytest
+
+from oracle import codecomp_oracle as orc
+from paper_2604_10235_amd import workloads as wl
+from tests import parity_util as pu
+from tests.test_gpu_select_cases import W, select_on_device
+
+pytestmark = pytest.mark.gpu
+
+
+# Workgroups of 1, 2, 3, 4 and 8 waves; 76 tiles of one head over 2 .. 76 workgroups, which is as many segments per row, on
+# both sides of the limit (40, which counts two more); a last tile of one key; several requests.
+@pytest.mark.parametrize("group,window", [(1, 32), (2, 50), (5, 32), (7, 32), (9, 32)])
+@pytest.mark.parametrize("lens,wgs", [([4801], 0), ([4801], 2), ([4801], 33), ([4801], 38), ([4801], 39), ([700, 64, 65, 1300], 0),
+                                      ([700, 64, 65, 1300], 5)])
+def test_row_statistics_folded_by_the_second_pass(group, window, lens, wgs):
+    import torch
+    from paper_2604_10235_amd import binding as b
+    w = wl.scaled(wl.qwen7b_32k(), n_layers=1, n_q_heads=group, n_kv_heads=1, window=window, seqlens=lens, budgets=lens)
+    q, k, v, prior = wl.make_all(w)
+    whole, steps = (b.DeviceProblem(w, q, k, v, prior, score_workgroups=wgs) for _ in range(2))
+    whole.workspace.fill_(0xFF)                                    # nothing may be read before it is written
+    whole.score()
+    for stage in (b.STAGE_ROW_STATS, b.STAGE_ROW_MERGE, b.STAGE_MASS, b.STAGE_FINISH):
+        steps.score_stages(stage)
+    torch.cuda.synchronize()
+    got = whole.scores.cpu().numpy()
+    # the two fold the same (reference, sum) pairs in another order: a normaliser below 2^5 in units of log2 is rounded twice
+    # on either side, 4 * 2^-19 * ln 2 = 5.3e-6
+    np.testing.assert_allclose(got, steps.scores.cpu().numpy(), rtol=5.3e-6, atol=1e-30)
+    pu.assert_scores_close(got, orc.score_packed(q, k, prior, w.cu_seqlens(), pool_kernel=w.pool_kernel, prior_weight=w.prior_weight))
