@@ -966,21 +966,37 @@ __device__ __forceinline__ void part_digit(PartShared& sh, const uint32_t* list,
   __syncthreads();
 }
 
-// resolve: one workgroup per problem finishes the radix select on the request's list (two more digits) and leaves
-// the key of the cut and the number of candidates tied at it that are admitted.
+// resolve: one workgroup per problem finds the cut in the request's list and leaves its key and the number of candidates
+// tied at it that are admitted.  A list of up to 16384 keys stays in registers and takes the counting rounds of the
+// one-workgroup selection (find_cut): a prior that puts every marked token into one bin of the first digit leaves thousands
+// of keys, most of them equal in the next digit too, whose LDS atomics then wait for one another.  Longer lists take two
+// more radix digits.
 constexpr int kResolveThreads = 1024;     // the list is read with 8 loads in flight per thread: many threads, few rounds
+constexpr int kResolveItems = 16;
 __global__ __launch_bounds__(kResolveThreads) void part_resolve_kernel(SelectArgs a, PartArgs c) {
   __shared__ PartShared sh;
+  __shared__ SelectShared<kResolveThreads> cut;
   const int seq = blockIdx.x, lz = blockIdx.y;
   uint32_t* h = c.head + ((int64_t)lz * a.n_seqs + seq) * 8;
   if ((int)h[0] != kModeSelect) return;                      // the same for every thread
   const uint32_t* list = c.list + (int64_t)lz * a.T + a.cu_seqlens[seq];
   const int m = (int)h[3];
-  uint32_t prefix = h[1] << 21, remaining = h[2];
-  part_digit<kResolveThreads>(sh, list, m, 10, 2048, 0xFFE00000u, prefix, remaining);
-  part_digit<kResolveThreads>(sh, list, m, 0, 1024, 0xFFFFFC00u, prefix, remaining);
-  const uint32_t tau = prefix;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  uint32_t tau = h[1] << 21, remaining = h[2];
+  if (m <= kResolveThreads * kResolveItems) {                // the same for every thread
+    const rsrc_t row = row_of(list, m);
+    const int slots = ((m + kResolveThreads - 1) / kResolveThreads + 3) / 4 * 4;
+    uint32_t keys[kResolveItems];
+#pragma unroll
+    for (int s = 0; s < kResolveItems; ++s)                  // past the list: 0, no candidate
+      keys[s] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(row, tid * 4, s * kResolveThreads * 4, 0);
+    int ties;
+    find_cut<kResolveThreads, kResolveItems>(cut, keys, slots, m, remaining, tau, ties);
+    remaining = (uint32_t)ties;
+  } else {
+    part_digit<kResolveThreads>(sh, list, m, 10, 2048, 0xFFE00000u, tau, remaining);
+    part_digit<kResolveThreads>(sh, list, m, 0, 1024, 0xFFFFFC00u, tau, remaining);
+  }
   // How many list entries of each part lie above the cut / are tied at it, as running totals over the parts: an
   // emitting part then knows what the earlier parts contribute without reading their stretch of the list again.
   const int npre = a.cu_seqlens[seq + 1] - a.cu_seqlens[seq] - a.W;
@@ -1025,21 +1041,34 @@ __global__ __launch_bounds__(kResolveThreads) void part_resolve_kernel(SelectArg
     __syncthreads();
   };
   running(seg_end, false);
+  // The 64 entries that a wave reads at once follow one another, so most of the time one part holds all of them: then two
+  // additions per wave instead of one per entry at the same address.
+  auto part_of_entry = [&](int i) __attribute__((always_inline)) {      // first part whose stretch ends beyond entry i
+    int lo = 0, hi = nparts - 1;
+    while (lo < hi) {
+      const int mid = (lo + hi) >> 1;
+      if (seg_end[mid] > (unsigned int)i) hi = mid; else lo = mid + 1;
+    }
+    return lo;
+  };
   constexpr int UNR = 8;
-  for (int i0 = tid; i0 < m; i0 += kResolveThreads * UNR) {
+  for (int w0 = wave * 64; w0 < m; w0 += kResolveThreads * UNR) {
     uint32_t k[UNR];
 #pragma unroll
-    for (int u = 0; u < UNR; ++u) k[u] = list[min(i0 + u * kResolveThreads, m - 1)];
+    for (int u = 0; u < UNR; ++u) k[u] = list[min(w0 + lane + u * kResolveThreads, m - 1)];
 #pragma unroll
     for (int u = 0; u < UNR; ++u) {
-      const int i = i0 + u * kResolveThreads;
-      if (i >= m || k[u] < tau) continue;
-      int lo = 0, hi = nparts - 1;                           // first part whose stretch ends beyond i
-      while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        if (seg_end[mid] > (unsigned int)i) hi = mid; else lo = mid + 1;
+      const int i0 = w0 + u * kResolveThreads, i = i0 + lane;
+      if (i0 >= m) continue;                                            // the same for the whole wave
+      const bool above = i < m && k[u] > tau, tied = i < m && k[u] == tau;
+      const int first_part = part_of_entry(i0);
+      if (seg_end[first_part] >= (unsigned int)min(i0 + 64, m)) {
+        const int na = __popcll(__ballot(above)), nt = __popcll(__ballot(tied));
+        if (lane == 0 && na > 0) atomicAdd(&n_above[first_part], (unsigned int)na);
+        if (lane == 0 && nt > 0) atomicAdd(&n_tied[first_part], (unsigned int)nt);
+      } else if (above || tied) {
+        atomicAdd(above ? &n_above[part_of_entry(i)] : &n_tied[part_of_entry(i)], 1u);
       }
-      atomicAdd(k[u] > tau ? &n_above[lo] : &n_tied[lo], 1u);
     }
   }
   __syncthreads();

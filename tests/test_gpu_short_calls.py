@@ -33,3 +33,23 @@ def test_row_statistics_folded_by_the_second_pass(group, window, lens, wgs):
     # on either side, 4 * 2^-19 * ln 2 = 5.3e-6
     np.testing.assert_allclose(got, steps.scores.cpu().numpy(), rtol=5.3e-6, atol=1e-30)
     pu.assert_scores_close(got, orc.score_packed(q, k, prior, w.cu_seqlens(), pool_kernel=w.pool_kernel, prior_weight=w.prior_weight))
+
+
+@pytest.mark.parametrize("crowd", [1, 63, 65, 16383, 16384, 16385, 40000])
+@pytest.mark.parametrize("together", [False, True])
+def test_cut_inside_a_crowded_first_digit(crowd, together):
+    """`crowd` candidates share the first digit (values in [1, 1.25)) and the cut lies among them; scattered over all parts or
+    next to one another (whole wavefronts of one part, and the seams between parts)."""
+    npre = 70001
+    g = np.random.default_rng(crowd)
+    rows = []
+    for values in (np.full(crowd, 1.125), 1.0 + g.integers(0, 5, crowd) / 32, 1.0 + g.random(crowd) * 0.2):
+        r = np.full(npre + W, 0.25, np.float32)
+        at = 8192 - crowd // 3 if together else 0
+        where = np.arange(max(at, 0), max(at, 0) + crowd) if together else g.choice(npre, size=crowd, replace=False)
+        r[where] = values.astype(np.float32)
+        rows.append(r)
+    rows = np.stack(rows)
+    for need in sorted({1, crowd // 2 + 1, crowd}):
+        idx, _, _ = select_on_device(rows, [npre + W], [need + W])
+        assert np.array_equal(idx[0].astype(np.int64), orc.select(rows.astype(np.float64), W, need + W)), need
