@@ -93,7 +93,11 @@ __global__ __launch_bounds__(kMergeThreads) void score_merge_kernel(ScoreArgs a,
   }
 }
 
-constexpr int kFinishTile = 2048;     // tokens per workgroup of the finish kernel (one round of workgroups at the bench size)
+// A workgroup of the finish kernel takes 256 * PER tokens.  It is a chain of latencies (bounds, masses, barrier, a sum over
+// neighbours per token), so few problems take short ones that fill the device: from 512 workgroups of 2048 tokens on (one round
+// or more of them) the long ones, which share the loads at the edges.  4 layers of 20011 tokens: 10.6 us as 160 workgroups of
+// 2048 tokens, 4.8 as 640 of 512.
+constexpr int kFinishLong = 8, kFinishShort = 2, kFinishFill = 512;
 
 __device__ __forceinline__ int request_of(const int32_t* cu, int n_seqs, int j) {
   int lo = 0, hi = n_seqs;              // cu[lo] <= j < cu[lo+1]
@@ -110,14 +114,15 @@ __device__ __forceinline__ int request_of(const int32_t* cu, int n_seqs, int j) 
 // Everything that comes from memory (request bounds, prior, u) is asked for before the one barrier, so
 // that a workgroup pays one memory round trip.  A tile that lies inside one request (the common case)
 // takes that request's bounds once; otherwise every token looks its request up.
+template <int PER>
 __global__ __launch_bounds__(256) void score_finish_kernel(FinishArgs a) {
-  constexpr int PER = kFinishTile / 256;
-  __shared__ float tile[kFinishTile + 2 * kFinishHalo];
+  constexpr int kTokens = 256 * PER;
+  __shared__ float tile[kTokens + 2 * kFinishHalo];
   const int tid = threadIdx.x;
   const int lz = blockIdx.y;
-  const int base = blockIdx.x * kFinishTile;
+  const int base = blockIdx.x * kTokens;
   const int half = (a.pool - 1) >> 1;
-  const int last = min(base + kFinishTile, a.T) - 1;
+  const int last = min(base + kTokens, a.T) - 1;
   const int r_first = request_of(a.cu_seqlens, a.n_seqs, base), r_last = request_of(a.cu_seqlens, a.n_seqs, last);
   const bool one_request = r_first == r_last;
   int lo_[PER], hi_[PER];               // request bounds [lo, hi) of each of this thread's tokens
@@ -160,7 +165,7 @@ __global__ __launch_bounds__(256) void score_finish_kernel(FinishArgs a) {
   }
   // the halo on both sides: 2 * half tokens that belong to the neighbouring tiles
   for (int i = tid; i < 2 * half; i += 256) {
-    const int x = i < half ? base - half + i : base + kFinishTile + (i - half);
+    const int x = i < half ? base - half + i : base + kTokens + (i - half);
     float val = 0.f;
     bool has_mass = x >= 0 && x < a.T;
     if (has_mass && a.mass_trim > 0)
@@ -248,7 +253,10 @@ int launch_score(const Plan& pl, const void* q, const void* k, const float* prio
   if (!(stages & CODECOMP_STAGE_FINISH)) return 0;
 
   const FinishArgs f = finish_args(pl, prior, scores, workspace);
-  score_finish_kernel<<<dim3((pl.T + kFinishTile - 1) / kFinishTile, pl.L * pl.Hkv), dim3(256), 0, stream>>>(f);
+  const int lh = pl.L * pl.Hkv;
+  const int64_t long_ones = (int64_t)((pl.T + 256 * kFinishLong - 1) / (256 * kFinishLong)) * lh;
+  if (long_ones >= kFinishFill) score_finish_kernel<kFinishLong><<<dim3((pl.T + 256 * kFinishLong - 1) / (256 * kFinishLong), lh), dim3(256), 0, stream>>>(f);
+  else score_finish_kernel<kFinishShort><<<dim3((pl.T + 256 * kFinishShort - 1) / (256 * kFinishShort), lh), dim3(256), 0, stream>>>(f);
   if (hipError_t e = hipGetLastError()) return (int)e;
   return 0;
 }

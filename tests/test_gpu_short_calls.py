@@ -53,3 +53,20 @@ def test_cut_inside_a_crowded_first_digit(crowd, together):
     for need in sorted({1, crowd // 2 + 1, crowd}):
         idx, _, _ = select_on_device(rows, [npre + W], [need + W])
         assert np.array_equal(idx[0].astype(np.int64), orc.select(rows.astype(np.float64), W, need + W)), need
+
+
+@pytest.mark.parametrize("heads", [511, 512])
+@pytest.mark.parametrize("pool,variant", [(1, 0), (7, 0), (1025, 0), (7, 4 | 8 | 16)])
+def test_pooling_by_short_and_long_workgroups(heads, pool, variant):
+    """Below 512 workgroups of 2048 tokens the scores are pooled by workgroups of 512: seams inside and between requests."""
+    import torch
+    from paper_2604_10235_amd import binding as b
+    from tests.test_gpu_parity import oracle_variant
+    lens = [509, 3, 70, 900]
+    w = wl.scaled(wl.tiny(), n_q_heads=heads, n_kv_heads=heads, window=2, seqlens=lens, budgets=lens, pool_kernel=pool)
+    q, k, v, prior = wl.make_all(w)
+    p = b.DeviceProblem(w, q, k, v, prior, score_variant=variant)
+    p.score()
+    torch.cuda.synchronize()
+    pu.assert_scores_close(p.scores.cpu().numpy(), orc.score_packed(q, k, prior, w.cu_seqlens(), pool_kernel=pool,
+                                                                    prior_weight=w.prior_weight, **oracle_variant(variant)))
