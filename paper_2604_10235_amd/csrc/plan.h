@@ -32,7 +32,6 @@ constexpr int kPartMinCandidates = 16384;
 constexpr int kPartFewProblems = 100;
 constexpr int kFirstDigitBins = 2048;
 constexpr int kFinishHalo = 512;      // largest supported (pool_kernel - 1) / 2
-constexpr int kSmallHalo = 32;        // ... by the 256-thread workgroups of the fused tail
 
 struct Plan {
   int L, Hq, Hkv, G, d, W, pool, n_seqs;
