@@ -14,7 +14,7 @@
 // instead of shuffles, register-to-register prefix sums, 16-byte loads and stores through buffer descriptors.  Measured
 // (kernel times, the separate pooling kernel + the three-digit radix selection of 1024 threads before -> now): 2048 tokens
 // x 4 problems 17.7 -> 4.6 us; 8192 x 8: 21.4 -> 7.7; 32768 x 112: 46.6 -> 26.4; 65536 x 256: 147 -> 69; sixteen requests
-// of 8K .. 48K x 4 (by parts before): 67 -> 34; 64 requests of 128 .. 2300 x 112: 130 -> 31 us.
+// of 8K .. 48K x 4 (by parts before): 67 -> 34; 64 requests of 135 .. 1831 x 112: 130 -> 31 us (142 .. 2313, next larger workgroup: 54).
 // A batch with a longer request: every request is cut into parts of 8192 candidates and four kernels run one 256-thread
 // workgroup per part (the third one per request), so that a problem is spread over as many compute units as it has parts:
 //   counts  every part counts the first digit of its candidates (2048 bins) and stores the counts;
@@ -1171,7 +1171,7 @@ __global__ __launch_bounds__(kPartThreads) void part_emit_kernel(SelectArgs a, P
 // its compute unit to itself, and many threads with few candidates each are quickest (8192 tokens: 7.7 us with 1024 x 8 against
 // 10.5 with 512 x 16; 4093: 6.1 with 1024 x 4 against 9.4 with 256 x 16; 2048: 4.6 with 512 x 4 against 6.8 with 1024 x 8).
 // Many problems: smaller workgroups, of which several share a compute unit, spend less on barriers and on work that every
-// wave repeats (7168 problems of 128 .. 2300 tokens: 31 us with 256 x 8).
+// wave repeats (7168 problems of 135 .. 1831 tokens: 31 us with 256 x 8; of 142 .. 2313: 54 with 256 x 16).
 template <class Launch>
 static void dispatch_items(int longest, int64_t problems, Launch launch) {
   auto with = [&](auto nt, auto items) { launch(nt, items); };
