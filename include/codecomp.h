@@ -165,8 +165,10 @@ int codecomp_score(const void* q_obs, const void* k, const float* prior, const c
  * order row statistics -> row merge -> attention mass -> pool + prior.  Meant for per-kernel
  * timing and stage-wise debugging: a later stage reads what the earlier ones left in `workspace`,
  * so the stages of one problem must be enqueued in order with the same arguments.
- * CODECOMP_STAGE_ALL is exactly codecomp_score (which in short calls does the row merge inside the mass kernel: there the
- * stages one by one differ from it by the regrouping of fp32 sums). */
+ * CODECOMP_STAGE_ALL is exactly codecomp_score, which in short calls does the row merge inside the mass kernel: there the
+ * stages one by one differ from it by the regrouping of fp32 sums.  The row normalisers are left in `workspace` either
+ * way, so that a stage asked for again after codecomp_score (or after the first three stages in one call) finds
+ * what it reads, and the mass kernel alone gives the same bits again. */
 enum {
   CODECOMP_STAGE_ROW_STATS = 1,   /* pass 1: per-chunk (max, sum) of every softmax row             */
   CODECOMP_STAGE_ROW_MERGE = 2,   /* log-sum-exp of every row over the chunks of its request       */

@@ -62,7 +62,7 @@ struct ScoreArgs {
   int blocks_per_head;               // largest-head-mass variant: row blocks of one query head (window / 32)
   uint32_t wave_desc[kMaxWaves];     // row block of slot 0 | row block of slot 1 << 8 | halves of slot 1 << 16 (bit 0: first, bit 1: second)
   uint32_t rb_holder[2 * kMaxWaves];     // per row block: the (wave * 2 + slot) indices that hold its statistics, first | second << 8, 255 = none
-  int merge_in_mass;                 // 1: pass 2 folds the row statistics itself, `lse` is not used
+  int merge_in_mass;                 // 1: pass 2 folds the row statistics itself and leaves them in `lse`
   int64_t q_sl, q_ss, q_sh, q_st, kv_sl, kv_sh, kv_st;
   float c;        // softmax_scale * log2(e)
   float inv_g;
@@ -387,6 +387,14 @@ __global__ __launch_bounds__(NW * 64, (NW >= 3 ? 2 : 1)) void score_pass_kernel(
 #pragma unroll
       for (int sl = 0; sl < 2; ++sl)
         if (sl == 0 || halves1 != 0) row_lse[sl] = merge_row(st, a.row_splits * a.srows, segments, a.rb_holder[rb_of[sl]], qhf);
+      // the workgroup with the request's first tile leaves them where the merge kernel would: a later call may ask for this
+      // pass alone on the same workspace
+      if (tile_in_seq == 0 && qhf == 0) {
+        float* lse = a.lse + ((int64_t)lz * a.n_seqs + seq) * a.lrows + split_row0 + ql32;
+#pragma unroll
+        for (int sl = 0; sl < 2; ++sl)
+          if (sl == 0 || halves1 != 0) lse[rb_of[sl] * 32] = row_lse[sl];        // row < lrows: in bounds
+      }
     } else {
       const float* lse = a.lse + ((int64_t)lz * a.n_seqs + seq) * a.lrows + split_row0 + ql32;
 #pragma unroll

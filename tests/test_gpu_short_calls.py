@@ -35,6 +35,31 @@ def test_row_statistics_folded_by_the_second_pass(group, window, lens, wgs):
     pu.assert_scores_close(got, orc.score_packed(q, k, prior, w.cu_seqlens(), pool_kernel=w.pool_kernel, prior_weight=w.prior_weight))
 
 
+@pytest.mark.parametrize("group,window", [(1, 32), (2, 50), (5, 32), (7, 32), (9, 32), (20, 32)])
+@pytest.mark.parametrize("lens,variant", [([700, 64, 65, 1300], 0), ([50, 700, 51, 1300], 8)])
+def test_stages_asked_for_again_after_a_whole_call(group, window, lens, variant):
+    """Whatever the whole call merges on its way, it leaves what the mass kernel and the pooling alone read afterwards: the
+    same bits from them (1, 2, 3, 4 and 8 waves, two row splits; requests without a key of their own included)."""
+    import torch
+    from paper_2604_10235_amd import binding as b
+    w = wl.scaled(wl.qwen7b_32k(), n_layers=2, n_q_heads=2 * group, n_kv_heads=2, window=window, seqlens=[max(n, window) for n in lens],
+                  budgets=[max(n, window) for n in lens])
+    q, k, v, prior = wl.make_all(w)
+    first_three = b.STAGE_ROW_STATS | b.STAGE_ROW_MERGE | b.STAGE_MASS
+    for whole in (lambda p: p.score(), lambda p: p.compress(), lambda p: p.score_stages(first_three)):
+        p = b.DeviceProblem(w, q, k, v, prior, score_variant=variant)
+        p.score()
+        want = p.scores.clone()
+        p.workspace.fill_(0xFF)
+        whole(p)
+        p.scores.fill_(float("nan"))
+        for stages in ((b.STAGE_MASS, b.STAGE_FINISH), (b.STAGE_MASS | b.STAGE_FINISH,), (b.STAGE_FINISH,)):
+            for stage in stages:
+                p.score_stages(stage)
+            torch.cuda.synchronize()
+            assert torch.equal(p.scores.view(torch.int32), want.view(torch.int32)), stages
+
+
 @pytest.mark.parametrize("crowd", [1, 63, 65, 16383, 16384, 16385, 40000])
 @pytest.mark.parametrize("together", [False, True])
 def test_cut_inside_a_crowded_first_digit(crowd, together):
