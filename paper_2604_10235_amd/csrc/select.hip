@@ -37,6 +37,7 @@
 //                tokens not in P.
 #include <type_traits>
 
+#include "cut_range.h"
 #include "plan.h"
 
 namespace codecomp {
@@ -56,7 +57,6 @@ __device__ __forceinline__ uint32_t order_key(float x) {
 // One workgroup per problem.
 // ---------------------------------------------------------------------------------------------------------
 
-constexpr int kCutBins = 2048;      // bins of one counting round
 constexpr int kCutList = 128;       // keys left to rank by comparing them with one another
 
 // Slot s of thread tid holds candidate j = (s / 4) * 4 * NT + 4 * tid + s % 4: four consecutive candidates per thread and
@@ -195,7 +195,7 @@ __device__ __forceinline__ void find_cut(SelectShared<NT>& sh, const uint32_t (&
   uint32_t from = 0, span = hi - lo;             // counted: keys lo + from .. lo + from + span
   for (;;) {
     const uint32_t width = hi - lo;
-    const int shift = width < (uint32_t)kCutBins ? 0 : 21 - __builtin_clz(width);
+    const int shift = cut_shift(width);
     for_slots<ITEMS>(slots, [&](int s) {
       if ((take >> (s % kSampleEvery != 0)) & 1) {
         const uint32_t d = keys[s] - lo;                      // 0 and kForced lie outside every range
@@ -223,14 +223,16 @@ __device__ __forceinline__ void find_cut(SelectShared<NT>& sh, const uint32_t (&
       continue;
     }
     take = kAll;
-    lo += bin << shift;
+    cut_narrow(lo, hi, bin, shift);
     rank = rank_in_bin;
     if (shift == 0) { tau = lo; ties = (int)rank; return; }
-    hi = min(hi, lo + ((1u << shift) - 1u));
     if (count <= kCutList) {
       const uint32_t w = hi - lo;
       for_slots<ITEMS>(slots, [&](int s) {
-        if (keys[s] - lo <= w) sh.list[atomicAdd(&sh.list_n, 1u)] = keys[s];     // `count` entries, in any order
+        if (keys[s] - lo <= w) {                              // `count` entries, in any order
+          const unsigned int at = atomicAdd(&sh.list_n, 1u);
+          if (at < (unsigned int)kCutList) sh.list[at] = keys[s];              // always: belt and braces
+        }
       });
       __syncthreads();
       if (tid < count) {
@@ -373,14 +375,16 @@ __device__ __forceinline__ void load_row(rsrc_t row, float (&x)[ITEMS]) {
 template <int NT>
 __device__ __forceinline__ int slots_of(int count) { return (count + 4 * NT - 1) / (4 * NT) * 4; }
 
-// Keys in registers -> indices of the kept tokens at `out`: the best `need` competing ones (and the forced ones).
+// Keys in registers -> indices of the `kept` tokens at `out`: the best `need` competing ones and the forced ones, or all.
 template <int NT, int ITEMS>
 __device__ __forceinline__ void select_and_emit(SelectShared<NT>& sh, const uint32_t (&keys)[ITEMS], int slots, int npre, int competing,
-                                                int need, bool all, int32_t* out) {
+                                                int need, bool all, int kept, int32_t* out) {
   uint32_t tau = all ? 0u : kForced - 1u;       // every candidate / the forced ones only
   int ties = 0;
   if (!all && need > 0) find_cut<NT, ITEMS>(sh, keys, slots, competing, (uint32_t)need, tau, ties);
-  emit_in_order<false, NT, ITEMS>(sh, keys, slots, npre, tau, ties, [&](int j, bool, int pos) { out[pos] = j; });
+  emit_in_order<false, NT, ITEMS>(sh, keys, slots, npre, tau, ties, [&](int j, bool, int pos) {
+    if ((unsigned)pos < (unsigned)kept) out[pos] = j;          // pos < kept always: belt and braces
+  });
 }
 
 // additive rule: one selection on the fused scores; two-stage rule, stage 2 (FILL): attention fills what stage 1 left
@@ -414,7 +418,7 @@ __global__ __launch_bounds__(NT) void select_kernel(SelectArgs a) {
     if constexpr (FILL) keys[s] = member[s] ? kForced : keys[s];
   }
   const int members = FILL ? a.member_count[seq] : 0;
-  select_and_emit<NT, ITEMS>(sh, keys, slots, npre, npre - members, bp - members, bp >= npre, out);
+  select_and_emit<NT, ITEMS>(sh, keys, slots, npre, npre - members, bp - members, bp >= npre, bp, out);
 }
 
 // The tail of the fused call in one kernel: the attention mass of a request is pooled, the prior added, the scores stored
@@ -538,7 +542,7 @@ __global__ __launch_bounds__(NT) void finish_select_kernel(SelectArgs a, FinishA
   if (bp <= 0) return;
   const int slots = slots_of<NT>(npre);
   const int members = FILL ? a.member_count[seq] : 0;
-  select_and_emit<NT, ITEMS>(sh, keys, slots, npre, npre - members, bp - members, bp >= npre, out);
+  select_and_emit<NT, ITEMS>(sh, keys, slots, npre, npre - members, bp - members, bp >= npre, bp, out);
 }
 
 // two-stage rule, stage 1: once per request (the prior is shared by layers and heads)

@@ -150,6 +150,34 @@ def test_select_with_small_workgroups(longest):
         assert np.array_equal(idx[l].astype(np.int64), want), l
 
 
+@pytest.mark.parametrize("npre,layers", [(700, 1), (1501, 1), (5000, 1), (12001, 1), (30001, 1), (60001, 1), (65537, 1), (70001, 1),
+                                         (2047, 128), (8190, 128)])
+def test_select_where_scores_are_nan(npre, layers):
+    """NaN of both signs and any payload, up to the one whose key is the largest of all: where they are ordered is not
+    specified, but the kept indices ascend, the others are the best of the ordinary scores, and nothing else is written."""
+    g = np.random.default_rng(npre)
+    n = npre + W
+    rows, nans = [], []
+    for bits, count in ((0x7FFFFFFF, 3), (None, 500), (0xFFFFFFFF, 40), (0x7FC00000, 1)):
+        r = g.uniform(0.2, 1.2, n).astype(np.float32)
+        at = g.choice(npre, size=count, replace=False)
+        r.view(np.uint32)[at] = g.integers(0x7FE00000, 0x80000000, count) if bits is None else bits
+        rows.append(r)
+        nans.append(np.isnan(r[:npre]))
+    rows = np.stack(rows)
+    for need in sorted({1, 2, 3, 4, 499, 500, 501, npre - 39, npre - 1}):
+        idx, _, _ = select_on_device(np.concatenate([rows, rows], axis=1), [n, n], [need + W, need + W], layers=layers)
+        for l in range(layers):
+            for r, nan in enumerate(nans):
+                a, b = idx[l, r, :need + W].astype(np.int64), idx[l, r, need + W:].astype(np.int64)
+                assert np.array_equal(a, b) and (np.diff(a) > 0).all() and a[0] >= 0
+                assert np.array_equal(a[need:], np.arange(npre, n))
+                kept_nan = nan[a[:need]]
+                assert int(kept_nan.sum()) <= need
+                best = np.sort(np.argsort(np.where(nan, -np.inf, -rows[r, :npre].astype(np.float64)), kind="stable")[nan.sum():][:need - kept_nan.sum()])
+                assert np.array_equal(a[:need][~kept_nan], best), (need, l, r)
+
+
 def two_stage_on_device(rows, prior, seqlens, budgets, ratio, bmin, layers=1):
     """rows [H][T] fp32 (pooled attention), prior [T] -> idx [L][H][TB] through codecomp_select_two_stage."""
     import torch
