@@ -71,14 +71,15 @@ template <int NT> struct SelectShared {
 };
 
 // Rows are read and written through buffer descriptors: an access past `n` elements reads 0 and writes nothing, so that no
-// index is clamped or compared and all loads of a thread are in flight together.
+// index is clamped or compared and all loads of a thread are in flight together.  The whole byte offset is given as the
+// vector offset, for that is what the bounds check covers: the builtins' scalar offset counts as outside of it.
 typedef __amdgpu_buffer_rsrc_t rsrc_t;
 template <class T>
 __device__ __forceinline__ rsrc_t row_of(const T* p, int n) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(static_cast<const void*>(p)), (short)0, max(n, 0) * (int)sizeof(T), 0x00020000);
 }
-__device__ __forceinline__ float4 row_f32x4(rsrc_t r, int lane_byte, int wave_byte) {
-  return __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(r, lane_byte, wave_byte, 0));
+__device__ __forceinline__ float4 row_f32x4(rsrc_t r, int byte) {
+  return __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(r, byte, 0, 0));
 }
 
 // Prefix operations over the 64 lanes of a wave in six register-to-register steps (row shifts, then the last lane of a
@@ -366,7 +367,7 @@ template <int NT, int ITEMS>
 __device__ __forceinline__ void load_row(rsrc_t row, float (&x)[ITEMS]) {
 #pragma unroll
   for (int s = 0; s < ITEMS; s += 4) {
-    const float4 v = row_f32x4(row, (int)threadIdx.x * 16, s * NT * 4);
+    const float4 v = row_f32x4(row, ((int)threadIdx.x * 4 + s * NT) * 4);
     x[s] = v.x; x[s + 1] = v.y; x[s + 2] = v.z; x[s + 3] = v.w;
   }
 }
@@ -410,7 +411,7 @@ __global__ __launch_bounds__(NT) void select_kernel(SelectArgs a) {
   if constexpr (FILL) {
     const rsrc_t mrow = row_of(a.member + s0, npre);
 #pragma unroll
-    for (int s = 0; s < ITEMS; ++s) member[s] = __builtin_amdgcn_raw_buffer_load_b8(mrow, tid * 4 + s % 4, s / 4 * NT * 4, 0);
+    for (int s = 0; s < ITEMS; ++s) member[s] = __builtin_amdgcn_raw_buffer_load_b8(mrow, (s / 4 * NT + tid) * 4 + s % 4, 0, 0);
   }
 #pragma unroll
   for (int s = 0; s < ITEMS; ++s) {
@@ -467,14 +468,14 @@ __global__ __launch_bounds__(NT) void finish_select_kernel(SelectArgs a, FinishA
       const rsrc_t row = row_of(u, mass_end);
 #pragma unroll
       for (int s = 0; s < BLOCK; s += 4)
-        if (s < width) v[s / 4] = row_f32x4(row, tid * 16, (base + s * NT) * 4);
+        if (s < width) v[s / 4] = row_f32x4(row, (base + s * NT + tid * 4) * 4);
     }
     for (int sp = 1; sp < f.row_splits; ++sp) {        // added in the order of the splits
       const rsrc_t row = row_of(u + sp * split_stride, mass_end);
       float4 w[BLOCK / 4];
 #pragma unroll
       for (int s = 0; s < BLOCK; s += 4)
-        if (s < width) w[s / 4] = row_f32x4(row, tid * 16, (base + s * NT) * 4);
+        if (s < width) w[s / 4] = row_f32x4(row, (base + s * NT + tid * 4) * 4);
 #pragma unroll
       for (int s = 0; s < BLOCK / 4; ++s)
         if (4 * s < width) { v[s].x += w[s].x; v[s].y += w[s].y; v[s].z += w[s].z; v[s].w += w[s].w; }
@@ -494,14 +495,14 @@ __global__ __launch_bounds__(NT) void finish_select_kernel(SelectArgs a, FinishA
 #pragma unroll
     for (int s = 0; s < BLOCK; s += 4) {
       if (s >= width || base + s * NT >= n) continue;
-      const int lane_byte = tid * 16, quad_byte = (base + s * NT) * 4;
+      const int quad = base + s * NT + tid * 4;        // the first of four tokens
       float acc[4] = {0.f, 0.f, 0.f, 0.f};
-      const float4 p4 = row_f32x4(prior, lane_byte, quad_byte);
+      const float4 p4 = row_f32x4(prior, quad * 4);
       const float p[4] = {p4.x, p4.y, p4.z, p4.w};
       uint8_t member[4] = {0, 0, 0, 0};
       if constexpr (FILL) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) member[e] = __builtin_amdgcn_raw_buffer_load_b8(members_row, tid * 4 + e, base + s * NT, 0);
+        for (int e = 0; e < 4; ++e) member[e] = __builtin_amdgcn_raw_buffer_load_b8(members_row, quad + e, 0, 0);
       }
       const float* m = mass + HALO + (s / 4 * NT + tid) * 4;
       if (half <= NEAR) {
@@ -530,13 +531,13 @@ __global__ __launch_bounds__(NT) void finish_select_kernel(SelectArgs a, FinishA
       float c[4];
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const int j = base + s * NT + tid * 4 + e;
+        const int j = quad + e;
         const float pooled = f.pool_max ? acc[e] : acc[e] * f.inv_pool;
         c[e] = __builtin_fmaf(f.lambda, p[e], j < pooled_end ? pooled : 0.f);
         keys[b0 + s + e] = j < npre ? (member[e] ? kForced : order_key(c[e])) : 0u;
       }
       typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-      __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, make_float4(c[0], c[1], c[2], c[3])), scores, lane_byte, quad_byte, 0);
+      __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, make_float4(c[0], c[1], c[2], c[3])), scores, quad * 4, 0, 0);
     }
   }
   if (bp <= 0) return;
@@ -993,7 +994,7 @@ __global__ __launch_bounds__(kResolveThreads) void part_resolve_kernel(SelectArg
     uint32_t keys[kResolveItems];
 #pragma unroll
     for (int s = 0; s < kResolveItems; ++s)                  // past the list: 0, no candidate
-      keys[s] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(row, tid * 4, s * kResolveThreads * 4, 0);
+      keys[s] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(row, (s * kResolveThreads + tid) * 4, 0, 0);
     int ties;
     find_cut<kResolveThreads, kResolveItems>(cut, keys, slots, m, remaining, tau, ties);
     remaining = (uint32_t)ties;

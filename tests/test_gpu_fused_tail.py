@@ -52,5 +52,15 @@ def test_pooling_widths_and_readings(pool, variant):
     both(batch([5003, 300, 33041, W + 40], pool_kernel=pool), score_variant=variant)
 
 
+@pytest.mark.parametrize("longest,quad,heads", [(8192, 4096, 2), (40000, 4096, 2), (2048, 1024, 86), (4096, 1024, 86), (8192, 2048, 86)])
+@pytest.mark.parametrize("pool,variant", [(7, 0), (1025, 0), (7, 8), (7, 16), (1025, 8 | 16)])
+def test_requests_whose_masses_end_just_below_a_quad_of_the_longest_one(longest, quad, heads, pool, variant):
+    """The longest request makes every workgroup ask for several quads; the masses of others end one to three tokens below one of
+    them, within the pooling reach of what lies past their row: the next request's masses, which must not come in."""
+    trim = W if variant & (8 | 16) else 0
+    both(batch([longest, quad - 1 + trim, W + 3, quad - 2 + trim, quad - 3 + trim, W + 1], heads=heads, pool_kernel=pool),
+         score_variant=variant)
+
+
 def test_masses_of_several_row_splits_are_added():
     both(wl.scaled(wl.qwen7b_32k(), n_layers=1, seqlens=[2000, 600], budgets=[700, 512], window=512, n_q_heads=8, n_kv_heads=2))
