@@ -62,5 +62,28 @@ def test_requests_whose_masses_end_just_below_a_quad_of_the_longest_one(longest,
          score_variant=variant)
 
 
+@pytest.mark.parametrize("pool", [1, 3, 7, 9, 11])
+@pytest.mark.parametrize("variant", [0, 4])
+def test_masses_that_are_not_finite_reach_no_further_than_the_pooling_width(pool, variant):
+    """A query row whose logits all lie below the smallest softmax reference has infinite masses, NaN where a logit is -inf: the
+    pooled scores of the fused call hold infinities and NaN at the same tokens as those of the separate calls."""
+    import torch
+    from paper_2604_10235_amd import binding as b
+    w = batch([3000, 700, 41], pool_kernel=pool)
+    q, k, v, prior = wl.make_all(w)
+    as_bits = lambda x: int(torch.tensor(x, dtype=torch.bfloat16).view(torch.int16)) & 0xFFFF
+    q[:, 0, 0] = 0                                                  # head 0 in the first request: even rows but for one ...
+    q[:, 0, 0, 3, :] = as_bits(1e18)
+    k[:, 0, :3000, :] = as_bits(-1e18)                             # ... that meets keys which give it about -6e37
+    k[:, 0, [0, 1000, 1012, 2047, 2999], :] = as_bits(-3e38)       # ... and -inf
+    steps, fused = (b.DeviceProblem(w, q, k, v, prior, score_variant=variant) for _ in range(2))
+    steps.score(); steps.select(); fused.compress()
+    torch.cuda.synchronize()
+    want, got = steps.scores.cpu().numpy(), fused.scores.cpu().numpy()
+    assert np.isinf(want[:, 0, :3000]).any() and np.isfinite(want[:, :, 3000:]).all() and np.isfinite(want[:, 1]).all()
+    assert np.array_equal(np.isnan(want), np.isnan(got)) and np.array_equal(want[~np.isnan(want)], got[~np.isnan(want)])
+    assert (np.diff(fused.idx.cpu().numpy()[:, :, :w.budgets[0]]) > 0).all()
+
+
 def test_masses_of_several_row_splits_are_added():
     both(wl.scaled(wl.qwen7b_32k(), n_layers=1, seqlens=[2000, 600], budgets=[700, 512], window=512, n_q_heads=8, n_kv_heads=2))
