@@ -422,13 +422,15 @@ __global__ __launch_bounds__(NT) void select_kernel(SelectArgs a) {
   select_and_emit<NT, ITEMS>(sh, keys, slots, npre, npre - members, bp - members, bp >= npre, bp, out);
 }
 
+constexpr int kFinishNear = 4;      // neighbours on a side that three 16-byte LDS reads cover
+
 // The tail of the fused call in one kernel: the attention mass of a request is pooled, the prior added, the scores stored
 // (what score_finish_kernel does, the same sums in the same order), and the selection goes on with the scores it holds in
 // registers.  The masses pass through LDS, up to 32768 tokens at a time, so that a thread finds its neighbours there.
 template <bool FILL, int NT, int ITEMS, int HALO>
 __global__ __launch_bounds__(NT) void finish_select_kernel(SelectArgs a, FinishArgs f) {
   constexpr int BLOCK = ITEMS < 32768 / NT ? ITEMS : 32768 / NT;   // slots per LDS filling
-  constexpr int NEAR = 4;                                          // neighbours on a side that three 16-byte LDS reads cover
+  constexpr int NEAR = kFinishNear;
   static_assert(HALO % 4 == 0 && HALO >= NEAR, "16-byte LDS accesses");
   __shared__ __attribute__((aligned(16))) float mass[BLOCK * NT + 2 * HALO];
   __shared__ SelectShared<NT> sh;
@@ -1236,8 +1238,21 @@ static int launch_stage1(const Plan& pl, const SelectArgs& a, hipStream_t stream
   return 0;
 }
 
-// One workgroup keeps a request's scores in registers (64 per thread of the large ones).
-bool fused_tail(const Plan& pl) { return pl.max_n <= kSelectMaxCandidates; }
+// One workgroup keeps a request's scores in registers (64 per thread of the large ones), if pooling leaves the fused kernel ahead.
+// Up to nine neighbours it does, at every size.  Wider ones are read from LDS one by one, by the one compute unit that has the
+// request (at about 24 tokens' reads of one neighbour per ns), where the pooling kernel spreads them over the device, for the
+// price of a launch and a trip of the scores through memory (about 7 us).  So the fused kernel takes them while the neighbours
+// that its busiest unit reads beyond an even share (of which the pooling kernel's halos and edges take back a quarter) cost less
+// than that.  Separate -> fused: 4 problems of 4096 tokens, width 33 30.6 -> 28.4 us, 65 30.5 -> 34.0; of 8192, 13 30.7 -> 29.6,
+// 25 30.4 -> 33.7; of 16384, 9 34.8 -> 34.1, 11 35.0 -> 39.2; of 65536, 1025 (all fused before) 2756 us against 443 with a
+// pooling kernel; 256 of 4096, 129 113 -> 89; 256 of 32768, 25 595 -> 588, 129 675 -> 723; 1792 of 1000, 65 142 -> 131.
+bool fused_tail(const Plan& pl) {
+  constexpr int64_t kUnits = 256, kWideReads = 160000;
+  if (pl.max_n > kSelectMaxCandidates) return false;
+  if (pl.pool <= 2 * kFinishNear + 1) return true;
+  const int64_t even = (int64_t)pl.L * pl.Hkv * pl.T / kUnits, busiest = even > pl.max_n ? even : pl.max_n;
+  return pl.pool * (busiest - even * 3 / 4) <= kWideReads;
+}
 
 int launch_finish_select(const Plan& pl, const float* prior, float* scores, int32_t* idx, void* workspace, hipStream_t stream) {
   const SelectArgs a = select_args(pl, scores, prior, idx, workspace);

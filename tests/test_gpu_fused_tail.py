@@ -85,5 +85,42 @@ def test_masses_that_are_not_finite_reach_no_further_than_the_pooling_width(pool
     assert (np.diff(fused.idx.cpu().numpy()[:, :, :w.budgets[0]]) > 0).all()
 
 
+# Widths above nine on both sides of the rule that gives them to the fused kernel (11 .. 215) or to the pooling kernel; quads of
+# one, two and four rounds, requests that end just below one of them.
+@pytest.mark.parametrize("longest,quad,heads,pool", [(150, 0, 2, 1025), (600, 0, 2, 257), (2000, 0, 2, 65), (4000, 0, 2, 33), (8192, 4096, 2, 19), (8192, 4096, 2, 21),
+                                                     (14000, 8192, 2, 11), (14000, 8192, 2, 13), (2048, 1024, 86, 65), (2048, 1024, 86, 215),
+                                                     (4096, 1024, 86, 65), (4096, 2048, 86, 129)])
+@pytest.mark.parametrize("variant", [0, 4, 8, 8 | 16])
+def test_wide_pooling_fused_and_separate(longest, quad, heads, pool, variant):
+    trim = W if variant & (8 | 16) else 0
+    lens = [quad - d + trim for d in (1, 2, 3)] if quad else [W + 1, W + 2, longest // 2]
+    both(batch([longest, lens[0], W + 3, lens[1], lens[2], W + 1], heads=heads, pool_kernel=pool), score_variant=variant)
+
+
+@pytest.mark.parametrize("pool", [7, 11, 19])
+@pytest.mark.parametrize("variant", [0, 4 | 16])
+def test_pooling_across_the_seam_of_two_fillings(pool, variant):
+    """Requests beyond 32768 tokens pass through LDS in two fillings; with 256 of them the widths above nine are fused too."""
+    import torch
+    from paper_2604_10235_amd import binding as b
+    heads, n, budget = 256, 33000, 3000
+    g = torch.Generator(device="cuda:0").manual_seed(pool)
+    q, k = (torch.randn((heads, rows, 64), generator=g, device="cuda:0").bfloat16() for rows in (W, n))
+    prior = torch.rand((n,), generator=g, device="cuda:0")
+    cu, cb = np.array([0, n], np.int32), np.array([0, budget], np.int32)
+    cud, cbd = (torch.from_numpy(x).cuda() for x in (cu, cb))
+    p = b.make_params(n_layers=1, n_q_heads=heads, n_kv_heads=heads, head_dim=64, window=W, pool_kernel=pool, prior_weight=1e-3,
+                      cu_seqlens_host=cu, cu_budgets_host=cb, cu_seqlens_dev=cud.data_ptr(), cu_budgets_dev=cbd.data_ptr(), score_variant=variant)
+    ws = torch.full((b.codecomp_workspace_bytes(p),), 0xFF, dtype=torch.uint8, device="cuda:0")
+    scores, fused_scores = (torch.full((heads, n), float("nan"), device="cuda:0") for _ in range(2))
+    idx, fused_idx = (torch.full((heads, budget), -1, dtype=torch.int32, device="cuda:0") for _ in range(2))
+    out = torch.empty((heads, budget, 64), dtype=torch.bfloat16, device="cuda:0")
+    b.codecomp_score(q, k, prior, p, scores, ws)
+    b.codecomp_select(scores, p, idx, ws)
+    b.codecomp_compress(q, k, k, prior, p, fused_scores, fused_idx, out, out.clone(), ws)
+    torch.cuda.synchronize()
+    assert torch.equal(scores.view(torch.int32), fused_scores.view(torch.int32)) and torch.equal(idx, fused_idx)
+
+
 def test_masses_of_several_row_splits_are_added():
     both(wl.scaled(wl.qwen7b_32k(), n_layers=1, seqlens=[2000, 600], budgets=[700, 512], window=512, n_q_heads=8, n_kv_heads=2))
