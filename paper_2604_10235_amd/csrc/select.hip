@@ -453,6 +453,9 @@ __global__ __launch_bounds__(NT) void finish_select_kernel(SelectArgs a, FinishA
   const rsrc_t prior = row_of(f.prior + s0, n);
   const rsrc_t scores = row_of(f.scores + (int64_t)lz * f.T + s0, n);
   const rsrc_t members_row = row_of(a.member + s0, FILL ? npre : 0);
+  float weight[NEAR + 1];                              // 1 for the neighbours that the pooling width reaches, else 0
+#pragma unroll
+  for (int t = 0; t <= NEAR; ++t) weight[t] = t <= half ? 1.f : 0.f;
   uint32_t keys[ITEMS];
 #pragma unroll
   for (int s = 0; s < ITEMS; ++s) keys[s] = 0u;
@@ -507,19 +510,26 @@ __global__ __launch_bounds__(NT) void finish_select_kernel(SelectArgs a, FinishA
       if (half <= NEAR) {
         const float4 w0 = *reinterpret_cast<const float4*>(m - 4), w1 = *reinterpret_cast<const float4*>(m), w2 = *reinterpret_cast<const float4*>(m + 4);
         const float w[12] = {w0.x, w0.y, w0.z, w0.w, w1.x, w1.y, w1.z, w1.w, w2.x, w2.y, w2.z, w2.w};
-        // neighbours out of reach stay out (a factor of 0 would let an infinite mass through as NaN)
         if (f.pool_max) {
 #pragma unroll
           for (int t = -NEAR; t <= NEAR; ++t)
-            if ((t < 0 ? -t : t) <= half)
 #pragma unroll
-              for (int e = 0; e < 4; ++e) acc[e] = fmaxf(acc[e], w[4 + e + t]);           // masses are >= 0
+            for (int e = 0; e < 4; ++e) acc[e] = fmaxf(acc[e], weight[t < 0 ? -t : t] * w[4 + e + t]);           // masses are >= 0; NaN (0 * inf) loses
         } else {
 #pragma unroll
           for (int t = -NEAR; t <= NEAR; ++t)
-            if ((t < 0 ? -t : t) <= half)
 #pragma unroll
-              for (int e = 0; e < 4; ++e) acc[e] += w[4 + e + t];
+            for (int e = 0; e < 4; ++e) acc[e] = __builtin_fmaf(weight[t < 0 ? -t : t], w[4 + e + t], acc[e]);
+          // 0 * inf has let a mass out of reach in as NaN, should there be infinite ones: once more without those out of reach
+          if (__ballot(!(fabsf((acc[0] + acc[1]) + (acc[2] + acc[3])) < INFINITY)) != 0) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[e] = 0.f;
+#pragma unroll
+            for (int t = -NEAR; t <= NEAR; ++t)
+              if ((t < 0 ? -t : t) <= half)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) acc[e] += w[4 + e + t];
+          }
         }
       } else if (f.pool_max) {
         for (int t = -half; t <= half; ++t)
