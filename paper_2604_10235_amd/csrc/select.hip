@@ -251,10 +251,38 @@ __device__ __forceinline__ void find_cut(SelectShared<NT>& sh, const uint32_t (&
       ties = __builtin_amdgcn_readfirstlane((int)sh.pick[1]);
       return;
     }
-    from = 0;
-    span = hi - lo;
+    // Many keys in one bin are often one key many times (masses that are exactly 0), and every further round would have its
+    // atomics wait for one another on that key's bin: the range is cut down to the keys in it first (65536 candidates, 97 % of
+    // them 0: 183 us without, 80 with).  That pass is worth it only if one key makes up much of the bin, which is asked of the
+    // first slot (15 % in one bin, nearly all different: 40.3 us with the pass always, 37.8 as it is).
+    const uint32_t w = hi - lo;
+    const bool many = count * 8 > slots * NT;
+    if (many) {
+      const unsigned long long in = __ballot(keys[0] - lo <= w);
+      const uint32_t one = (uint32_t)__builtin_amdgcn_readlane((int)keys[0], in != 0 ? __ffsll(in) - 1 : 0);
+      const int same = __popcll(__ballot(keys[0] == one) & in);
+      if (lane == 0) sh.wave_a[wave] = (unsigned int)same;
+    }
     hist_clear(sh);
     __syncthreads();
+    if (many && over_waves<NW>(sh.wave_a, 0, NW, OpAdd{}) * 16u > (unsigned int)NT) {
+      mn = 0xFFFFFFFFu, mx = 0u;
+      for_slots<ITEMS>(slots, [&](int s) {
+        const bool in = keys[s] - lo <= w;
+        mn = in ? min(mn, keys[s]) : mn;
+        mx = in ? max(mx, keys[s]) : mx;
+      });
+      mn = last_lane(wave_scan(mn, OpMin{}));
+      mx = last_lane(wave_scan(mx, OpMax{}));
+      __syncthreads();                             // wave_a has been read
+      if (lane == 0) { sh.wave_a[wave] = mn; sh.wave_b[wave] = mx; }
+      __syncthreads();
+      lo = over_waves<NW>(sh.wave_a, 0, NW, OpMin{});
+      hi = over_waves<NW>(sh.wave_b, 0, NW, OpMax{});
+      if (lo == hi) { tau = lo; ties = (int)rank; return; }
+    }
+    from = 0;
+    span = hi - lo;
   }
 }
 
@@ -1254,8 +1282,8 @@ static int launch_stage1(const Plan& pl, const SelectArgs& a, hipStream_t stream
 // price of a launch and a trip of the scores through memory (about 7 us).  So the fused kernel takes them while the neighbours
 // that its busiest unit reads beyond an even share (of which the pooling kernel's halos and edges take back a quarter) cost less
 // than that.  Separate -> fused: 4 problems of 4096 tokens, width 33 30.6 -> 28.4 us, 65 30.5 -> 34.0; of 8192, 13 30.7 -> 29.6,
-// 25 30.4 -> 33.7; of 16384, 9 34.8 -> 34.1, 11 35.0 -> 39.2; of 65536, 1025 (all fused before) 2756 us against 443 with a
-// pooling kernel; 256 of 4096, 129 113 -> 89; 256 of 32768, 25 595 -> 588, 129 675 -> 723; 1792 of 1000, 65 142 -> 131.
+// 25 30.4 -> 33.7; of 16384, 9 34.8 -> 34.1, 11 35.0 -> 39.2; of 65536, 1025 147 -> 2756;
+// 256 of 4096, 129 113 -> 89; 256 of 32768, 25 595 -> 588, 129 675 -> 723; 1792 of 1000, 65 142 -> 131.
 bool fused_tail(const Plan& pl) {
   constexpr int64_t kUnits = 256, kWideReads = 160000;
   if (pl.max_n > kSelectMaxCandidates) return false;

@@ -178,6 +178,28 @@ def test_select_where_scores_are_nan(npre, layers):
                 assert np.array_equal(a[:need][~kept_nan], best), (need, l, r)
 
 
+@pytest.mark.parametrize("npre,layers", [(700, 1), (1501, 1), (3500, 1), (5000, 1), (12001, 1), (30001, 1), (45000, 1), (65536, 1), (70001, 1),
+                                         (2047, 128), (4095, 128), (8190, 128), (16380, 128)])
+def test_select_where_one_bin_holds_most_scores(npre, layers):
+    """A sea of zeros, alone in the first counting round's bin or with subnormals around it (which shrink the bin's range but do
+    not empty it), and ordinary scores that put the bins far apart: the cut above, in and below the sea."""
+    g = np.random.default_rng(npre)
+    n = npre + W
+    rows = []
+    for other in (0.0, 0.03, 0.4):
+        r = np.where(g.random(n) < 0.05, g.uniform(0.2, 1.2, n), 0.0).astype(np.float32)
+        tiny = (r == 0) & (g.random(n) < other)
+        r[tiny] = (g.integers(-300, 300, int(tiny.sum())) * 1e-45).astype(np.float32)
+        rows.append(r)
+    rows.append(np.where(g.random(n) < 0.9, np.float32(0.5), g.uniform(0.4, 0.6, n)).astype(np.float32))
+    rows = np.stack(rows)
+    for need in sorted({1, npre // 30, npre // 6, npre // 2, npre - npre // 50, npre - 1}):
+        idx, _, _ = select_on_device(rows, [n], [need + W], layers=layers)
+        want = orc.select(rows.astype(np.float64), W, need + W)
+        for l in range(layers):
+            assert np.array_equal(idx[l].astype(np.int64), want), (need, l)
+
+
 def two_stage_on_device(rows, prior, seqlens, budgets, ratio, bmin, layers=1):
     """rows [H][T] fp32 (pooled attention), prior [T] -> idx [L][H][TB] through codecomp_select_two_stage."""
     import torch
