@@ -411,8 +411,9 @@ __device__ __forceinline__ void select_and_emit(SelectShared<NT>& sh, const uint
   uint32_t tau = all ? 0u : kForced - 1u;       // every candidate / the forced ones only
   int ties = 0;
   if (!all && need > 0) find_cut<NT, ITEMS>(sh, keys, slots, competing, (uint32_t)need, tau, ties);
+  const rsrc_t row = row_of(out, kept);         // pos < kept always; the descriptor is belt and braces
   emit_in_order<false, NT, ITEMS>(sh, keys, slots, npre, tau, ties, [&](int j, bool, int pos) {
-    if ((unsigned)pos < (unsigned)kept) out[pos] = j;          // pos < kept always: belt and braces
+    __builtin_amdgcn_raw_buffer_store_b32((uint32_t)j, row, pos * 4, 0, 0);
   });
 }
 
