@@ -166,9 +166,7 @@ int make_plan(const codecomp_params* p, Plan* pl) {
   // the cut; per (layer*head, request) what the parts agreed on.  The keys near the cut reuse the raw attention mass
   // (dead once the scores exist): one 32-bit word per token and layer*head, exactly its size.
   pl->sel_parts = 0;
-  pl->by_parts = max_n - p->window > kSelectMaxCandidates;
-  const int max_npre = max_n - p->window;
-  if (max_npre > kSelectMaxCandidates || (max_npre >= kPartMinCandidates && LH * (size_t)p->n_seqs < (size_t)kPartFewProblems)) {
+  if (max_n - p->window > kSelectMaxCandidates) {
     int64_t parts = 0;
     for (int r = 0; r < p->n_seqs; ++r) {
       const int npre = p->cu_seqlens_host[r + 1] - p->cu_seqlens_host[r] - p->window;

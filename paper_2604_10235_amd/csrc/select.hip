@@ -1310,7 +1310,7 @@ int launch_finish_select(const Plan& pl, const float* prior, float* scores, int3
 
 int launch_select(const Plan& pl, const float* scores, int32_t* idx, void* workspace, hipStream_t stream) {
   const SelectArgs a = select_args(pl, scores, nullptr, idx, workspace);
-  if (pl.by_parts) return launch_parts<RuleAdditive>(pl, a, part_args(pl, workspace), pl.L * pl.Hkv, stream);
+  if (pl.sel_parts > 0) return launch_parts<RuleAdditive>(pl, a, part_args(pl, workspace), pl.L * pl.Hkv, stream);
   dispatch_items(pl.max_n - pl.W, (int64_t)pl.n_seqs * pl.L * pl.Hkv, [&](auto nt, auto items) {
     select_kernel<false, nt(), items()><<<dim3(pl.n_seqs, pl.L * pl.Hkv), dim3(nt()), 0, stream>>>(a);
   });
@@ -1321,7 +1321,7 @@ int launch_select(const Plan& pl, const float* scores, int32_t* idx, void* works
 int launch_select_two_stage(const Plan& pl, const float* scores, const float* prior, int32_t* idx, void* workspace,
                             hipStream_t stream) {
   const SelectArgs a = select_args(pl, scores, prior, idx, workspace);
-  if (pl.by_parts) {
+  if (pl.sel_parts > 0) {
     const PartArgs c = part_args(pl, workspace);
     if (int rc = launch_parts<RuleStage1>(pl, a, c, 1, stream)) return rc;
     return launch_parts<RuleStage2>(pl, a, c, pl.L * pl.Hkv, stream);

@@ -109,14 +109,14 @@ int main(void) {
 
 
 def test_selection_by_parts_shows_in_the_workspace_size():
-    # a request beyond 65536 candidates (or a long one among few problems) is selected by parts of 8192 candidates:
-    # 2048 16-bit counts per (layer * head, part)
+    # a request beyond 65536 candidates is selected by parts of 8192 candidates: 2048 16-bit counts per (layer * head, part);
+    # any other takes one workgroup per (layer, head, request) and no such counts, however few the problems
     def ws(n, layers):
         return b.codecomp_workspace_bytes(good(n_layers=layers, cu_seqlens_host=np.array([0, n]), cu_budgets_host=np.array([0, 100])))
-    few, many = 2, 60                                    # 2 KV heads: 4 and 120 (layer, head, request) problems
-    assert ws(16 + 16384, few) - ws(16 + 16383, few) >= few * 2 * 2 * 2048 * 2           # two parts from 16384 candidates on
-    assert ws(16 + 16384, many) - ws(16 + 16383, many) < 4096 * many                      # many problems: one workgroup each
-    assert ws(16 + 65537, many) - ws(16 + 65536, many) >= many * 2 * 9 * 2048 * 2         # nine parts beyond 65536
+    for layers in (2, 60):                               # 2 KV heads: 4 and 120 problems
+        for n in (16384, 40000):
+            assert ws(16 + n, layers) - ws(16 + n - 1, layers) < 4096 * layers
+        assert ws(16 + 65537, layers) - ws(16 + 65536, layers) >= layers * 2 * 9 * 2048 * 2         # nine parts beyond 65536
 
 
 def test_struct_layout_matches_header():
