@@ -167,26 +167,20 @@ __host__ __device__ __forceinline__ void team_of(int b, int grid, int row_splits
 // reciprocal and of the product moves it by less than 65536 / W * 2^-22 = 0.016 / W.
 __device__ __forceinline__ int row_group(int row, float inv_w) { return (int)(((float)row + 0.5f) * inv_w); }
 
-// log2-sum-exp of one row: its statistics are (reference, sum) pairs, one per segment (`slot` pairs apart) and holder.  Two
-// half waves share them, each asks for BATCH at once; all lanes return the whole row's value.
+// log2-sum-exp of one row: its statistics are (reference, sum) pairs, one per segment (`slot` pairs apart).  Two half waves share
+// them, each asks for BATCH at once; all lanes return the whole row's value.
 constexpr int kMergeBatch = 4;
-__device__ __forceinline__ float merge_row(const float2* st, int slot, int segments, uint32_t holders, int hf) {
+__device__ __forceinline__ float merge_row(const float2* st, int slot, int segments, int hf) {
   constexpr int BATCH = 2 * kMergeBatch;
-  const int h0 = (int)(holders & 255u), h1 = (int)((holders >> 8) & 255u);
-  const int two = h1 != 255 ? 1 : 0;
-  const int items = segments << two;
   float M = NEG_BIG, L = 0.f;
-  for (int i = 0; i < items; i += 2 * BATCH) {
+  for (int i = 0; i < segments; i += 2 * BATCH) {
     float2 s[BATCH];
 #pragma unroll
-    for (int u = 0; u < BATCH; ++u) {
-      const int at = min(i + 2 * u + hf, items - 1);
-      s[u] = st[(int64_t)(at >> two) * slot + ((at & two) ? h1 : h0) * 32];
-    }
+    for (int u = 0; u < BATCH; ++u) s[u] = st[(int64_t)min(i + 2 * u + hf, segments - 1) * slot];
     float Mn = M;
 #pragma unroll
     for (int u = 0; u < BATCH; ++u) {
-      if (i + 2 * u + hf >= items) s[u] = make_float2(NEG_BIG, 0.f);
+      if (i + 2 * u + hf >= segments) s[u] = make_float2(NEG_BIG, 0.f);
       Mn = fmaxf(Mn, s[u].x);
     }
     L *= __builtin_amdgcn_exp2f(M - Mn);
@@ -386,7 +380,8 @@ __global__ __launch_bounds__(NW * 64, (NW >= 3 ? 2 : 1)) void score_pass_kernel(
                          ((int64_t)(lz * a.n_seqs + seq + g0) * a.row_splits + split) * a.srows + ql32;
 #pragma unroll
       for (int sl = 0; sl < 2; ++sl)
-        if (sl == 0 || halves1 != 0) row_lse[sl] = merge_row(st, a.row_splits * a.srows, segments, a.rb_holder[rb_of[sl]], qhf);
+        if (sl == 0 || halves1 != 0)       // up to four waves: every row block has one holder
+          row_lse[sl] = merge_row(st + (int)(a.rb_holder[rb_of[sl]] & 255u) * 32, a.row_splits * a.srows, segments, qhf);
       // the workgroup with the request's first tile leaves them where the merge kernel would: a later call may ask for this
       // pass alone on the same workspace
       if (tile_in_seq == 0 && qhf == 0) {
