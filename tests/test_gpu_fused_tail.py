@@ -33,12 +33,22 @@ def batch(lens, heads=2, **over):
     return wl.scaled(wl.tiny(), seqlens=lens, budgets=budgets, window=W, n_q_heads=heads, n_kv_heads=heads, **over)
 
 
-@pytest.mark.parametrize("edge", [4, 1024, 2048, 4096, 8192, 16384, 32768, 49152, 65536])
+@pytest.mark.parametrize("edge", [1024, 2048, 4096, 8192, 16384, 32768, 49152, 65536])
 @pytest.mark.parametrize("off", [-1, 0, 1])
 def test_edges_of_the_workgroup_shapes(edge, off):
-    n = max(W, edge + off)
+    n = edge + off
     both(batch([n, W + 5, W, W + 1]))                              # the longest request picks the shape
     both(batch([n], prior_weight=0.0), select_mode=1, span_budget_ratio=0.5)
+
+
+@pytest.mark.parametrize("candidates", [0, 1, 2, 3, 4, 5])
+def test_prefixes_about_one_group_of_four(candidates):
+    for window in (1, 2, 3, 4, W):                                 # the end of the prefix inside a group of four tokens, and of the request
+        n = window + candidates
+        for kept in range(candidates + 1):
+            w = wl.scaled(wl.tiny(), seqlens=[n, window], budgets=[window + kept, window], window=window, n_q_heads=2, n_kv_heads=2)
+            both(w)
+        both(w, select_mode=1, span_budget_ratio=0.5)
 
 
 @pytest.mark.parametrize("longest", [2048, 4096, 8192, 16384])

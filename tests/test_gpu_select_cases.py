@@ -72,10 +72,10 @@ def select_on_device(rows, seqlens, budgets, layers=1):
     return idx.cpu().numpy(), cu, cb
 
 
-# Which kernels run depends on the longest request and on the number of (layer, head, request) problems: with 26
-# problems (2 layers x 13 rows) requests of 16384 candidates or more are cut into parts of 8192 (2, 3, 4, 5, 8, 9, 18
-# parts here, including the budgets that keep nothing or everything); with 104 problems (8 layers) one workgroup per
-# problem keeps 8 / 16 / 32 / 48 / 64 candidates per thread in registers up to 65536 candidates, parts beyond.
+# Which kernel runs depends on the longest request and on the number of (layer, head, request) problems: one workgroup per
+# problem up to 65536 candidates, with 4 to 64 candidates per thread (smaller workgroups from 512 problems on; 26 problems with
+# 2 layers x 13 rows here, 104 with 8 layers), parts of 8192 candidates beyond (9 and 18 of them here).  Budgets keep nothing, one,
+# some or all.
 @pytest.mark.parametrize("npre,need,layers", [
     (3000, 200, 2), (9000, 1000, 2), (16383, 5000, 2), (16384, 5000, 2), (30000, 2000, 2), (40000, 3100, 2),
     (60000, 4096, 2), (70000, 5000, 2), (140000, 13043, 2), (9000, 8999, 2), (9000, 1, 2), (20000, 20000, 2),
@@ -87,6 +87,18 @@ def test_select_on_crafted_scores(npre, need, layers):
     want = orc.select(rows.astype(np.float64), W, need + W)
     for l in range(layers):
         assert np.array_equal(idx[l].astype(np.int64), want), (npre, need, l)
+
+
+@pytest.mark.parametrize("npre,need", [(1, 1), (700, 0), (3000, 200), (8192, 800), (8193, 8192), (16383, 5000), (16384, 5000), (20000, 20000),
+                                       (20000, 0), (20000, 1), (20000, 19999), (30000, 2000), (40000, 3100), (60000, 4096), (65536, 8192)])
+def test_select_by_parts_beside_a_longer_request(npre, need):
+    """A request beyond 65536 candidates sends its whole batch through the selection by parts: the others as 1, 2, 3, 4, 5
+    and 8 parts, whole ones and parts with a single candidate."""
+    other = np.random.default_rng(npre).random((13, 65537 + W)).astype(np.float32)
+    rows = np.concatenate([crafted_rows(npre, max(1, need), seed=npre + need), other], axis=1)
+    lens, budgets = [npre + W, 65537 + W], [need + W, 6000 + W]
+    idx, cu, cb = select_on_device(rows, lens, budgets)
+    assert np.array_equal(idx.astype(np.int64), orc.select_packed(rows.astype(np.float64)[None], cu, cb, W))
 
 
 def test_select_beyond_the_table_of_the_resolve_kernel():
@@ -118,12 +130,14 @@ def test_select_on_crafted_scores_ragged():
     assert np.array_equal(idx.astype(np.int64), want)
 
 
-def test_select_by_parts_in_a_batch_of_many_requests():
-    """One long request among 600 short ones: the whole batch is selected by parts (most requests are a single part,
-    some have no candidate at all), and a workgroup finds its request among many."""
+@pytest.mark.parametrize("longest", [40000, 66000])
+def test_select_by_parts_in_a_batch_of_many_requests(longest):
+    """One long request among 600 short ones.  Beyond 65536 candidates the whole batch is selected by parts (most requests are a
+    single part, some have no candidate at all), and a workgroup finds its request among many; below, large workgroups run on
+    mostly short requests."""
     g = np.random.default_rng(99)
     lens = [int(x) + W for x in g.integers(0, 700, size=600)]
-    lens[0] = W; lens[599] = W + 1; lens[311] = 40000 + W; lens[312] = 17000 + W
+    lens[0] = W; lens[599] = W + 1; lens[311] = longest + W; lens[312] = 17000 + W
     needs = [int(g.integers(0, n - W + 1)) for n in lens]
     rows = np.concatenate([crafted_rows(n - W, max(1, b), seed=1000 + i)[[(i + k_) % 13 for k_ in range(3)]] if n > W
                            else np.zeros((3, W), np.float32) for i, (n, b) in enumerate(zip(lens, needs))], axis=1)
@@ -134,9 +148,8 @@ def test_select_by_parts_in_a_batch_of_many_requests():
 
 @pytest.mark.parametrize("longest", [1500, 2048, 3000, 4096, 4097])
 def test_select_with_small_workgroups(longest):
-    """Batches of requests of at most 4096 candidates with a thousand problems or more run 256-thread workgroups
-    holding 8 or 16 candidates per thread (the longest request decides; one candidate more and the 1024-thread
-    kernel runs): 120 requests x 3 rows x 3 layers, crafted rows."""
+    """Batches of 512 problems or more with at most 4096 candidates each run 256-thread workgroups holding 8 or 16 candidates per
+    thread (the longest request decides; one candidate more and 512 threads run): 120 requests x 3 rows x 3 layers, crafted rows."""
     g = np.random.default_rng(longest)
     lens = [int(x) + W for x in g.integers(0, min(longest, 2000), size=120)]
     lens[0] = W; lens[7] = W + 1; lens[60] = longest + W
@@ -222,17 +235,20 @@ def two_stage_on_device(rows, prior, seqlens, budgets, ratio, bmin, layers=1):
     return idx.cpu().numpy(), cu, cb
 
 
+@pytest.mark.parametrize("parts", [False, True])
 @pytest.mark.parametrize("seed", range(10))
-def test_random_batches_with_long_requests(seed):
-    """Seeded random batches that hold at least one long request (so that the selection runs by parts), budgets from
-    the window alone to everything, scores with many ties; the additive rule and the two-stage rule (graded or binary
-    prior, any span budget) against the oracle's rules on the same fp32 values."""
+def test_random_batches_with_long_requests(seed, parts):
+    """Seeded random batches that hold at least one long request (`parts`: and one of 66000 candidates, so that the selection runs
+    by parts whatever the others are), budgets from the window alone to everything, scores with many ties; the additive rule and
+    the two-stage rule (graded or binary prior, any span budget) against the oracle's rules on the same fp32 values."""
     g = np.random.default_rng(31000 + seed)
     n_seqs = int(g.integers(1, 7))
     lens = [W + int(g.integers(0, 3000)) for _ in range(n_seqs)]
     lens[int(g.integers(0, n_seqs))] = W + int(g.choice([16384, 20000, 33333, 65536, 65537, 90000]))
     if g.random() < 0.5:
         lens.append(W + int(g.integers(16384, 40000)))
+    if parts:
+        lens.insert(int(g.integers(0, len(lens) + 1)), W + 66000)
     needs = [int(g.choice([0, 1, (n - W) // 10, (n - W) // 2, max(0, n - W - 1), n - W])) for n in lens]
     total = sum(lens)
     kind = int(g.integers(0, 3))
