@@ -56,7 +56,7 @@ def read_traffic(name: str):
             k, v = line.split("=", 1)
             v = v.strip()
             try:
-                vals[k.strip()] = float(v.split()[0])
+                vals[k.strip()] = v if k.strip() in ("commit", "date") else float(v.split()[0])    # (12095e6 is a commit, not a number)
             except (ValueError, IndexError):
                 vals[k.strip()] = v
     return vals
