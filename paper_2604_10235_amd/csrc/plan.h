@@ -14,11 +14,19 @@ constexpr int kTileKeys = 64;         // keys staged through LDS per pipeline st
 constexpr int kMaxScoreGrid = 2048;   // most workgroups a score pass is launched with
 constexpr int kLeadTiles = 4;         // a segment start (query fragments, first K tile) costs about this many tiles
 // Calls of up to this many (tile, row split) pairs get no leads: a workgroup then has one tile or two and nearly all of them start
-// exactly one segment, so that a lead only leaves some workgroups idle and others with twice the tiles.  With -> without leads:
-// one layer of 1000 tokens (64 pairs) 26.7 -> 24.7 us, 2048 (128) 29.3 -> 26.8, 4093 with window 128 (512) 35.0 -> 32.4; 3000
-// tokens of 8 KV heads (376) 30.3 -> 28.4; 6000 (376) 33.1 -> 33.2.
+// exactly one segment, so that a lead only leaves some workgroups idle and others with twice the tiles.  Scores, with -> without
+// leads: one layer of 2000 tokens, head_dim 64 (128 pairs) 16.0 -> 15.3 us, 8192 of 28 query heads (512) 29.2 -> 27.4, 4096 with
+// window 128 (512) 30.0 -> 28.2, 16 requests of 512 (512) 34.5 -> 33.1, 9000 of 2 KV heads (282) 28.0 -> 28.1.  Above the line one
+// request still gains or stays (8192 x 2 layers (1024) 36.0 -> 34.7, 9000 (564) 29.2 -> 29.2, 20000 (1252) 36.4 -> 36.6), but
+// many problems or requests of different lengths start two segments in some workgroups and lose: 28 layers of 2048 (3584)
+// 76.4 -> 80.6, five requests of up to 5000 (596) 31.3 -> 39.8.  Such a batch loses below it too (298 pairs: 28.8 -> 36.6).
 constexpr int kNoLeadTiles = 512;
-constexpr int kSelectManyProblems = 512;    // (layer, head, request) problems from which on several selection workgroups share a compute unit
+// (layer, head, request) problems from which on smaller selection workgroups, several to a compute unit, are taken.  Selection with
+// small -> with large ones: 256 problems of 8000 candidates 8.3 -> 7.3 us, of 16000 11.9 -> 10.4; 384 of 8000 9.9 -> 8.4, of 16000
+// 15.6 -> 18.6; 512 of 8000 10.1 -> 8.6, of 12000 13.6 -> 17.0; 1024 of 4000 10.1 -> 10.9, of 8000 15.3 -> 15.4, of 16000
+// 30.6 -> 38.8; 2048 of 2000 8.4 -> 10.4.  From two problems per compute unit on the small ones are ahead or (up to 8192
+// candidates, 512 and 640 problems) up to 17 % behind.
+constexpr int kSelectManyProblems = 512;
 // Longer requests are selected by several workgroups each: parts of kPartChunk candidates, one 256-thread workgroup
 // per part and step (first-digit counts, the candidates near the cut, the ordered output; between the last two one
 // workgroup per request finishes the radix select on those candidates).
