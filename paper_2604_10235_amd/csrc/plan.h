@@ -29,7 +29,7 @@ constexpr int kNoLeadTiles = 512;
 constexpr int kSelectManyProblems = 512;
 // Longer requests are selected by several workgroups each: parts of kPartChunk candidates, one 256-thread workgroup
 // per part and step (first-digit counts, the candidates near the cut, the ordered output; between the last two one
-// workgroup per request finishes the radix select on those candidates).
+// workgroup per request finds the cut among those candidates).
 constexpr int kPartThreads = 256;
 constexpr int kPartItems = 32;                             // candidates a thread holds
 constexpr int kPartChunk = kPartThreads * kPartItems;      // candidates per part

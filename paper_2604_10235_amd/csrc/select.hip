@@ -13,7 +13,7 @@
 // What bounds it is instruction issue and barriers of the one compute unit that works on a problem, so: few rounds, ballots
 // instead of shuffles, register-to-register prefix sums, 16-byte loads and stores through buffer descriptors.  Measured
 // (kernel times, the separate pooling kernel + the three-digit radix selection of 1024 threads before -> now): 2048 tokens
-// x 4 problems 17.7 -> 4.6 us; 8192 x 8: 21.4 -> 7.7; 32768 x 112: 46.6 -> 26.4; 65536 x 256: 147 -> 69; sixteen requests
+// x 4 problems 17.7 -> 4.6 us (binary prior: 5.6); 8192 x 8: 21.4 -> 7.7; 32768 x 112: 46.6 -> 26.4; 65536 x 256: 147 -> 69; sixteen requests
 // of 8K .. 48K x 4 (by parts before): 67 -> 34; 64 requests of 135 .. 1831 x 112: 130 -> 31 us (142 .. 2313, next larger workgroup: 54).
 // A batch with a longer request: every request is cut into parts of 8192 candidates and four kernels run one 256-thread
 // workgroup per part (the third one per request), so that a problem is spread over as many compute units as it has parts:
@@ -21,8 +21,8 @@
 //   near    every part adds up the counts of its request, finds the bin that holds the cut, and appends its
 //           candidates of that bin (keys only, in token order) to the request's list, at the place the
 //           counts of the earlier parts give it; it also stores how many of its candidates lie above that bin;
-//   resolve one workgroup per request finishes the radix select on the list (two more digits; the list is short
-//           unless the scores crowd into one bin);
+//   resolve one workgroup per request finds the cut in the list (counting rounds in registers up to 16384 keys, two more
+//           radix digits beyond; the list is short unless the scores crowd into one bin);
 //   emit    every part counts what the earlier parts contribute and writes its own admitted indices at their
 //           final places.
 //
