@@ -121,16 +121,44 @@ int make_plan(const codecomp_params* p, Plan* pl) {
   if ((pl->variant & CODECOMP_VARIANT_GROUP_MAX) && (pl->W % 32 != 0 || pl->row_splits != 1)) return CODECOMP_EINVAL_MODE;
   if (p->score_workgroups < 0 || p->score_lead_tiles > 64) return CODECOMP_EINVAL_SHAPE;
   pl->grid_override = p->score_workgroups;
-  int64_t tiles = 0;
+  int64_t tiles = 0, tiles_once = 0;
+  int once_short = 0, once_long = 0;
   for (int r = 0; r < p->n_seqs; ++r) {
     int n = p->cu_seqlens_host[r + 1] - p->cu_seqlens_host[r] - pl->key_trim;     // >= 0: W <= N_r was checked
-    tiles += (n + kTileKeys - 1) / kTileKeys;
+    const int t = (n + kTileKeys - 1) / kTileKeys;
+    tiles += t;
+    if (n > 0 && n <= kOnceKeys) { tiles_once += t; ++(n <= kOnceKeys / 2 ? once_short : once_long); }
   }
   const int64_t problems = (int64_t)pl->L * pl->Hkv * pl->row_splits;
   const int automatic_lead = tiles > 0 && tiles * problems <= kNoLeadTiles ? 0 : kLeadTiles;
   pl->lead_tiles = p->score_lead_tiles == 0 ? automatic_lead : (p->score_lead_tiles < 0 ? 0 : p->score_lead_tiles);
-  const int64_t positions = tiles + (int64_t)pl->lead_tiles * pl->n_seqs;
+  int64_t positions = tiles + (int64_t)pl->lead_tiles * pl->n_seqs;
   if (positions * problems > (1 << 30)) return CODECOMP_EINVAL_SHAPE;
+  const int64_t once_problems = (int64_t)(once_short + once_long) * pl->L * pl->Hkv;
+  const bool all_once = once_problems > 0 && tiles_once == tiles;
+  const bool once = (all_once || once_problems >= kOnceMixed) && !(pl->variant & CODECOMP_VARIANT_GROUP_MAX) &&
+                    p->score_workgroups == 0 && p->score_lead_tiles == 0;
+  pl->once_keys = once ? kOnceKeys : 0;
+  pl->once_short = once ? once_short : 0;
+  pl->once_long = once ? once_long : 0;
+  pl->once_rows = pl->row_blocks * 32;
+  pl->once_chunks = pl->row_splits;
+  pl->once_shared_out = false;
+  if (once && all_once && once_problems < kOnceFill) {
+    // few problems: smaller chunks of rows, of at least four blocks of 16, until the compute units are used
+    const int blocks = (pl->R + 15) / 16;
+    int64_t chunks = kOnceFill / once_problems;
+    if (chunks > (blocks + 3) / 4) chunks = (blocks + 3) / 4;
+    if (chunks < pl->row_splits) chunks = pl->row_splits;
+    pl->once_rows = (int)((blocks + chunks - 1) / chunks) * 16;
+    pl->once_chunks = (pl->R + pl->once_rows - 1) / pl->once_rows;
+    pl->once_shared_out = pl->once_chunks > 1 && once_problems * pl->once_chunks <= kOnceFill;
+  }
+  pl->mass_parts = once && all_once ? pl->once_chunks : pl->row_splits;
+  if (once) {
+    tiles -= tiles_once;
+    positions -= tiles_once + (int64_t)pl->lead_tiles * (once_short + once_long);
+  }
   pl->tiles_per_problem = (int)positions;
   pl->total_tiles = (int)(positions * pl->L * pl->Hkv);      // the row splits of a problem walk the same positions
   pl->real_tiles = (int)(tiles * pl->L * pl->Hkv);
@@ -180,6 +208,16 @@ int make_plan(const codecomp_params* p, Plan* pl) {
     pl->off_part_before = off; off = align256(off + LH * (size_t)parts * 2 * sizeof(int32_t));
   }
   pl->ws_bytes = off;
+  // calls without two-pass requests keep no statistics: more mass arrays than row splits take their place as well
+  if (pl->mass_parts > pl->row_splits) {
+    if ((size_t)pl->mass_parts * LH * pl->T * sizeof(float) <= pl->off_member) {
+      pl->off_uraw = 0;
+    } else {                   // long windows that the softmax leaves out
+      pl->once_rows = pl->row_blocks * 32;
+      pl->once_chunks = pl->mass_parts = pl->row_splits;
+      pl->once_shared_out = false;
+    }
+  }
   return CODECOMP_OK;
 }
 

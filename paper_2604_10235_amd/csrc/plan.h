@@ -11,6 +11,17 @@ namespace codecomp {
 constexpr int kRowsPerWave = 64;      // query rows (window x group) one wavefront can own: two blocks of 32
 constexpr int kMaxWaves = 8;          // wavefronts per workgroup in the score kernels
 constexpr int kTileKeys = 64;         // keys staged through LDS per pipeline step
+// One pass over the logits (score_once.h): the keys of a request in the registers of one workgroup.  A call whose requests are all
+// that short always takes it: 1.1 to 2.4 times faster than two passes from one problem of 130 keys to 4096 of 760, head_dim 64 and
+// 128, 32 to 896 rows (figures there).
+constexpr int kOnceTiles = 6;           // most tiles of 16 keys a wave holds; with seven the eight-wave kernel spills inside its loop
+constexpr int kOnceKeys = 16 * kOnceTiles * 8;      // keys of the longest request that takes one pass
+constexpr int kOnceRows = 512;          // most query rows of a chunk
+// In a call with longer requests too, the kernel runs after their two passes: a launch of 20 to 40 us with few problems, which they
+// would have taken along.  28 query heads on 4, window 64, all -> short ones apart: 160 short problems among 80 of 2000 keys 43 -> 55
+// us, 640 among 32 109 -> 90, 448 of 200 among 448 of 4000 498 -> 494, 4480 among 224 611 -> 375.
+constexpr int kOnceMixed = 512;
+constexpr int kOnceFill = 256;          // workgroups that find a compute unit of their own at once: up to here a problem's rows are shared out
 constexpr int kMaxScoreGrid = 2048;   // most workgroups a score pass is launched with
 constexpr int kLeadTiles = 4;         // a segment start (query fragments, first K tile) costs about this many tiles
 // Calls of up to this many (tile, row split) pairs get no leads: a workgroup then has one tile or two and nearly all of them start
@@ -59,6 +70,11 @@ struct Plan {
   // ones slot 1 covers (0: the wave has no slot 1).
   uint32_t wave_desc[kMaxWaves];
   uint8_t rb_holder[2 * kMaxWaves][2];   // per row block: wave * 2 + slot of its (one or two) owners, 255 = none
+  int once_keys;             // requests of up to this many keys take the one-pass kernel (0: none does)
+  int once_short, once_long; // how many of up to kOnceKeys / 2 keys, and of more
+  int once_rows, once_chunks;            // query rows of a chunk, chunks
+  bool once_shared_out;      // the chunks of a problem go to workgroups of their own
+  int mass_parts;            // arrays of raw attention mass that add up: row splits, or chunks where every request takes one pass
   int grid_override;         // > 0: the caller fixed the number of workgroups of the score passes
   int lead_tiles;            // empty positions before each request's tiles in the sequence below: the cost of starting a segment
   int tiles_per_problem;     // sum over requests of (lead_tiles + ceil(N_r / kTileKeys)): positions of one (layer, head)

@@ -1,7 +1,7 @@
 // Score step, small kernels and entry: row merge between the two MFMA passes, pooling + prior, and the
 // launch sequence.  The passes themselves live in score_pass.h and are instantiated per (head_dim, key
 // type) in score_pass_*.hip.
-#include "score_pass.h"
+#include "score_once.h"
 
 namespace codecomp {
 
@@ -9,6 +9,10 @@ extern template int dispatch_waves<128, false>(const Plan&, const ScoreArgs&, hi
 extern template int dispatch_waves<128, true>(const Plan&, const ScoreArgs&, hipStream_t, unsigned);
 extern template int dispatch_waves<64, false>(const Plan&, const ScoreArgs&, hipStream_t, unsigned);
 extern template int dispatch_waves<64, true>(const Plan&, const ScoreArgs&, hipStream_t, unsigned);
+extern template int launch_once<128, false>(const Plan&, const ScoreArgs&, hipStream_t);
+extern template int launch_once<128, true>(const Plan&, const ScoreArgs&, hipStream_t);
+extern template int launch_once<64, false>(const Plan&, const ScoreArgs&, hipStream_t);
+extern template int launch_once<64, true>(const Plan&, const ScoreArgs&, hipStream_t);
 
 // Per (layer*head, request, row): log2-sum-exp over the segments (of the teams) that cover the request and over the (at
 // most two) wave slots that hold a share of the row's keys.
@@ -24,11 +28,13 @@ __global__ __launch_bounds__(kMergeThreads) void score_merge_kernel(ScoreArgs a,
   const int tid = threadIdx.x;
   const int seq = blockIdx.y;
   const int lz = blockIdx.z;
-  const int nt = tiles_of(a.cu_seqlens[seq + 1] - a.cu_seqlens[seq], a.key_trim);
+  const TileRule rule = {a.key_trim, a.once_keys, a.lead};
+  const int nt = tiles_of(a.cu_seqlens[seq + 1] - a.cu_seqlens[seq], rule);
+  if (nt < 0) return;            // the one-pass kernel's: nothing reads its normalisers
   int tile_off = a.lead;
   if (a.n_seqs > 1) {            // positions of the earlier requests in a problem's sequence: summed by the whole workgroup
     int mine = 0;
-    for (int r = tid; r < seq; r += kMergeThreads) mine += a.lead + tiles_of(a.cu_seqlens[r + 1] - a.cu_seqlens[r], a.key_trim);
+    for (int r = tid; r < seq; r += kMergeThreads) mine += a.lead + tiles_of(a.cu_seqlens[r + 1] - a.cu_seqlens[r], rule);
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) mine += __shfl_xor(mine, off);
     if ((tid & 63) == 0) part[tid >> 6] = mine;
@@ -200,7 +206,7 @@ FinishArgs finish_args(const Plan& pl, const float* prior, float* scores, void* 
   FinishArgs f;
   f.uraw = reinterpret_cast<const float*>(static_cast<char*>(workspace) + pl.off_uraw);
   f.prior = prior; f.cu_seqlens = pl.cu_seqlens_dev; f.scores = scores;
-  f.n_seqs = pl.n_seqs; f.T = pl.T; f.LH = pl.L * pl.Hkv; f.row_splits = pl.row_splits; f.pool = pl.pool;
+  f.n_seqs = pl.n_seqs; f.T = pl.T; f.LH = pl.L * pl.Hkv; f.row_splits = pl.mass_parts; f.pool = pl.pool;
   f.lambda = pl.lambda; f.inv_pool = 1.0f / (float)pl.pool;
   f.mass_trim = pl.key_trim;
   f.pool_trim = (pl.variant & CODECOMP_VARIANT_POOL_PREFIX) ? pl.W : 0;
@@ -245,11 +251,17 @@ int launch_score(const Plan& pl, const void* q, const void* k, const float* prio
   a.inv_g = (pl.variant & CODECOMP_VARIANT_GROUP_SUM) ? 1.0f : 1.0f / (float)pl.G;
   a.inv_w = 1.0f / (float)pl.W;
   a.key_trim = pl.key_trim;
+  a.once_keys = pl.once_keys; a.once_rows = pl.once_rows; a.once_chunks = pl.once_chunks;
   a.blocks_per_head = (pl.variant & CODECOMP_VARIANT_GROUP_MAX) ? pl.W / 32 : 1;
   int rc;
   if (pl.kv_fp8) rc = pl.d == 128 ? dispatch_waves<128, true>(pl, a, stream, stages) : dispatch_waves<64, true>(pl, a, stream, stages);
   else rc = pl.d == 128 ? dispatch_waves<128, false>(pl, a, stream, stages) : dispatch_waves<64, false>(pl, a, stream, stages);
   if (rc) return rc;
+  if ((stages & CODECOMP_STAGE_MASS) && pl.once_keys > 0) {
+    if (pl.kv_fp8) rc = pl.d == 128 ? launch_once<128, true>(pl, a, stream) : launch_once<64, true>(pl, a, stream);
+    else rc = pl.d == 128 ? launch_once<128, false>(pl, a, stream) : launch_once<64, false>(pl, a, stream);
+    if (rc) return rc;
+  }
   if (!(stages & CODECOMP_STAGE_FINISH)) return 0;
 
   const FinishArgs f = finish_args(pl, prior, scores, workspace);

@@ -58,6 +58,8 @@ struct ScoreArgs {
   int tiles_per_problem;             // sum over requests of (lead + ceil(N_r / 64))
   int total_tiles;                   // L*Hkv * tiles_per_problem
   int stat_teams;                    // teams of the pass-1 launch whose statistics `stats` holds
+  int once_rows, once_chunks;        // one-pass kernel: query rows of a chunk (a multiple of 16), chunks
+  int once_keys;                     // requests of up to this many keys are not in the sequence (0: all are)
   int key_trim;                      // keys at the end of every request left out of the softmax (prefix-only variant)
   int blocks_per_head;               // largest-head-mass variant: row blocks of one query head (window / 32)
   uint32_t wave_desc[kMaxWaves];     // row block of slot 0 | row block of slot 1 << 8 | halves of slot 1 << 16 (bit 0: first, bit 1: second)
@@ -87,22 +89,27 @@ __device__ __forceinline__ u32x4 to_bf16x8(u32x2 v) {
   return r;
 }
 
-// Positions that request r takes in the tile sequence of a problem: its lead and its tiles.
-__device__ __forceinline__ int tiles_of(int len, int trim) { return (len - trim + kTileKeys - 1) / kTileKeys; }
+// Tiles of a request of `len` tokens.  A request that the one-pass kernel takes has no place in the tile sequence: minus its
+// lead, so that lead and tiles together take no position.
+struct TileRule { int trim, once_keys, lead; };
+__device__ __forceinline__ int tiles_of(int len, TileRule r) {
+  const int n = len - r.trim;
+  return n <= r.once_keys && n > 0 ? -r.lead : (n + kTileKeys - 1) / kTileKeys;
+}
 
 // Where a workgroup enters a problem's sequence: the request that holds position `xr` and the position at which
 // that request's lead begins.  All threads of the workgroup call it together (two barriers): every thread adds up
 // a contiguous share of the requests, a prefix sum over the threads finds the share that holds xr, and its owner
 // walks that share.  The segment loop then only ever steps from one request to the next.
 template <int NT>
-__device__ __forceinline__ void locate_first(const int32_t* cu, int n_seqs, int lead, int trim, int xr, int& seq, int& acc) {
+__device__ __forceinline__ void locate_first(const int32_t* cu, int n_seqs, TileRule rule, int xr, int& seq, int& acc) {
   __shared__ int wave_total[NT / 64];
   __shared__ int found[2];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int per = (n_seqs + NT - 1) / NT;
   const int r0 = min(tid * per, n_seqs), r1 = min(r0 + per, n_seqs);
   int mine = 0;
-  for (int r = r0; r < r1; ++r) mine += lead + tiles_of(cu[r + 1] - cu[r], trim);
+  for (int r = r0; r < r1; ++r) mine += rule.lead + tiles_of(cu[r + 1] - cu[r], rule);
   int incl = mine;                                   // inclusive prefix sum inside the wave
 #pragma unroll
   for (int off = 1; off < 64; off <<= 1) {
@@ -117,7 +124,7 @@ __device__ __forceinline__ void locate_first(const int32_t* cu, int n_seqs, int 
   if (xr >= start && xr < start + mine) {            // exactly one thread, when xr lies inside the sequence
     int pos = start, r = r0;
     for (;; ++r) {
-      const int span = lead + tiles_of(cu[r + 1] - cu[r], trim);
+      const int span = rule.lead + tiles_of(cu[r + 1] - cu[r], rule);
       if (xr < pos + span) break;
       pos += span;
     }
@@ -127,7 +134,7 @@ __device__ __forceinline__ void locate_first(const int32_t* cu, int n_seqs, int 
   seq = found[0]; acc = found[1];
   if (acc < 0) {                                     // past the end (never for a position inside the sequence): last request
     acc = 0;
-    for (int r = 0; r < n_seqs - 1; ++r) acc += lead + tiles_of(cu[r + 1] - cu[r], trim);
+    for (int r = 0; r < n_seqs - 1; ++r) acc += rule.lead + tiles_of(cu[r + 1] - cu[r], rule);
   }
 }
 
@@ -242,10 +249,11 @@ __global__ __launch_bounds__(NW * 64, (NW >= 3 ? 2 : 1)) void score_pass_kernel(
   const int teams = (int)gridDim.x / a.row_splits;
   const int x_begin = __builtin_amdgcn_readfirstlane(first_tile(team, a.total_tiles, teams));
   const int x_end = __builtin_amdgcn_readfirstlane(first_tile(team + 1, a.total_tiles, teams));
+  const TileRule rule = {a.key_trim, a.once_keys, a.lead};
   // the request the walk stands in: request cur_seq of problem cur_lz, whose lead begins at position cur_acc
   int cur_lz = x_begin / a.tiles_per_problem, cur_seq = 0, cur_acc = 0;
   if (a.n_seqs > 16 && x_begin < x_end)                      // few requests: walking there from the first one is as quick
-    locate_first<NT>(a.cu_seqlens, a.n_seqs, a.lead, a.key_trim, x_begin - cur_lz * a.tiles_per_problem, cur_seq, cur_acc);
+    locate_first<NT>(a.cu_seqlens, a.n_seqs, rule, x_begin - cur_lz * a.tiles_per_problem, cur_seq, cur_acc);
   cur_seq = __builtin_amdgcn_readfirstlane(cur_seq);         // the same in every lane: scalar registers from here on
   cur_acc = __builtin_amdgcn_readfirstlane(cur_acc);
   for (int x = x_begin; x < x_end;) {
@@ -255,12 +263,12 @@ __global__ __launch_bounds__(NW * 64, (NW >= 3 ? 2 : 1)) void score_pass_kernel(
   if (lz != cur_lz) { cur_lz = lz; cur_seq = 0; cur_acc = 0; }     // crossed into the next problem: its first request
   const int xr = x - lz * a.tiles_per_problem;
   int tok0 = a.cu_seqlens[cur_seq], tok1 = a.cu_seqlens[cur_seq + 1];
-  int tiles_of_seq = tiles_of(tok1 - tok0, a.key_trim);
+  int tiles_of_seq = tiles_of(tok1 - tok0, rule);
   while (xr >= cur_acc + a.lead + tiles_of_seq && cur_seq < a.n_seqs - 1) {       // usually no step or one
     cur_acc += a.lead + tiles_of_seq;
     ++cur_seq;
     tok0 = tok1; tok1 = a.cu_seqlens[cur_seq + 1];
-    tiles_of_seq = tiles_of(tok1 - tok0, a.key_trim);
+    tiles_of_seq = tiles_of(tok1 - tok0, rule);
   }
   const int seq = cur_seq, n = tok1 - tok0 - a.key_trim;     // keys of the request: all but the last key_trim
   int tile_in_seq = xr - cur_acc - a.lead;                   // < 0 inside the lead
@@ -833,7 +841,7 @@ int launch_passes(const Plan& pl, ScoreArgs a, hipStream_t stream, unsigned stag
   const int64_t max_segments = pl.total_tiles > 0 ? (int64_t)max_tiles * a.stat_teams / pl.total_tiles + 2 : 0;
   constexpr unsigned kAllThree = CODECOMP_STAGE_ROW_STATS | CODECOMP_STAGE_ROW_MERGE | CODECOMP_STAGE_MASS;
   a.merge_in_mass = NW <= 4 && (stages & kAllThree) == kAllThree && max_segments <= kMergeInMassSegments;
-  if ((stages & CODECOMP_STAGE_ROW_MERGE) && !a.merge_in_mass) {
+  if ((stages & CODECOMP_STAGE_ROW_MERGE) && !a.merge_in_mass && any_tile) {
     if (int rc = launch_row_merge(pl, a, stream)) return rc;
   }
   if ((stages & CODECOMP_STAGE_MASS) && any_tile) {

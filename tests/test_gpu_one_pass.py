@@ -1,0 +1,132 @@
+"""Requests of up to 768 keys, whose logits are formed once (one workgroup holds the keys): against the oracle and against the
+two passes, which calls with a given number of workgroups take for every request."""
+import numpy as np
+import pytest
+
+from oracle import codecomp_oracle as orc
+from paper_2604_10235_amd import workloads as wl
+from tests import parity_util as pu
+
+pytestmark = pytest.mark.gpu
+
+# Both ways round the argument of an exponential (below 2^6 in units of log2, scores of normal keys) and take a normaliser that
+# is as exact: 2^6 * 2^-24 * ln 2 = 2.6e-6 a side; sums of up to 1200 rows of 768 keys add less than 1e-6 each.
+TWO_WAYS = 8e-6
+
+
+def both_ways(w, kv="bf16", q_scale=1.0, **over):
+    import torch
+    from paper_2604_10235_amd import binding as b
+    q, k, v, prior = wl.make_all(w)
+    if q_scale != 1.0:
+        q = wl.f32_to_bf16_bits(orc.bf16_bits_to_f64(q).astype(np.float32) * np.float32(q_scale))
+    if kv == "fp8":
+        k, v = wl.bf16_bits_to_fp8_codes(k), wl.bf16_bits_to_fp8_codes(v)
+    got = []
+    for wgs in (0, 40):
+        p = b.DeviceProblem(w, q, k, v, prior, score_workgroups=wgs, **over)
+        p.workspace.fill_(0xFF)                                    # nothing may be read before it is written
+        p.score()
+        first = p.scores.clone()
+        p.scores.fill_(float("nan"))
+        p.score()
+        torch.cuda.synchronize()
+        assert torch.equal(first.view(torch.int32), p.scores.view(torch.int32))      # the same bits again
+        got.append(p.scores.cpu().numpy())
+    return q, k, prior, got
+
+
+# Rows: one, a part of a block of 16, 1 .. 3 row splits, odd numbers of blocks; few problems (rows shared out), more problems than
+# compute units; tiles of 16 keys: one key, full, one over, one tile per wave of four and of eight, the longest of each kind.
+@pytest.mark.parametrize("heads,d,window,layers", [((1, 1), 64, 1, 1), ((5, 1), 128, 3, 2), ((14, 2), 128, 50, 1), ((4, 4), 64, 16, 70),
+                                                   ((12, 1), 128, 100, 1), ((18, 2), 128, 64, 3)])
+@pytest.mark.parametrize("lens", [[1, 15, 16, 17, 63, 64], [65, 128, 129, 384], [385, 767, 768, 200]])
+@pytest.mark.parametrize("kv", ["bf16", "fp8"])
+def test_short_requests(heads, d, window, layers, lens, kv):
+    lens = [max(n, window) for n in lens]
+    w = wl.scaled(wl.qwen7b_32k(), n_layers=layers, n_q_heads=heads[0], n_kv_heads=heads[1], head_dim=d, window=window, seqlens=lens, budgets=lens)
+    q, k, prior, (one, two) = both_ways(w, kv)
+    np.testing.assert_allclose(one, two, rtol=TWO_WAYS, atol=1e-30)
+    some = slice(0, min(layers, 2))
+    pu.assert_scores_close(one[some], orc.score_packed(q[some], k[some], prior, w.cu_seqlens(), pool_kernel=w.pool_kernel, prior_weight=w.prior_weight,
+                                                        k_format="fp8_e4m3" if kv == "fp8" else "bf16"))
+
+
+# More than 512 problems of short requests next to longer ones, which take two passes in the same call; a window that the
+# softmax leaves out (a request that is nothing else among them)
+@pytest.mark.parametrize("lens,variant", [([300, 769, 100, 768, 32, 2000, 500], 0), ([300, 801, 100, 32, 800, 500, 400], 8), ([33, 64, 900, 40, 41], 1 | 4 | 8 | 16)])
+def test_short_requests_among_longer_ones(lens, variant):
+    from tests.test_gpu_parity import oracle_variant
+    w = wl.scaled(wl.qwen7b_32k(), n_layers=2, n_q_heads=140, n_kv_heads=70, head_dim=64, window=32, seqlens=lens, budgets=lens)
+    q, k, prior, (one, two) = both_ways(w, score_variant=variant)
+    np.testing.assert_allclose(one, two, rtol=TWO_WAYS, atol=1e-30)
+    pu.assert_scores_close(one[:1], orc.score_packed(q[:1], k[:1], prior, w.cu_seqlens(), pool_kernel=w.pool_kernel, prior_weight=w.prior_weight,
+                                                     **oracle_variant(variant)))
+
+
+# Logits hundreds of nats apart: the exponentials outrun the references and the rows are done again from their largest logits.
+# An argument below 2^10 in units of log2 is off by 2^10 * 2^-24 * ln 2 = 4.2e-5 a side, its logit (128 products) by as much again.
+@pytest.mark.parametrize("lens", [[700, 130], [384, 200, 96]])
+@pytest.mark.parametrize("kv", ["bf16", "fp8"])
+def test_logits_far_apart(lens, kv):
+    w = wl.scaled(wl.qwen7b_32k(), n_layers=1, window=64, seqlens=lens, budgets=lens, prior_weight=0.0)
+    q, k, prior, (one, two) = both_ways(w, kv, q_scale=40.0)
+    np.testing.assert_allclose(one, two, rtol=2e-4, atol=1e-30)
+    # masses below 2^-126 are 0 in 32 bits
+    ref = orc.score_packed(q, k, prior, w.cu_seqlens(), pool_kernel=w.pool_kernel, prior_weight=0.0,
+                           k_format="fp8_e4m3" if kv == "fp8" else "bf16")
+    np.testing.assert_allclose(one, ref, rtol=1e-3, atol=1e-30)
+
+
+def test_strided_queries_and_keys():
+    """Token-major keys and queries, padded rows: the strides that the two passes take."""
+    import torch
+    from paper_2604_10235_amd import binding as b
+    lens, L, HQ, H, W, d = [700, 64, 385], 2, 6, 2, 48, 128
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    T = int(cu[-1])
+    g = torch.Generator(device="cuda").manual_seed(3)
+    q = torch.randn((L, W, len(lens), HQ, d + 8), generator=g, device="cuda").bfloat16()
+    k = torch.randn((L, T, H, d + 24), generator=g, device="cuda").bfloat16()
+    prior = torch.rand(T, generator=g, device="cuda")
+    dev = torch.from_numpy(cu).cuda()
+    scores = []
+    for layout in ("strided", "packed"):
+        qq = q if layout == "strided" else q[..., :d].permute(0, 2, 3, 1, 4).contiguous()
+        kk = k if layout == "strided" else k[..., :d].permute(0, 2, 1, 3).contiguous()
+        strides = {} if layout == "packed" else dict(
+            q_stride_layer=q.stride(0), q_stride_tok=q.stride(1), q_stride_seq=q.stride(2), q_stride_head=q.stride(3),
+            kv_stride_layer=k.stride(0), kv_stride_tok=k.stride(1), kv_stride_head=k.stride(2))
+        p = b.make_params(n_layers=L, n_q_heads=HQ, n_kv_heads=H, head_dim=d, window=W, pool_kernel=7, prior_weight=1.0, cu_seqlens_host=cu,
+                          cu_budgets_host=cu, cu_seqlens_dev=dev.data_ptr(), cu_budgets_dev=dev.data_ptr(), **strides)
+        ws = torch.empty(b.codecomp_workspace_bytes(p), dtype=torch.uint8, device="cuda")
+        out = torch.empty((L, H, T), dtype=torch.float32, device="cuda")
+        b.codecomp_score(qq, kk, prior, p, out, ws)
+        scores.append(out)
+    torch.cuda.synchronize()
+    assert torch.equal(scores[0].view(torch.int32), scores[1].view(torch.int32))
+
+
+def test_replayed_in_a_graph():
+    """The kernels (loads straight into LDS, no memset) under capture: every replay gives the eager result."""
+    import torch
+    from paper_2604_10235_amd import binding as b
+    lens = [700, 100, 385]
+    w = wl.scaled(wl.qwen7b_32k(), n_layers=2, seqlens=lens, budgets=[80, 64, 100])
+    p = b.DeviceProblem(w, *wl.make_all(w))
+    p.compress()
+    torch.cuda.synchronize()
+    want = [x.clone() for x in (p.scores, p.idx, p.k_out, p.v_out)]
+    graph = torch.cuda.CUDAGraph()
+    side = torch.cuda.Stream()
+    with torch.cuda.graph(graph, stream=side):
+        p.compress()
+    for _ in range(4):
+        for x in (p.scores, p.idx, p.k_out, p.v_out):
+            x.zero_()
+        p.workspace.fill_(0x7F)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        for got, ref in zip((p.scores, p.idx, p.k_out, p.v_out), want):
+            assert torch.equal(got, ref)
