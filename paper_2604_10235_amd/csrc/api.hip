@@ -78,7 +78,7 @@ int make_plan(const codecomp_params* p, Plan* pl) {
     return CODECOMP_EINVAL_NULL;
   if (p->window < 1) return CODECOMP_EINVAL_WINDOW;
   if (p->cu_seqlens_host[0] != 0 || p->cu_budgets_host[0] != 0) return CODECOMP_EINVAL_SEQLENS;
-  int max_n = 0;
+  int max_n = 0, max_b = 0;
   for (int r = 0; r < p->n_seqs; ++r) {
     int64_t n = (int64_t)p->cu_seqlens_host[r + 1] - p->cu_seqlens_host[r];
     int64_t b = (int64_t)p->cu_budgets_host[r + 1] - p->cu_budgets_host[r];
@@ -86,6 +86,7 @@ int make_plan(const codecomp_params* p, Plan* pl) {
     if (p->window > n) return CODECOMP_EINVAL_WINDOW;
     if (b < p->window || b > n) return CODECOMP_EINVAL_BUDGET;
     if (n > max_n) max_n = (int)n;
+    if (b > max_b) max_b = (int)b;
   }
   const int64_t strides[] = {p->q_stride_layer, p->q_stride_seq, p->q_stride_head, p->q_stride_tok,
                              p->kv_stride_layer, p->kv_stride_head, p->kv_stride_tok,
@@ -109,6 +110,7 @@ int make_plan(const codecomp_params* p, Plan* pl) {
   pl->T = p->cu_seqlens_host[p->n_seqs];
   pl->TB = p->cu_budgets_host[p->n_seqs];
   pl->max_n = max_n;
+  pl->max_b = max_b;
   int64_t R = (int64_t)pl->G * pl->W;
   if (R > (1 << 16)) return CODECOMP_EINVAL_SHAPE;
   pl->R = (int)R;
@@ -225,7 +227,8 @@ int launch_compress(const Plan& pl, const void* q, const void* k, const void* v,
                     void* k_out, void* v_out, void* workspace, hipStream_t stream) {
   if (fused_tail(pl)) {
     if (int rc = launch_score(pl, q, k, prior, scores, workspace, stream, CODECOMP_STAGE_ALL & ~CODECOMP_STAGE_FINISH)) return rc;
-    if (int rc = launch_finish_select(pl, prior, scores, idx, workspace, stream)) return rc;
+    if (int rc = launch_finish_select(pl, prior, scores, idx, k, v, k_out, v_out, workspace, stream)) return rc;
+    if (fused_copy(pl)) return 0;
   } else {
     if (int rc = launch_score(pl, q, k, prior, scores, workspace, stream)) return rc;
     const int rc = pl.select_mode == CODECOMP_SELECT_TWO_STAGE ? launch_select_two_stage(pl, scores, prior, idx, workspace, stream)

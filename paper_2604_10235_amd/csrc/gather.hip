@@ -2,28 +2,12 @@
 // compressed chunk of section "Position Encoding": rows keep their original order).
 // Pure data movement: a row of d elements (bf16, or one-byte FP8 codes) is moved as 16-byte pieces
 // by consecutive lanes, so both the reads and the writes of a row are one contiguous segment.
-#include "plan.h"
+#include "gather.h"
 
 namespace codecomp {
 
-struct GatherArgs {
-  const unsigned char* k;
-  const unsigned char* v;
-  const int32_t* idx;
-  const int32_t* cu_seqlens;
-  const int32_t* cu_budgets;
-  unsigned char* k_out;
-  unsigned char* v_out;
-  int n_seqs, Hkv, TB, pieces_log2;    // 16-byte pieces per row = d * element size / 16 (4, 8 or 16)
-  int64_t kv_sl, kv_sh, kv_st, o_sl, o_sh, o_st;     // in bytes
-};
-
 constexpr int kGatherThreads = 256;
 constexpr int kGatherRowsPerThread = 2;     // rows of K and of V a thread has in flight
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ u32x4 ld16(const unsigned char* p) { return *reinterpret_cast<const u32x4*>(p); }
-__device__ __forceinline__ void st16(unsigned char* p, u32x4 v) { *reinterpret_cast<u32x4*>(p) = v; }
 
 __global__ __launch_bounds__(kGatherThreads) void gather_kernel(GatherArgs a) {
   const int pieces = 1 << a.pieces_log2;
@@ -78,8 +62,7 @@ __global__ __launch_bounds__(kGatherThreads) void gather_kernel(GatherArgs a) {
   }
 }
 
-int launch_gather(const Plan& pl, const void* k, const void* v, const int32_t* idx, void* k_out, void* v_out,
-                  hipStream_t stream) {
+GatherArgs gather_args(const Plan& pl, const void* k, const void* v, const int32_t* idx, void* k_out, void* v_out) {
   GatherArgs a;
   a.k = static_cast<const unsigned char*>(k); a.v = static_cast<const unsigned char*>(v); a.idx = idx;
   a.cu_seqlens = pl.cu_seqlens_dev; a.cu_budgets = pl.cu_budgets_dev;
@@ -89,6 +72,12 @@ int launch_gather(const Plan& pl, const void* k, const void* v, const int32_t* i
   a.pieces_log2 = (pl.d == 128 ? 4 : 3) - (pl.kv_fp8 ? 1 : 0);
   a.kv_sl = pl.kv_sl * esz; a.kv_sh = pl.kv_sh * esz; a.kv_st = pl.kv_st * esz;
   a.o_sl = pl.o_sl * esz; a.o_sh = pl.o_sh * esz; a.o_st = pl.o_st * esz;
+  return a;
+}
+
+int launch_gather(const Plan& pl, const void* k, const void* v, const int32_t* idx, void* k_out, void* v_out,
+                  hipStream_t stream) {
+  const GatherArgs a = gather_args(pl, k, v, idx, k_out, v_out);
   const int rows_per_block = (kGatherThreads >> a.pieces_log2) * kGatherRowsPerThread;
   gather_kernel<<<dim3((pl.TB + rows_per_block - 1) / rows_per_block, pl.L * pl.Hkv), dim3(kGatherThreads), 0,
                   stream>>>(a);

@@ -48,6 +48,10 @@ constexpr int kSelectMaxCandidates = 65536;                // most candidates on
 // Up to there one workgroup per problem is quicker than parts, however few the problems.  Parts -> one workgroup: one problem of
 // 16384 candidates 34.5 -> 9.9 us, of 65536 37.5 -> 29.1; 64 of 65536 49.6 -> 31.0; one of 65536 with a binary prior 45.2 ->
 // 37.0, of one value only 128 -> 75; two-stage, 64 of 65536 107 -> 86.
+// A workgroup that selects copies the kept rows, too, up to this many bytes of K and V (read): a launch less.  Whole call, own kernel ->
+// copied along: 4 KV heads of 2048 tokens, head_dim 64, 256 kept (64 KB) 19.6 -> 18.1 us, 512 kept 20.0 -> 20.0, 1024 20.4 -> 22.6;
+// head_dim 128, 2000 tokens, 128 kept (64 KB) 27.8 -> 27.1, 512 28.2 -> 31.0; 112 heads of 2048, 256 kept 29.4 -> 28.1.
+constexpr int64_t kCopyBytes = 65536;
 constexpr int kFirstDigitBins = 2048;
 constexpr int kFinishHalo = 512;      // largest supported (pool_kernel - 1) / 2
 
@@ -61,6 +65,7 @@ struct Plan {
   float span_ratio; int span_min;
   int T, TB;                 // total tokens / total output slots over the packed requests
   int max_n;                 // longest request
+  int max_b;                 // largest budget
   int R;                     // G * W softmax rows per (layer, KV head, request)
   int row_splits;            // workgroups along the row axis (each <= kMaxWaves * kRowsPerWave rows)
   int row_blocks;            // blocks of 32 rows per split
@@ -122,7 +127,9 @@ int launch_compress(const Plan& pl, const void* q, const void* k, const void* v,
                     void* k_out, void* v_out, void* workspace, hipStream_t stream);
 // Pooling, prior and selection of requests that one workgroup each can take (fused_tail says whether these parameters can).
 bool fused_tail(const Plan& pl);
-int launch_finish_select(const Plan& pl, const float* prior, float* scores, int32_t* idx, void* workspace, hipStream_t stream);
+bool fused_copy(const Plan& pl);          // whether it copies the kept rows, too
+int launch_finish_select(const Plan& pl, const float* prior, float* scores, int32_t* idx, const void* k, const void* v, void* k_out,
+                         void* v_out, void* workspace, hipStream_t stream);
 int launch_gather(const Plan& pl, const void* k, const void* v, const int32_t* idx, void* k_out, void* v_out,
                   hipStream_t stream);
 

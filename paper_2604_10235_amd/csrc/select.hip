@@ -38,7 +38,7 @@
 #include <type_traits>
 
 #include "cut_range.h"
-#include "plan.h"
+#include "gather.h"
 
 namespace codecomp {
 
@@ -456,8 +456,8 @@ constexpr int kFinishNear = 4;      // neighbours on a side that three 16-byte L
 // The tail of the fused call in one kernel: the attention mass of a request is pooled, the prior added, the scores stored
 // (what score_finish_kernel does, the same sums in the same order), and the selection goes on with the scores it holds in
 // registers.  The masses pass through LDS, up to 32768 tokens at a time, so that a thread finds its neighbours there.
-template <bool FILL, int NT, int ITEMS, int HALO>
-__global__ __launch_bounds__(NT) void finish_select_kernel(SelectArgs a, FinishArgs f) {
+template <bool FILL, int NT, int ITEMS, int HALO, bool COPY>
+__global__ __launch_bounds__(NT) void finish_select_kernel(SelectArgs a, FinishArgs f, GatherArgs g) {
   constexpr int BLOCK = ITEMS < 32768 / NT ? ITEMS : 32768 / NT;   // slots per LDS filling
   constexpr int NEAR = kFinishNear;
   static_assert(HALO % 4 == 0 && HALO >= NEAR, "16-byte LDS accesses");
@@ -581,10 +581,12 @@ __global__ __launch_bounds__(NT) void finish_select_kernel(SelectArgs a, FinishA
       __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, make_float4(c[0], c[1], c[2], c[3])), scores, quad * 4, 0, 0);
     }
   }
-  if (bp <= 0) return;
-  const int slots = slots_of<NT>(npre);
-  const int members = FILL ? a.member_count[seq] : 0;
-  select_and_emit<NT, ITEMS>(sh, keys, slots, npre, npre - members, bp - members, bp >= npre, bp, out);
+  if (bp > 0) {
+    const int slots = slots_of<NT>(npre);
+    const int members = FILL ? a.member_count[seq] : 0;
+    select_and_emit<NT, ITEMS>(sh, keys, slots, npre, npre - members, bp - members, bp >= npre, bp, out);
+  }
+  if constexpr (COPY) gather_request<NT>(g, lz, s0, n, o0, bp + a.W);
 }
 
 // two-stage rule, stage 1: once per request (the prior is shared by layers and heads)
@@ -1293,16 +1295,27 @@ bool fused_tail(const Plan& pl) {
   return pl.pool * (busiest - even * 3 / 4) <= kWideReads;
 }
 
-int launch_finish_select(const Plan& pl, const float* prior, float* scores, int32_t* idx, void* workspace, hipStream_t stream) {
+// Requests that keep little: the workgroup that selects the rows copies them too, and a launch is saved.
+bool fused_copy(const Plan& pl) {
+  const int64_t bytes = (int64_t)pl.max_b * pl.d * (pl.kv_fp8 ? 1 : 2) * 2;
+  return fused_tail(pl) && bytes <= kCopyBytes;
+}
+
+int launch_finish_select(const Plan& pl, const float* prior, float* scores, int32_t* idx, const void* k, const void* v, void* k_out,
+                         void* v_out, void* workspace, hipStream_t stream) {
   const SelectArgs a = select_args(pl, scores, prior, idx, workspace);
   const FinishArgs f = finish_args(pl, prior, scores, workspace);
-  const bool fill = pl.select_mode == CODECOMP_SELECT_TWO_STAGE;
+  const GatherArgs g = gather_args(pl, k, v, idx, k_out, v_out);
+  const bool fill = pl.select_mode == CODECOMP_SELECT_TWO_STAGE, copy = fused_copy(pl);
   if (fill)
     if (int rc = launch_stage1(pl, a, stream)) return rc;
   dispatch_items(pl.max_n, (int64_t)pl.n_seqs * pl.L * pl.Hkv, [&](auto nt, auto items) {
     const dim3 grid(pl.n_seqs, pl.L * pl.Hkv), block(nt());
-    if (fill) finish_select_kernel<true, nt(), items(), kFinishHalo><<<grid, block, 0, stream>>>(a, f);
-    else finish_select_kernel<false, nt(), items(), kFinishHalo><<<grid, block, 0, stream>>>(a, f);
+    auto go = [&](auto filled, auto copied) {
+      finish_select_kernel<filled(), nt(), items(), kFinishHalo, copied()><<<grid, block, 0, stream>>>(a, f, g);
+    };
+    if (copy) { if (fill) go(std::true_type{}, std::true_type{}); else go(std::false_type{}, std::true_type{}); }
+    else { if (fill) go(std::true_type{}, std::false_type{}); else go(std::false_type{}, std::false_type{}); }
   });
   if (hipError_t e = hipGetLastError()) return (int)e;
   return 0;
