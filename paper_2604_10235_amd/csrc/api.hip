@@ -138,7 +138,10 @@ int make_plan(const codecomp_params* p, Plan* pl) {
   if (positions * problems > (1 << 30)) return CODECOMP_EINVAL_SHAPE;
   const int64_t once_problems = (int64_t)(once_short + once_long) * pl->L * pl->Hkv;
   const bool all_once = once_problems > 0 && tiles_once == tiles;
-  const bool once = (all_once || once_problems >= kOnceMixed) && !(pl->variant & CODECOMP_VARIANT_GROUP_MAX) &&
+  pl->rows_at_once = pl->R <= kRowsMost && max_n - pl->key_trim > kOnceKeys && max_n - pl->key_trim <= 128 * rows_tiles((pl->R + 15) / 16) &&
+                     (int64_t)pl->n_seqs * pl->L * pl->Hkv >= kRowsProblems && !(pl->variant & CODECOMP_VARIANT_GROUP_MAX) &&
+                     p->score_workgroups == 0 && p->score_lead_tiles == 0;
+  const bool once = !pl->rows_at_once && (all_once || once_problems >= kOnceMixed) && !(pl->variant & CODECOMP_VARIANT_GROUP_MAX) &&
                     p->score_workgroups == 0 && p->score_lead_tiles == 0;
   pl->once_keys = once ? kOnceKeys : 0;
   pl->once_short = once ? once_short : 0;
@@ -157,6 +160,7 @@ int make_plan(const codecomp_params* p, Plan* pl) {
     pl->once_shared_out = pl->once_chunks > 1 && once_problems * pl->once_chunks <= kOnceFill;
   }
   pl->mass_parts = once && all_once ? pl->once_chunks : pl->row_splits;
+  if (pl->rows_at_once) tiles = 0;
   if (once) {
     tiles -= tiles_once;
     positions -= tiles_once + (int64_t)pl->lead_tiles * (once_short + once_long);

@@ -22,6 +22,13 @@ constexpr int kOnceRows = 512;          // most query rows of a chunk
 // us, 640 among 32 109 -> 90, 448 of 200 among 448 of 4000 498 -> 494, 4480 among 224 611 -> 375.
 constexpr int kOnceMixed = 512;
 constexpr int kOnceFill = 256;          // workgroups that find a compute unit of their own at once: up to here a problem's rows are shared out
+// Few rows (up to kRowsMost): tiles of 16 keys per wave whose logits eight waves hold, by blocks of 16 rows; taken where a request is
+// too long for its keys to stay in registers and the problems use the device.  Whole call, two passes -> all rows at once: 128
+// problems of 1000 keys, 16 rows, head_dim 64 20 -> 12 us, 32 rows, head_dim 128 31 -> 18, of 2500 47 -> 32; 4096 of 1000 and 2500, 32
+// rows, head_dim 64 263 -> 176, 583 -> 376.  With 4 to 32 problems it is 30 % faster to 30 % slower (2500 keys), and requests of up to
+// kOnceKeys are up to twice as fast with their keys in registers.
+constexpr int kRowsMost = 64, kRowsProblems = 96;
+constexpr int rows_tiles(int blocks) { return blocks == 1 ? 32 : blocks == 2 ? 20 : blocks == 3 ? 12 : 8; }
 constexpr int kMaxScoreGrid = 2048;   // most workgroups a score pass is launched with
 constexpr int kLeadTiles = 4;         // a segment start (query fragments, first K tile) costs about this many tiles
 // Calls of up to this many (tile, row split) pairs get no leads: a workgroup then has one tile or two and nearly all of them start
@@ -75,6 +82,7 @@ struct Plan {
   // ones slot 1 covers (0: the wave has no slot 1).
   uint32_t wave_desc[kMaxWaves];
   uint8_t rb_holder[2 * kMaxWaves][2];   // per row block: wave * 2 + slot of its (one or two) owners, 255 = none
+  bool rows_at_once;         // few rows and no request longer than their logits' place in registers: one kernel (score_rows_kernel)
   int once_keys;             // requests of up to this many keys take the one-pass kernel (0: none does)
   int once_short, once_long; // how many of up to kOnceKeys / 2 keys, and of more
   int once_rows, once_chunks;            // query rows of a chunk, chunks

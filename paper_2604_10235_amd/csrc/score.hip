@@ -10,9 +10,13 @@ extern template int dispatch_waves<128, true>(const Plan&, const ScoreArgs&, hip
 extern template int dispatch_waves<64, false>(const Plan&, const ScoreArgs&, hipStream_t, unsigned);
 extern template int dispatch_waves<64, true>(const Plan&, const ScoreArgs&, hipStream_t, unsigned);
 extern template int launch_once<128, false>(const Plan&, const ScoreArgs&, hipStream_t);
+extern template int launch_rows<128, false>(const Plan&, const ScoreArgs&, hipStream_t);
 extern template int launch_once<128, true>(const Plan&, const ScoreArgs&, hipStream_t);
+extern template int launch_rows<128, true>(const Plan&, const ScoreArgs&, hipStream_t);
 extern template int launch_once<64, false>(const Plan&, const ScoreArgs&, hipStream_t);
+extern template int launch_rows<64, false>(const Plan&, const ScoreArgs&, hipStream_t);
 extern template int launch_once<64, true>(const Plan&, const ScoreArgs&, hipStream_t);
+extern template int launch_rows<64, true>(const Plan&, const ScoreArgs&, hipStream_t);
 
 // Per (layer*head, request, row): log2-sum-exp over the segments (of the teams) that cover the request and over the (at
 // most two) wave slots that hold a share of the row's keys.
@@ -257,6 +261,11 @@ int launch_score(const Plan& pl, const void* q, const void* k, const float* prio
   if (pl.kv_fp8) rc = pl.d == 128 ? dispatch_waves<128, true>(pl, a, stream, stages) : dispatch_waves<64, true>(pl, a, stream, stages);
   else rc = pl.d == 128 ? dispatch_waves<128, false>(pl, a, stream, stages) : dispatch_waves<64, false>(pl, a, stream, stages);
   if (rc) return rc;
+  if ((stages & CODECOMP_STAGE_MASS) && pl.rows_at_once) {
+    if (pl.kv_fp8) rc = pl.d == 128 ? launch_rows<128, true>(pl, a, stream) : launch_rows<64, true>(pl, a, stream);
+    else rc = pl.d == 128 ? launch_rows<128, false>(pl, a, stream) : launch_rows<64, false>(pl, a, stream);
+    if (rc) return rc;
+  }
   if ((stages & CODECOMP_STAGE_MASS) && pl.once_keys > 0) {
     if (pl.kv_fp8) rc = pl.d == 128 ? launch_once<128, true>(pl, a, stream) : launch_once<64, true>(pl, a, stream);
     else rc = pl.d == 128 ? launch_once<128, false>(pl, a, stream) : launch_once<64, false>(pl, a, stream);

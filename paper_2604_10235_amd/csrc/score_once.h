@@ -58,6 +58,16 @@ __device__ __forceinline__ float dpp_add(float own, float other) {
   return own + __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, other), CTRL, 0xF, 0xF, true));
 }
 
+// The masses that a lane group holds of four keys, summed over its 16 rows: lane r gets key r % 4.
+__device__ __forceinline__ float mass_of_rows(f32x4 mass, int l16) {
+  const bool odd = l16 & 1, upper = l16 & 2;
+  const float x0 = dpp_add<0xB1>(odd ? mass[1] : mass[0], odd ? mass[0] : mass[1]);      // with lane ^ 1
+  const float x1 = dpp_add<0xB1>(odd ? mass[3] : mass[2], odd ? mass[2] : mass[3]);
+  float x = dpp_add<0x4E>(upper ? x1 : x0, upper ? x0 : x1);                             // with lane ^ 2
+  x = dpp_add<0x124>(x, x);                                                              // row_ror:4
+  return dpp_add<0x128>(x, x);                                                           // row_ror:8
+}
+
 // Keeps a value where it is written: left alone, the compiler puts the masses off, so that both sets of exponentials live on beside
 // new ones, and the exponentials behind the next wait, away from the MFMAs.
 template <class T>
@@ -337,16 +347,11 @@ __device__ __forceinline__ void once_run(const ScoreArgs& a, typename Once<D, NW
       barrier();
   }
 
-  // ---- masses: sums over the 16 rows of a lane group (after them lane r holds key r % 4 of the group's four), one store per tile
+  // ---- masses, one store per tile
   float* u = a.uraw + ((int64_t)chunk * a.LH + lz) * a.T + tok0;
-  const bool odd = l16 & 1, upper = l16 & 2;
 #pragma unroll
   for (int t = 0; t < NT; ++t) {
-    const float x0 = dpp_add<0xB1>(odd ? mass[t][1] : mass[t][0], odd ? mass[t][0] : mass[t][1]);      // with lane ^ 1
-    const float x1 = dpp_add<0xB1>(odd ? mass[t][3] : mass[t][2], odd ? mass[t][2] : mass[t][3]);
-    float x = dpp_add<0x4E>(upper ? x1 : x0, upper ? x0 : x1);                                         // with lane ^ 2
-    x = dpp_add<0x124>(x, x);                                                                          // row_ror:4
-    x = dpp_add<0x128>(x, x);                                                                          // row_ror:8
+    const float x = mass_of_rows(mass[t], l16);
     const int key = key0 + t * 16 + 4 * grp + l16;
     if (l16 < 4 && t < mine && key < n) u[key] = x * a.inv_g;
   }
@@ -392,6 +397,157 @@ int launch_once(const Plan& pl, const ScoreArgs& a, hipStream_t stream) {
     score_once_kernel<D, 4, K8><<<grid, dim3(256), 0, stream>>>(a, 0, kOnceKeys / 2);
     if (hipError_t e = hipGetLastError()) return (int)e;
   }
+  return 0;
+}
+
+// ---------------------------------------------------------------------------------------------------------
+// Few query rows: all of them at once.
+// ---------------------------------------------------------------------------------------------------------
+// Up to 64 rows leave room for all logits of a longer request in one workgroup's registers (RB blocks of 16 rows, TT tiles of 16
+// keys per wave: 4 RB TT registers), so that the keys only pass through.  The rows' largest logits and sums are exchanged
+// between the waves once each.  Bound by the memory round trips of a compute unit,
+// then by issue; figures at kRowsProblems.
+template <int RB>
+struct Rows {
+  static constexpr int TT = rows_tiles(RB);
+  struct Shared {
+    float largest[RB][16][8], sums[RB][16][8];
+  };
+};
+
+template <int D, bool K8, int RB>
+__global__ __launch_bounds__(512, 2) void score_rows_kernel(ScoreArgs a) {
+  constexpr int KS = D / 32, ESZ = K8 ? 1 : 2, NW = 8, TT = Rows<RB>::TT;
+  constexpr int GROUP = D == 128 && !K8 ? 2 : 4;   // tiles sent for together, a group ahead
+  using stage_t = std::conditional_t<K8, u32x2, u32x4>;
+  __shared__ __attribute__((aligned(16))) typename Rows<RB>::Shared sh;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int l16 = lane & 15, grp = lane >> 4;
+  const int seq = (int)blockIdx.x / a.LH, lz = (int)blockIdx.x - seq * a.LH;
+  const int tok0 = a.cu_seqlens[seq];
+  const int n = a.cu_seqlens[seq + 1] - tok0 - a.key_trim;
+  if (n <= 0 || n > TT * NW * 16) return;          // longer ones: the host has taken another kernel
+  const int layer = lz / a.Hkv, head = lz - layer * a.Hkv;
+  const int tiles = (n + 15) >> 4, base = tiles / NW, extra = tiles - base * NW;
+  const int key0 = (wave * base + max(0, wave - (NW - extra))) * 16;
+  const int mine = base + (wave >= NW - extra ? 1 : 0);
+  const float c = a.c;
+
+  const unsigned char* kb = a.k + ((int64_t)layer * a.kv_sl + (int64_t)head * a.kv_sh + (int64_t)tok0 * a.kv_st) * ESZ + grp * 8 * ESZ;
+  stage_t kf[2][GROUP][KS];
+  auto load = [&](int t0, stage_t (&dst)[GROUP][KS]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < GROUP; ++i) {
+      const unsigned char* p = kb + (int64_t)min(key0 + (t0 + i) * 16 + l16, n - 1) * a.kv_st * ESZ;
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks) dst[i][ks] = *reinterpret_cast<const stage_t*>(p + ks * 32 * ESZ);
+    }
+  };
+  load(0, kf[0]);
+  u32x4 qf[RB][KS];
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb) {
+    const int row = rb * 16 + l16 < a.R ? rb * 16 + l16 : 0;               // rows past the end read the first one
+    const int g = row_group(row, a.inv_w);
+    const uint16_t* p = a.q + (int64_t)layer * a.q_sl + (int64_t)seq * a.q_ss + (int64_t)(head * a.G + g) * a.q_sh +
+                        (int64_t)(row - g * a.W) * a.q_st + grp * 8;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) qf[rb][ks] = *reinterpret_cast<const u32x4*>(p + ks * 32);
+  }
+  f32x4 e[TT][RB];
+  const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+  float m[RB];
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb) m[rb] = -INFINITY;
+#pragma unroll
+  for (int t0 = 0; t0 < TT; t0 += GROUP) {
+    if (t0 < mine) {
+      if (t0 + GROUP < TT && t0 + GROUP < mine) load(t0 + GROUP, kf[(t0 / GROUP + 1) & 1]);
+#pragma unroll
+      for (int i = 0; i < GROUP; ++i) {
+        const int t = t0 + i;
+        if (t >= TT) continue;
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb) {
+          f32x4 s = zero;
+#pragma unroll
+          for (int ks = 0; ks < KS; ++ks) s = once_mma(to_bf16x8(kf[(t0 / GROUP) & 1][i][ks]), qf[rb][ks], s);
+          if (t >= mine - 1) {                     // the wave's last tile may hold places without a key, those after it do not count
+#pragma unroll
+            for (int v = 0; v < 4; ++v) s[v] = t == mine - 1 && key0 + t * 16 + 4 * grp + v < n ? s[v] : -INFINITY;
+          }
+          e[t][rb] = s;
+          m[rb] = fmaxf(fmaxf(m[rb], fmaxf(s[0], s[1])), fmaxf(s[2], s[3]));
+        }
+      }
+    }
+  }
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb) {
+    const float x = row_max4(m[rb]);
+    if (lane < 16) sh.largest[rb][l16][wave] = x;
+  }
+  __syncthreads();
+  float sum[RB];
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb) {
+    const float4 x = *reinterpret_cast<const float4*>(&sh.largest[rb][l16][0]), y = *reinterpret_cast<const float4*>(&sh.largest[rb][l16][4]);
+    m[rb] = fmaxf(fmaxf(fmaxf(x.x, x.y), fmaxf(x.z, x.w)), fmaxf(fmaxf(y.x, y.y), fmaxf(y.z, y.w))) * c;
+    sum[rb] = 0.f;
+  }
+#pragma unroll
+  for (int t0 = 0; t0 < TT; t0 += GROUP) {
+    if (t0 < mine) {
+#pragma unroll
+      for (int t = t0; t < t0 + GROUP && t < TT; ++t)
+#pragma unroll
+        for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            const float x = __builtin_amdgcn_exp2f(__builtin_fmaf(e[t][rb][v], c, -m[rb]));
+            e[t][rb][v] = x;
+            sum[rb] += x;
+          }
+    }
+  }
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb) {
+    const float x = row_sum4(sum[rb]);
+    if (lane < 16) sh.sums[rb][l16][wave] = x;
+  }
+  __syncthreads();
+  float w[RB];
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb) {
+    const float4 x = *reinterpret_cast<const float4*>(&sh.sums[rb][l16][0]), y = *reinterpret_cast<const float4*>(&sh.sums[rb][l16][4]);
+    const float total = ((x.x + x.y) + (x.z + x.w)) + ((y.x + y.y) + (y.z + y.w));
+    w[rb] = rb * 16 + l16 < a.R ? 1.0f / total : 0.f;
+  }
+  float* u = a.uraw + (int64_t)lz * a.T + tok0;
+#pragma unroll
+  for (int t = 0; t < TT; ++t) {
+    if (t >= mine) continue;
+    f32x4 mass = zero;
+#pragma unroll
+    for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) mass[v] = __builtin_fmaf(e[t][rb][v], w[rb], mass[v]);
+    const float x = mass_of_rows(mass, l16);
+    const int key = key0 + t * 16 + 4 * grp + l16;
+    if (l16 < 4 && key < n) u[key] = x * a.inv_g;
+  }
+}
+
+template <int D, bool K8>
+int launch_rows(const Plan& pl, const ScoreArgs& a, hipStream_t stream) {
+  const dim3 grid((unsigned)((int64_t)pl.n_seqs * pl.L * pl.Hkv)), block(512);
+  switch ((pl.R + 15) / 16) {
+    case 1: score_rows_kernel<D, K8, 1><<<grid, block, 0, stream>>>(a); break;
+    case 2: score_rows_kernel<D, K8, 2><<<grid, block, 0, stream>>>(a); break;
+    case 3: score_rows_kernel<D, K8, 3><<<grid, block, 0, stream>>>(a); break;
+    default: score_rows_kernel<D, K8, 4><<<grid, block, 0, stream>>>(a); break;
+  }
+  if (hipError_t e = hipGetLastError()) return (int)e;
   return 0;
 }
 

@@ -3,5 +3,7 @@
 
 namespace codecomp {
 template int launch_once<128, false>(const Plan&, const ScoreArgs&, hipStream_t);
+template int launch_rows<128, false>(const Plan&, const ScoreArgs&, hipStream_t);
 template int launch_once<128, true>(const Plan&, const ScoreArgs&, hipStream_t);
+template int launch_rows<128, true>(const Plan&, const ScoreArgs&, hipStream_t);
 }  // namespace codecomp

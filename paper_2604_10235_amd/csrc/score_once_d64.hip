@@ -3,5 +3,7 @@
 
 namespace codecomp {
 template int launch_once<64, false>(const Plan&, const ScoreArgs&, hipStream_t);
+template int launch_rows<64, false>(const Plan&, const ScoreArgs&, hipStream_t);
 template int launch_once<64, true>(const Plan&, const ScoreArgs&, hipStream_t);
+template int launch_rows<64, true>(const Plan&, const ScoreArgs&, hipStream_t);
 }  // namespace codecomp

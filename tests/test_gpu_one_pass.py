@@ -130,3 +130,32 @@ def test_replayed_in_a_graph():
         torch.cuda.synchronize()
         for got, ref in zip((p.scores, p.idx, p.k_out, p.v_out), want):
             assert torch.equal(got, ref)
+
+
+# Few rows: all logits of a request of up to 4096 keys (16 rows) to 1024 (64 rows) at once, from 96 problems on.  Blocks of 16 rows
+# full and begun; one tile more than fits the keys' own registers, the longest, the next longer (two passes), short ones among them.
+@pytest.mark.parametrize("heads,d,window", [((50, 50), 64, 16), ((100, 100), 64, 7), ((100, 50), 64, 16), ((50, 50), 128, 17), ((50, 50), 128, 48),
+                                            ((200, 50), 64, 16), ((50, 50), 128, 63)])
+@pytest.mark.parametrize("which", ["shortest", "longest", "too long"])
+@pytest.mark.parametrize("kv", ["bf16", "fp8"])
+def test_few_rows(heads, d, window, which, kv):
+    rows = heads[0] // heads[1] * window
+    most = {1: 4096, 2: 2560, 3: 1536, 4: 1024}[(rows + 15) // 16]
+    lens = {"shortest": [769, 20, 300], "longest": [most, most - 127], "too long": [most + 1, 100]}[which]
+    lens = [max(n, window) for n in lens]
+    w = wl.scaled(wl.qwen7b_32k(), n_layers=1, n_q_heads=heads[0], n_kv_heads=heads[1], head_dim=d, window=window, seqlens=lens, budgets=lens)
+    q, k, prior, (one, two) = both_ways(w, kv)
+    np.testing.assert_allclose(one, two, rtol=TWO_WAYS, atol=1e-30)
+    ref = orc.score_packed(q, k, prior, w.cu_seqlens(), pool_kernel=w.pool_kernel, prior_weight=w.prior_weight, k_format="fp8_e4m3" if kv == "fp8" else "bf16")
+    pu.assert_scores_close(one, ref)
+
+
+@pytest.mark.parametrize("variant", [8, 1 | 4 | 8 | 16])
+def test_few_rows_other_readings(variant):
+    from tests.test_gpu_parity import oracle_variant
+    lens = [1500, 32, 40, 33]                                       # a request without a key of its own among them
+    w = wl.scaled(wl.qwen7b_32k(), n_layers=2, n_q_heads=30, n_kv_heads=30, head_dim=64, window=32, seqlens=lens, budgets=lens)
+    q, k, prior, (one, two) = both_ways(w, score_variant=variant)
+    np.testing.assert_allclose(one, two, rtol=TWO_WAYS, atol=1e-30)
+    pu.assert_scores_close(one, orc.score_packed(q, k, prior, w.cu_seqlens(), pool_kernel=w.pool_kernel, prior_weight=w.prior_weight,
+                                                 **oracle_variant(variant)))
