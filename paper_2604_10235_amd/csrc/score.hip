@@ -254,6 +254,8 @@ int launch_score(const Plan& pl, const void* q, const void* k, const float* prio
   a.c = pl.scale * 1.4426950408889634f;
   a.inv_g = (pl.variant & CODECOMP_VARIANT_GROUP_SUM) ? 1.0f : 1.0f / (float)pl.G;
   a.inv_w = 1.0f / (float)pl.W;
+  a.inv_problem = 1.0f / (float)pl.tiles_per_problem; a.inv_heads = 1.0f / (float)pl.Hkv; a.inv_splits = 1.0f / (float)pl.row_splits;
+  a.teams = a.tile_each = a.tile_left = a.by_die = 0; a.inv_teams = 0.f;
   a.key_trim = pl.key_trim;
   a.once_keys = pl.once_keys; a.once_rows = pl.once_rows; a.once_chunks = pl.once_chunks;
   a.blocks_per_head = (pl.variant & CODECOMP_VARIANT_GROUP_MAX) ? pl.W / 32 : 1;

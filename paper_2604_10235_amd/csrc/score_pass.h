@@ -25,6 +25,7 @@
 #include <atomic>
 #include <type_traits>
 
+#include "divide.h"
 #include "plan.h"
 
 namespace codecomp {
@@ -57,6 +58,9 @@ struct ScoreArgs {
   int lead;                          // empty positions before the tiles of each problem
   int tiles_per_problem;             // sum over requests of (lead + ceil(N_r / 64))
   int total_tiles;                   // L*Hkv * tiles_per_problem
+  int teams, tile_each, tile_left;   // teams of this launch; total_tiles / teams and what it leaves
+  int by_die;                        // 1: the members of a team are 8 workgroups apart
+  float inv_teams, inv_problem, inv_heads, inv_splits;      // 1 / teams, / tiles_per_problem, / Hkv, / row_splits
   int stat_teams;                    // teams of the pass-1 launch whose statistics `stats` holds
   int once_rows, once_chunks;        // one-pass kernel: query rows of a chunk (a multiple of 16), chunks
   int once_keys;                     // requests of up to this many keys are not in the sequence (0: all are)
@@ -138,11 +142,8 @@ __device__ __forceinline__ void locate_first(const int32_t* cu, int n_seqs, Tile
   }
 }
 
-// First tile of team g of `wgs`: floor(g * total / wgs) in 32 bits (g <= wgs <= 2048).
-__device__ __forceinline__ int first_tile(int g, int total, int wgs) {
-  const unsigned int each = (unsigned int)total / (unsigned int)wgs, left = (unsigned int)total - each * (unsigned int)wgs;
-  return (int)((unsigned int)g * each + (unsigned int)g * left / (unsigned int)wgs);
-}
+// First tile of team g of a launch: floor(g * total / teams) (g <= teams <= 2048).
+__device__ __forceinline__ int first_tile(int g, const ScoreArgs& a) { return g * a.tile_each + divide(g * a.tile_left, a.teams, a.inv_teams); }
 
 // Team (of `wgs`) whose tile range [first_tile(g), first_tile(g + 1)) holds tile x: the largest g with
 // g * total < (x + 1) * wgs.  The product in floats is off by far less than one (x * wgs / total < 2048, error below
@@ -155,19 +156,14 @@ __device__ __forceinline__ int wg_of_tile(int x, int total, int wgs) {
   return g;
 }
 
-// Team and row split of workgroup b in a launch of `grid` workgroups (grid = teams * row_splits).  Workgroups are
-// handed to the eight accelerator dies in turn (b % 8), so the members of a team are 8 apart wherever the number of
-// teams allows it: they then share a die, and its L2.
-__host__ __device__ __forceinline__ void team_of(int b, int grid, int row_splits, int& team, int& split) {
-  if (row_splits == 1) { team = b; split = 0; return; }
-  if (grid % (8 * row_splits) == 0) {
-    const int die = b & 7, t = b >> 3;
-    team = 8 * (t / row_splits) + die;
-    split = t % row_splits;
-  } else {
-    team = b / row_splits;
-    split = b % row_splits;
-  }
+// Team and row split of workgroup b in a launch of teams * row_splits workgroups.  Workgroups are handed to the eight accelerator
+// dies in turn (b % 8), so the members of a team are 8 apart wherever the number of teams allows it (by_die): they then share a
+// die, and its L2.
+__device__ __forceinline__ void team_of(int b, const ScoreArgs& a, int& team, int& split) {
+  if (a.row_splits == 1) { team = b; split = 0; return; }
+  const int t = a.by_die ? b >> 3 : b, q = divide(t, a.row_splits, a.inv_splits);
+  team = a.by_die ? 8 * q + (b & 7) : q;
+  split = t - q * a.row_splits;
 }
 
 // row / W for a row below 65536.  (row + 0.5) / W lies at least 0.5 / W away from every integer, and the rounding of the
@@ -231,34 +227,36 @@ __global__ __launch_bounds__(NW * 64, (NW >= 3 ? 2 : 1)) void score_pass_kernel(
   // row per (wave, slot, half wave), because the two slots of a wave may belong to different query heads
   __shared__ float colbuf[PASS == 2 ? 4 : 1][PASS == 2 ? NW * (GMAX ? 4 : 2) : 1][kTileKeys];
 
+  // The arguments lie in seven cache lines that nothing has touched yet: one value of each, all asked for at once (left to
+  // their uses, they arrive one line after another, ahead of the first load of keys).
+  asm volatile("" ::"s"(a.q), "s"(a.row_splits), "s"(a.inv_teams), "s"(a.wave_desc[0]), "s"(a.rb_holder[8]), "s"(a.q_ss), "s"(a.kv_st));
   const int tid = threadIdx.x;
   const int lane = tid & 63;
-  const int wave = tid >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31;
   const int hf = lane >> 5;
   // ---- what this wave owns (the same for every lane: keep it in scalar registers)
-  const uint32_t desc = __builtin_amdgcn_readfirstlane(a.wave_desc[wave]);
+  const uint32_t desc = a.wave_desc[wave];
   const int rb_of[2] = {(int)(desc & 255u), (int)((desc >> 8) & 255u)};
   const uint32_t halves1 = (desc >> 16) & 3u;              // halves of every tile that slot 1 computes
 
   // ---- this workgroup's share of the tile sequence, one segment (part of one problem) at a time
   int team, split;
-  team_of((int)blockIdx.x, (int)gridDim.x, a.row_splits, team, split);
+  team_of((int)blockIdx.x, a, team, split);
   team = __builtin_amdgcn_readfirstlane(team);
   split = __builtin_amdgcn_readfirstlane(split);
-  const int teams = (int)gridDim.x / a.row_splits;
-  const int x_begin = __builtin_amdgcn_readfirstlane(first_tile(team, a.total_tiles, teams));
-  const int x_end = __builtin_amdgcn_readfirstlane(first_tile(team + 1, a.total_tiles, teams));
+  const int x_begin = __builtin_amdgcn_readfirstlane(first_tile(team, a));
+  const int x_end = __builtin_amdgcn_readfirstlane(first_tile(team + 1, a));
   const TileRule rule = {a.key_trim, a.once_keys, a.lead};
   // the request the walk stands in: request cur_seq of problem cur_lz, whose lead begins at position cur_acc
-  int cur_lz = x_begin / a.tiles_per_problem, cur_seq = 0, cur_acc = 0;
+  int cur_lz = __builtin_amdgcn_readfirstlane(divide(x_begin, a.tiles_per_problem, a.inv_problem)), cur_seq = 0, cur_acc = 0;
   if (a.n_seqs > 16 && x_begin < x_end)                      // few requests: walking there from the first one is as quick
     locate_first<NT>(a.cu_seqlens, a.n_seqs, rule, x_begin - cur_lz * a.tiles_per_problem, cur_seq, cur_acc);
   cur_seq = __builtin_amdgcn_readfirstlane(cur_seq);         // the same in every lane: scalar registers from here on
   cur_acc = __builtin_amdgcn_readfirstlane(cur_acc);
   for (int x = x_begin; x < x_end;) {
-  const int lz = x / a.tiles_per_problem;                  // layer * Hkv + head
-  const int layer = lz / a.Hkv;
+  const int lz = __builtin_amdgcn_readfirstlane(divide(x, a.tiles_per_problem, a.inv_problem));                  // layer * Hkv + head
+  const int layer = __builtin_amdgcn_readfirstlane(divide(lz, a.Hkv, a.inv_heads));
   const int head = lz - layer * a.Hkv;
   if (lz != cur_lz) { cur_lz = lz; cur_seq = 0; cur_acc = 0; }     // crossed into the next problem: its first request
   const int xr = x - lz * a.tiles_per_problem;
@@ -830,10 +828,18 @@ template <int D, int NW, bool K8>
 int launch_passes(const Plan& pl, ScoreArgs a, hipStream_t stream, unsigned stages) {
   static std::atomic<int> cache1[kMaxDevices], cache2[kMaxDevices], cache2m[kMaxDevices];   // zero-initialised
   const dim3 block(NW * 64);
+  auto deal = [&](int teams) {                  // shares of the tile sequence for a launch of that many teams
+    a.teams = teams;
+    a.tile_each = pl.total_tiles / teams; a.tile_left = pl.total_tiles - a.tile_each * teams;
+    a.inv_teams = 1.0f / (float)teams;
+    a.by_die = teams % 8 == 0;
+    return dim3(teams * pl.row_splits);
+  };
   a.stat_teams = score_teams(pl, resident_workgroups(score_pass_kernel<D, NW, 1, false, K8>, NW * 64, cache1));
   const bool any_tile = pl.real_tiles > 0;      // false: prefix-only softmax with no prefix anywhere
   if ((stages & CODECOMP_STAGE_ROW_STATS) && any_tile) {
-    score_pass_kernel<D, NW, 1, false, K8><<<dim3(a.stat_teams * pl.row_splits), block, 0, stream>>>(a);
+    const dim3 grid = deal(a.stat_teams);
+    score_pass_kernel<D, NW, 1, false, K8><<<grid, block, 0, stream>>>(a);
     if (hipError_t e = hipGetLastError()) return (int)e;
   }
   // segments of the longest request at most
@@ -847,10 +853,12 @@ int launch_passes(const Plan& pl, ScoreArgs a, hipStream_t stream, unsigned stag
   if ((stages & CODECOMP_STAGE_MASS) && any_tile) {
     if (pl.variant & CODECOMP_VARIANT_GROUP_MAX) {
       const int g = score_teams(pl, resident_workgroups(score_pass_kernel<D, NW, 2, true, K8>, NW * 64, cache2m));
-      score_pass_kernel<D, NW, 2, true, K8><<<dim3(g * pl.row_splits), block, 0, stream>>>(a);
+      const dim3 grid = deal(g);
+      score_pass_kernel<D, NW, 2, true, K8><<<grid, block, 0, stream>>>(a);
     } else {
       const int g = score_teams(pl, resident_workgroups(score_pass_kernel<D, NW, 2, false, K8>, NW * 64, cache2));
-      score_pass_kernel<D, NW, 2, false, K8><<<dim3(g * pl.row_splits), block, 0, stream>>>(a);
+      const dim3 grid = deal(g);
+      score_pass_kernel<D, NW, 2, false, K8><<<grid, block, 0, stream>>>(a);
     }
     if (hipError_t e = hipGetLastError()) return (int)e;
   }
