@@ -749,10 +749,22 @@ __device__ __forceinline__ void part_scan2(PartShared& sh, int a, int b, int& be
 }
 
 // Which request and which of its parts workgroup `gp` of a launch works on; `first` = number of the request's first
-// part.  All threads call it (two barriers): every thread adds up the parts of a share of the requests, a prefix sum
-// over the threads finds the share that holds gp, its owner walks it.
+// part.  All threads call it.  Up to 64 requests: every wave finds out by itself, one request a lane, without a barrier.
+// More: every thread adds up the parts of a share of the requests, a prefix sum over the threads finds the share that
+// holds gp, its owner walks it: four barriers before the first load of a candidate (16 problems of 131072 candidates,
+// one request a call: counts 8.0 us with them, 7.1 without; near 11.2 and 10.9; emit 10.2 and 9.0).
 __device__ __forceinline__ void locate_part(PartShared& sh, const int32_t* cu, int n_seqs, int W, int gp, int& seq, int& part, int& first) {
   const int tid = threadIdx.x;
+  if (n_seqs <= 64) {
+    const int lane = tid & 63;
+    const int mine = lane < n_seqs ? parts_of(cu[lane + 1] - cu[lane] - W) : 0;
+    const int end = (int)wave_scan((uint32_t)mine, OpAdd{});
+    const uint64_t beyond = __ballot(gp < end);                     // never empty (grid = total parts)
+    seq = beyond ? __builtin_ctzll(beyond) : n_seqs - 1;
+    first = __builtin_amdgcn_readlane(end - mine, seq);
+    part = gp - first;
+    return;
+  }
   const int per = (n_seqs + kPartThreads - 1) / kPartThreads;
   const int r0 = min(tid * per, n_seqs), r1 = min(r0 + per, n_seqs);
   int mine = 0;
@@ -881,12 +893,13 @@ __global__ __launch_bounds__(kPartThreads) void part_near_kernel(SelectArgs a, P
   unsigned elig, forc;
   part_load(Rule::source(a, lz, s0), npre, part, keys, elig, forc);
 
-  // counts of the 8 bins this thread owns (bins 8 * tid ...), over all parts of the request and in this part alone
+  // counts of the 8 bins this thread owns (bins 8 * tid ...): over all parts of the request, in this part alone, and in the
+  // parts before it (which say where this part's share of the list begins)
   constexpr int OWN = kFirstDigitBins / kPartThreads;
   static_assert(OWN == 8, "one 16-byte load per part and thread");
-  unsigned int tot[OWN], own[OWN];
+  unsigned int tot[OWN], own[OWN], early[OWN];
 #pragma unroll
-  for (int i = 0; i < OWN; ++i) { tot[i] = 0; own[i] = 0; }
+  for (int i = 0; i < OWN; ++i) { tot[i] = 0; own[i] = 0; early[i] = 0; }
   const uint16_t* hp = c.hist + ((int64_t)lz * c.parts + first) * kFirstDigitBins + tid * OWN;
   constexpr int BATCH = 8;                                // loads in flight
   for (int q0 = 0; q0 < nparts; q0 += BATCH) {
@@ -903,6 +916,7 @@ __global__ __launch_bounds__(kPartThreads) void part_near_kernel(SelectArgs a, P
         const unsigned int x = (w[i >> 1] >> (16 * (i & 1))) & 0xFFFFu;
         tot[i] += x;
         if (q0 + u == part) own[i] = x;
+        if (q0 + u < part) early[i] += x;
       }
     }
   }
@@ -915,12 +929,15 @@ __global__ __launch_bounds__(kPartThreads) void part_near_kernel(SelectArgs a, P
   const int above = total - below - mine;
   int mode;
   const int need = Rule::need(a, seq, budget, npre, total, mode);
-  if (tid == 0) { sh.found[0] = 0; sh.found[1] = 0; sh.found[2] = 0; }
+  if (tid == 0) { sh.found[0] = 0; sh.found[1] = 0; sh.found[2] = 0; sh.found[3] = 0; }
   __syncthreads();
   if (mode == kModeSelect && above < need && need <= above + mine) {   // exactly one thread: the cut lies in one of its bins
     int higher = above;
+#pragma unroll
     for (int i = OWN - 1; i >= 0; --i) {
-      if (need <= higher + (int)tot[i]) { sh.found[0] = tid * OWN + i; sh.found[1] = need - higher; sh.found[2] = (int)tot[i]; break; }
+      if (higher < need && need <= higher + (int)tot[i]) {             // one bin of the 8
+        sh.found[0] = tid * OWN + i; sh.found[1] = need - higher; sh.found[2] = (int)tot[i]; sh.found[3] = (int)early[i];
+      }
       higher += (int)tot[i];
     }
   }
@@ -940,10 +957,7 @@ __global__ __launch_bounds__(kPartThreads) void part_near_kernel(SelectArgs a, P
   sure = part_sum(sh, sure, 2);
   if (tid == 0) c.sure[(int64_t)lz * c.parts + gp] = sure;
   if (mode != kModeSelect) return;                                     // the same for every thread
-  // where this part's share of the list begins: candidates of the earlier parts in bin b0
-  int off = 0;
-  for (int q = tid; q < part; q += kPartThreads) off += c.hist[((int64_t)lz * c.parts + first + q) * kFirstDigitBins + b0];
-  off = part_sum(sh, off, 3);
+  const int off = sh.found[3];
   unsigned int cnt[kPartTiles], before[kPartTiles];
 #pragma unroll
   for (int t = 0; t < kPartTiles; ++t) {
@@ -1019,78 +1033,74 @@ __device__ __forceinline__ void part_digit(PartShared& sh, const uint32_t* list,
 // one-workgroup selection (find_cut): a prior that puts every marked token into one bin of the first digit leaves thousands
 // of keys, most of them equal in the next digit too, whose LDS atomics then wait for one another.  Longer lists take two
 // more radix digits.
+// Bound by a chain of latencies in one workgroup, so what does not need the cut goes before it, with its loads beside the
+// list's: where each part's stretch of the list ends, and which part each of a wave's reads begins in.  Counting per part
+// then takes the keys from the registers that still hold them (16 problems of 131072 candidates, 13107 of them marked and in
+// one bin: 16.5 -> 14.2 us).
 constexpr int kResolveThreads = 1024;     // the list is read with 8 loads in flight per thread: many threads, few rounds
 constexpr int kResolveItems = 16;
 __global__ __launch_bounds__(kResolveThreads) void part_resolve_kernel(SelectArgs a, PartArgs c) {
   __shared__ PartShared sh;
   __shared__ SelectShared<kResolveThreads> cut;
+  __shared__ unsigned int table[kPartHistWords];
   const int seq = blockIdx.x, lz = blockIdx.y;
   uint32_t* h = c.head + ((int64_t)lz * a.n_seqs + seq) * 8;
+  const int s0 = a.cu_seqlens[seq];
+  const int npre = a.cu_seqlens[seq + 1] - s0 - a.W;
   if ((int)h[0] != kModeSelect) return;                      // the same for every thread
-  const uint32_t* list = c.list + (int64_t)lz * a.T + a.cu_seqlens[seq];
-  const int m = (int)h[3];
+  const uint32_t* list = c.list + (int64_t)lz * a.T + s0;
+  const int b0 = (int)h[1], m = (int)h[3];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  uint32_t tau = h[1] << 21, remaining = h[2];
-  if (m <= kResolveThreads * kResolveItems) {                // the same for every thread
+  const bool held = m <= kResolveThreads * kResolveItems;    // the same for every thread
+  uint32_t keys[kResolveItems];
+  if (held) {
     const rsrc_t row = row_of(list, m);
-    const int slots = ((m + kResolveThreads - 1) / kResolveThreads + 3) / 4 * 4;
-    uint32_t keys[kResolveItems];
 #pragma unroll
     for (int s = 0; s < kResolveItems; ++s)                  // past the list: 0, no candidate
       keys[s] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(row, (s * kResolveThreads + tid) * 4, 0, 0);
-    int ties;
-    find_cut<kResolveThreads, kResolveItems>(cut, keys, slots, m, remaining, tau, ties);
-    remaining = (uint32_t)ties;
-  } else {
-    part_digit<kResolveThreads>(sh, list, m, 10, 2048, 0xFFE00000u, tau, remaining);
-    part_digit<kResolveThreads>(sh, list, m, 0, 1024, 0xFFFFFC00u, tau, remaining);
   }
   // How many list entries of each part lie above the cut / are tied at it, as running totals over the parts: an
   // emitting part then knows what the earlier parts contribute without reading their stretch of the list again.
-  const int npre = a.cu_seqlens[seq + 1] - a.cu_seqlens[seq] - a.W;
   const int nparts = parts_of(npre);
   const bool fits = 3 * nparts <= kPartHistWords;            // else the emitting parts count for themselves
-  if (tid == 0) { h[5] = tau; h[6] = remaining; h[7] = fits ? 1u : 0u; }
-  if (!fits) return;                                         // the same for every thread
-  int mine = 0;                                              // number of this request's first part
-  for (int r = tid; r < seq; r += kResolveThreads) mine += parts_of(a.cu_seqlens[r + 1] - a.cu_seqlens[r] - a.W);
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) mine += __shfl_xor(mine, off);
-  if (lane == 0) sh.red[0][wave] = mine;
-  __syncthreads();
-  int first = 0;
-#pragma unroll
-  for (int w = 0; w < kResolveThreads / 64; ++w) first += sh.red[0][w];
-  unsigned int* seg_end = sh.hist;                           // end of each part's stretch of the list
-  unsigned int* n_above = sh.hist + nparts;
-  unsigned int* n_tied = sh.hist + 2 * nparts;
-  const int b0 = (int)h[1];
-  for (int q = tid; q < nparts; q += kResolveThreads) {
-    seg_end[q] = c.hist[((int64_t)lz * c.parts + first + q) * kFirstDigitBins + b0];
-    n_above[q] = 0; n_tied[q] = 0;
-  }
-  __syncthreads();
-  // running totals over the parts, 64 at a time, by the first wave: seg_end becomes the end offsets
+  unsigned int* seg_end = table;                             // end of each part's stretch of the list
+  unsigned int* n_above = table + nparts;
+  unsigned int* n_tied = table + 2 * nparts;
+  int first = 0;                                             // number of this request's first part
+  // running totals over the parts, 64 at a time, by one wave
   auto running = [&](unsigned int* v, bool exclusive) __attribute__((always_inline)) {
-    if (wave == 0) {
-      unsigned int carry = 0;
-      for (int base = 0; base < nparts; base += 64) {
-        const unsigned int x = base + lane < nparts ? v[base + lane] : 0u;
-        unsigned int incl = x;
+    unsigned int carry = 0;
+    for (int base = 0; base < nparts; base += 64) {
+      const unsigned int x = base + lane < nparts ? v[base + lane] : 0u;
+      unsigned int incl = x;
 #pragma unroll
-        for (int off = 1; off < 64; off <<= 1) {
-          const unsigned int o = __shfl_up(incl, off);
-          if (lane >= off) incl += o;
-        }
-        if (base + lane < nparts) v[base + lane] = carry + (exclusive ? incl - x : incl);
-        carry += __shfl(incl, 63);
+      for (int off = 1; off < 64; off <<= 1) {
+        const unsigned int o = __shfl_up(incl, off);
+        if (lane >= off) incl += o;
       }
+      if (base + lane < nparts) v[base + lane] = carry + (exclusive ? incl - x : incl);
+      carry += __shfl(incl, 63);
+    }
+  };
+  if (fits) {                                                // the same for every thread
+    if (seq > 0) {
+      int mine = 0;
+      for (int r = tid; r < seq; r += kResolveThreads) mine += parts_of(a.cu_seqlens[r + 1] - a.cu_seqlens[r] - a.W);
+#pragma unroll
+      for (int off = 32; off > 0; off >>= 1) mine += __shfl_xor(mine, off);
+      if (lane == 0) sh.red[0][wave] = mine;
+      __syncthreads();
+#pragma unroll
+      for (int w = 0; w < kResolveThreads / 64; ++w) first += sh.red[0][w];
+    }
+    for (int q = tid; q < nparts; q += kResolveThreads) {
+      seg_end[q] = c.hist[((int64_t)lz * c.parts + first + q) * kFirstDigitBins + b0];
+      n_above[q] = 0; n_tied[q] = 0;
     }
     __syncthreads();
-  };
-  running(seg_end, false);
-  // The 64 entries that a wave reads at once follow one another, so most of the time one part holds all of them: then two
-  // additions per wave instead of one per entry at the same address.
+    if (wave == 0) running(seg_end, false);
+    __syncthreads();
+  }
   auto part_of_entry = [&](int i) __attribute__((always_inline)) {      // first part whose stretch ends beyond entry i
     int lo = 0, hi = nparts - 1;
     while (lo < hi) {
@@ -1099,29 +1109,58 @@ __global__ __launch_bounds__(kResolveThreads) void part_resolve_kernel(SelectArg
     }
     return lo;
   };
-  constexpr int UNR = 8;
-  for (int w0 = wave * 64; w0 < m; w0 += kResolveThreads * UNR) {
-    uint32_t k[UNR];
+  // A wave's reads lie kResolveThreads entries apart: lane u looks up the part that its read u (of 64) begins in.
+  int begins = fits && held ? part_of_entry(min(lane * kResolveThreads + wave * 64, m - 1)) : 0;
+  uint32_t tau = (uint32_t)b0 << 21, remaining = h[2];
+  if (held) {
+    const int slots = ((m + kResolveThreads - 1) / kResolveThreads + 3) / 4 * 4;
+    int ties;
+    find_cut<kResolveThreads, kResolveItems>(cut, keys, slots, m, remaining, tau, ties);
+    remaining = (uint32_t)ties;
+  } else {
+    part_digit<kResolveThreads>(sh, list, m, 10, 2048, 0xFFE00000u, tau, remaining);
+    part_digit<kResolveThreads>(sh, list, m, 0, 1024, 0xFFFFFC00u, tau, remaining);
+  }
+  if (tid == 0) { h[5] = tau; h[6] = remaining; h[7] = fits ? 1u : 0u; }
+  if (!fits) return;                                         // the same for every thread
+  // The 64 entries of a read follow one another, so most of the time one part holds all of them: one round, two additions.
+  auto count_read = [&](int i0, int part, uint32_t key) __attribute__((always_inline)) {
+    const int end = min(i0 + 64, m);
+    const uint64_t above = __ballot(i0 + lane < m && key > tau), tied = __ballot(i0 + lane < m && key == tau);
+    for (int lo = i0; lo < end && part < nparts; ++part) {
+      const int hi = min((int)__builtin_amdgcn_readfirstlane((int)seg_end[part]), end);
+      if (hi <= lo) continue;                                // a part without entries in the list
+      const uint64_t of_part = (~0ull >> (64 - (hi - lo))) << (lo - i0);
+      const int na = __popcll(above & of_part), nt = __popcll(tied & of_part);
+      if (lane == 0 && na > 0) atomicAdd(&n_above[part], (unsigned int)na);
+      if (lane == 0 && nt > 0) atomicAdd(&n_tied[part], (unsigned int)nt);
+      lo = hi;
+    }
+  };
+  if (held) {
 #pragma unroll
-    for (int u = 0; u < UNR; ++u) k[u] = list[min(w0 + lane + u * kResolveThreads, m - 1)];
+    for (int s = 0; s < kResolveItems; ++s) {
+      const int i0 = s * kResolveThreads + wave * 64;
+      if (i0 < m) count_read(i0, __builtin_amdgcn_readlane(begins, s), keys[s]);
+    }
+  } else {
+    constexpr int UNR = 8;
+    for (int w0 = wave * 64; w0 < m; w0 += kResolveThreads * UNR) {
+      uint32_t k[UNR];
 #pragma unroll
-    for (int u = 0; u < UNR; ++u) {
-      const int i0 = w0 + u * kResolveThreads, i = i0 + lane;
-      if (i0 >= m) continue;                                            // the same for the whole wave
-      const bool above = i < m && k[u] > tau, tied = i < m && k[u] == tau;
-      const int first_part = part_of_entry(i0);
-      if (seg_end[first_part] >= (unsigned int)min(i0 + 64, m)) {
-        const int na = __popcll(__ballot(above)), nt = __popcll(__ballot(tied));
-        if (lane == 0 && na > 0) atomicAdd(&n_above[first_part], (unsigned int)na);
-        if (lane == 0 && nt > 0) atomicAdd(&n_tied[first_part], (unsigned int)nt);
-      } else if (above || tied) {
-        atomicAdd(above ? &n_above[part_of_entry(i)] : &n_tied[part_of_entry(i)], 1u);
+      for (int u = 0; u < UNR; ++u) k[u] = list[min(w0 + lane + u * kResolveThreads, m - 1)];
+      begins = part_of_entry(min(w0 + (lane & (UNR - 1)) * kResolveThreads, m - 1));
+#pragma unroll
+      for (int u = 0; u < UNR; ++u) {
+        const int i0 = w0 + u * kResolveThreads;
+        if (i0 < m) count_read(i0, __builtin_amdgcn_readlane(begins, u), k[u]);
       }
     }
   }
   __syncthreads();
-  running(n_above, true);
-  running(n_tied, true);
+  if (wave == 0) running(n_above, true);
+  if (wave == 1) running(n_tied, true);
+  __syncthreads();
   for (int q = tid; q < nparts; q += kResolveThreads) {
     int32_t* out = c.before + ((int64_t)lz * c.parts + first + q) * 2;
     out[0] = (int32_t)n_above[q]; out[1] = (int32_t)n_tied[q];
@@ -1142,6 +1181,8 @@ __global__ __launch_bounds__(kPartThreads) void part_emit_kernel(SelectArgs a, P
   uint32_t keys[kPartItems];
   unsigned elig, forc;
   part_load(Rule::source(a, lz, s0), npre, part, keys, elig, forc);
+  int sure_before = 0;                                       // asked for beside the candidates
+  for (int q = tid; q < part; q += kPartThreads) sure_before += c.sure[(int64_t)lz * c.parts + first + q];
   const uint32_t* h = c.head + ((int64_t)lz * a.n_seqs + seq) * 8;
   const int mode = (int)h[0], b0 = (int)h[1], need = (int)h[4];
   if (part == 0)
@@ -1160,11 +1201,12 @@ __global__ __launch_bounds__(kPartThreads) void part_emit_kernel(SelectArgs a, P
     const uint32_t* list = c.list + (int64_t)lz * a.T + s0;
     tau = h[5];
     ties = (int)h[6];
-    int ab = 0, tb = 0;
     if (h[7] != 0u) {                                     // the resolve kernel has counted for every part
       const int32_t* bf = c.before + ((int64_t)lz * c.parts + gp) * 2;
-      if (tid == 0) { ab = bf[0]; tb = bf[1]; }
+      above_before = bf[0];
+      ties_before = bf[1];
     } else {
+      int ab = 0, tb = 0;
       // what the earlier parts hold of the list: their entries come first
       int off = 0;
       for (int q = tid; q < part; q += kPartThreads) off += c.hist[((int64_t)lz * c.parts + first + q) * kFirstDigitBins + b0];
@@ -1179,14 +1221,12 @@ __global__ __launch_bounds__(kPartThreads) void part_emit_kernel(SelectArgs a, P
           if (i0 + u * kPartThreads < off) { ab += k[u] > tau; tb += k[u] == tau; }
       }
       __syncthreads();
+      above_before = part_sum(sh, ab, 3);
+      __syncthreads();
+      ties_before = part_sum(sh, tb, 2);
+      __syncthreads();
     }
-    above_before = part_sum(sh, ab, 3);
-    __syncthreads();
-    ties_before = part_sum(sh, tb, 2);
   }
-  int sure_before = 0;
-  for (int q = tid; q < part; q += kPartThreads) sure_before += c.sure[(int64_t)lz * c.parts + first + q];
-  __syncthreads();
   sure_before = part_sum(sh, sure_before, 3) + above_before;
   // classes of this thread's candidates: in whatever the cut / tied at the cut / out
   unsigned in2 = 0, in1 = 0;
