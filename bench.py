@@ -62,18 +62,31 @@ def read_traffic(name: str):
     return vals
 
 
-def binding_roofline(flops_pass: float, logits_pass: float, ab: dict, k_bytes: int, ms_per_step: float, peaks):
-    """Floors of one step of the two-pass design (the logits are formed twice: row normalisers, then column sums) at
-    the published peaks and, when measured, at what this GPU sustained in this run.  hbm_one_read is the method's own
-    traffic (K once); hbm_two_reads adds K's second read.  issue_mix is the measured instruction mix of the passes
-    without memory (MFMA and softmax VALU work compete for issue slots).  frac = largest floor / time per step."""
+ONE_PASS_KEYS = 768             # requests up to here have all their score work in the mass kernels, in one pass ...
+ONE_PASS_PROBLEMS = 512         # ... in batches of no longer ones, or with this many such (layer, head, request) problems
+
+
+def two_pass_share(w) -> float:
+    """Share of the logits that are formed twice (the other requests are short enough for one pass)."""
+    short = [n for n in w.seqlens if n <= ONE_PASS_KEYS]
+    if len(short) < w.n_seqs and len(short) * w.n_layers * w.n_kv_heads < ONE_PASS_PROBLEMS:
+        return 1.0
+    return 1.0 - sum(short) / w.total_tokens
+
+
+def binding_roofline(flops_pass: float, logits_pass: float, twice: float, ab: dict, k_bytes: int, ms_per_step: float, peaks):
+    """Floors of one step of the two-pass design (the logits are formed twice, or the share `twice` of them: row
+    normalisers, then column sums) at the published peaks and, when measured, at what this GPU sustained in this run.
+    hbm_one_read is the method's own traffic (K once); hbm_two_reads adds K's second read.  issue_mix is the measured
+    instruction mix of the passes without memory (MFMA and softmax VALU work compete for issue slots).  frac = largest
+    floor / time per step."""
     def floors(mfma_tflops, exp_per_s, hbm_gbs, mix_logits_per_s=None):
-        f = {"mfma_two_passes": 2 * flops_pass / (mfma_tflops * 1e12) * 1e3,
-             "exp_two_passes": 2 * logits_pass / exp_per_s * 1e3,
+        f = {"mfma_two_passes": (1 + twice) * flops_pass / (mfma_tflops * 1e12) * 1e3,
+             "exp_two_passes": (1 + twice) * logits_pass / exp_per_s * 1e3,
              "hbm_one_read": ab["total"] / (hbm_gbs * 1e9) * 1e3,
-             "hbm_two_reads": (ab["total"] + k_bytes) / (hbm_gbs * 1e9) * 1e3}
+             "hbm_two_reads": (ab["total"] + twice * k_bytes) / (hbm_gbs * 1e9) * 1e3}
         if mix_logits_per_s:
-            f["issue_mix_two_passes"] = 2 * logits_pass / mix_logits_per_s * 1e3
+            f["issue_mix_two_passes"] = (1 + twice) * logits_pass / mix_logits_per_s * 1e3
         return f
 
     def pack(f):
@@ -258,16 +271,19 @@ def main() -> int:
     ab = algorithmic_bytes(w, 1 if args.kv_dtype == "fp8_e4m3" else 2)
     hbm_gbs = ab["total"] / (ms_per_step * 1e-3) / 1e9
 
-    # dominant kernel: one of the two MFMA passes; flops of one launch = 2 * R * sum(N_r) * d per (layer, KV head)
+    # dominant stage: one of the two MFMA passes; its flops = 2 * R * sum(N_r) * d per (layer, KV head), for the row statistics
+    # over the requests whose logits are formed twice
     dom = max(("score_row_stats", "score_mass"), key=lambda n: stage_ms[n])
     flops = 2.0 * w.group * w.window * T * w.head_dim * w.n_kv_heads * L
-    achieved = flops / (stage_ms[dom] * 1e-3) / 1e12
+    twice = two_pass_share(w)
+    flops_dom = flops if dom == "score_mass" else flops * twice
+    achieved = flops_dom / (stage_ms[dom] * 1e-3) / 1e12
     traffic = read_traffic(w.name if args.kv_dtype == "bf16" else f"{w.name}_{args.kv_dtype}")
     roofline = {"kernel": dom, "bound": "mfma", "achieved": round(achieved, 2), "peak": MFMA_BF16_PEAK_TFLOPS,
                 "unit": "TFLOP/s", "frac": round(achieved / MFMA_BF16_PEAK_TFLOPS, 4),
                 "traffic": None if not traffic else traffic.get(f"{dom}_hbm_bytes_per_launch"),
                 "traffic_source": None if not traffic else {k_: traffic.get(k_) for k_ in ("file", "commit", "date")},
-                "kernel_ms": round(stage_ms[dom], 4), "flop_per_launch": flops}
+                "kernel_ms": round(stage_ms[dom], 4), "flop_per_launch": flops_dom}
     logits = float(w.group * w.window * T * w.n_kv_heads * L)
 
     out = {
@@ -286,7 +302,7 @@ def main() -> int:
         "stage_ms": {k_: round(v_, 4) for k_, v_ in stage_ms.items()},
         "stage_ms_sum": round(sum(stage_ms.values()), 4),
         "roofline": roofline,
-        "binding_roofline": binding_roofline(flops, logits, ab, ab["k_read"], ms_per_step, peaks_now),
+        "binding_roofline": binding_roofline(flops, logits, twice, ab, ab["k_read"], ms_per_step, peaks_now),
         "peaks": {"spec": {"mfma_bf16_tflops": MFMA_BF16_PEAK_TFLOPS, "hbm_gb_per_s": HBM_PEAK_GBS,
                            "exp_per_s": EXP_PEAK_PER_S}, "measured": peaks_now},
         "input_generation_s": round(t_gen, 1),
