@@ -198,7 +198,9 @@ __device__ __forceinline__ void once_run(const ScoreArgs& a, typename Once<D, NW
       float total = (part[0] + part[1]) + (part[2] + part[3]);
       if constexpr (NW == 8) total += (part[4] + part[5]) + (part[6] + part[7]);
       const bool row = b >= 0 && b * 16 + l16 < rows;
-      bad |= row && !(total <= 1.0e30f);             // a logit outran the reference by 69 nats (or is NaN)
+      // A logit outran the reference by 69 nats (or is NaN).  Rows past the end count: each repeats a row that may be in range, against
+      // another reference, and its weight of 0 does not take away an infinite exponential.
+      bad |= b >= 0 && !(total <= 1.0e30f);
       const float r0 = __builtin_amdgcn_rcpf(total);
       w = row ? __builtin_fmaf(__builtin_fmaf(-total, r0, 1.0f), r0, r0) : 0.f;
     };

@@ -78,6 +78,36 @@ def test_logits_far_apart(lens, kv):
     np.testing.assert_allclose(one, ref, rtol=1e-3, atol=1e-30)
 
 
+# One logit of 100 nats, all others 0.  Layer l has it in row 16 l and key 0: among the 16 keys that give that row its reference, but
+# not those of the rows that repeat it where the row count is no multiple of 16.  Every other probability is 1 / n: an exponential
+# of 0, a sum of up to 768 ones and one reciprocal (a few 2^-24), added up over up to 539 rows (539 * 2^-24 = 3.2e-5 at worst).
+@pytest.mark.parametrize("window,rows_per_head", [(17, 1), (33, 1), (35, 2), (100, 1), (77, 7)])
+@pytest.mark.parametrize("d,kv", [(64, "bf16"), (128, "bf16"), (64, "fp8"), (128, "fp8")])
+@pytest.mark.parametrize("n", [100, 300, 500, 768])
+def test_one_large_logit_beside_unfinished_row_blocks(window, rows_per_head, d, kv, n):
+    import torch
+    from paper_2604_10235_amd import binding as b
+    R = window * rows_per_head
+    layers = (R + 15) // 16
+    w = wl.scaled(wl.qwen7b_32k(), n_layers=layers, n_q_heads=rows_per_head, n_kv_heads=1, head_dim=d, window=window, seqlens=[n], budgets=[n],
+                  prior_weight=0.0, pool_kernel=1)
+    q = np.zeros((layers, 1, rows_per_head, window, d), np.float32)
+    k = np.zeros((layers, 1, n, d), np.float32)
+    for l in range(layers):
+        q[l, 0, 16 * l // window, 16 * l % window, 0] = 100.0 * np.sqrt(d) / 16
+    k[:, :, 0, 0] = 16.0
+    qb, kb = wl.f32_to_bf16_bits(q), wl.f32_to_bf16_bits(k)
+    if kv == "fp8":
+        kb = wl.bf16_bits_to_fp8_codes(kb)
+    prior = np.zeros(n, np.float32)
+    p = b.DeviceProblem(w, qb, kb, None, prior)
+    p.workspace.fill_(0xFF)
+    p.score()
+    torch.cuda.synchronize()
+    ref = orc.score_packed(qb, kb, prior, w.cu_seqlens(), pool_kernel=1, prior_weight=0.0, k_format="fp8_e4m3" if kv == "fp8" else "bf16")
+    np.testing.assert_allclose(p.scores.cpu().numpy(), ref, rtol=4e-5)
+
+
 def test_strided_queries_and_keys():
     """Token-major keys and queries, padded rows: the strides that the two passes take."""
     import torch
