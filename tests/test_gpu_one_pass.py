@@ -189,3 +189,66 @@ def test_few_rows_other_readings(variant):
     np.testing.assert_allclose(one, two, rtol=TWO_WAYS, atol=1e-30)
     pu.assert_scores_close(one, orc.score_packed(q, k, prior, w.cu_seqlens(), pool_kernel=w.pool_kernel, prior_weight=w.prior_weight,
                                                  **oracle_variant(variant)))
+
+
+def scores_on_device(lens, layers, q_heads, kv_heads, d, window, q, k):
+    """The scores of packed q [layers][requests][..] and k [layers][heads][tokens][..], and the fastest of five calls (ms)."""
+    import torch
+    from paper_2604_10235_amd import binding as b
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    dev = torch.from_numpy(cu).cuda()
+    p = b.make_params(n_layers=layers, n_q_heads=q_heads, n_kv_heads=kv_heads, head_dim=d, window=window, pool_kernel=5, prior_weight=0.0,
+                      cu_seqlens_host=cu, cu_budgets_host=cu, cu_seqlens_dev=dev.data_ptr(), cu_budgets_dev=dev.data_ptr(),
+                      q_stride_layer=q.stride(0), kv_stride_layer=k.stride(0), kv_stride_head=k.stride(1))
+    ws = torch.empty(b.codecomp_workspace_bytes(p), dtype=torch.uint8, device="cuda")
+    out = torch.empty((layers, kv_heads, int(cu[-1])), dtype=torch.float32, device="cuda")
+    prior = torch.zeros(int(cu[-1]), device="cuda")
+    best = float("inf")
+    for _ in range(5):
+        start, stop = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        start.record()
+        b.codecomp_score(q, k, prior, p, out, ws)
+        stop.record()
+        stop.synchronize()
+        best = min(best, start.elapsed_time(stop))
+    return out, best
+
+
+@pytest.mark.parametrize("between", [1, 62, 63, 64, 65, 127, 128, 129, 1087, 1088, 1089, 2300])
+def test_long_requests_behind_many_short_ones(between):
+    """Long requests whose next long one lies any number of short ones further: the walk of a workgroup through the requests."""
+    import torch
+    layers, heads, d, window = 3, 5, 64, 16
+    lens = []
+    for n in (1400, 2100, 900, 1700):
+        lens += [20 + i % 30 for i in range(between)] + [n]
+    lens += [33] * 200                                               # so that the call has 512 short problems and more, and ends with some
+    g = torch.Generator(device="cuda").manual_seed(5)
+    q = torch.randn((layers, len(lens), heads, window, d), generator=g, device="cuda").bfloat16()
+    k = torch.randn((layers, 1, sum(lens), d), generator=g, device="cuda").bfloat16()
+    got, _ = scores_on_device(lens, layers, heads, 1, d, window, q, k)
+    at = 0
+    for i, n in enumerate(lens):
+        if n > 768:
+            alone, _ = scores_on_device([n], layers, heads, 1, d, window, q[:, i:i + 1], k[:, :, at:at + n])
+            np.testing.assert_allclose(got[:, :, at:at + n].cpu().numpy(), alone.cpu().numpy(), rtol=TWO_WAYS)
+        at += n
+
+
+def test_many_short_requests_do_not_hold_up_long_ones():
+    """A call with 20000 short requests ahead of forty long ones takes about as long as the two calls apart (8 times as long while a
+    workgroup that came to the next head stepped over them one by one); half as long again leaves room for the machine."""
+    import torch
+    layers, heads, d, window = 3, 5, 64, 16
+    short, long = [20] * 20000, [1000 + 61 * (7 * i % 40) for i in range(40)]
+    g = torch.Generator(device="cuda").manual_seed(6)
+    q = torch.randn((layers, len(short + long), heads, window, d), generator=g, device="cuda").bfloat16()
+    k = torch.randn((layers, 1, sum(short + long), d), generator=g, device="cuda").bfloat16()
+    cut = sum(short)
+    both, t_both = scores_on_device(short + long, layers, heads, 1, d, window, q, k)
+    first, t_first = scores_on_device(short, layers, heads, 1, d, window, q, k)
+    then, t_then = scores_on_device(long, layers, heads, 1, d, window, q[:, len(short):], k[:, :, cut:])
+    assert torch.equal(both[:, :, :cut], first)
+    np.testing.assert_allclose(both[:, :, cut:].cpu().numpy(), then.cpu().numpy(), rtol=TWO_WAYS)
+    print(f"{t_both:.3f} ms, apart {t_first:.3f} + {t_then:.3f}")
+    assert t_both < 1.5 * (t_first + t_then)
