@@ -360,16 +360,13 @@ __device__ __forceinline__ void once_run(const ScoreArgs& a, typename Once<D, NW
   }   // chunks
 }
 
-// Requests with more than n_above and at most n_most keys.  One workgroup per problem takes its row chunks in turn, or (more
-// workgroups than problems) one per problem and chunk.
+// Requests with more than n_above and at most n_most keys.  One workgroup per problem takes its row chunks in turn, or (a grid with a
+// third axis) one per problem and chunk.  Heads and requests on axes of their own: one axis holds no more than 2^32 threads.
 template <int D, int NW, bool K8>
 __global__ __launch_bounds__(NW * 64, 2) void score_once_kernel(ScoreArgs a, int n_above, int n_most) {
   __shared__ __attribute__((aligned(16))) typename Once<D, NW, K8>::Shared sh;
-  const int problems = a.n_seqs * a.LH;
-  const bool shared_out = (int)gridDim.x > problems;
-  const int chunk0 = shared_out ? (int)blockIdx.x / problems : 0, problem = (int)blockIdx.x - chunk0 * problems;
-  const int chunk1 = shared_out ? chunk0 + 1 : a.once_chunks;
-  const int seq = problem / a.LH, lz = problem - seq * a.LH;                  // neighbours are heads of one request: as much work on every die
+  const int chunk0 = (int)blockIdx.z, chunk1 = gridDim.z > 1 ? chunk0 + 1 : a.once_chunks;
+  const int seq = (int)blockIdx.y, lz = (int)blockIdx.x;                      // neighbours are heads of one request: as much work on every die
   const int tok0 = a.cu_seqlens[seq];
   const int n = a.cu_seqlens[seq + 1] - tok0 - a.key_trim;
   if (n <= n_above || n > n_most) return;
@@ -388,9 +385,8 @@ __global__ __launch_bounds__(NW * 64, 2) void score_once_kernel(ScoreArgs a, int
 // others in workgroups of eight.  Where all workgroups find a compute unit at once, a second launch would only come after the first.
 template <int D, bool K8>
 int launch_once(const Plan& pl, const ScoreArgs& a, hipStream_t stream) {
-  const int64_t problems = (int64_t)pl.n_seqs * pl.L * pl.Hkv;
-  const dim3 grid((unsigned)(pl.once_shared_out ? problems * pl.once_chunks : problems));
-  const bool together = pl.once_long && pl.once_short && grid.x <= kOnceFill;
+  const dim3 grid(pl.L * pl.Hkv, pl.n_seqs, pl.once_shared_out ? pl.once_chunks : 1);
+  const bool together = pl.once_long && pl.once_short && (int64_t)grid.x * grid.y * grid.z <= kOnceFill;
   if (pl.once_long) {
     score_once_kernel<D, 8, K8><<<grid, dim3(512), 0, stream>>>(a, together ? 0 : kOnceKeys / 2, kOnceKeys);
     if (hipError_t e = hipGetLastError()) return (int)e;
@@ -425,7 +421,7 @@ __global__ __launch_bounds__(512, 2) void score_rows_kernel(ScoreArgs a) {
   __shared__ __attribute__((aligned(16))) typename Rows<RB>::Shared sh;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int l16 = lane & 15, grp = lane >> 4;
-  const int seq = (int)blockIdx.x / a.LH, lz = (int)blockIdx.x - seq * a.LH;
+  const int seq = (int)blockIdx.y, lz = (int)blockIdx.x;
   const int tok0 = a.cu_seqlens[seq];
   const int n = a.cu_seqlens[seq + 1] - tok0 - a.key_trim;
   if (n <= 0 || n > TT * NW * 16) return;          // longer ones: the host has taken another kernel
@@ -542,7 +538,7 @@ __global__ __launch_bounds__(512, 2) void score_rows_kernel(ScoreArgs a) {
 
 template <int D, bool K8>
 int launch_rows(const Plan& pl, const ScoreArgs& a, hipStream_t stream) {
-  const dim3 grid((unsigned)((int64_t)pl.n_seqs * pl.L * pl.Hkv)), block(512);
+  const dim3 grid(pl.L * pl.Hkv, pl.n_seqs), block(512);
   switch ((pl.R + 15) / 16) {
     case 1: score_rows_kernel<D, K8, 1><<<grid, block, 0, stream>>>(a); break;
     case 2: score_rows_kernel<D, K8, 2><<<grid, block, 0, stream>>>(a); break;

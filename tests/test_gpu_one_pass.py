@@ -191,17 +191,18 @@ def test_few_rows_other_readings(variant):
                                                  **oracle_variant(variant)))
 
 
-def scores_on_device(lens, layers, q_heads, kv_heads, d, window, q, k):
+def scores_on_device(lens, layers, q_heads, kv_heads, d, window, q, k, pool=5):
     """The scores of packed q [layers][requests][..] and k [layers][heads][tokens][..], and the fastest of five calls (ms)."""
     import torch
     from paper_2604_10235_amd import binding as b
     cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
     dev = torch.from_numpy(cu).cuda()
-    p = b.make_params(n_layers=layers, n_q_heads=q_heads, n_kv_heads=kv_heads, head_dim=d, window=window, pool_kernel=5, prior_weight=0.0,
+    p = b.make_params(n_layers=layers, n_q_heads=q_heads, n_kv_heads=kv_heads, head_dim=d, window=window, pool_kernel=pool, prior_weight=0.0,
                       cu_seqlens_host=cu, cu_budgets_host=cu, cu_seqlens_dev=dev.data_ptr(), cu_budgets_dev=dev.data_ptr(),
                       q_stride_layer=q.stride(0), kv_stride_layer=k.stride(0), kv_stride_head=k.stride(1))
     ws = torch.empty(b.codecomp_workspace_bytes(p), dtype=torch.uint8, device="cuda")
-    out = torch.empty((layers, kv_heads, int(cu[-1])), dtype=torch.float32, device="cuda")
+    ws.fill_(0xFF)
+    out = torch.full((layers, kv_heads, int(cu[-1])), float("nan"), device="cuda")
     prior = torch.zeros(int(cu[-1]), device="cuda")
     best = float("inf")
     for _ in range(5):
@@ -252,3 +253,18 @@ def test_many_short_requests_do_not_hold_up_long_ones():
     np.testing.assert_allclose(both[:, :, cut:].cpu().numpy(), then.cpu().numpy(), rtol=TWO_WAYS)
     print(f"{t_both:.3f} ms, apart {t_first:.3f} + {t_then:.3f}")
     assert t_both < 1.5 * (t_first + t_then)
+
+
+# As many requests and heads as 2^32 threads on one axis of a launch do not hold: 65535 requests, all but one of a single key, whose
+# only row gives it all its mass.
+@pytest.mark.parametrize("first,heads", [(300, 257), (500, 129), (500, 257), (900, 129)])
+def test_millions_of_problems(first, heads):
+    import torch
+    lens = [first] + [1] * 65534
+    g = torch.Generator(device="cuda").manual_seed(7)
+    q = torch.randn((1, len(lens), heads, 1, 64), generator=g, device="cuda").bfloat16()
+    k = torch.randn((1, heads, sum(lens), 64), generator=g, device="cuda").bfloat16()
+    got, _ = scores_on_device(lens, 1, heads, heads, 64, 1, q, k, pool=1)
+    alone, _ = scores_on_device([first], 1, heads, heads, 64, 1, q[:, :1], k[:, :, :first], pool=1)
+    assert float((got[:, :, first:] - 1.0).abs().max()) <= 4 * 2.0**-24           # an exponential of almost 1 over itself
+    np.testing.assert_allclose(got[:, :, :first].cpu().numpy(), alone.cpu().numpy(), rtol=TWO_WAYS)
