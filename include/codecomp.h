@@ -153,6 +153,15 @@ int codecomp_validate(const codecomp_params* params);
 int codecomp_score_layout(const codecomp_params* params, int32_t* row_splits, int32_t* row_blocks,
                           int32_t* waves, uint32_t* wave_desc);
 
+/* Host-only: which kernels codecomp_score takes for these parameters: route[r] (array of n_seqs) per request, one of
+ *   TWO_PASSES: row statistics, then attention mass (requests without a key for the softmax among them: nothing to do);
+ *   ONE_PASS  : a workgroup holds all keys of the request, every logit is formed once; its softmax rows are cut into row_chunks
+ *               chunks, of which a workgroup takes chunks_in_turn one after the other;
+ *   FEW_ROWS  : a workgroup holds all logits of the request.
+ * For tests and reports.  Returns 0 or a CODECOMP_E* code; any output pointer may be NULL. */
+enum { CODECOMP_ROUTE_TWO_PASSES = 0, CODECOMP_ROUTE_ONE_PASS = 1, CODECOMP_ROUTE_FEW_ROWS = 2 };
+int codecomp_score_route(const codecomp_params* params, int32_t* route, int32_t* row_chunks, int32_t* chunks_in_turn);
+
 /* scores[l][h][j] = pooled_u[l][h][j] + lambda * prior[j], where u is the window attention mass
  * of the equation above averaged over the query-head group, and pooled_u its zero-padded
  * stride-1 average over pool_kernel neighbours (divisor always pool_kernel), per request.

@@ -71,6 +71,9 @@ def lib() -> C.CDLL:
         l.codecomp_score_layout.restype = C.c_int
         l.codecomp_score_layout.argtypes = [P, C.POINTER(C.c_int32), C.POINTER(C.c_int32), C.POINTER(C.c_int32),
                                             C.POINTER(C.c_uint32)]
+        IP = C.POINTER(C.c_int32)
+        l.codecomp_score_route.restype = C.c_int
+        l.codecomp_score_route.argtypes = [P, IP, IP, IP]
         l.codecomp_score.restype = C.c_int
         l.codecomp_score.argtypes = [C.c_void_p, C.c_void_p, C.c_void_p, P, C.c_void_p, C.c_void_p, C.c_size_t,
                                      C.c_void_p]
@@ -91,7 +94,7 @@ def lib() -> C.CDLL:
                                                C.c_void_p, C.c_void_p, C.c_void_p]
         l.codecomp_structure_score.restype = C.c_int
         l.codecomp_structure_score.argtypes = [C.c_void_p, C.c_void_p, P, C.c_void_p, C.c_void_p]
-        DP, IP = C.POINTER(C.c_double), C.POINTER(C.c_int32)
+        DP = C.POINTER(C.c_double)
         l.codecomp_chunk_structure_scores.restype = C.c_int
         l.codecomp_chunk_structure_scores.argtypes = [DP, DP, DP, C.c_int32, C.c_int32, DP]
         l.codecomp_chunk_budgets.restype = C.c_int
@@ -144,6 +147,16 @@ def codecomp_score_layout(params: codecomp_params):
     desc = (C.c_uint32 * 8)()
     rc = lib().codecomp_score_layout(C.byref(params), C.byref(rs), C.byref(rb), C.byref(nw), desc)
     return rc, rs.value, rb.value, nw.value, list(desc)
+
+
+ROUTE_TWO_PASSES, ROUTE_ONE_PASS, ROUTE_FEW_ROWS = 0, 1, 2
+
+
+def codecomp_score_route(params: codecomp_params):
+    """(route per request (ROUTE_*), row chunks of a one-pass request, how many of them a workgroup takes in turn)."""
+    route, chunks, turn = (C.c_int32 * max(1, params.n_seqs))(), C.c_int32(0), C.c_int32(0)
+    _check(lib().codecomp_score_route(C.byref(params), route, C.byref(chunks), C.byref(turn)), "codecomp_score_route")
+    return np.ctypeslib.as_array(route).copy(), chunks.value, turn.value
 
 
 def codecomp_workspace_bytes(params: codecomp_params) -> int:

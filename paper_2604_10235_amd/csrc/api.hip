@@ -278,6 +278,19 @@ int codecomp_score_layout(const codecomp_params* params, int32_t* row_splits, in
   return CODECOMP_OK;
 }
 
+int codecomp_score_route(const codecomp_params* params, int32_t* route, int32_t* row_chunks, int32_t* chunks_in_turn) {
+  Plan pl;
+  if (int rc = make_plan(params, &pl)) return rc;
+  for (int r = 0; route && r < pl.n_seqs; ++r) {
+    const int n = params->cu_seqlens_host[r + 1] - params->cu_seqlens_host[r] - pl.key_trim;
+    route[r] = n <= 0 ? CODECOMP_ROUTE_TWO_PASSES : pl.rows_at_once ? CODECOMP_ROUTE_FEW_ROWS
+             : n <= pl.once_keys ? CODECOMP_ROUTE_ONE_PASS : CODECOMP_ROUTE_TWO_PASSES;
+  }
+  if (row_chunks) *row_chunks = pl.once_keys > 0 ? pl.once_chunks : 0;
+  if (chunks_in_turn) *chunks_in_turn = pl.once_keys == 0 ? 0 : pl.once_shared_out ? 1 : pl.once_chunks;
+  return CODECOMP_OK;
+}
+
 int codecomp_score(const void* q_obs, const void* k, const float* prior, const codecomp_params* params,
                    float* scores, void* workspace, size_t workspace_bytes, void* hip_stream) {
   if (!q_obs || !k || !prior || !params || !scores) return CODECOMP_EINVAL_NULL;

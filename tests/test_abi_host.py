@@ -30,7 +30,8 @@ def test_every_declared_symbol_is_exported():
     assert {"codecomp_score", "codecomp_select", "codecomp_gather", "codecomp_compress",
             "codecomp_workspace_bytes", "codecomp_validate", "codecomp_status_string", "codecomp_version",
             "codecomp_score_stages", "codecomp_select_two_stage", "codecomp_structure_score",
-            "codecomp_chunk_budgets", "codecomp_chunk_structure_scores", "codecomp_score_layout"} <= set(names)
+            "codecomp_chunk_budgets", "codecomp_chunk_structure_scores", "codecomp_score_layout",
+            "codecomp_score_route"} <= set(names)
     lib = b.lib()
     for n in names:
         assert hasattr(lib, n), n
@@ -314,3 +315,26 @@ def test_score_layout_covers_every_row_block_once_and_evens_out_the_simds(group,
         simd = load[:4] + load[4:]
         assert simd.max() - simd.min() <= 1, (desc, simd)
         assert simd.max() == -(-2 * blocks // 4)
+
+
+def packed(lens, **over):
+    cu = np.concatenate([[0], np.cumsum(lens)])
+    return good(cu_seqlens_host=cu, cu_budgets_host=cu, **over)
+
+
+def test_score_route_says_which_kernels_take_a_request():
+    one, two, few = b.ROUTE_ONE_PASS, b.ROUTE_TWO_PASSES, b.ROUTE_FEW_ROWS
+    route = lambda *a, **kw: b.codecomp_score_route(packed(*a, **kw))[0].tolist()
+    assert route([768, 16, 300]) == [one] * 3
+    assert route([768, 769, 300]) == [two] * 3                                       # few short ones: the passes take them along
+    assert route([768, 16, 300], score_workgroups=64) == [two] * 3                   # the caller's own division of the passes
+    assert route([768, 16, 300], score_lead_tiles=-1) == [two] * 3
+    assert route([768, 32, 300], window=32, score_variant=2) == [two] * 3            # largest head mass
+    assert route([768, 784, 16], score_variant=8) == [one, one, two]                 # 16 window keys less; nothing left of the last one
+    assert route([900] * 96, n_layers=1, n_q_heads=2) == [few] * 96                  # 16 rows, 192 problems
+    assert route([900] * 96, n_layers=1, n_q_heads=10) == [two] * 96                 # 80 rows
+    _, chunks, in_turn = b.codecomp_score_route(packed([300] * 400, n_layers=4, n_q_heads=14, window=128))
+    assert (chunks, in_turn) == (2, 2)                                               # 896 rows, 3200 problems: a workgroup for each
+    assert b.codecomp_score_route(packed([900]))[1:] == (0, 0)
+    with pytest.raises(b.CodecompError):
+        b.codecomp_score_route(packed([300], pool_kernel=2))

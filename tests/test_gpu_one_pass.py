@@ -5,6 +5,7 @@ import pytest
 
 from oracle import codecomp_oracle as orc
 from paper_2604_10235_amd import workloads as wl
+from paper_2604_10235_amd.binding import ROUTE_FEW_ROWS, ROUTE_ONE_PASS, ROUTE_TWO_PASSES
 from tests import parity_util as pu
 
 pytestmark = pytest.mark.gpu
@@ -14,7 +15,8 @@ pytestmark = pytest.mark.gpu
 TWO_WAYS = 8e-6
 
 
-def both_ways(w, kv="bf16", q_scale=1.0, **over):
+def both_ways(w, kv="bf16", q_scale=1.0, route=None, **over):
+    """Scores by the library's own rules and by two passes; `route`: what the first call has to take for its requests (b.ROUTE_*)."""
     import torch
     from paper_2604_10235_amd import binding as b
     q, k, v, prior = wl.make_all(w)
@@ -25,6 +27,8 @@ def both_ways(w, kv="bf16", q_scale=1.0, **over):
     got = []
     for wgs in (0, 40):
         p = b.DeviceProblem(w, q, k, v, prior, score_workgroups=wgs, **over)
+        if route is not None:
+            assert (b.codecomp_score_route(p.params)[0] == (route if wgs == 0 else b.ROUTE_TWO_PASSES)).all()
         p.workspace.fill_(0xFF)                                    # nothing may be read before it is written
         p.score()
         first = p.scores.clone()
@@ -45,7 +49,7 @@ def both_ways(w, kv="bf16", q_scale=1.0, **over):
 def test_short_requests(heads, d, window, layers, lens, kv):
     lens = [max(n, window) for n in lens]
     w = wl.scaled(wl.qwen7b_32k(), n_layers=layers, n_q_heads=heads[0], n_kv_heads=heads[1], head_dim=d, window=window, seqlens=lens, budgets=lens)
-    q, k, prior, (one, two) = both_ways(w, kv)
+    q, k, prior, (one, two) = both_ways(w, kv, route=ROUTE_ONE_PASS)
     np.testing.assert_allclose(one, two, rtol=TWO_WAYS, atol=1e-30)
     some = slice(0, min(layers, 2))
     pu.assert_scores_close(one[some], orc.score_packed(q[some], k[some], prior, w.cu_seqlens(), pool_kernel=w.pool_kernel, prior_weight=w.prior_weight,
@@ -70,7 +74,7 @@ def test_short_requests_among_longer_ones(lens, variant):
 @pytest.mark.parametrize("kv", ["bf16", "fp8"])
 def test_logits_far_apart(lens, kv):
     w = wl.scaled(wl.qwen7b_32k(), n_layers=1, window=64, seqlens=lens, budgets=lens, prior_weight=0.0)
-    q, k, prior, (one, two) = both_ways(w, kv, q_scale=40.0)
+    q, k, prior, (one, two) = both_ways(w, kv, q_scale=40.0, route=ROUTE_ONE_PASS)
     np.testing.assert_allclose(one, two, rtol=2e-4, atol=1e-30)
     # masses below 2^-126 are 0 in 32 bits
     ref = orc.score_packed(q, k, prior, w.cu_seqlens(), pool_kernel=w.pool_kernel, prior_weight=0.0,
@@ -101,6 +105,7 @@ def test_one_large_logit_beside_unfinished_row_blocks(window, rows_per_head, d, 
         kb = wl.bf16_bits_to_fp8_codes(kb)
     prior = np.zeros(n, np.float32)
     p = b.DeviceProblem(w, qb, kb, None, prior)
+    assert (b.codecomp_score_route(p.params)[0] == ROUTE_ONE_PASS).all()
     p.workspace.fill_(0xFF)
     p.score()
     torch.cuda.synchronize()
@@ -174,7 +179,7 @@ def test_few_rows(heads, d, window, which, kv):
     lens = {"shortest": [769, 20, 300], "longest": [most, most - 127], "too long": [most + 1, 100]}[which]
     lens = [max(n, window) for n in lens]
     w = wl.scaled(wl.qwen7b_32k(), n_layers=1, n_q_heads=heads[0], n_kv_heads=heads[1], head_dim=d, window=window, seqlens=lens, budgets=lens)
-    q, k, prior, (one, two) = both_ways(w, kv)
+    q, k, prior, (one, two) = both_ways(w, kv, route=ROUTE_TWO_PASSES if which == "too long" else ROUTE_FEW_ROWS)
     np.testing.assert_allclose(one, two, rtol=TWO_WAYS, atol=1e-30)
     ref = orc.score_packed(q, k, prior, w.cu_seqlens(), pool_kernel=w.pool_kernel, prior_weight=w.prior_weight, k_format="fp8_e4m3" if kv == "fp8" else "bf16")
     pu.assert_scores_close(one, ref)
