@@ -56,6 +56,19 @@ void assign_row_blocks(Plan* pl) {
   }
 }
 
+// Few rows: whether all rows of a problem at once (score_rows_kernel, a compute unit for each problem) are quicker than two passes, from
+// what both take in us: a start, a time per problem and one per key, shared by 256 compute units; with all rows at once not less than
+// the longest problem takes by itself, which may be the last to start where there are more problems than compute units.
+static bool rows_quicker(int blocks, int d, bool fp8, int64_t problems, int64_t keys, int64_t most) {
+  const float wide = (float)(d / 64), n = (float)problems, mean = (float)keys / n;
+  const float longest = 1.5f * blocks + 0.0045f * wide * (float)most;
+  const float shared = (n * (3.5f + 1.2f * blocks) + 0.0064f * wide * (float)keys) / 256.0f;
+  const float last = n > 256.0f ? 0.0034f * wide * ((float)most - mean) : 0.0f;
+  const float rows = 7.0f + fmaxf(longest, shared + last);
+  const float passes = 11.0f + 2.0f * blocks + 1.5f * wide + (n * (1.7f + 0.4f * blocks) + (fp8 ? 0.0105f : 0.0117f) * wide * (float)keys) / 256.0f;
+  return rows < passes;
+}
+
 int make_plan(const codecomp_params* p, Plan* pl) {
   if (!p) return CODECOMP_EINVAL_NULL;
   if (p->n_layers < 1 || p->n_seqs < 1 || p->n_seqs > 65535) return CODECOMP_EINVAL_SHAPE;
@@ -123,12 +136,13 @@ int make_plan(const codecomp_params* p, Plan* pl) {
   if ((pl->variant & CODECOMP_VARIANT_GROUP_MAX) && (pl->W % 32 != 0 || pl->row_splits != 1)) return CODECOMP_EINVAL_MODE;
   if (p->score_workgroups < 0 || p->score_lead_tiles > 64) return CODECOMP_EINVAL_SHAPE;
   pl->grid_override = p->score_workgroups;
-  int64_t tiles = 0, tiles_once = 0;
+  int64_t tiles = 0, keys = 0, tiles_once = 0;
   int once_short = 0, once_long = 0;
   for (int r = 0; r < p->n_seqs; ++r) {
     int n = p->cu_seqlens_host[r + 1] - p->cu_seqlens_host[r] - pl->key_trim;     // >= 0: W <= N_r was checked
     const int t = (n + kTileKeys - 1) / kTileKeys;
     tiles += t;
+    keys += n;
     if (n > 0 && n <= kOnceKeys) { tiles_once += t; ++(n <= kOnceKeys / 2 ? once_short : once_long); }
   }
   const int64_t problems = (int64_t)pl->L * pl->Hkv * pl->row_splits;
@@ -136,13 +150,14 @@ int make_plan(const codecomp_params* p, Plan* pl) {
   pl->lead_tiles = p->score_lead_tiles == 0 ? automatic_lead : (p->score_lead_tiles < 0 ? 0 : p->score_lead_tiles);
   int64_t positions = tiles + (int64_t)pl->lead_tiles * pl->n_seqs;
   if (positions * problems > (1 << 30)) return CODECOMP_EINVAL_SHAPE;
-  const int64_t once_problems = (int64_t)(once_short + once_long) * pl->L * pl->Hkv;
+  const int64_t LH64 = (int64_t)pl->L * pl->Hkv;
+  const int64_t most = max_n - pl->key_trim;           // keys of the longest request
+  const int64_t once_problems = (once_short + once_long) * LH64;
+  const bool own_rules = !(pl->variant & CODECOMP_VARIANT_GROUP_MAX) && p->score_workgroups == 0 && p->score_lead_tiles == 0;
   const bool all_once = once_problems > 0 && tiles_once == tiles;
-  pl->rows_at_once = pl->R <= kRowsMost && max_n - pl->key_trim > kOnceKeys && max_n - pl->key_trim <= 128 * rows_tiles((pl->R + 15) / 16) &&
-                     (int64_t)pl->n_seqs * pl->L * pl->Hkv >= kRowsProblems && !(pl->variant & CODECOMP_VARIANT_GROUP_MAX) &&
-                     p->score_workgroups == 0 && p->score_lead_tiles == 0;
-  const bool once = !pl->rows_at_once && (all_once || once_problems >= kOnceMixed) && !(pl->variant & CODECOMP_VARIANT_GROUP_MAX) &&
-                    p->score_workgroups == 0 && p->score_lead_tiles == 0;
+  pl->rows_at_once = own_rules && pl->R <= kRowsMost && most > kOnceKeys && most <= 128 * rows_tiles((pl->R + 15) / 16) &&
+                     LH64 * pl->n_seqs >= kRowsProblems && rows_quicker((pl->R + 15) / 16, pl->d, pl->kv_fp8 != 0, LH64 * pl->n_seqs, LH64 * keys, most);
+  const bool once = !pl->rows_at_once && (all_once || once_problems >= kOnceMixed) && own_rules;
   pl->once_keys = once ? kOnceKeys : 0;
   pl->once_short = once ? once_short : 0;
   pl->once_long = once ? once_long : 0;

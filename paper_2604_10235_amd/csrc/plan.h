@@ -23,10 +23,12 @@ constexpr int kOnceRows = 512;          // most query rows of a chunk
 constexpr int kOnceMixed = 512;
 constexpr int kOnceFill = 256;          // workgroups that find a compute unit of their own at once: up to here a problem's rows are shared out
 // Few rows (up to kRowsMost): tiles of 16 keys per wave whose logits eight waves hold, by blocks of 16 rows; taken where a request is
-// too long for its keys to stay in registers and the problems use the device.  Whole call, two passes -> all rows at once: 128
-// problems of 1000 keys, 16 rows, head_dim 64 20 -> 12 us, 32 rows, head_dim 128 31 -> 18, of 2500 47 -> 32; 4096 of 1000 and 2500, 32
-// rows, head_dim 64 263 -> 176, 583 -> 376.  With 4 to 32 problems it is 30 % faster to 30 % slower (2500 keys), and requests of up to
-// kOnceKeys are up to twice as fast with their keys in registers.
+// too long for its keys to stay in registers, the problems use the device and the longest request does not set the time (rows_quicker in
+// api.hip).  Two passes -> all rows at once: 128 problems of 1000 keys, 16 rows, head_dim 64 20 -> 12 us (call), 32 rows, head_dim 128
+// 31 -> 18, of 2500 47 -> 32; 4096 of 1000 and 2500, 32 rows, head_dim 64 263 -> 176, 583 -> 376.  With 4 to 32 problems it is 30 %
+// faster to 30 % slower (2500 keys), and requests of up to kOnceKeys are up to twice as fast with their keys in registers.  Lengths mixed,
+// 16 rows, 4 KV heads, scores: 50 requests of 100 to 4096 tokens, head_dim 128 52 -> 39 us, but 2000 of 100 and one of 1000 98 -> 140, 100 of
+// 100 and one of 4096 27 -> 45.
 constexpr int kRowsMost = 64, kRowsProblems = 96;
 constexpr int rows_tiles(int blocks) { return blocks == 1 ? 32 : blocks == 2 ? 20 : blocks == 3 ? 12 : 8; }
 constexpr int kMaxScoreGrid = 2048;   // most workgroups a score pass is launched with

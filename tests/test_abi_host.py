@@ -338,3 +338,19 @@ def test_score_route_says_which_kernels_take_a_request():
     assert b.codecomp_score_route(packed([900]))[1:] == (0, 0)
     with pytest.raises(b.CodecompError):
         b.codecomp_score_route(packed([300], pool_kernel=2))
+
+
+# All rows of a problem at once is for requests of one length or about it: where one long request among short ones sets the time, or where
+# thousands of short ones would each take a compute unit, it was up to twice as slow as two passes.
+@pytest.mark.parametrize("rows,d", [(16, 64), (16, 128), (32, 64), (32, 128), (48, 128), (64, 64), (64, 128)])
+def test_few_rows_at_once_where_lengths_are_alike(rows, d):
+    most = {1: 4096, 2: 2560, 3: 1536, 4: 1024}[rows // 16]
+    def few(lens):
+        route = b.codecomp_score_route(packed(lens, n_layers=1, n_q_heads=4, n_kv_heads=4, head_dim=d, window=rows))[0]
+        assert set(route) == {b.ROUTE_FEW_ROWS} or b.ROUTE_FEW_ROWS not in route
+        return route[0] == b.ROUTE_FEW_ROWS
+    assert few([most] * 24) and few([800] * 100) and few([most // 2 + 50 * (i % 8) for i in range(50)])
+    assert not few([100] * 2000 + [1000])
+    if most > 1536:
+        assert not few([100] * 100 + [most])
+    assert not few([most + 1] * 24)
