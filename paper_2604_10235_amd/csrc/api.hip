@@ -157,22 +157,33 @@ int make_plan(const codecomp_params* p, Plan* pl) {
   const bool all_once = once_problems > 0 && tiles_once == tiles;
   pl->rows_at_once = own_rules && pl->R <= kRowsMost && most > kOnceKeys && most <= 128 * rows_tiles((pl->R + 15) / 16) &&
                      LH64 * pl->n_seqs >= kRowsProblems && rows_quicker((pl->R + 15) / 16, pl->d, pl->kv_fp8 != 0, LH64 * pl->n_seqs, LH64 * keys, most);
-  const bool once = !pl->rows_at_once && (all_once || once_problems >= kOnceMixed) && own_rules;
+  const bool few_wide = pl->row_splits >= kOnceWide && once_problems <= kOnceWideProblems;
+  const bool once = !pl->rows_at_once && (all_once ? !few_wide : once_problems >= kOnceMixed) && own_rules;
   pl->once_keys = once ? kOnceKeys : 0;
   pl->once_short = once ? once_short : 0;
   pl->once_long = once ? once_long : 0;
   pl->once_rows = pl->row_blocks * 32;
   pl->once_chunks = pl->row_splits;
-  pl->once_shared_out = false;
   if (once && all_once && once_problems < kOnceFill) {
     // few problems: smaller chunks of rows, of at least four blocks of 16, until the compute units are used
     const int blocks = (pl->R + 15) / 16;
     int64_t chunks = kOnceFill / once_problems;
     if (chunks > (blocks + 3) / 4) chunks = (blocks + 3) / 4;
+    while (4 * chunks * chunks > kOnceArrays * blocks) --chunks;           // an array of masses each
     if (chunks < pl->row_splits) chunks = pl->row_splits;
     pl->once_rows = (int)((blocks + chunks - 1) / chunks) * 16;
     pl->once_chunks = (pl->R + pl->once_rows - 1) / pl->once_rows;
-    pl->once_shared_out = pl->once_chunks > 1 && once_problems * pl->once_chunks <= kOnceFill;
+  }
+  // how many of them a workgroup takes in turn: what fills the compute units best (figures at kOnceReload)
+  pl->once_group = 1;
+  if (once && pl->once_chunks > 1) {
+    const float slots = once_long > 0 ? (float)kOnceFill : 2.0f * (float)kOnceFill;
+    float best = INFINITY;
+    for (int group = 1; group <= pl->once_chunks; ++group) {
+      const float rounds = (float)(once_problems * ((pl->once_chunks + group - 1) / group)) / slots;
+      const float cost = (rounds > 4.0f ? rounds + 0.5f : ceilf(rounds)) * ((float)group + kOnceReload);
+      if (cost < best) { best = cost; pl->once_group = group; }
+    }
   }
   pl->mass_parts = once && all_once ? pl->once_chunks : pl->row_splits;
   if (pl->rows_at_once) tiles = 0;
@@ -236,7 +247,7 @@ int make_plan(const codecomp_params* p, Plan* pl) {
     } else {                   // long windows that the softmax leaves out
       pl->once_rows = pl->row_blocks * 32;
       pl->once_chunks = pl->mass_parts = pl->row_splits;
-      pl->once_shared_out = false;
+      pl->once_group = 1;
     }
   }
   return CODECOMP_OK;
@@ -302,7 +313,7 @@ int codecomp_score_route(const codecomp_params* params, int32_t* route, int32_t*
              : n <= pl.once_keys ? CODECOMP_ROUTE_ONE_PASS : CODECOMP_ROUTE_TWO_PASSES;
   }
   if (row_chunks) *row_chunks = pl.once_keys > 0 ? pl.once_chunks : 0;
-  if (chunks_in_turn) *chunks_in_turn = pl.once_keys == 0 ? 0 : pl.once_shared_out ? 1 : pl.once_chunks;
+  if (chunks_in_turn) *chunks_in_turn = pl.once_keys > 0 ? pl.once_group : 0;
   return CODECOMP_OK;
 }
 

@@ -22,6 +22,19 @@ constexpr int kOnceRows = 512;          // most query rows of a chunk
 // us, 640 among 32 109 -> 90, 448 of 200 among 448 of 4000 498 -> 494, 4480 among 224 611 -> 375.
 constexpr int kOnceMixed = 512;
 constexpr int kOnceFill = 256;          // workgroups that find a compute unit of their own at once: up to here a problem's rows are shared out
+// Each chunk has an array of masses of its own, which the pooling adds up: 0.3 to 0.5 us an array in a short call, against 0.9 us for
+// each block of 16 rows that a chunk has more.  So at most 1.5 * sqrt(blocks) chunks (their square at most kOnceArrays / 4 * blocks), unless
+// chunks of kOnceRows are more.  One request of 768 tokens, scores, 4096 rows: 64 chunks 45.1 us, 32 33.7, 16 32.6, 8 41.1.
+constexpr int kOnceArrays = 9;
+// From 1537 rows on, one or two problems take two passes, whose workgroups share out the keys, too: 768 keys, two passes and one pass, one
+// problem of 2048 rows 23.2 and 26.1 us, of 4096 25.6 and 32.6, of 16384 44.6 and 52.5; two problems 25.1 and 27.0, 27.9 and 33.2, 52.6 and
+// 54.2; four 26.3 and 27.7, 33.9 and 33.9, 65.5 and 54.8; eight 32.5 and 28.3, 41.6 and 34.8, 81.8 and 56.5.
+constexpr int kOnceWide = 4, kOnceWideProblems = 2;         // row splits, problems
+// A workgroup may take several chunks of a problem in turn: the keys are loaded once.  That saves kOnceReload of a chunk's time and
+// is taken only where it leaves no compute unit idle: 896 rows (two chunks), scores, apart and in turn: 256 problems of 768 keys 76.9 and
+// 70.0 us, 400 136 and 123, but 260 110 and 126.  (In turn wherever a chunk each had not found a compute unit at once: 16 problems of 16384
+// rows 838 us, of which two passes take 130.)
+constexpr float kOnceReload = 0.16f;
 // Few rows (up to kRowsMost): tiles of 16 keys per wave whose logits eight waves hold, by blocks of 16 rows; taken where a request is
 // too long for its keys to stay in registers, the problems use the device and the longest request does not set the time (rows_quicker in
 // api.hip).  Two passes -> all rows at once: 128 problems of 1000 keys, 16 rows, head_dim 64 20 -> 12 us (call), 32 rows, head_dim 128
@@ -88,7 +101,7 @@ struct Plan {
   int once_keys;             // requests of up to this many keys take the one-pass kernel (0: none does)
   int once_short, once_long; // how many of up to kOnceKeys / 2 keys, and of more
   int once_rows, once_chunks;            // query rows of a chunk, chunks
-  bool once_shared_out;      // the chunks of a problem go to workgroups of their own
+  int once_group;            // chunks that one workgroup takes in turn
   int mass_parts;            // arrays of raw attention mass that add up: row splits, or chunks where every request takes one pass
   int grid_override;         // > 0: the caller fixed the number of workgroups of the score passes
   int lead_tiles;            // empty positions before each request's tiles in the sequence below: the cost of starting a segment

@@ -360,12 +360,12 @@ __device__ __forceinline__ void once_run(const ScoreArgs& a, typename Once<D, NW
   }   // chunks
 }
 
-// Requests with more than n_above and at most n_most keys.  One workgroup per problem takes its row chunks in turn, or (a grid with a
-// third axis) one per problem and chunk.  Heads and requests on axes of their own: one axis holds no more than 2^32 threads.
+// Requests with more than n_above and at most n_most keys; a workgroup takes `group` row chunks of its problem in turn.  Heads and requests
+// on axes of their own: one axis holds no more than 2^32 threads.
 template <int D, int NW, bool K8>
-__global__ __launch_bounds__(NW * 64, 2) void score_once_kernel(ScoreArgs a, int n_above, int n_most) {
+__global__ __launch_bounds__(NW * 64, 2) void score_once_kernel(ScoreArgs a, int n_above, int n_most, int group) {
   __shared__ __attribute__((aligned(16))) typename Once<D, NW, K8>::Shared sh;
-  const int chunk0 = (int)blockIdx.z, chunk1 = gridDim.z > 1 ? chunk0 + 1 : a.once_chunks;
+  const int chunk0 = (int)blockIdx.z * group, chunk1 = min(chunk0 + group, a.once_chunks);
   const int seq = (int)blockIdx.y, lz = (int)blockIdx.x;                      // neighbours are heads of one request: as much work on every die
   const int tok0 = a.cu_seqlens[seq];
   const int n = a.cu_seqlens[seq + 1] - tok0 - a.key_trim;
@@ -385,14 +385,14 @@ __global__ __launch_bounds__(NW * 64, 2) void score_once_kernel(ScoreArgs a, int
 // others in workgroups of eight.  Where all workgroups find a compute unit at once, a second launch would only come after the first.
 template <int D, bool K8>
 int launch_once(const Plan& pl, const ScoreArgs& a, hipStream_t stream) {
-  const dim3 grid(pl.L * pl.Hkv, pl.n_seqs, pl.once_shared_out ? pl.once_chunks : 1);
+  const dim3 grid(pl.L * pl.Hkv, pl.n_seqs, (pl.once_chunks + pl.once_group - 1) / pl.once_group);
   const bool together = pl.once_long && pl.once_short && (int64_t)grid.x * grid.y * grid.z <= kOnceFill;
   if (pl.once_long) {
-    score_once_kernel<D, 8, K8><<<grid, dim3(512), 0, stream>>>(a, together ? 0 : kOnceKeys / 2, kOnceKeys);
+    score_once_kernel<D, 8, K8><<<grid, dim3(512), 0, stream>>>(a, together ? 0 : kOnceKeys / 2, kOnceKeys, pl.once_group);
     if (hipError_t e = hipGetLastError()) return (int)e;
   }
   if (pl.once_short && !together) {
-    score_once_kernel<D, 4, K8><<<grid, dim3(256), 0, stream>>>(a, 0, kOnceKeys / 2);
+    score_once_kernel<D, 4, K8><<<grid, dim3(256), 0, stream>>>(a, 0, kOnceKeys / 2, pl.once_group);
     if (hipError_t e = hipGetLastError()) return (int)e;
   }
   return 0;

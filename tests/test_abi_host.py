@@ -354,3 +354,23 @@ def test_few_rows_at_once_where_lengths_are_alike(rows, d):
     if most > 1536:
         assert not few([100] * 100 + [most])
     assert not few([most + 1] * 24)
+
+
+def test_chunks_of_many_rows_find_all_compute_units():
+    """One-pass requests with more than 512 rows: chunks taken in turn must not leave the device to a few workgroups (16 problems of 16384 rows
+    were 16 workgroups of 32 chunks each), nor a problem have more arrays of masses to add up than its rows are worth."""
+    def route(rows, problems, n=600):
+        q_heads = max(1, rows // 128)
+        return b.codecomp_score_route(packed([n] * problems, n_layers=1, n_q_heads=q_heads, n_kv_heads=1, window=rows // q_heads))
+    for rows in (640, 896, 1024, 2048, 4096, 16384, 32768, 65536):
+        for problems in (3, 4, 8, 16, 17, 64, 200, 256, 257, 300, 1000, 5000):
+            r, chunks, turn = route(rows, problems)
+            assert (r == b.ROUTE_ONE_PASS).all()
+            splits = -(-rows // 512)
+            assert splits <= chunks <= max(splits, 1.5 * (rows / 16) ** 0.5 + 1) and 1 <= turn <= chunks
+            groups = -(-chunks // turn)
+            rounds = -(-problems * groups // 256) * turn                # chunks that the busiest compute unit works through
+            assert rounds <= 1.16 * -(-problems * chunks // 256)
+    for rows, problems in ((2048, 1), (4096, 2), (16384, 1)):
+        assert (route(rows, problems)[0] == b.ROUTE_TWO_PASSES).all()
+    assert (route(1024, 1)[0] == b.ROUTE_ONE_PASS).all()
