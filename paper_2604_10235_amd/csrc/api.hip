@@ -136,14 +136,15 @@ int make_plan(const codecomp_params* p, Plan* pl) {
   if ((pl->variant & CODECOMP_VARIANT_GROUP_MAX) && (pl->W % 32 != 0 || pl->row_splits != 1)) return CODECOMP_EINVAL_MODE;
   if (p->score_workgroups < 0 || p->score_lead_tiles > 64) return CODECOMP_EINVAL_SHAPE;
   pl->grid_override = p->score_workgroups;
-  int64_t tiles = 0, keys = 0, tiles_once = 0;
+  int64_t tiles = 0, keys = 0, tiles_short = 0, tiles_long = 0;          // short, long: of those that one pass could take
   int once_short = 0, once_long = 0;
   for (int r = 0; r < p->n_seqs; ++r) {
     int n = p->cu_seqlens_host[r + 1] - p->cu_seqlens_host[r] - pl->key_trim;     // >= 0: W <= N_r was checked
     const int t = (n + kTileKeys - 1) / kTileKeys;
     tiles += t;
     keys += n;
-    if (n > 0 && n <= kOnceKeys) { tiles_once += t; ++(n <= kOnceKeys / 2 ? once_short : once_long); }
+    if (n > 0 && n <= kOnceKeys / 2) { tiles_short += t; ++once_short; }
+    else if (n > 0 && n <= kOnceKeys) { tiles_long += t; ++once_long; }
   }
   const int64_t problems = (int64_t)pl->L * pl->Hkv * pl->row_splits;
   const int automatic_lead = tiles > 0 && tiles * problems <= kNoLeadTiles ? 0 : kLeadTiles;
@@ -152,16 +153,27 @@ int make_plan(const codecomp_params* p, Plan* pl) {
   if (positions * problems > (1 << 30)) return CODECOMP_EINVAL_SHAPE;
   const int64_t LH64 = (int64_t)pl->L * pl->Hkv;
   const int64_t most = max_n - pl->key_trim;           // keys of the longest request
-  const int64_t once_problems = (once_short + once_long) * LH64;
   const bool own_rules = !(pl->variant & CODECOMP_VARIANT_GROUP_MAX) && p->score_workgroups == 0 && p->score_lead_tiles == 0;
-  const bool all_once = once_problems > 0 && tiles_once == tiles;
+  const bool all_once = once_short + once_long > 0 && tiles_short + tiles_long == tiles;
   pl->rows_at_once = own_rules && pl->R <= kRowsMost && most > kOnceKeys && most <= 128 * rows_tiles((pl->R + 15) / 16) &&
                      LH64 * pl->n_seqs >= kRowsProblems && rows_quicker((pl->R + 15) / 16, pl->d, pl->kv_fp8 != 0, LH64 * pl->n_seqs, LH64 * keys, most);
-  const bool few_wide = pl->row_splits >= kOnceWide && once_problems <= kOnceWideProblems;
-  const bool once = !pl->rows_at_once && (all_once ? !few_wide : once_problems >= kOnceMixed) && own_rules;
-  pl->once_keys = once ? kOnceKeys : 0;
-  pl->once_short = once ? once_short : 0;
-  pl->once_long = once ? once_long : 0;
+  if (!own_rules || pl->rows_at_once) {
+    once_short = once_long = 0;
+  } else if (all_once) {
+    if (pl->row_splits >= kOnceWide && (once_short + once_long) * LH64 <= kOnceWideProblems) once_short = once_long = 0;
+  } else {
+    const int64_t workgroups = LH64 * pl->row_splits;          // per request
+    const bool few = pl->R <= kRowsMost;
+    const float rounds = (float)(once_long * workgroups) / (float)kOnceFill;
+    const bool long_pays = few ? once_long * workgroups >= kOnceMixedLongFew : rounds - kOnceRound * ceilf(rounds) >= kOnceAhead + kOnceStart / (2.0f * (float)pl->row_blocks);
+    if (once_short * workgroups < (few ? kOnceMixedShortFew : kOnceMixedShort) || (few && 2 * tiles_short < 5 * once_short)) once_short = 0;
+    if (!long_pays || (once_short == 0 && tiles_short > 0)) once_long = 0;
+  }
+  const bool once = once_short + once_long > 0;
+  const int64_t once_problems = (once_short + once_long) * LH64;
+  pl->once_keys = once_long > 0 ? kOnceKeys : once ? kOnceKeys / 2 : 0;
+  pl->once_short = once_short;
+  pl->once_long = once_long;
   pl->once_rows = pl->row_blocks * 32;
   pl->once_chunks = pl->row_splits;
   if (once && all_once && once_problems < kOnceFill) {
@@ -188,8 +200,9 @@ int make_plan(const codecomp_params* p, Plan* pl) {
   pl->mass_parts = once && all_once ? pl->once_chunks : pl->row_splits;
   if (pl->rows_at_once) tiles = 0;
   if (once) {
-    tiles -= tiles_once;
-    positions -= tiles_once + (int64_t)pl->lead_tiles * (once_short + once_long);
+    const int64_t taken = (once_short > 0 ? tiles_short : 0) + (once_long > 0 ? tiles_long : 0);
+    tiles -= taken;
+    positions -= taken + (int64_t)pl->lead_tiles * (once_short + once_long);
   }
   pl->tiles_per_problem = (int)positions;
   pl->total_tiles = (int)(positions * pl->L * pl->Hkv);      // the row splits of a problem walk the same positions

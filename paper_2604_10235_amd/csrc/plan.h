@@ -17,10 +17,20 @@ constexpr int kTileKeys = 64;         // keys staged through LDS per pipeline st
 constexpr int kOnceTiles = 6;           // most tiles of 16 keys a wave holds; with seven the eight-wave kernel spills inside its loop
 constexpr int kOnceKeys = 16 * kOnceTiles * 8;      // keys of the longest request that takes one pass
 constexpr int kOnceRows = 512;          // most query rows of a chunk
-// In a call with longer requests too, the kernel runs after their two passes: a launch of 20 to 40 us with few problems, which they
-// would have taken along.  28 query heads on 4, window 64, all -> short ones apart: 160 short problems among 80 of 2000 keys 43 -> 55
-// us, 640 among 32 109 -> 90, 448 of 200 among 448 of 4000 498 -> 494, 4480 among 224 611 -> 375.
-constexpr int kOnceMixed = 512;
+// In a call with longer requests too, the kernel runs after their two passes: one launch for requests of up to kOnceKeys / 2 keys (512
+// workgroups at a time), one for the others (256 at a time), each of 15 to 30 us however little it has to do, while the passes would have
+// taken its requests along.  The shorter ones gain about half their time and pay from little more than one round on; the others gain a
+// fifth to a third, so that a begun round costs more than it brings unless there are many or it is nearly full (kOnceRound, kOnceAhead:
+// 256 problems of 700 in one full round 98 -> 116 us), and the start costs about as much as kOnceStart blocks of 16 rows; workgroups of a request counted as heads * row splits.  With few rows the passes' workgroups are small, many
+// to a compute unit, and lose less to short requests: later lines, and requests of 128 keys or more on average.  One pass takes what is
+// shorter than some length, so the longer ones go only with the shorter.  Scores, all in two passes -> short ones apart: 28 query heads
+// on 4, window 64: 520 short problems of 200 among 8 of 4000 85 -> 82 us, 520 of 700 133 -> 146, 512 of 600 among 512 of 5000 738 -> 700; window 128: 520 of 200 139 -> 121; 16 rows,
+// 4000 of 20 among 96 of 4096, head_dim 128 88 -> 100; 40 rows, 1792 of 43 98 % as fast, 2064 of 260 84 -> 72, 7000 of 686 628 -> 479.  600
+// batches of 45 to 8192 short problems among longer ones, 16 to 896 rows: with one line at 512 short problems of any length 41 were slower
+// than two passes by 3 % or more (the worst 0.75), with these 11 (0.91).
+constexpr int kOnceMixedShort = 640;
+constexpr float kOnceRound = 0.8f, kOnceAhead = 0.2f, kOnceStart = 3.0f;
+constexpr int kOnceMixedShortFew = 2560, kOnceMixedLongFew = 1536;             // up to kRowsMost rows
 constexpr int kOnceFill = 256;          // workgroups that find a compute unit of their own at once: up to here a problem's rows are shared out
 // Each chunk has an array of masses of its own, which the pooling adds up: 0.3 to 0.5 us an array in a short call, against 0.9 us for
 // each block of 16 rows that a chunk has more.  So at most 1.5 * sqrt(blocks) chunks (their square at most kOnceArrays / 4 * blocks), unless

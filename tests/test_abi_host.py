@@ -374,3 +374,24 @@ def test_chunks_of_many_rows_find_all_compute_units():
     for rows, problems in ((2048, 1), (4096, 2), (16384, 1)):
         assert (route(rows, problems)[0] == b.ROUTE_TWO_PASSES).all()
     assert (route(1024, 1)[0] == b.ROUTE_ONE_PASS).all()
+
+
+def test_short_requests_go_apart_where_they_fill_the_device():
+    one, two = b.ROUTE_ONE_PASS, b.ROUTE_TWO_PASSES
+    def route(lens, **over):
+        kw = dict(n_layers=4, n_q_heads=14, window=16)                                # 8 problems a request, 112 rows
+        kw.update(over)
+        return b.codecomp_score_route(packed(lens, **kw))[0].tolist()
+    assert route([200] * 80 + [2000]) == [one] * 80 + [two]
+    assert route([200] * 79 + [2000]) == [two] * 80
+    assert route([200] * 319 + [5000], n_q_heads=8) == [two] * 320                    # 64 rows
+    assert route([200] * 320 + [5000], n_q_heads=8) == [one] * 320 + [two]
+    assert route([100] * 320 + [5000], n_q_heads=8) == [two] * 321
+    assert route([700] * 192 + [5000], n_q_heads=8) == [one] * 192 + [two]
+    assert route([700] * 66 + [2000]) == [two] * 67                                   # 528 workgroups: three rounds for two and a bit
+    assert route([700] * 32 + [2000]) == [two] * 33                                   # one round
+    assert route([700] * 128 + [2000]) == [one] * 128 + [two]
+    assert route([700] * 66 + [200] * 80 + [2000]) == [two] * 66 + [one] * 80 + [two]      # too few of the longer ones: those stay
+    assert route([700] * 128 + [200] * 80 + [2000]) == [one] * 208 + [two]
+    assert route([700] * 128 + [200] * 79 + [2000]) == [two] * 208                     # one pass takes what is shorter than some length
+    assert route([200] * 40 + [2000], n_q_heads=2 * 40) == [one] * 40 + [two]         # 640 rows: two workgroups a problem

@@ -16,7 +16,7 @@ TWO_WAYS = 8e-6
 
 
 def both_ways(w, kv="bf16", q_scale=1.0, route=None, **over):
-    """Scores by the library's own rules and by two passes; `route`: what the first call has to take for its requests (b.ROUTE_*)."""
+    """Scores by the library's own rules and by two passes; `route`: what the first call has to take for its requests (b.ROUTE_*, one for all or one each)."""
     import torch
     from paper_2604_10235_amd import binding as b
     q, k, v, prior = wl.make_all(w)
@@ -28,7 +28,8 @@ def both_ways(w, kv="bf16", q_scale=1.0, route=None, **over):
     for wgs in (0, 40):
         p = b.DeviceProblem(w, q, k, v, prior, score_workgroups=wgs, **over)
         if route is not None:
-            assert (b.codecomp_score_route(p.params)[0] == (route if wgs == 0 else b.ROUTE_TWO_PASSES)).all()
+            got_route = b.codecomp_score_route(p.params)[0]
+            assert (got_route == (b.ROUTE_TWO_PASSES if wgs else route)).all()
         p.workspace.fill_(0xFF)                                    # nothing may be read before it is written
         p.score()
         first = p.scores.clone()
@@ -273,3 +274,20 @@ def test_millions_of_problems(first, heads):
     alone, _ = scores_on_device([first], 1, heads, heads, 64, 1, q[:, :1], k[:, :, :first], pool=1)
     assert float((got[:, :, first:] - 1.0).abs().max()) <= TWO_WAYS           # (NaN fails, too)
     np.testing.assert_allclose(got[:, :, :first].cpu().numpy(), alone.cpu().numpy(), rtol=TWO_WAYS)
+
+
+# Requests of up to 384 keys apart while the longer short ones stay in the passes; both apart; more rows than one workgroup holds,
+# chunks in turn.  Lengths on both sides of every line, a window that the softmax leaves out.
+@pytest.mark.parametrize("heads,window,times,longer,variant", [((14, 2), 16, 24, 0, 0), ((14, 2), 16, 24, 62, 0), ((14, 2), 16, 24, 0, 8), ((14, 2), 100, 24, 62, 1 | 4 | 8 | 16)])
+@pytest.mark.parametrize("kv", ["bf16", "fp8"])
+def test_short_requests_apart(heads, window, times, longer, variant, kv):
+    from tests.test_gpu_parity import oracle_variant
+    trim = window if variant & 8 else 0
+    lens = [n + trim for n in ([384, 20, 383, 17, 16, 65, 1, 300] * times + [385, 767, 768, 769, 1500] + [500, 768] * longer)]
+    lens = [max(window, n) for n in lens]
+    w = wl.scaled(wl.qwen7b_32k(), n_layers=4, n_q_heads=heads[0], n_kv_heads=heads[1], head_dim=64, window=window, seqlens=lens, budgets=lens)
+    q, k, prior, (one, two) = both_ways(w, kv, score_variant=variant, route=[ROUTE_ONE_PASS if 0 < n - trim <= (768 if longer else 384) else ROUTE_TWO_PASSES for n in lens])
+    np.testing.assert_allclose(one, two, rtol=TWO_WAYS, atol=1e-30)
+    ref = orc.score_packed(q[:1], k[:1], prior, w.cu_seqlens(), pool_kernel=w.pool_kernel, prior_weight=w.prior_weight,
+                           k_format="fp8_e4m3" if kv == "fp8" else "bf16", **oracle_variant(variant))
+    pu.assert_scores_close(one[:1], ref)
