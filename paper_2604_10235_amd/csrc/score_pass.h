@@ -97,8 +97,9 @@ __device__ __forceinline__ u32x4 to_bf16x8(u32x2 v) {
 // lead, so that lead and tiles together take no position.
 struct TileRule { int trim, once_keys, lead; };
 __device__ __forceinline__ int tiles_of(int len, TileRule r) {
-  const int n = len - r.trim;
-  return n <= r.once_keys && n > 0 ? -r.lead : (n + kTileKeys - 1) / kTileKeys;
+  const int n = len - r.trim;                          // >= 0
+  static_assert(kTileKeys == 64, "shift");
+  return n <= r.once_keys && n > 0 ? -r.lead : (n + kTileKeys - 1) >> 6;
 }
 
 // Where a workgroup enters a problem's sequence: the request that holds position `xr` and the position at which
@@ -245,8 +246,11 @@ __device__ __forceinline__ f32x16 mma_step(u32x4 qfrag, u32x4 kfrag, f32x16 acc)
 
 // GMAX (pass 2 only): the largest query-head mass of the group instead of the (scaled) sum over its heads.
 // K8: the keys are FP8 E4M3 codes; they are widened to bf16 on their way into LDS, everything after is the same.
+// A short call waits for instructions before it waits for keys: the kernel begins on a page of its own, and what few calls come past (the
+// walk to a later request) lies behind the tile loops.  Two layers of 8192 tokens, 28 query heads: pass 1 16.4 -> 16.2 us, pass 2 15.9 ->
+// 15.4, against the walk inside the start and the kernels where they came to lie.
 template <int D, int NW, int PASS, bool GMAX = false, bool K8 = false>
-__global__ __launch_bounds__(NW * 64, (NW >= 3 ? 2 : 1)) void score_pass_kernel(ScoreArgs a) {
+__global__ __launch_bounds__(NW * 64, (NW >= 3 ? 2 : 1)) __attribute__((aligned(4096))) void score_pass_kernel(ScoreArgs a) {
   static_assert(PASS == 2 || !GMAX, "the group reduction happens in pass 2");
   constexpr int NT = NW * 64;
   constexpr int KS = D / 16;                   // MFMA k-steps per logit
@@ -299,12 +303,12 @@ __global__ __launch_bounds__(NW * 64, (NW >= 3 ? 2 : 1)) void score_pass_kernel(
   const int xr = x - lz * a.tiles_per_problem;
   int tok0 = a.cu_seqlens[cur_seq], tok1 = a.cu_seqlens[cur_seq + 1];
   int tiles_of_seq = tiles_of(tok1 - tok0, rule);
-  if (xr >= cur_acc + a.lead + tiles_of_seq) {               // usually the next request then
+  if (__builtin_expect(xr >= cur_acc + a.lead + tiles_of_seq, 0)) {               // usually the next request then
     cur_acc += a.lead + tiles_of_seq;
     if (++cur_seq >= a.n_seqs) break;                        // never for a position inside the sequence
     tok0 = tok1; tok1 = a.cu_seqlens[cur_seq + 1];
     tiles_of_seq = tiles_of(tok1 - tok0, rule);
-    if (xr >= cur_acc + a.lead + tiles_of_seq) {
+    if (__builtin_expect(xr >= cur_acc + a.lead + tiles_of_seq, 0)) {
       if (!skip_to(a.cu_seqlens, a.n_seqs, rule, xr, cur_seq, cur_acc)) break;
       tok0 = a.cu_seqlens[cur_seq]; tok1 = a.cu_seqlens[cur_seq + 1];
       tiles_of_seq = tiles_of(tok1 - tok0, rule);
