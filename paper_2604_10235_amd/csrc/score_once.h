@@ -147,7 +147,7 @@ __device__ __forceinline__ void once_run(const ScoreArgs& a, typename Once<D, NW
   };
   auto fetch = [&](int round, const uint16_t* from) __attribute__((always_inline)) {
     const uint32_t to = fetch_to + (uint32_t)((round * O::ROUND) % O::RING) * (KS * 1024u);
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(to), "v"(from) : "memory");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(to), "v"(from) : "memory", "m0");
   };
   const uint16_t* next_place;          // of the round to be sent for next: its rows are looked up a round ahead
   auto fetch_first = [&]() __attribute__((always_inline)) {
