@@ -253,16 +253,11 @@ int make_plan(const codecomp_params* p, Plan* pl) {
     pl->off_part_before = off; off = align256(off + LH * (size_t)parts * 2 * sizeof(int32_t));
   }
   pl->ws_bytes = off;
-  // calls without two-pass requests keep no statistics: more mass arrays than row splits take their place as well
-  if (pl->mass_parts > pl->row_splits) {
-    if ((size_t)pl->mass_parts * LH * pl->T * sizeof(float) <= pl->off_member) {
-      pl->off_uraw = 0;
-    } else {                   // long windows that the softmax leaves out
-      pl->once_rows = pl->row_blocks * 32;
-      pl->once_chunks = pl->mass_parts = pl->row_splits;
-      pl->once_group = 1;
-    }
-  }
+  // Calls without two-pass requests keep no statistics: more mass arrays than row splits take their place as well.  They fit: problems *
+  // chunks <= kOnceFill and a problem has at most R + kOnceKeys tokens, so the arrays beyond the row splits hold 4 * kOnceFill *
+  // (R + kOnceKeys) * (1 - splits / chunks) bytes at most, which with chunks <= 1.5 * sqrt(R / 16) is below 5.9 MB (at R = 16384); the
+  // statistics have kMaxScoreGrid slots of 4 KB above 256 rows, and of 512 bytes per two blocks of 32 rows below.
+  if (pl->mass_parts > pl->row_splits) pl->off_uraw = 0;
   return CODECOMP_OK;
 }
 

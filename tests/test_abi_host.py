@@ -395,3 +395,22 @@ def test_short_requests_go_apart_where_they_fill_the_device():
     assert route([700] * 128 + [200] * 80 + [2000]) == [one] * 208 + [two]
     assert route([700] * 128 + [200] * 79 + [2000]) == [two] * 208                     # one pass takes what is shorter than some length
     assert route([200] * 40 + [2000], n_q_heads=2 * 40) == [one] * 40 + [two]         # 640 rows: two workgroups a problem
+
+
+def test_mass_arrays_of_row_chunks_fit_where_the_statistics_would_be():
+    """More mass arrays than row splits begin at the start of the workspace; behind them lie the arrays of the selection.  Tightest with a
+    window that the softmax leaves out and one query head: then a request has the most tokens for its 768 keys."""
+    tightest = 0.0
+    for rows in (65, 96, 128, 129, 256, 257, 448, 512, 513, 896, 1536, 2048, 4096, 8192, 12000, 14000, 16384, 18000, 20000, 32768, 65536):
+        for problems in (1, 2, 3, 4, 5, 6, 7, 8, 10, 16, 32, 64, 85, 128, 255):
+            for n_seqs, heads in ((1, problems), (problems, 1)):
+                p = packed([rows + 768] * n_seqs, n_layers=1, n_q_heads=heads, n_kv_heads=heads, window=rows, score_variant=8)
+                _, chunks, _ = b.codecomp_score_route(p)
+                _, splits, blocks, waves, _ = b.codecomp_score_layout(p)
+                if chunks <= splits:
+                    continue
+                array = 4 * heads * n_seqs * (rows + 768)
+                before = (2048 + heads * n_seqs * splits) * waves * 64 * 8 + 4 * heads * n_seqs * splits * blocks * 32
+                assert chunks * array <= before + splits * array, (rows, problems, n_seqs)
+                tightest = max(tightest, (chunks - splits) * array / before)
+    assert 0.3 < tightest < 1.0
