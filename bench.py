@@ -62,16 +62,10 @@ def read_traffic(name: str):
     return vals
 
 
-ONE_PASS_KEYS = 768             # requests up to here have all their score work in the mass kernels, in one pass ...
-ONE_PASS_PROBLEMS = 512         # ... in batches of no longer ones, or with this many such (layer, head, request) problems
-
-
-def two_pass_share(w) -> float:
-    """Share of the logits that are formed twice (the other requests are short enough for one pass)."""
-    short = [n for n in w.seqlens if n <= ONE_PASS_KEYS]
-    if len(short) < w.n_seqs and len(short) * w.n_layers * w.n_kv_heads < ONE_PASS_PROBLEMS:
-        return 1.0
-    return 1.0 - sum(short) / w.total_tokens
+def two_pass_share(w, params, binding) -> float:
+    """Share of the logits that are formed twice, by the route that the library takes for each request (the others are formed once)."""
+    route = binding.codecomp_score_route(params)[0]
+    return sum(n for n, r in zip(w.seqlens, route) if r == binding.ROUTE_TWO_PASSES) / w.total_tokens
 
 
 def binding_roofline(flops_pass: float, logits_pass: float, twice: float, ab: dict, k_bytes: int, ms_per_step: float, peaks):
@@ -273,9 +267,9 @@ def main() -> int:
 
     # dominant stage: one of the two MFMA passes; its flops = 2 * R * sum(N_r) * d per (layer, KV head), for the row statistics
     # over the requests whose logits are formed twice
-    dom = max(("score_row_stats", "score_mass"), key=lambda n: stage_ms[n])
+    twice = two_pass_share(w, prob.params, binding)
+    dom = max(("score_row_stats", "score_mass"), key=lambda n: stage_ms[n]) if twice > 0.0 else "score_mass"
     flops = 2.0 * w.group * w.window * T * w.head_dim * w.n_kv_heads * L
-    twice = two_pass_share(w)
     flops_dom = flops if dom == "score_mass" else flops * twice
     achieved = flops_dom / (stage_ms[dom] * 1e-3) / 1e12
     traffic = read_traffic(w.name if args.kv_dtype == "bf16" else f"{w.name}_{args.kv_dtype}")
