@@ -20,7 +20,7 @@ def both_ways(w, kv="bf16", q_scale=1.0, route=None, **over):
     import torch
     from paper_2604_10235_amd import binding as b
     q, k, v, prior = wl.make_all(w)
-    if q_scale != 1.0:
+    if not np.isscalar(q_scale) or q_scale != 1.0:                       # one factor, or one per row of the window
         q = wl.f32_to_bf16_bits(orc.bf16_bits_to_f64(q).astype(np.float32) * np.float32(q_scale))
     if kv == "fp8":
         k, v = wl.bf16_bits_to_fp8_codes(k), wl.bf16_bits_to_fp8_codes(v)
@@ -112,6 +112,26 @@ def test_one_large_logit_beside_unfinished_row_blocks(window, rows_per_head, d, 
     torch.cuda.synchronize()
     ref = orc.score_packed(qb, kb, prior, w.cu_seqlens(), pool_kernel=1, prior_weight=0.0, k_format="fp8_e4m3" if kv == "fp8" else "bf16")
     np.testing.assert_allclose(p.scores.cpu().numpy(), ref, rtol=4e-5)
+
+
+# The second run from the largest logits on other shapes: row counts that are no multiple of 16, both widths of keys, 32 blocks in a
+# workgroup (the ring of query blocks twice over), two chunks in turn, short requests beside longer ones.  Every row scaled, or every
+# third: then the blocks in range wait for the others and are done again with them.
+@pytest.mark.parametrize("heads,d,window,layers,lens", [((3, 1), 64, 37, 3, [70, 300, 384]), ((3, 1), 128, 37, 3, [500, 768, 40]), ((4, 4), 64, 17, 2, [17, 600, 33]),
+                                                        ((16, 4), 64, 128, 65, [130]), ((8, 2), 128, 128, 130, [400]), ((14, 2), 64, 128, 200, [130]), ((14, 2), 64, 128, 200, [390]),
+                                                        ((14, 2), 64, 17, 4, [100, 17, 384, 33] * 20 + [800, 1500])])
+@pytest.mark.parametrize("kv,rows", [("bf16", "all"), ("fp8", "some")])
+def test_logits_far_apart_on_other_shapes(heads, d, window, layers, lens, kv, rows):
+    from paper_2604_10235_amd import binding as b
+    lens = [max(n, window) for n in lens]
+    w = wl.scaled(wl.qwen7b_32k(), n_layers=layers, n_q_heads=heads[0], n_kv_heads=heads[1], head_dim=d, window=window, seqlens=lens, budgets=lens, prior_weight=0.0)
+    scale = np.full((window, 1), 40.0, np.float32)
+    if rows == "some":
+        scale[np.arange(window) % 3 != 0] = 1.0
+    q, k, prior, (one, two) = both_ways(w, kv, q_scale=scale, route=[ROUTE_ONE_PASS if n <= 768 else ROUTE_TWO_PASSES for n in lens])
+    np.testing.assert_allclose(one, two, rtol=2e-4, atol=1e-30)
+    ref = orc.score_packed(q[:1], k[:1], prior, w.cu_seqlens(), pool_kernel=w.pool_kernel, prior_weight=0.0, k_format="fp8_e4m3" if kv == "fp8" else "bf16")
+    np.testing.assert_allclose(one[:1], ref, rtol=1e-3, atol=1e-30)
 
 
 def test_strided_queries_and_keys():
