@@ -174,13 +174,12 @@ int codecomp_score(const void* q_obs, const void* k, const float* prior, const c
  * order row statistics -> row merge -> attention mass -> pool + prior.  Meant for per-kernel
  * timing and stage-wise debugging: a later stage reads what the earlier ones left in `workspace`,
  * so the stages of one problem must be enqueued in order with the same arguments.
- * Where a request is short enough for its score to be formed in one pass (up to 768 keys, in batches of no longer ones or with
- * many of them; a few thousand keys with at most 64 softmax rows per KV head in larger batches; never with score_workgroups,
- * score_lead_tiles or CODECOMP_VARIANT_GROUP_MAX), CODECOMP_STAGE_MASS does all of it and the two stages before leave it out.
+ * Requests that codecomp_score_route does not give to TWO_PASSES have all of it done by CODECOMP_STAGE_MASS; the two stages before
+ * leave them out, and they leave no row normalisers (nothing reads any).
  * CODECOMP_STAGE_ALL is exactly codecomp_score, which in short calls does the row merge inside the mass kernel: there the
- * stages one by one differ from it by the regrouping of fp32 sums.  The row normalisers are left in `workspace` either
- * way, so that a stage asked for again after codecomp_score (or after the first three stages in one call) finds
- * what it reads, and the mass kernel alone gives the same bits again. */
+ * stages one by one differ from it by the regrouping of fp32 sums.  The row normalisers of two-pass requests are left in
+ * `workspace` either way, so that a stage asked for again after codecomp_score (or after the first three stages in one
+ * call) finds what it reads, and the mass kernel alone gives the same bits again. */
 enum {
   CODECOMP_STAGE_ROW_STATS = 1,   /* pass 1: per-chunk (max, sum) of every softmax row             */
   CODECOMP_STAGE_ROW_MERGE = 2,   /* log-sum-exp of every row over the chunks of its request       */

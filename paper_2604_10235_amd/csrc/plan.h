@@ -12,38 +12,40 @@ constexpr int kRowsPerWave = 64;      // query rows (window x group) one wavefro
 constexpr int kMaxWaves = 8;          // wavefronts per workgroup in the score kernels
 constexpr int kTileKeys = 64;         // keys staged through LDS per pipeline step
 // One pass over the logits (score_once.h): the keys of a request in the registers of one workgroup.  A call whose requests are all
-// that short always takes it: 1.1 to 2.4 times faster than two passes from one problem of 130 keys to 4096 of 760, head_dim 64 and
-// 128, 32 to 896 rows (figures there).
+// that short takes it (but for a few problems of very many rows, below): 1.1 to 2.4 times faster than two passes from one problem of
+// 130 keys to 4096 of 760, head_dim 64 and 128, 32 to 896 rows (figures there).
 constexpr int kOnceTiles = 6;           // most tiles of 16 keys a wave holds; with seven the eight-wave kernel spills inside its loop
 constexpr int kOnceKeys = 16 * kOnceTiles * 8;      // keys of the longest request that takes one pass
 constexpr int kOnceRows = 512;          // most query rows of a chunk
-// In a call with longer requests too, the kernel runs after their two passes: one launch for requests of up to kOnceKeys / 2 keys (512
-// workgroups at a time), one for the others (256 at a time), each of 15 to 30 us however little it has to do, while the passes would have
-// taken its requests along.  The shorter ones gain about half their time and pay from little more than one round on; the others gain a
-// fifth to a third, so that a begun round costs more than it brings unless there are many or it is nearly full (kOnceRound, kOnceAhead:
-// 256 problems of 700 in one full round 98 -> 116 us), and the start costs about as much as kOnceStart blocks of 16 rows; workgroups of a request counted as heads * row splits.  With few rows the passes' workgroups are small, many
-// to a compute unit, and lose less to short requests: later lines, and requests of 128 keys or more on average.  One pass takes what is
-// shorter than some length, so the longer ones go only with the shorter.  Scores, all in two passes -> short ones apart: 28 query heads
-// on 4, window 64: 520 short problems of 200 among 8 of 4000 85 -> 82 us, 520 of 700 133 -> 146, 512 of 600 among 512 of 5000 738 -> 700; window 128: 520 of 200 139 -> 121; 16 rows,
-// 4000 of 20 among 96 of 4096, head_dim 128 88 -> 100; 40 rows, 1792 of 43 98 % as fast, 2064 of 260 84 -> 72, 7000 of 686 628 -> 479.  600
-// batches of 45 to 8192 short problems among longer ones, 16 to 896 rows: with one line at 512 short problems of any length 41 were slower
-// than two passes by 3 % or more (the worst 0.75), with these 11 (0.91).
+constexpr int kOnceFill = 256;          // workgroups that find a compute unit of their own at once: up to here a problem's rows are shared out
+// In a call with longer requests too, the kernel runs after their two passes: one launch for requests of up to kOnceKeys / 2 keys
+// (512 workgroups at a time), one for the others (256 at a time), each of 15 to 30 us however little it has to do, while the passes
+// would have taken its requests along.  Workgroups counted as requests * heads * row splits, the shorter ones gain about half their
+// time and pay from little more than one round on (kOnceMixedShort).  The others gain a fifth to a third, so that a begun round
+// costs more than it brings unless there are many or it is nearly full (kOnceRound, kOnceAhead: 256 problems of 700 in one full round
+// 98 -> 116 us), and the start costs about as much as kOnceStart blocks of 16 rows.  With few rows the passes' workgroups are small,
+// many to a compute unit, and lose less to short requests: later lines, and requests of 128 keys or more on average.  One pass takes
+// what is shorter than some length, so the longer ones go only with the shorter.
+// Scores, all in two passes -> short ones apart: 28 query heads on 4, window 64: 520 short problems of 200 among 8 of 4000 85 -> 82 us,
+// 520 of 700 133 -> 146, 512 of 600 among 512 of 5000 738 -> 700; window 128: 520 of 200 139 -> 121; 16 rows, 4000 of 20 among 96 of
+// 4096, head_dim 128 88 -> 100; 40 rows, 1792 of 43 98 % as fast, 2064 of 260 84 -> 72, 7000 of 686 628 -> 479.  600 batches of 45 to
+// 8192 short problems among longer ones, 16 to 896 rows: with one line at 512 short problems of any length 41 were slower than two
+// passes by 3 % or more (the worst 0.75), with these 11 (0.91).
 constexpr int kOnceMixedShort = 640;
 constexpr float kOnceRound = 0.8f, kOnceAhead = 0.2f, kOnceStart = 3.0f;
 constexpr int kOnceMixedShortFew = 2560, kOnceMixedLongFew = 1536;             // up to kRowsMost rows
-constexpr int kOnceFill = 256;          // workgroups that find a compute unit of their own at once: up to here a problem's rows are shared out
 // Each chunk has an array of masses of its own, which the pooling adds up: 0.3 to 0.5 us an array in a short call, against 0.9 us for
-// each block of 16 rows that a chunk has more.  So at most 1.5 * sqrt(blocks) chunks (their square at most kOnceArrays / 4 * blocks), unless
-// chunks of kOnceRows are more.  One request of 768 tokens, scores, 4096 rows: 64 chunks 45.1 us, 32 33.7, 16 32.6, 8 41.1.
+// each block of 16 rows that a chunk has more.  So at most 1.5 * sqrt(blocks) chunks (their square at most kOnceArrays / 4 * blocks),
+// unless chunks of kOnceRows are more.  One request of 768 tokens, 4096 rows, scores: 64 chunks 45.1 us, 32 33.7, 16 32.6, 8 41.1.
 constexpr int kOnceArrays = 9;
-// From 1537 rows on, one or two problems take two passes, whose workgroups share out the keys, too: 768 keys, two passes and one pass, one
-// problem of 2048 rows 23.2 and 26.1 us, of 4096 25.6 and 32.6, of 16384 44.6 and 52.5; two problems 25.1 and 27.0, 27.9 and 33.2, 52.6 and
-// 54.2; four 26.3 and 27.7, 33.9 and 33.9, 65.5 and 54.8; eight 32.5 and 28.3, 41.6 and 34.8, 81.8 and 56.5.
+// From 1537 rows on, one or two problems take two passes, whose workgroups share out the keys, too.  Scores of 768 keys, two passes
+// and one pass: one problem of 2048 rows 23.2 and 26.1 us, of 4096 25.6 and 32.6, of 16384 44.6 and 52.5; two 25.1 and 27.0, 27.9 and
+// 33.2, 52.6 and 54.2; four 26.3 and 27.7, 33.9 and 33.9, 65.5 and 54.8; eight 32.5 and 28.3, 41.6 and 34.8, 81.8 and 56.5.
 constexpr int kOnceWide = 4, kOnceWideProblems = 2;         // row splits, problems
 // A workgroup may take several chunks of a problem in turn: the keys are loaded once.  That saves kOnceReload of a chunk's time and
-// is taken only where it leaves no compute unit idle: 896 rows (two chunks), scores, apart and in turn: 256 problems of 768 keys 76.9 and
-// 70.0 us, 400 136 and 123, but 260 110 and 126.  (In turn wherever a chunk each had not found a compute unit at once: 16 problems of 16384
-// rows 838 us, of which two passes take 130.)
+// is taken only where it leaves no compute unit idle: 896 rows (two chunks), scores, a chunk each and two in turn: 256 problems of 768
+// keys 76.9 and 70.0 us, 400 136 and 123, but 260 104 and 125.  (In turn wherever all chunks did not find a compute unit at once, 16
+// problems of 16384 rows took 838 us, two passes 130; now 96.)
 constexpr float kOnceReload = 0.16f;
 // Few rows (up to kRowsMost): tiles of 16 keys per wave whose logits eight waves hold, by blocks of 16 rows; taken where a request is
 // too long for its keys to stay in registers, the problems use the device and the longest request does not set the time (rows_quicker in
@@ -80,9 +82,11 @@ constexpr int kSelectMaxCandidates = 65536;                // most candidates on
 // Up to there one workgroup per problem is quicker than parts, however few the problems.  Parts -> one workgroup: one problem of
 // 16384 candidates 34.5 -> 9.9 us, of 65536 37.5 -> 29.1; 64 of 65536 49.6 -> 31.0; one of 65536 with a binary prior 45.2 ->
 // 37.0, of one value only 128 -> 75; two-stage, 64 of 65536 107 -> 86.
+
 // A workgroup that selects copies the kept rows, too, up to this many bytes of K and V (read): a launch less.  Whole call, own kernel ->
-// copied along: 4 KV heads of 2048 tokens, head_dim 64, 256 kept (64 KB) 19.6 -> 18.1 us, 512 kept 20.0 -> 20.0, 1024 20.4 -> 22.6;
-// head_dim 128, 2000 tokens, 128 kept (64 KB) 27.8 -> 27.1, 512 28.2 -> 31.0; 112 heads of 2048, 256 kept 29.4 -> 28.1.
+// copied along, 64 KB: 4 KV heads of 2048 tokens, head_dim 64, 256 kept 18.8 -> 17.8 us; head_dim 128, 2000 tokens, 128 kept 21.0 -> 20.1;
+// 28 layers of them 24.9 -> 23.4 and 32.4 -> 31.1.  More: head_dim 64, 512 kept 20.0 -> 20.0, 1024 20.4 -> 22.6; head_dim 128, 512 kept
+// 28.2 -> 31.0.
 constexpr int64_t kCopyBytes = 65536;
 constexpr int kFirstDigitBins = 2048;
 constexpr int kFinishHalo = 512;      // largest supported (pool_kernel - 1) / 2
@@ -109,7 +113,7 @@ struct Plan {
   uint8_t rb_holder[2 * kMaxWaves][2];   // per row block: wave * 2 + slot of its (one or two) owners, 255 = none
   bool rows_at_once;         // few rows and no request longer than their logits' place in registers: one kernel (score_rows_kernel)
   int once_keys;             // requests of up to this many keys take the one-pass kernel (0: none does)
-  int once_short, once_long; // how many of up to kOnceKeys / 2 keys, and of more
+  int once_short, once_long; // how many take it, of up to kOnceKeys / 2 keys and of more
   int once_rows, once_chunks;            // query rows of a chunk, chunks
   int once_group;            // chunks that one workgroup takes in turn
   int mass_parts;            // arrays of raw attention mass that add up: row splits, or chunks where every request takes one pass

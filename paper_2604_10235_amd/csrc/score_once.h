@@ -12,12 +12,13 @@
 // rows are through.  Blocks of 16 rows and not 32, as the two passes have: the waiting exponentials would take twice the
 // registers, and half the keys would fit.
 //
-// Bound by instruction issue: 16 VALU instructions (fma, exponential, row sum, mass) and 4 MFMAs per tile and block.  A block
-// of 24 tiles per SIMD takes 1430 cycles in workgroups of four waves (two of them share a compute unit and fill each other's
-// waits) and 1880 in workgroups of eight (384 and 768 keys, head_dim 128); its 24 tiles cost 56 and 62 ns per 32x32x16 MFMA's
-// worth of logits against 88 for the two passes together on such requests.  Scores, two passes -> one pass: 28 query heads
-// (window 128) on 4 KV heads, one request of 130 tokens 22 -> 13 us, of 700 23 -> 21, 64 requests of 300 78 -> 31, of 760 122 ->
-// 60, 16 layers of those 968 -> 470 and 1768 -> 1000; 28 layers of 64 chunks of 135 to 1831 tokens (50 of them short) 2.73 -> 1.96 ms.
+// Bound by instruction issue: 16 VALU instructions (fma, exponential, row sum, mass) and 4 MFMAs per tile and block.  A SIMD has 12
+// tiles at most, six in each of its two waves: a block of 16 rows takes a compute unit 0.89 us for 768 keys (one workgroup of eight
+// waves) and 0.97 us for two times 384 (two workgroups of four, which fill each other's waits), head_dim 128, that is 37 and 40 ns for a
+// 32x32x16 MFMA's worth of logits; head_dim 64 0.68 and 0.72 us.  With its starts and unequal lengths a batch of chunks takes 62 and 56 ns,
+// where the two passes together take 88.  Scores, two passes -> one pass: 28 query heads (window 128) on 4 KV heads, one request of 130
+// tokens 22 -> 13 us, of 700 23 -> 21, 64 requests of 300 78 -> 31, of 760 122 -> 60, 16 layers of those 968 -> 470 and 1768 -> 1000; 28
+// layers of 64 chunks of 135 to 1831 tokens (48 of them of up to 768) 2.73 -> 1.96 ms.
 // Error against 64 bits (2-norm, 130 .. 768 keys): 5e-8 to 9e-8, of the two passes 1.8e-7 to 2.4e-7: the weight of a row is the
 // reciprocal of its sum and not an exponent that was rounded.
 #pragma once
@@ -31,7 +32,6 @@ __device__ __forceinline__ f32x4 once_mma(u32x4 k, u32x4 q, f32x4 acc) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(frag(k), frag(q), acc, 0, 0, 0);
 }
 
-// Sum or largest of the four lanes that hold one query row (lane, lane ^ 16, lane ^ 32, lane ^ 48).
 // x of this lane and of lane ^ 16 (lane ^ 32), in either order.
 __device__ __forceinline__ void swap16(float x, float& a, float& b) {
   a = x; b = x;
@@ -41,6 +41,7 @@ __device__ __forceinline__ void swap32(float x, float& a, float& b) {
   a = x; b = x;
   asm volatile("s_nop 1\n\tv_permlane32_swap_b32 %0, %1" : "+v"(a), "+v"(b));
 }
+// Sum or largest of the four lanes that hold one query row (lane, lane ^ 16, lane ^ 32, lane ^ 48).
 __device__ __forceinline__ float row_sum4(float x) {
   float a, b;
   swap16(x, a, b); swap32(a + b, a, b);
@@ -404,7 +405,7 @@ int launch_once(const Plan& pl, const ScoreArgs& a, hipStream_t stream) {
 // Up to 64 rows leave room for all logits of a longer request in one workgroup's registers (RB blocks of 16 rows, TT tiles of 16
 // keys per wave: 4 RB TT registers), so that the keys only pass through.  The rows' largest logits and sums are exchanged
 // between the waves once each.  Bound by the memory round trips of a compute unit,
-// then by issue; figures at kRowsProblems.
+// then by issue; figures at kRowsProblems and rows_quicker (api.hip).
 template <int RB>
 struct Rows {
   static constexpr int TT = rows_tiles(RB);
