@@ -176,12 +176,19 @@ int make_plan(const codecomp_params* p, Plan* pl) {
   pl->once_long = once_long;
   pl->once_rows = pl->row_blocks * 32;
   pl->once_chunks = pl->row_splits;
+  // statistics (one slot per segment and row split; slot numbers stay below (teams + problems) * row_splits) and merged row normalisers
+  const int64_t stat_bytes = (kMaxScoreGrid + LH64 * pl->row_splits * pl->n_seqs) * (pl->waves * kRowsPerWave) * 2 * (int64_t)sizeof(float);
+  const int64_t lse_bytes = LH64 * pl->n_seqs * pl->row_splits * pl->row_blocks * 32 * (int64_t)sizeof(float);
   if (once && all_once && once_problems < kOnceFill) {
     // few problems: smaller chunks of rows, of at least four blocks of 16, until the compute units are used
     const int blocks = (pl->R + 15) / 16;
     int64_t chunks = kOnceFill / once_problems;
     if (chunks > (blocks + 3) / 4) chunks = (blocks + 3) / 4;
     while (4 * chunks * chunks > kOnceArrays * blocks) --chunks;           // an array of masses each
+    // More arrays than row splits lie over statistics and normalisers (below).  Requests without a key need no chunk, but every array
+    // has a place for their tokens.
+    const int64_t room = pl->row_splits + (stat_bytes + lse_bytes) / (LH64 * pl->T * (int64_t)sizeof(float));
+    if (chunks > room) chunks = room;
     if (chunks < pl->row_splits) chunks = pl->row_splits;
     pl->once_rows = (int)((blocks + chunks - 1) / chunks) * 16;
     pl->once_chunks = (pl->R + pl->once_rows - 1) / pl->once_rows;
@@ -226,12 +233,9 @@ int make_plan(const codecomp_params* p, Plan* pl) {
 
   // workspace: per-chunk softmax statistics, merged row normalisers, raw attention mass
   const size_t LH = (size_t)pl->L * pl->Hkv;
-  const size_t lpad = (size_t)pl->row_splits * pl->row_blocks * 32;        // normaliser rows
   size_t off = 0;
-  // one statistics slot per segment and row split; slot numbers stay below (teams + problems) * row_splits
-  const size_t slots = (size_t)kMaxScoreGrid + LH * pl->row_splits * pl->n_seqs;
-  pl->off_stats = off; off = align256(off + slots * (pl->waves * kRowsPerWave) * 2 * sizeof(float));
-  pl->off_lse = off;   off = align256(off + LH * pl->n_seqs * lpad * sizeof(float));
+  pl->off_stats = off; off = align256(off + (size_t)stat_bytes);
+  pl->off_lse = off;   off = align256(off + (size_t)lse_bytes);
   pl->off_uraw = off;  off = align256(off + (size_t)pl->row_splits * LH * pl->T * sizeof(float));
   pl->off_member = off; off = align256(off + (size_t)pl->T);
   pl->off_member_count = off; off = align256(off + (size_t)pl->n_seqs * sizeof(int32_t));
@@ -253,10 +257,11 @@ int make_plan(const codecomp_params* p, Plan* pl) {
     pl->off_part_before = off; off = align256(off + LH * (size_t)parts * 2 * sizeof(int32_t));
   }
   pl->ws_bytes = off;
-  // Calls without two-pass requests keep no statistics: more mass arrays than row splits take their place as well.  They fit: problems *
-  // chunks <= kOnceFill and a problem has at most R + kOnceKeys tokens, so the arrays beyond the row splits hold 4 * kOnceFill *
-  // (R + kOnceKeys) * (1 - splits / chunks) bytes at most, which with chunks <= 1.5 * sqrt(R / 16) is below 5.9 MB (at R = 16384); the
-  // statistics have kMaxScoreGrid slots of 4 KB above 256 rows, and of 512 bytes per two blocks of 32 rows below.
+  // Calls without two-pass requests keep no statistics: more mass arrays than row splits take their place as well.  The number of chunks
+  // is bounded by what fits.  Without requests that have no key it always does: problems * chunks <= kOnceFill and a problem has at most
+  // R + kOnceKeys tokens, so the arrays beyond the row splits hold 4 * kOnceFill * (R + kOnceKeys) * (1 - splits / chunks) bytes at most,
+  // which with chunks <= 1.5 * sqrt(R / 16) is below 5.9 MB (at R = 16384); the statistics have kMaxScoreGrid slots of 4 KB above 256
+  // rows, and of 512 bytes per two blocks of 32 rows below.
   if (pl->mass_parts > pl->row_splits) pl->off_uraw = 0;
   return CODECOMP_OK;
 }

@@ -414,3 +414,16 @@ def test_mass_arrays_of_row_chunks_fit_where_the_statistics_would_be():
                 assert chunks * array <= before + splits * array, (rows, problems, n_seqs)
                 tightest = max(tightest, (chunks - splits) * array / before)
     assert 0.3 < tightest < 1.0
+
+
+@pytest.mark.parametrize("rows,empty", [(512, 1000), (512, 1500), (512, 60000), (256, 3000), (2048, 300), (16384, 40)])
+@pytest.mark.parametrize("kv_heads", [1, 3])
+def test_mass_arrays_fit_beside_requests_without_a_key(rows, empty, kv_heads):
+    """Requests that the softmax leaves without a key are no work, but each array of masses has a place for their tokens, too."""
+    p = packed([rows] * empty + [rows + 700], n_layers=1, n_q_heads=kv_heads, n_kv_heads=kv_heads, window=rows, score_variant=8)
+    route, chunks, _ = b.codecomp_score_route(p)
+    assert route[-1] == b.ROUTE_ONE_PASS or (rows > 1536 and kv_heads < 3)
+    _, splits, blocks, waves, _ = b.codecomp_score_layout(p)
+    problems, array = kv_heads * (empty + 1), 4 * kv_heads * (rows * (empty + 1) + 700)
+    before = (2048 + problems * splits) * waves * 64 * 8 + 4 * problems * splits * blocks * 32
+    assert chunks * array <= before + splits * array

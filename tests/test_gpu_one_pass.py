@@ -311,3 +311,30 @@ def test_short_requests_apart(heads, window, times, longer, variant, kv):
     ref = orc.score_packed(q[:1], k[:1], prior, w.cu_seqlens(), pool_kernel=w.pool_kernel, prior_weight=w.prior_weight,
                            k_format="fp8_e4m3" if kv == "fp8" else "bf16", **oracle_variant(variant))
     pu.assert_scores_close(one[:1], ref)
+
+
+@pytest.mark.parametrize("window,empty", [(512, 1500), (512, 40)])
+def test_row_chunks_beside_requests_without_a_key(window, empty):
+    """The last request alone has keys for the softmax: its chunks' arrays of masses, with a place for all tokens, stay inside the workspace."""
+    import torch
+    from paper_2604_10235_amd import binding as b
+    lens = [window] * empty + [window + 700]
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    dev = torch.from_numpy(cu).cuda()
+    g = torch.Generator(device="cuda").manual_seed(8)
+    q = torch.randn((1, len(lens), 1, window, 64), generator=g, device="cuda").bfloat16()
+    k = torch.randn((1, 1, sum(lens), 64), generator=g, device="cuda").bfloat16()
+    prior, got = torch.zeros(sum(lens), device="cuda"), []
+    for wgs in (0, 40):
+        p = b.make_params(n_layers=1, n_q_heads=1, n_kv_heads=1, head_dim=64, window=window, pool_kernel=5, prior_weight=0.0, cu_seqlens_host=cu,
+                          cu_budgets_host=cu, cu_seqlens_dev=dev.data_ptr(), cu_budgets_dev=dev.data_ptr(), score_variant=8, score_workgroups=wgs)
+        route = b.codecomp_score_route(p)[0]
+        assert (route[:-1] == ROUTE_TWO_PASSES).all() and route[-1] == (ROUTE_TWO_PASSES if wgs else ROUTE_ONE_PASS)
+        need = b.codecomp_workspace_bytes(p)
+        ws = torch.full((need + 65536,), 0x5A, dtype=torch.uint8, device="cuda")
+        ws[:need] = 0xFF
+        out = torch.full((1, 1, sum(lens)), float("nan"), device="cuda")
+        b.codecomp_score(q, k, prior, p, out, ws)
+        got.append(out.cpu().numpy())
+        assert bool((ws[need:] == 0x5A).all())
+    np.testing.assert_allclose(got[0], got[1], rtol=TWO_WAYS, atol=1e-30)
