@@ -63,7 +63,8 @@ def read_traffic(name: str):
 
 
 def two_pass_share(w, params, binding) -> float:
-    """Share of the logits that are formed twice, by the route that the library takes for each request (the others are formed once)."""
+    """Share of the logits that two passes form twice, by the route that the library takes for each request (the others are formed once;
+    so are these where teams of workgroups take them)."""
     route = binding.codecomp_score_route(params)[0]
     return sum(n for n, r in zip(w.seqlens, route) if r == binding.ROUTE_TWO_PASSES) / w.total_tokens
 
@@ -267,7 +268,7 @@ def main() -> int:
 
     # dominant stage: one of the two MFMA passes; its flops = 2 * R * sum(N_r) * d per (layer, KV head), for the row statistics
     # over the requests whose logits are formed twice
-    twice = two_pass_share(w, prob.params, binding)
+    twice = 0.0 if binding.codecomp_score_teams(prob.params) else two_pass_share(w, prob.params, binding)
     dom = max(("score_row_stats", "score_mass"), key=lambda n: stage_ms[n]) if twice > 0.0 else "score_mass"
     flops = 2.0 * w.group * w.window * T * w.head_dim * w.n_kv_heads * L
     flops_dom = flops if dom == "score_mass" else flops * twice

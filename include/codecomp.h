@@ -154,13 +154,22 @@ int codecomp_score_layout(const codecomp_params* params, int32_t* row_splits, in
                           int32_t* waves, uint32_t* wave_desc);
 
 /* Host-only: which kernels codecomp_score takes for these parameters: route[r] (array of n_seqs) per request, one of
- *   TWO_PASSES: row statistics, then attention mass (requests without a key for the softmax among them: nothing to do);
+ *   TWO_PASSES: more keys than a workgroup holds: row statistics, then attention mass (requests without a key for the softmax among
+ *               them: nothing to do), or both in one pass by teams of workgroups: see codecomp_score_teams;
  *   ONE_PASS  : a workgroup holds all keys of the request, every logit is formed once; its softmax rows are cut into row_chunks
  *               chunks, of which a workgroup takes chunks_in_turn one after the other;
  *   FEW_ROWS  : a workgroup holds all logits of the request.
  * For tests and reports.  Returns 0 or a CODECOMP_E* code; any output pointer may be NULL. */
 enum { CODECOMP_ROUTE_TWO_PASSES = 0, CODECOMP_ROUTE_ONE_PASS = 1, CODECOMP_ROUTE_FEW_ROWS = 2 };
 int codecomp_score_route(const codecomp_params* params, int32_t* route, int32_t* row_chunks, int32_t* chunks_in_turn);
+
+/* Host-only: *members = workgroups of the largest team where codecomp_score gives the TWO_PASSES requests of these parameters to teams
+ * (all of them or none), else 0.  A team holds all keys of a request and takes its softmax rows in step: every logit is formed once, but
+ * the members wait for one another, so the launch needs as many compute units (256 at most) to itself.  A device with fewer takes two
+ * passes.  Where other work on the device (a call on another stream, say) keeps members from starting, the waits end after 0.1 ms, and
+ * a kernel that waits for nobody does the work: the same bits, in a few times the time.  Programs that run calls side by side on several
+ * streams set codecomp_params.score_workgroups (to 256, say): such calls take two passes. */
+int codecomp_score_teams(const codecomp_params* params, int32_t* members);
 
 /* scores[l][h][j] = pooled_u[l][h][j] + lambda * prior[j], where u is the window attention mass
  * of the equation above averaged over the query-head group, and pooled_u its zero-padded
@@ -174,8 +183,8 @@ int codecomp_score(const void* q_obs, const void* k, const float* prior, const c
  * order row statistics -> row merge -> attention mass -> pool + prior.  Meant for per-kernel
  * timing and stage-wise debugging: a later stage reads what the earlier ones left in `workspace`,
  * so the stages of one problem must be enqueued in order with the same arguments.
- * Requests that codecomp_score_route does not give to TWO_PASSES have all of it done by CODECOMP_STAGE_MASS; the two stages before
- * leave them out, and they leave no row normalisers (nothing reads any).
+ * Requests that codecomp_score_route does not give to TWO_PASSES, and those of teams (codecomp_score_teams), have all of it done by
+ * CODECOMP_STAGE_MASS; the two stages before leave them out, and they leave no row normalisers (nothing reads any).
  * CODECOMP_STAGE_ALL is exactly codecomp_score, which in short calls does the row merge inside the mass kernel: there the
  * stages one by one differ from it by the regrouping of fp32 sums.  The row normalisers of two-pass requests are left in
  * `workspace` either way, so that a stage asked for again after codecomp_score (or after the first three stages in one

@@ -74,6 +74,8 @@ def lib() -> C.CDLL:
         IP = C.POINTER(C.c_int32)
         l.codecomp_score_route.restype = C.c_int
         l.codecomp_score_route.argtypes = [P, IP, IP, IP]
+        l.codecomp_score_teams.restype = C.c_int
+        l.codecomp_score_teams.argtypes = [P, IP]
         l.codecomp_score.restype = C.c_int
         l.codecomp_score.argtypes = [C.c_void_p, C.c_void_p, C.c_void_p, P, C.c_void_p, C.c_void_p, C.c_size_t,
                                      C.c_void_p]
@@ -157,6 +159,13 @@ def codecomp_score_route(params: codecomp_params):
     route, chunks, turn = (C.c_int32 * max(1, params.n_seqs))(), C.c_int32(0), C.c_int32(0)
     _check(lib().codecomp_score_route(C.byref(params), route, C.byref(chunks), C.byref(turn)), "codecomp_score_route")
     return np.ctypeslib.as_array(route).copy(), chunks.value, turn.value
+
+
+def codecomp_score_teams(params: codecomp_params) -> int:
+    """Workgroups of the largest team where the ROUTE_TWO_PASSES requests are given to teams, which form every logit once; else 0."""
+    members = C.c_int32(0)
+    _check(lib().codecomp_score_teams(C.byref(params), C.byref(members)), "codecomp_score_teams")
+    return members.value
 
 
 def codecomp_workspace_bytes(params: codecomp_params) -> int:

@@ -69,6 +69,87 @@ static bool rows_quicker(int blocks, int d, bool fp8, int64_t problems, int64_t 
   return rows < passes;
 }
 
+// Are the teams quicker than the two passes, for requests that are all beyond one workgroup?  Estimates in us, without what both need:
+// a round takes its start and a time per pair of row blocks, however few of the 256 workgroups are in it; the passes take a time per key
+// and pair, and one per key.  Measured, scores, 4 KV heads of 7 query heads, window 64 (448 rows), passes -> teams: 28 x 32K keys 873 ->
+// 689 us (8-bit keys 815 -> 660), 28 x 20011 581 -> 449, 4 x 20011 96 -> 85, 16 x 8192 150 -> 120, 4 x 8192 58 -> 49, sixteen of 8K ..
+// 48K 549 -> 477; 896 rows: 28 x 32K 1648 -> 1187, 28 x 5000 276 -> 237, 8 x 64K 948 -> 761; 8 KV heads, 256 rows: 8 x 64K 639 -> 563,
+// 28 x 16K 558 -> 472; 224 rows: 4 x 32K 89 -> 73.  Not taken, passes / teams: 1 x 8192 32 / 42, 1 x 16384 42 / 42, 2 x 20000 700 rows
+// 86 / 88 (rounds that are nearly empty), 8 x 49152 398 / 398 (192 of 256 workgroups in a round), 28 x 50000 224 rows 803 / 848.
+static bool teams_quicker(int rounds, int pairs, int most, bool fp8, float keys) {
+  const float teams = 4.0f + (float)rounds * (5.1f + (most <= 64 ? 1.27f : 1.35f) * (float)pairs);
+  const float passes = keys / (256.0f * 512.0f) * (4.5f + 1.85f * (float)pairs) * (fp8 ? 0.93f : 1.0f);
+  return teams < passes;
+}
+
+// Rounds of teams for the requests beyond one workgroup: a request takes as many members as its keys need, all problems the same time
+// (they have the same rows), so a round is filled with teams, the largest first, and repeated while they last.
+static void schedule_teams(const codecomp_params* p, const Plan& pl, int64_t room, TeamSchedule* ts) {
+  constexpr int nt = kTeamTiles;
+  ts->steps = 0;
+  const int LH = pl.L * pl.Hkv;
+  struct Kind { int seq, chunks, left, next; } kind[kTeamEntries];
+  int kinds = 0;
+  int64_t keys = 0;
+  for (int r = 0; r < pl.n_seqs; ++r) {
+    const int n = p->cu_seqlens_host[r + 1] - p->cu_seqlens_host[r] - pl.key_trim;
+    if (n <= pl.once_keys) return;
+    keys += n;
+    const int tiles = (n + 15) / 16, chunks = (tiles + 8 * nt - 1) / (8 * nt);
+    // waves hold nt tiles or one less, the last wave of the last member nt: only a wave's tile nt - 1 may have places without a key
+    if (chunks > kTeamMost || kinds == kTeamEntries || tiles / chunks <= 8 * (nt - 1)) return;
+    int at = kinds++;
+    for (; at > 0 && kind[at - 1].chunks < chunks; --at) kind[at] = kind[at - 1];
+    kind[at] = {r, chunks, LH, 0};
+  }
+  struct Step { int rounds, used, first, count; } step[kTeamSteps];
+  uint32_t entry[kTeamEntries][2];
+  int steps = 0, entries = 0;
+  for (;;) {
+    Step s = {0, 0, entries, 0};
+    for (int i = 0; i < kinds; ++i) {
+      const int teams = kind[i].left < (kTeamMembers - s.used) / kind[i].chunks ? kind[i].left : (kTeamMembers - s.used) / kind[i].chunks;
+      if (teams == 0) continue;
+      if (entries == kTeamEntries) return;
+      entry[entries][0] = (uint32_t)kind[i].seq | (uint32_t)teams << 16;
+      entry[entries][1] = (uint32_t)kind[i].next | (uint32_t)kind[i].chunks << 16;
+      ++entries; ++s.count;
+      s.used += teams * kind[i].chunks;
+      const int rounds = kind[i].left / teams;
+      if (s.rounds == 0 || rounds < s.rounds) s.rounds = rounds;
+    }
+    if (s.count == 0) break;
+    if (steps == kTeamSteps) return;
+    for (int e = s.first, i = 0; e < entries; ++i)
+      if ((int)(entry[e][0] & 0xFFFFu) == kind[i].seq) {
+        const int done = (int)(entry[e][0] >> 16) * s.rounds;
+        kind[i].left -= done; kind[i].next += done;
+        ++e;
+      }
+    step[steps++] = s;
+  }
+  // fullest rounds first: a workgroup that has nothing to do in a round is through
+  for (int i = 1; i < steps; ++i)
+    for (int j = i; j > 0 && step[j - 1].used < step[j].used; --j) { const Step t = step[j]; step[j] = step[j - 1]; step[j - 1] = t; }
+  int rounds = 0, n = 0;
+  ts->most = kind[0].chunks;
+  for (int i = 0; i < steps; ++i) {
+    rounds += step[i].rounds;
+    ts->step[i] = (uint32_t)step[i].rounds | (uint32_t)n << 16;
+    for (int e = 0; e < step[i].count; ++e, ++n) { ts->entry[n][0] = entry[step[i].first + e][0]; ts->entry[n][1] = entry[step[i].first + e][1]; }
+  }
+  ts->step[steps] = (uint32_t)n << 16;
+  ts->members = (step[0].used + 7) / 8 * 8;
+  const int pairs = (pl.R + 31) / 32;
+  ts->ring = kinds == 1;
+  ts->line_pairs = ts->ring ? 16 : rounds * pairs;
+  const int64_t counters = (int64_t)LH * pl.n_seqs * 5 * (int64_t)sizeof(uint32_t), per_problem = (int64_t)pairs * ts->most * 128;
+  ts->done_at = (room - counters) & ~(int64_t)255;
+  if (room < counters || rounds > 0xFFFF || ts->done_at < (int64_t)ts->line_pairs * ts->members * 128 || ts->done_at < per_problem) return;
+  ts->slots = (int)(ts->done_at / per_problem < LH * (int64_t)pl.n_seqs ? ts->done_at / per_problem : LH * (int64_t)pl.n_seqs);
+  if (teams_quicker(rounds, pairs, ts->most, pl.kv_fp8, (float)(keys * LH))) ts->steps = steps;
+}
+
 int make_plan(const codecomp_params* p, Plan* pl) {
   if (!p) return CODECOMP_EINVAL_NULL;
   if (p->n_layers < 1 || p->n_seqs < 1 || p->n_seqs > 65535) return CODECOMP_EINVAL_SHAPE;
@@ -257,6 +338,12 @@ int make_plan(const codecomp_params* p, Plan* pl) {
     pl->off_part_before = off; off = align256(off + LH * (size_t)parts * 2 * sizeof(int32_t));
   }
   pl->ws_bytes = off;
+  pl->team.steps = 0;
+  if (own_rules && !once && !pl->rows_at_once && pl->R >= 192 && pl->R <= kTeamRows && pl->d == 128 &&
+      (once_short + once_long) == 0 && LH64 * pl->n_seqs <= 65535 &&
+      (int64_t)max_n * pl->kv_st * (pl->kv_fp8 ? 1 : 2) <= 0xFFFFFFFFll - 4096 &&
+      ((int64_t)(pl->G - 1) * pl->q_sh + (int64_t)(pl->W - 1) * pl->q_st) / 8 <= 0xFFFF)
+    schedule_teams(p, *pl, (int64_t)(pl->off_lse - pl->off_stats), &pl->team);
   // Calls without two-pass requests keep no statistics: more mass arrays than row splits take their place as well.  The number of chunks
   // is bounded by what fits.  Without requests that have no key it always does: problems * chunks <= kOnceFill and a problem has at most
   // R + kOnceKeys tokens, so the arrays beyond the row splits hold 4 * kOnceFill * (R + kOnceKeys) * (1 - splits / chunks) bytes at most,
@@ -327,6 +414,13 @@ int codecomp_score_route(const codecomp_params* params, int32_t* route, int32_t*
   }
   if (row_chunks) *row_chunks = pl.once_keys > 0 ? pl.once_chunks : 0;
   if (chunks_in_turn) *chunks_in_turn = pl.once_keys > 0 ? pl.once_group : 0;
+  return CODECOMP_OK;
+}
+
+int codecomp_score_teams(const codecomp_params* params, int32_t* members) {
+  Plan pl;
+  if (int rc = make_plan(params, &pl)) return rc;
+  if (members) *members = pl.team.steps > 0 ? pl.team.most : 0;
   return CODECOMP_OK;
 }
 

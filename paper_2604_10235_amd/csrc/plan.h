@@ -56,6 +56,24 @@ constexpr float kOnceReload = 0.16f;
 // 100 and one of 4096 27 -> 45.
 constexpr int kRowsMost = 64, kRowsProblems = 96;
 constexpr int rows_tiles(int blocks) { return blocks == 1 ? 32 : blocks == 2 ? 20 : blocks == 3 ? 12 : 8; }
+// Long requests in one pass, by teams of workgroups (score_team.h).
+constexpr int kTeamMembers = 256;     // workgroups of a launch, each with a compute unit of its own
+// Most members of a team.  In every pair of row blocks each reads the sums of all, past its own L2: with 256 members that bounds it (4 x
+// 100000 keys, 896 rows 926 us, by two passes 723; 8 x 128K, 256 rows 1373 and 1265).
+constexpr int kTeamMost = 128;
+constexpr int kTeamTiles = 4;         // tiles of 16 keys per wave
+constexpr int kTeamRows = 1024;       // most query rows
+constexpr int kTeamSteps = 48, kTeamEntries = 96;          // rounds that are alike, groups of teams in them
+struct TeamSchedule {
+  int steps;                          // 0: not taken
+  int members, most;                  // workgroups; members of the largest team
+  int ring;                           // 1: teams stay the same, the places of sums are used in turn
+  int line_pairs;                     // places, in pairs of row blocks
+  int slots;                          // problems whose sums have a place at a time when the work has to be done again
+  int64_t done_at;                    // counters of that, in bytes from the places
+  uint32_t step[kTeamSteps + 1];      // rounds | first entry << 16
+  uint32_t entry[kTeamEntries][2];    // request | teams << 16, first (layer, head) | members of a team << 16
+};
 constexpr int kMaxScoreGrid = 2048;   // most workgroups a score pass is launched with
 constexpr int kLeadTiles = 4;         // a segment start (query fragments, first K tile) costs about this many tiles
 // Calls of up to this many (tile, row split) pairs get no leads: a workgroup then has one tile or two and nearly all of them start
@@ -117,6 +135,7 @@ struct Plan {
   int once_rows, once_chunks;            // query rows of a chunk, chunks
   int once_group;            // chunks that one workgroup takes in turn
   int mass_parts;            // arrays of raw attention mass that add up: row splits, or chunks where every request takes one pass
+  TeamSchedule team;         // requests beyond one workgroup, in one pass
   int grid_override;         // > 0: the caller fixed the number of workgroups of the score passes
   int lead_tiles;            // empty positions before each request's tiles in the sequence below: the cost of starting a segment
   int tiles_per_problem;     // sum over requests of (lead_tiles + ceil(N_r / kTileKeys)): positions of one (layer, head)

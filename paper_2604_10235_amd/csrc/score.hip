@@ -1,7 +1,7 @@
 // Score step, small kernels and entry: row merge between the two MFMA passes, pooling + prior, and the
 // launch sequence.  The passes themselves live in score_pass.h and are instantiated per (head_dim, key
 // type) in score_pass_*.hip.
-#include "score_once.h"
+#include "score_team.h"
 
 namespace codecomp {
 
@@ -9,6 +9,10 @@ extern template int dispatch_waves<128, false>(const Plan&, const ScoreArgs&, hi
 extern template int dispatch_waves<128, true>(const Plan&, const ScoreArgs&, hipStream_t, unsigned);
 extern template int dispatch_waves<64, false>(const Plan&, const ScoreArgs&, hipStream_t, unsigned);
 extern template int dispatch_waves<64, true>(const Plan&, const ScoreArgs&, hipStream_t, unsigned);
+extern template int launch_team<128, false>(const Plan&, const ScoreArgs&, char*, hipStream_t);
+extern template int launch_team<128, true>(const Plan&, const ScoreArgs&, char*, hipStream_t);
+extern template bool team_fits<128, false>(const Plan&);
+extern template bool team_fits<128, true>(const Plan&);
 extern template int launch_once<128, false>(const Plan&, const ScoreArgs&, hipStream_t);
 extern template int launch_rows<128, false>(const Plan&, const ScoreArgs&, hipStream_t);
 extern template int launch_once<128, true>(const Plan&, const ScoreArgs&, hipStream_t);
@@ -264,7 +268,9 @@ int launch_score(const Plan& pl, const void* q, const void* k, const float* prio
   a.once_keys = pl.once_keys; a.once_rows = pl.once_rows; a.once_chunks = pl.once_chunks;
   a.blocks_per_head = (pl.variant & CODECOMP_VARIANT_GROUP_MAX) ? pl.W / 32 : 1;
   int rc;
-  if (pl.kv_fp8) rc = pl.d == 128 ? dispatch_waves<128, true>(pl, a, stream, stages) : dispatch_waves<64, true>(pl, a, stream, stages);
+  if (pl.team.steps > 0 && (pl.kv_fp8 ? team_fits<128, true>(pl) : team_fits<128, false>(pl))) {
+    rc = !(stages & CODECOMP_STAGE_MASS) ? 0 : pl.kv_fp8 ? launch_team<128, true>(pl, a, ws, stream) : launch_team<128, false>(pl, a, ws, stream);
+  } else if (pl.kv_fp8) rc = pl.d == 128 ? dispatch_waves<128, true>(pl, a, stream, stages) : dispatch_waves<64, true>(pl, a, stream, stages);
   else rc = pl.d == 128 ? dispatch_waves<128, false>(pl, a, stream, stages) : dispatch_waves<64, false>(pl, a, stream, stages);
   if (rc) return rc;
   if ((stages & CODECOMP_STAGE_MASS) && pl.rows_at_once) {

@@ -1,0 +1,7 @@
+// Long requests in one pass by teams (see score_team.h): head_dim 128, bf16 keys.
+#include "score_team.h"
+
+namespace codecomp {
+template bool team_fits<128, false>(const Plan&);
+template int launch_team<128, false>(const Plan&, const ScoreArgs&, char*, hipStream_t);
+}
