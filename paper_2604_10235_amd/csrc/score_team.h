@@ -207,14 +207,17 @@ __global__ __launch_bounds__(512, 2) void score_team_kernel(TeamKernelArgs args)
     return key * key_bytes + (uint32_t)(grp * 16);
   };
   auto stage = [&](int u) __attribute__((always_inline)) {             // unit u of this wave's keys
-    // of four pieces, 0 and 2, 1 and 3: what is loaded when the problem begins (the last unit) then lies in cache lines that have come already
-    constexpr int APART = PER == 4 ? 128 : 64;
+    // A unit is a cache line of each key, so that the pairs ask alike of memory (with a half of both lines at a time, every second pair
+    // asked for everything: 8 x 64K keys, 256 rows 544 us, now 526); but of a tile that is not all in LDS the first half of both lines is
+    // there, and what is loaded when the problem begins is found in the cache.
     const int i = u * UNIT;
-    const unsigned char* from = keys.from + (PER == 4 ? (u & 1) * 64 : UNIT == 2 ? 0 : (i & (PER - 1)) * 64);
+    const bool parted = PER == 4 && STAGED % PER != 0 && i >= STAGED / PER * PER;
+    const int apart = parted ? 128 : 64;
+    const unsigned char* from = keys.from + (PER == 4 ? (u & 1) * (parted ? 64 : 128) : UNIT == 2 ? 0 : (i & (PER - 1)) * 64);
     const uint32_t at = key_at(i), to = k_to + (uint32_t)i * 1024u;
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(to), "v"(at), "s"(from) : "memory", "m0");
     if constexpr (UNIT == 2)
-      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(to + 1024u), "v"(at), "s"(from + APART) : "memory", "m0");
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(to + 1024u), "v"(at), "s"(from + apart) : "memory", "m0");
   };
   const uint32_t q_to = lds_address(&sh.q[0][0][0][0]) + (uint32_t)wave * 1024u;
   const uint32_t ref_to = lds_address(&sh.ref[0][0]);
@@ -255,7 +258,7 @@ __global__ __launch_bounds__(512, 2) void score_team_kernel(TeamKernelArgs args)
         const unsigned char* piece = reinterpret_cast<const unsigned char*>(&sh.k[wave][t * PER + ks / 2][0]);
         kf[t][ks] = to_bf16x8(*reinterpret_cast<const u32x2*>(piece + (((ks & 1) * 2 + (grp >> 1)) * 16 + l16) * 16 + (grp & 1) * 8));
       } else {
-        const int i = t * PER + (PER == 4 ? (ks & 1) * 2 + (ks >> 1) : ks);
+        const int i = t * PER + (PER == 4 && t * PER + PER > STAGED ? (ks & 1) * 2 + (ks >> 1) : ks);
         kf[t][ks] = i < STAGED ? sh.k[wave][i < STAGED ? i : 0][lane] : *reinterpret_cast<const u32x4*>(keys.from + key_at(i) + ks * 64);
         if (i >= STAGED) pin(kf[t][ks]);               // waited for here: left to its use, every pair would wait for all loads there
       }
@@ -295,8 +298,7 @@ __global__ __launch_bounds__(512, 2) void score_team_kernel(TeamKernelArgs args)
   int fpair = 2;                                       // pair of its problem that is sent for next
   bool more = true;                                    // there is one
   keys = keys_of(nxt);
-  int staged = nxt.valid ? 0 : UNITS;                  // units of the next problem's keys that are on their way
-  const bool slowly = pairs - 2 >= UNITS;              // one in a pair, or two: spread out, all compute units load at once
+  int staged = nxt.valid ? 0 : UNITS;                  // units of the next problem's keys that are on their way: one in a pair, two where too few are left before the last
   int on_way = 0;                                      // ... sent for in this pair
   int ask_lines = 0, ask_rows = 0;                     // members whose sums are collected; rows of that pair and the later ones of its problem, 0: no such pair
   const char* ask_from = reinterpret_cast<const char*>(args.t.lines);
@@ -453,7 +455,7 @@ __global__ __launch_bounds__(512, 2) void score_team_kernel(TeamKernelArgs args)
       if (staged < UNITS) {
         stage(staged++);
         on_way = UNIT;
-        if (!slowly) { stage(min(staged++, UNITS - 1)); on_way = 2 * UNIT; }
+        if (UNITS - staged > cur_start + pairs - 2 - q) { stage(staged++); on_way = 2 * UNIT; }
       }
     }
 #pragma unroll
@@ -465,7 +467,7 @@ __global__ __launch_bounds__(512, 2) void score_team_kernel(TeamKernelArgs args)
           if (on_way == 0) {
             if (publisher) asm volatile("s_waitcnt vmcnt(3)" ::: "memory");
             else asm volatile("s_waitcnt vmcnt(1)" ::: "memory");
-          } else if (slowly) {
+          } else if (on_way == UNIT) {
             if (publisher) asm volatile("s_waitcnt vmcnt(%0)" ::"i"(3 + UNIT) : "memory");
             else asm volatile("s_waitcnt vmcnt(%0)" ::"i"(1 + UNIT) : "memory");
           } else {
