@@ -58,8 +58,8 @@ constexpr int kRowsMost = 64, kRowsProblems = 96;
 constexpr int rows_tiles(int blocks) { return blocks == 1 ? 32 : blocks == 2 ? 20 : blocks == 3 ? 12 : 8; }
 // Long requests in one pass, by teams of workgroups (score_team.h).
 constexpr int kTeamMembers = 256;     // workgroups of a launch, each with a compute unit of its own
-// Most members of a team.  In every pair of row blocks each reads the sums of all, past its own L2: with 256 members that bounds it (4 x
-// 100000 keys, 896 rows 926 us, by two passes 723; 8 x 128K, 256 rows 1373 and 1265).
+// Most members of a team.  In every pair of row blocks each waits for the sums of all and adds them up: with 256 members a pair takes 1.87
+// us instead of 1.3 (4 x 100000 keys, 896 rows 926 us, by two passes 723; 8 x 128K, 256 rows 1373 and 1265).
 constexpr int kTeamMost = 128;
 constexpr int kTeamTiles = 4;         // tiles of 16 keys per wave
 constexpr int kTeamRows = 1024;       // most query rows

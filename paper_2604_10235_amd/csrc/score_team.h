@@ -13,12 +13,12 @@
 // arithmetic, bit for bit, without any wait for a workgroup that might not run: it hands out its tasks in an order in which a task
 // only waits for tasks handed out before it.
 //
-// What bounds it: instructions issued.  Two waves on a SIMD take 32 rows and their 64 keys each in 1.25 .. 1.3 us, about 4.1 cycles an
-// instruction (32 MFMAs, 32 exponentials, and 32 each of scaling, summing and weighing to a wave, and 60 for everything else); the two
-// passes take 1.85 us for the same and 0.32 us a key more per problem.  Why this split: the sums of a pair of row blocks need 1.4 (32
+// What bounds it: instructions issued.  Two waves on a SIMD take 32 rows and their 64 keys each in 1.25 .. 1.3 us (32 MFMAs, 32
+// exponentials, and 32 each of scaling, summing and weighing to a wave, and 60 for everything else: the VALU is busy 55 % of the time, the
+// matrix cores 28 %); the two passes take 1.85 us for the same.  Why this split: the sums of a pair of row blocks need 1.4 (32
 // members) .. 1.7 us (256) from the first store to the last load, so the exponentials of three pairs wait in registers: 96 of them, beside
-// 64 of keys, which leaves 4 tiles of 16 keys to a wave and one workgroup to a compute unit.  A round costs 5 us beyond its pairs: keys of
-// the next problem go to LDS meanwhile, but all waves take them up at once, and the pipeline of three pairs drains into the next one.
+// 64 of keys, which leaves 4 tiles of 16 keys to a wave and one workgroup to a compute unit.  A round costs 5 us beyond its pairs (the two
+// passes: 4.5): half of it while the next problem's keys are on their way to LDS, the rest where all waves take them up at once.
 // Workgroups wait for counts in LDS, not at barriers: with a barrier in each block the slowest wave of every block was waited for.
 // Measured, scores of 28 layers, 4 KV heads of 7 query heads, window 64, 32K keys: two passes 873 us, teams 689; 1 layer 54 and 44; window
 // 128 1648 and 1187; 8-bit keys 815 and 660.  Error against 64 bits 7e-8 (2-norm), by two passes 3.4e-7.
