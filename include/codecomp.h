@@ -87,7 +87,7 @@ typedef struct codecomp_params {
    * floor(span_budget_ratio * Bp))) with Bp = B_r - W; the paper uses a ratio of 0.5 */
   float span_budget_ratio;     /* rho_span in [0, 1]                                              */
   int32_t span_budget_min;     /* B_min >= 0                                                      */
-  int32_t score_variant;       /* bit flags CODECOMP_VARIANT_*; 0 = the default readings          */
+  int32_t score_variant;       /* bit flags CODECOMP_VARIANT_*; 0 = the default readings and routes */
   int32_t kv_dtype;            /* CODECOMP_KV_BF16 (0) or CODECOMP_KV_FP8_E4M3 (1): element type of k, v, k_out, v_out */
   /* How the two logit passes of codecomp_score are cut into workgroups; the results do not depend on either
    * value beyond the regrouping of fp32 sums (for tests of exactly that, and for tuning).  Leave both 0. */
@@ -107,13 +107,17 @@ typedef struct codecomp_params {
  *   SOFTMAX_PREFIX the softmax runs over the N - W context keys only (the K with one row per context token of the
  *                  section); window positions get no attention mass;
  *   POOL_PREFIX    pooling stays inside the N - W context positions; window positions get none.
- * GROUP_SUM and GROUP_MAX exclude each other.  Unknown bits are rejected (CODECOMP_EINVAL_MODE). */
+ * GROUP_SUM and GROUP_MAX exclude each other.  Unknown bits are rejected (CODECOMP_EINVAL_MODE).
+ * One more bit chooses no reading but kernels (the scores differ by the regrouping of fp32 sums):
+ *   NO_TEAMS       no request is given to teams of workgroups (codecomp_score_teams); all other routes stay as they are.  For programs
+ *                  whose calls share the device with other work, and for callers that want the row normalisers of long requests. */
 enum {
   CODECOMP_VARIANT_GROUP_SUM = 1,
   CODECOMP_VARIANT_GROUP_MAX = 2,
   CODECOMP_VARIANT_POOL_MAX = 4,
   CODECOMP_VARIANT_SOFTMAX_PREFIX = 8,
-  CODECOMP_VARIANT_POOL_PREFIX = 16
+  CODECOMP_VARIANT_POOL_PREFIX = 16,
+  CODECOMP_VARIANT_NO_TEAMS = 256
 };
 
 /* Storage type of the KV cache (k, v and the compact k_out, v_out; q_obs is always bf16).  Not from the paper,
@@ -167,8 +171,8 @@ int codecomp_score_route(const codecomp_params* params, int32_t* route, int32_t*
  * (all of them or none), else 0.  A team holds all keys of a request and takes its softmax rows in step: every logit is formed once, but
  * the members wait for one another, so the launch needs as many compute units (256 at most) to itself.  A device with fewer takes two
  * passes.  Where other work on the device (a call on another stream, say) keeps members from starting, the waits end after 0.1 ms, and
- * a kernel that waits for nobody does the work: the same bits, in a few times the time.  Programs that run calls side by side on several
- * streams set codecomp_params.score_workgroups (to 256, say): such calls take two passes. */
+ * a kernel that waits for nobody does the work: the same bits, in a few times the time.  Programs that run calls beside other work set
+ * CODECOMP_VARIANT_NO_TEAMS: such calls take two passes. */
 int codecomp_score_teams(const codecomp_params* params, int32_t* members);
 
 /* scores[l][h][j] = pooled_u[l][h][j] + lambda * prior[j], where u is the window attention mass

@@ -158,7 +158,7 @@ int make_plan(const codecomp_params* p, Plan* pl) {
       (!(p->span_budget_ratio >= 0.0f) || !(p->span_budget_ratio <= 1.0f) || p->span_budget_min < 0))
     return CODECOMP_EINVAL_MODE;
   constexpr int kKnownVariants = CODECOMP_VARIANT_GROUP_SUM | CODECOMP_VARIANT_GROUP_MAX | CODECOMP_VARIANT_POOL_MAX |
-                                 CODECOMP_VARIANT_SOFTMAX_PREFIX | CODECOMP_VARIANT_POOL_PREFIX;
+                                 CODECOMP_VARIANT_SOFTMAX_PREFIX | CODECOMP_VARIANT_POOL_PREFIX | CODECOMP_VARIANT_NO_TEAMS;
   if ((p->score_variant & ~kKnownVariants) != 0) return CODECOMP_EINVAL_MODE;
   if (p->kv_dtype != CODECOMP_KV_BF16 && p->kv_dtype != CODECOMP_KV_FP8_E4M3) return CODECOMP_EINVAL_MODE;
   if ((p->score_variant & CODECOMP_VARIANT_GROUP_SUM) && (p->score_variant & CODECOMP_VARIANT_GROUP_MAX)) return CODECOMP_EINVAL_MODE;
@@ -339,7 +339,7 @@ int make_plan(const codecomp_params* p, Plan* pl) {
   }
   pl->ws_bytes = off;
   pl->team.steps = 0;
-  if (own_rules && !once && !pl->rows_at_once && pl->R >= 192 && pl->R <= kTeamRows && pl->d == 128 &&
+  if (own_rules && !(pl->variant & CODECOMP_VARIANT_NO_TEAMS) && !once && !pl->rows_at_once && pl->R >= 192 && pl->R <= kTeamRows && pl->d == 128 &&
       (once_short + once_long) == 0 && LH64 * pl->n_seqs <= 65535 &&
       (int64_t)max_n * pl->kv_st * (pl->kv_fp8 ? 1 : 2) <= 0xFFFFFFFFll - 4096 &&
       ((int64_t)(pl->G - 1) * pl->q_sh + (int64_t)(pl->W - 1) * pl->q_st) / 8 <= 0xFFFF)

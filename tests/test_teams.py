@@ -42,6 +42,46 @@ def test_which_calls_are_given_to_teams():
     assert members([32768], q_stride_tok=8 * 1038, **far) == 64 and members([32768], q_stride_tok=8 * 1039, **far) == 0
 
 
+# A program whose calls share the device refuses teams, and nothing else: what one workgroup or a few rows take stays where it is.
+def test_teams_refused_by_the_caller():
+    def routes(lens, layers, window=64, heads=(28, 4), **over):
+        cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+        p = b.make_params(n_layers=layers, n_q_heads=heads[0], n_kv_heads=heads[1], head_dim=128, window=window, pool_kernel=7, prior_weight=1.0, cu_seqlens_host=cu,
+                          cu_budgets_host=np.arange(len(lens) + 1, dtype=np.int32) * window, cu_seqlens_dev=0x1000, cu_budgets_dev=0x2000, **over)
+        route, chunks, turn = b.codecomp_score_route(p)
+        return list(route), chunks, turn, b.codecomp_workspace_bytes(p)
+    for lens, layers, window, heads, kind in (([32768], 28, 64, (28, 4), b.ROUTE_TWO_PASSES), ([700] * 8, 4, 64, (28, 4), b.ROUTE_ONE_PASS),
+                                              ([300, 2000] * 64, 8, 64, (28, 4), b.ROUTE_ONE_PASS), ([2000], 64, 16, (4, 4), b.ROUTE_FEW_ROWS)):
+        default = routes(lens, layers, window, heads)
+        assert kind in default[0] and routes(lens, layers, window, heads, score_variant=b.VARIANT_NO_TEAMS) == default
+    def members(**over):
+        p = problem([32768], layers=28)
+        cu, cb = p.cu_seqlens(), p.cu_budgets()
+        return b.codecomp_score_teams(b.make_params(n_layers=28, n_q_heads=28, n_kv_heads=4, head_dim=128, window=64, pool_kernel=7, prior_weight=1.0, cu_seqlens_host=cu,
+                                                    cu_budgets_host=cb, cu_seqlens_dev=0x1000, cu_budgets_dev=0x2000, **over))
+    assert members() == 64 and members(score_variant=1 | 4 | 8 | 16) > 0
+    assert members(score_variant=b.VARIANT_NO_TEAMS) == 0 and members(score_variant=b.VARIANT_NO_TEAMS | 1 | 4 | 8 | 16) == 0
+
+
+@pytest.mark.gpu
+def test_teams_refused_take_two_passes():
+    import torch
+    w = problem([20011, 2000], layers=4)
+    q, k, v, prior = data = inputs(w)
+    p = b.DeviceProblem(w, *data, score_variant=b.VARIANT_NO_TEAMS)
+    p.score()
+    one = p.scores.cpu().numpy()
+    pu.assert_scores_close(one[-1:], orc.score_packed(q[-1:], k[-1:], prior, w.cu_seqlens(), pool_kernel=w.pool_kernel, prior_weight=w.prior_weight))
+    # the row normalisers are there: the mass kernel alone gives the same bits again
+    b.codecomp_score_stages(p.q, p.k, p.prior, p.params, p.scores, p.workspace, 1 | 2 | 4)
+    p.scores.fill_(float("nan"))
+    b.codecomp_score_stages(p.q, p.k, p.prior, p.params, p.scores, p.workspace, 4 | 8)
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(one.view(np.int32), p.scores.cpu().numpy().view(np.int32))
+    teams = scores(w, data, 0).scores.cpu().numpy()
+    np.testing.assert_allclose(one, teams, rtol=TWO_WAYS, atol=1e-30)
+
+
 def scores(w, data, wgs, **over):
     import torch
     p = b.DeviceProblem(w, *data, score_workgroups=wgs, **over)
