@@ -108,16 +108,20 @@ typedef struct codecomp_params {
  *                  section); window positions get no attention mass;
  *   POOL_PREFIX    pooling stays inside the N - W context positions; window positions get none.
  * GROUP_SUM and GROUP_MAX exclude each other.  Unknown bits are rejected (CODECOMP_EINVAL_MODE).
- * One more bit chooses no reading but kernels (the scores differ by the regrouping of fp32 sums):
+ * Two more bits choose no reading but kernels:
  *   NO_TEAMS       no request is given to teams of workgroups (codecomp_score_teams); all other routes stay as they are.  For programs
- *                  whose calls share the device with other work, and for callers that want the row normalisers of long requests. */
+ *                  whose calls share the device with other work, and for callers that want the row normalisers of long requests.  The scores differ by the regrouping of fp32 sums.
+ *   TEAMS_APART    what would be given to teams is done by the kernel that steps in where their members can not run: the same bits in
+ *                  more time.  For tests.
+ * NO_TEAMS and TEAMS_APART exclude each other. */
 enum {
   CODECOMP_VARIANT_GROUP_SUM = 1,
   CODECOMP_VARIANT_GROUP_MAX = 2,
   CODECOMP_VARIANT_POOL_MAX = 4,
   CODECOMP_VARIANT_SOFTMAX_PREFIX = 8,
   CODECOMP_VARIANT_POOL_PREFIX = 16,
-  CODECOMP_VARIANT_NO_TEAMS = 256
+  CODECOMP_VARIANT_NO_TEAMS = 256,
+  CODECOMP_VARIANT_TEAMS_APART = 512
 };
 
 /* Storage type of the KV cache (k, v and the compact k_out, v_out; q_obs is always bf16).  Not from the paper,

@@ -193,7 +193,7 @@ def codecomp_score(q_obs, k, prior, params, scores, workspace) -> None:
 
 STAGE_ROW_STATS, STAGE_ROW_MERGE, STAGE_MASS, STAGE_FINISH, STAGE_ALL = 1, 2, 4, 8, 15
 VARIANT_GROUP_SUM, VARIANT_GROUP_MAX, VARIANT_POOL_MAX, VARIANT_SOFTMAX_PREFIX, VARIANT_POOL_PREFIX = 1, 2, 4, 8, 16
-VARIANT_NO_TEAMS = 256
+VARIANT_NO_TEAMS, VARIANT_TEAMS_APART = 256, 512
 KV_BF16, KV_FP8_E4M3 = 0, 1
 
 

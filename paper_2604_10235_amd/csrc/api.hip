@@ -158,10 +158,12 @@ int make_plan(const codecomp_params* p, Plan* pl) {
       (!(p->span_budget_ratio >= 0.0f) || !(p->span_budget_ratio <= 1.0f) || p->span_budget_min < 0))
     return CODECOMP_EINVAL_MODE;
   constexpr int kKnownVariants = CODECOMP_VARIANT_GROUP_SUM | CODECOMP_VARIANT_GROUP_MAX | CODECOMP_VARIANT_POOL_MAX |
-                                 CODECOMP_VARIANT_SOFTMAX_PREFIX | CODECOMP_VARIANT_POOL_PREFIX | CODECOMP_VARIANT_NO_TEAMS;
+                                 CODECOMP_VARIANT_SOFTMAX_PREFIX | CODECOMP_VARIANT_POOL_PREFIX | CODECOMP_VARIANT_NO_TEAMS |
+                                 CODECOMP_VARIANT_TEAMS_APART;
   if ((p->score_variant & ~kKnownVariants) != 0) return CODECOMP_EINVAL_MODE;
   if (p->kv_dtype != CODECOMP_KV_BF16 && p->kv_dtype != CODECOMP_KV_FP8_E4M3) return CODECOMP_EINVAL_MODE;
   if ((p->score_variant & CODECOMP_VARIANT_GROUP_SUM) && (p->score_variant & CODECOMP_VARIANT_GROUP_MAX)) return CODECOMP_EINVAL_MODE;
+  if ((p->score_variant & CODECOMP_VARIANT_NO_TEAMS) && (p->score_variant & CODECOMP_VARIANT_TEAMS_APART)) return CODECOMP_EINVAL_MODE;
   if ((int64_t)p->n_layers * p->n_kv_heads > 65535) return CODECOMP_EINVAL_SHAPE;   // one grid axis
   if (p->n_kv_heads < 1 || p->n_q_heads < 1 || p->n_q_heads % p->n_kv_heads != 0) return CODECOMP_EINVAL_HEADS;
   if (p->head_dim != 64 && p->head_dim != 128) return CODECOMP_EINVAL_HEADDIM;

@@ -43,6 +43,7 @@ struct TeamArgs {
   int problems, slots, most;   // problems; how many of them have a place for their sums at a time there; members of the largest team
   int pairs;                   // of row blocks in a problem
   int members, ring, line_pairs, steps;
+  int apart;                   // 1: score_team_again_kernel does it all
   uint32_t step[kTeamSteps + 1];
   uint32_t entry[kTeamEntries][2];
 };
@@ -885,7 +886,7 @@ __global__ __launch_bounds__(256) void score_team_prepare_kernel(ScoreArgs a, Te
   using stage_t = std::conditional_t<K8, u32x2, u32x4>;
   const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, grp = lane >> 4;
   const int64_t at = ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * 256 + tid, all = (int64_t)gridDim.x * gridDim.y * 256;
-  if (at < 64) ta.ctl[at] = 0;
+  if (at < 64) ta.ctl[at] = at == kTeamAbsent && ta.apart ? 1 : 0;
   u32x4* lines = reinterpret_cast<u32x4*>(ta.lines);
   for (int64_t i = at; i < (int64_t)ta.line_pairs * ta.members * 8; i += all) lines[i] = u32x4{kTeamEmpty, kTeamEmpty, kTeamEmpty, kTeamEmpty};
   for (int64_t i = at; i < (int64_t)ta.problems * 5; i += all) ta.done[i] = 0;
@@ -933,6 +934,7 @@ int launch_team(const Plan& pl, const ScoreArgs& a, char* ws, hipStream_t stream
   ta.pairs = (pl.R + 31) / 32;
   ta.problems = a.LH * a.n_seqs; ta.slots = s.slots; ta.most = s.most;
   ta.done = reinterpret_cast<uint32_t*>(ws + pl.off_stats + s.done_at);
+  ta.apart = (pl.variant & CODECOMP_VARIANT_TEAMS_APART) != 0;
   ta.members = s.members; ta.ring = s.ring; ta.line_pairs = s.line_pairs; ta.steps = s.steps;
   for (int i = 0; i <= s.steps; ++i) ta.step[i] = s.step[i];
   for (int i = 0; i < (int)(s.step[s.steps] >> 16); ++i) { ta.entry[i][0] = s.entry[i][0]; ta.entry[i][1] = s.entry[i][1]; }
@@ -942,7 +944,7 @@ int launch_team(const Plan& pl, const ScoreArgs& a, char* ws, hipStream_t stream
   const dim3 grid(ta.members), block(512);
   return with_members<K8>(s.most, [&](auto ml) {
     constexpr int ML = decltype(ml)::value;
-    score_team_kernel<D, NT, K8, ML><<<grid, block, 0, stream>>>(args);
+    if (!ta.apart) score_team_kernel<D, NT, K8, ML><<<grid, block, 0, stream>>>(args);
     if (hipError_t e = hipGetLastError()) return (int)e;
     score_team_again_kernel<D, NT, K8, ML><<<dim3(kTeamMembers), block, 0, stream>>>(args);
     return (int)hipGetLastError();

@@ -240,3 +240,89 @@ def test_strided_queries_and_keys():
         scores.append(out)
     torch.cuda.synchronize()
     assert torch.equal(scores[0].view(torch.int32), scores[1].view(torch.int32))
+
+
+class Made:
+    """A problem whose inputs are made on the GPU: N(0, 1) keys and queries, keys in 8 bits where kv says so."""
+
+    def __init__(self, lens, heads, window, layers, kv="bf16", **over):
+        import torch
+        cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+        g = torch.Generator(device="cuda").manual_seed(11)
+        self.q = torch.randn((layers, len(lens), heads[0], window, 128), generator=g, device="cuda").bfloat16()
+        self.k = torch.empty((layers, heads[1], cu[-1], 128), dtype=torch.uint8 if kv == "fp8" else torch.bfloat16, device="cuda")
+        for layer in range(layers):
+            x = torch.randn(self.k.shape[1:], generator=g, device="cuda")
+            self.k[layer] = x.to(torch.float8_e4m3fn).view(torch.uint8) if kv == "fp8" else x
+        self.prior = torch.zeros(int(cu[-1]), device="cuda")
+        self.dev = torch.from_numpy(cu).cuda()
+        self.make = lambda **more: b.make_params(n_layers=layers, n_q_heads=heads[0], n_kv_heads=heads[1], head_dim=128, window=window, pool_kernel=1, prior_weight=0.0,
+                                                 cu_seqlens_host=cu, cu_budgets_host=cu, cu_seqlens_dev=self.dev.data_ptr(), cu_budgets_dev=self.dev.data_ptr(),
+                                                 kv_dtype=b.KV_FP8_E4M3 if kv == "fp8" else b.KV_BF16, **over, **more)
+        self.ws = torch.empty(b.codecomp_workspace_bytes(self.make()), dtype=torch.uint8, device="cuda")
+
+    def score(self, variant=0, **more):
+        """Scores, with scratch memory full of ones."""
+        import torch
+        p = self.make(score_variant=variant, **more)
+        self.ws.fill_(0xFF)
+        out = torch.full(tuple(self.k.shape[:2]) + (len(self.prior),), float("nan"), device="cuda")
+        b.codecomp_score(self.q, self.k, self.prior, p, out, self.ws)
+        torch.cuda.synchronize()
+        return out
+
+
+def test_teams_apart_is_a_flag_of_its_own():
+    cu = np.array([0, 32768], np.int32)
+    make = lambda variant: b.make_params(n_layers=28, n_q_heads=28, n_kv_heads=4, head_dim=128, window=64, pool_kernel=7, prior_weight=1.0, cu_seqlens_host=cu,
+                                         cu_budgets_host=np.array([0, 64], np.int32), cu_seqlens_dev=0x1000, cu_budgets_dev=0x2000, score_variant=variant)
+    assert b.codecomp_score_teams(make(b.VARIANT_TEAMS_APART)) == 64 and b.codecomp_workspace_bytes(make(b.VARIANT_TEAMS_APART)) == b.codecomp_workspace_bytes(make(0))
+    assert b.codecomp_validate(make(b.VARIANT_TEAMS_APART | b.VARIANT_NO_TEAMS)) == -11 and b.codecomp_validate(make(128)) == -11 and b.codecomp_validate(make(1024)) == -11
+
+
+# All of the work by the kernel that steps in where members can not run: one place for the sums of each problem, fewer places than
+# problems (36 problems of 64 members and 1024 rows, 39 of 128 members and 224 rows, 72 of 64 members and 512 rows: the statistics hold 33, 37
+# and 66 of them), requests of unlike lengths, 8-bit keys; and with rows whose logits outrun the references (the same scores as by two passes, as in test_logits_far_apart).
+@pytest.mark.gpu
+@pytest.mark.parametrize("lens,heads,window,layers,kv", [([20011], (28, 4), 64, 4, "bf16"), ([32753], (16, 2), 128, 18, "bf16"), ([65521], (21, 3), 32, 13, "bf16"), ([32768], (8, 2), 128, 36, "fp8"),
+                                                         ([5000, 2000, 12345], (28, 4), 50, 6, "bf16"), ([1536], (28, 4), 48, 42, "fp8")])
+def test_members_that_can_not_run(lens, heads, window, layers, kv):
+    import torch
+    p = Made(lens, heads, window, layers, kv)
+    assert b.codecomp_score_teams(p.make()) > 0
+    assert torch.equal(p.score().view(torch.int32), p.score(b.VARIANT_TEAMS_APART).view(torch.int32))
+    p.q[:, :, :, ::3] *= 40.0
+    far = p.score(b.VARIANT_TEAMS_APART)
+    assert torch.equal(far.view(torch.int32), p.score().view(torch.int32))
+    np.testing.assert_allclose(far.cpu().numpy(), p.score(b.VARIANT_NO_TEAMS).cpu().numpy(), rtol=2e-4, atol=1e-30)
+
+
+# More problems with rows out of range than the list of them holds (1024): all are done again.
+@pytest.mark.gpu
+def test_more_problems_out_of_range_than_are_listed():
+    import torch
+    p = Made([1536], (32, 16), 128, 65)
+    assert b.codecomp_score_teams(p.make()) == 3
+    p.q[:, :, :, 5] *= 40.0
+    far = p.score()
+    assert torch.equal(far.view(torch.int32), p.score(b.VARIANT_TEAMS_APART).view(torch.int32))
+    np.testing.assert_allclose(far.cpu().numpy(), p.score(b.VARIANT_NO_TEAMS).cpu().numpy(), rtol=2e-4, atol=1e-30)
+
+
+# Some problems out of range, far from one another: their place in the list is not their number.  Key and query logits as in test_logits_far_apart.
+@pytest.mark.gpu
+@pytest.mark.parametrize("lens", [[9000], [5000, 12345, 2000]])
+def test_problems_done_again_alone(lens):
+    import torch
+    p = Made(lens, (28, 4), 64, 12)
+    assert b.codecomp_score_teams(p.make()) > 0
+    clean = p.score()
+    keep = torch.ones(clean.shape, dtype=torch.bool, device="cuda")
+    first = np.concatenate([[0], np.cumsum(lens)])
+    for layer, head, request in ((0, 1, 0), (5, 2, len(lens) - 1), (5, 3, len(lens) // 2), (11, 3, 0)):
+        p.k[layer, head, first[request] + 777] *= 80
+        keep[layer, head, first[request]:first[request + 1]] = False
+    hit = p.score()
+    assert torch.equal(clean[keep], hit[keep])
+    np.testing.assert_allclose(hit.cpu().numpy(), p.score(b.VARIANT_NO_TEAMS).cpu().numpy(), rtol=2e-4, atol=1e-30)
+    assert torch.equal(hit.view(torch.int32), p.score(b.VARIANT_TEAMS_APART).view(torch.int32))
