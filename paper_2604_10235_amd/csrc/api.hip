@@ -143,9 +143,9 @@ static void schedule_teams(const codecomp_params* p, const Plan& pl, int64_t roo
   const int pairs = (pl.R + 31) / 32;
   ts->ring = kinds == 1;
   ts->line_pairs = ts->ring ? 16 : rounds * pairs;
-  const int64_t counters = (int64_t)LH * pl.n_seqs * 5 * (int64_t)sizeof(uint32_t), per_problem = (int64_t)pairs * ts->most * 128;
+  const int64_t counters = (int64_t)LH * pl.n_seqs * kTeamCounters * (int64_t)sizeof(uint32_t), per_problem = (int64_t)pairs * ts->most * 256;          // again, by half members; three at a time at least (team_tasks.h)
   ts->done_at = (room - counters) & ~(int64_t)255;
-  if (room < counters || rounds > 0xFFFF || ts->done_at < (int64_t)ts->line_pairs * ts->members * 128 || ts->done_at < per_problem) return;
+  if (room < counters || rounds > 0xFFFF || ts->done_at < (int64_t)ts->line_pairs * ts->members * 128 || ts->done_at < 3 * per_problem) return;
   ts->slots = (int)(ts->done_at / per_problem < LH * (int64_t)pl.n_seqs ? ts->done_at / per_problem : LH * (int64_t)pl.n_seqs);
   if (teams_quicker(rounds, pairs, ts->most, pl.kv_fp8, (float)(keys * LH))) ts->steps = steps;
 }

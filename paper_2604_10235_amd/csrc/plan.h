@@ -63,6 +63,7 @@ constexpr int kTeamMembers = 256;     // workgroups of a launch, each with a com
 constexpr int kTeamMost = 128;
 constexpr int kTeamTiles = 4;         // tiles of 16 keys per wave
 constexpr int kTeamRows = 1024;       // most query rows
+constexpr int kTeamCounters = 8;      // words of a problem that count what has been done again
 constexpr int kTeamSteps = 48, kTeamEntries = 96;          // rounds that are alike, groups of teams in them
 struct TeamSchedule {
   int steps;                          // 0: not taken

@@ -24,6 +24,7 @@
 // 128 1648 and 1187; 8-bit keys 815 and 660.  Error against 64 bits 7e-8 (2-norm), by two passes 3.4e-7.
 #pragma once
 #include "score_once.h"
+#include "team_tasks.h"
 
 namespace codecomp {
 
@@ -32,6 +33,8 @@ constexpr int kTeamRing = 16;                      // pairs of row blocks whose 
 
 enum { kTeamAbsent = 0, kTeamRange = 1, kTeamTicket = 32 };        // control words: a wait has failed; rows of some problems are out of range; tasks handed out
 constexpr uint32_t kTeamOut = 1, kTeamRedo = 2;    // a problem has rows out of range, as the team kernel found; as found again
+// Counters of a problem in score_team_again_kernel: tasks of a phase that are done, weights that are there; last, what the two above say.
+enum { kTeamSumsDone, kTeamWeighed, kTeamLargestDone, kTeamReferred, kTeamSumsAgainDone, kTeamWeighedAgain, kTeamMassesDone, kTeamFlags };
 
 __device__ __forceinline__ uint32_t team_load(const uint32_t* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 __device__ __forceinline__ void team_store(uint32_t* p, uint32_t v) { __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
@@ -39,7 +42,7 @@ __device__ __forceinline__ void team_store(uint32_t* p, uint32_t v) { __hip_atom
 struct TeamArgs {
   uint32_t* lines;             // [place of a pair of row blocks][member][32]: row sums over the member's keys
   uint32_t* ctl;
-  uint32_t* done;              // [problem][4] tasks of a phase that are done (score_team_again_kernel), then [problem] kTeamOut, kTeamRedo
+  uint32_t* done;              // [problem][kTeamCounters]; counters by position among the problems that are done, flags by problem
   int problems, slots, most;   // problems; how many of them have a place for their sums at a time there; members of the largest team
   int pairs;                   // of row blocks in a problem
   int members, ring, line_pairs, steps;
@@ -598,8 +601,10 @@ __global__ __launch_bounds__(512, 2) void score_team_kernel(TeamKernelArgs args)
     }
     if (q == cur_start + LAG - 1) {                    // the pair whose sums are collected is the current problem's first
       const team_args_t x = team_args();
-      if (bad != 0 && lane == 0) {                     // the problem before has rows out of range
-        team_store(x->t.done + x->t.problems * 4 + done_seq * x->a.LH + done_lz, kTeamOut);
+      // The problem before has rows out of range.  All waves of its team know; one says so (all of them, 512 stores to a word in every
+      // problem, took the kernel from 0.75 to 2.1 ms where each of 112 problems of 32K keys had such rows).
+      if (bad != 0 && lane == 0 && done_share.key0 == 0) {
+        team_store(x->t.done + (int64_t)(done_seq * x->a.LH + done_lz) * kTeamCounters + kTeamFlags, kTeamOut);
         team_store(x->t.ctl + kTeamRange, 1);
       }
       bad = 0;
@@ -654,93 +659,261 @@ __global__ __launch_bounds__(512, 2) void score_team_kernel(TeamKernelArgs args)
 }
 
 // Does the team kernel's work again where that could not be finished: the same sums in the same order, so the same bits, but without
-// waiting for a workgroup that might not run.  Its tasks, one member's part of one problem in one of four phases, are handed out by a
-// counter; a task waits only for tasks with smaller numbers, which run or are done.
-//   0  row sums of the member, to memory          1  where a row of the problem is out of range: its largest logits become the references
-//   2  ... and the sums are formed again          3  masses
-// Where no wait has failed, only the problems with rows out of range are taken, without their phase 0.  The sums of some problems
-// have a place at a time: their tasks come one phase after the other, and phase 0 of a problem waits for phase 3 of the one that had
-// its place.
+// waiting for a workgroup that might not run.  Its tasks (team_tasks.h) are handed out by a counter; a task waits only for tasks with
+// smaller numbers, which run or are done: one number is taken ahead, so a workgroup may hold two, and does the smaller one first.
+// Where no wait has failed, only the problems with rows out of range are taken.
+//
+// Bound by instruction issue as the passes are, in twice the work of the team kernel: every logit is formed for the row sums and again
+// for the masses.  The query rows come through LDS, four blocks of 16 at a time, the next four on their way in registers; the MFMAs of
+// a block stand beside the exponentials of the one before.  A task is taken by half members, so that a compute unit holds two workgroups
+// of four waves, of which one works while the other waits for keys (2 us), the next number (2) and counters: 8 us of a task's 22, in which its
+// loop runs 14 (28 x 32K keys, 448 rows).  Measured, scores, by two passes / by teams / all of it by this kernel: 28 x 32K keys, 448 rows 1009
+// / 663 / 1129 us (with eight waves, rows from memory to registers, a fence and the totals of all members in each task 6239); 896 rows 1659 /
+// 1161 / 2026; 8 x 64K, 256 rows 661 / 534 / 1005; sixteen requests of 8K .. 45K 473 / 373 / 689; 4 x 20011 95 / 89 / 139.  Teams and then a row
+// of every problem out of range: 28 x 32K 2542 us (9409), 4 x 20011 321 (881).  Three workgroups a compute unit spill: 1790 instead of 1129.
 template <int D, int NT, bool K8, int ML>
-__global__ __launch_bounds__(512, 2) void score_team_again_kernel(TeamKernelArgs args) {
-  constexpr int KS = D / 32, ESZ = K8 ? 1 : 2, PL = ML / 8, kListed = 1024;
+__global__ __launch_bounds__(256, 2) void score_team_again_kernel(TeamKernelArgs args) {
+  constexpr int KS = D / 32, ESZ = K8 ? 1 : 2, PL = ML / 8, kListed = 1024, NW = 4, kAhead = NW;
   using stage_t = std::conditional_t<K8, u32x2, u32x4>;
   const ScoreArgs& a = args.a;
   const TeamArgs& ta = args.t;
-  bool whole = team_load(ta.ctl + kTeamAbsent) != 0;
-  if (!whole && team_load(ta.ctl + kTeamRange) == 0) return;
-  __shared__ float sums[kTeamRows / 32][8][32], weight[kTeamRows], ref[kTeamRows];
-  __shared__ uint16_t list[kListed];
-  __shared__ int ticket, listed, any;
+  const uint32_t absent = team_load(ta.ctl + kTeamAbsent), range = team_load(ta.ctl + kTeamRange);
+  bool whole = absent != 0;
+  if (!whole && range == 0) return;
+  struct Shared {
+    u32x4 q[2][kAhead][KS][64];                        // blocks of query rows, fragment order
+    float part[kTeamRows / 32 + 1][NW][32];            // row sums (largest logits) of the waves; [0]: of the rows before the first
+    float weight[32 + kTeamRows], ref[32 + kTeamRows];
+    uint16_t list[kListed];
+    struct { TeamTaskAt at; int problem, halves; } task[2];            // the task at hand and the next one
+    int listed, out, last;
+  };
+  __shared__ __attribute__((aligned(16))) Shared sh;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l16 = lane & 15, grp = lane >> 4, l32 = lane & 31, hf = lane >> 5;
   const int pairs = ta.pairs;
   const float c = a.c;
   const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+  if (tid < 32) sh.weight[tid] = sh.ref[tid] = 0.f;
   if (!whole) {                                        // the problems with rows out of range, the same list in every workgroup
     if (wave == 0) {
       int count = 0;
-      for (int at = 0; at < ta.problems; at += 64) {
-        const bool mine = at + lane < ta.problems && (team_load(ta.done + (int64_t)ta.problems * 4 + at + lane) & kTeamOut) != 0;
-        const uint64_t all = __ballot(mine);
-        const int to = count + __popcll(all & ((1ull << lane) - 1));
-        if (mine && to < kListed) list[to] = (uint16_t)(at + lane);
-        count += __popcll(all);
+      for (int at = 0; at < ta.problems; at += 64 * 8) {
+        uint32_t flag[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) flag[i] = team_load(ta.done + (int64_t)min(at + i * 64 + lane, ta.problems - 1) * kTeamCounters + kTeamFlags);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          const int problem = at + i * 64 + lane;
+          const bool mine = problem < ta.problems && (flag[i] & kTeamOut) != 0;
+          const uint64_t all = __ballot(mine);
+          const int to = count + __popcll(all & ((1ull << lane) - 1));
+          if (mine && to < kListed) sh.list[to] = (uint16_t)problem;
+          count += __popcll(all);
+        }
       }
-      if (lane == 0) listed = count;
+      if (lane == 0) sh.listed = count;
     }
     __syncthreads();
-    whole = __builtin_amdgcn_readfirstlane(listed) > kListed;
+    whole = __builtin_amdgcn_readfirstlane(sh.listed) > kListed;
   }
-  const int problems = whole ? ta.problems : __builtin_amdgcn_readfirstlane(listed);
-  auto problem_at = [&](int i) { return whole ? i : __builtin_amdgcn_readfirstlane((int)list[i]); };
-  auto members_of = [&](int problem) {
+  const int problems = whole ? ta.problems : __builtin_amdgcn_readfirstlane(sh.listed);
+  const int most = 2 * ta.most;                        // in half members
+  const TeamTasks tasks = TeamTasks::make(problems, ta.slots, most, whole, (int)gridDim.x);
+  auto problem_at = [&](int i) { return whole ? i : __builtin_amdgcn_readfirstlane((int)sh.list[i]); };
+  auto halves_of = [&](int problem) {
     const int seq = problem / a.LH;
-    return ((a.cu_seqlens[seq + 1] - a.cu_seqlens[seq] - a.key_trim + 15) / 16 + 8 * NT - 1) / (8 * NT);
+    return ((a.cu_seqlens[seq + 1] - a.cu_seqlens[seq] - a.key_trim + 15) / 16 + 8 * NT - 1) / (8 * NT) * 2;
   };
-  for (;;) {
-    if (tid == 0) {
-      ticket = (int)__hip_atomic_fetch_add(ta.ctl + kTeamTicket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      any = 0;
-    }
+  // What a task leaves and takes in memory (sums, weights, references, counters) goes past the caches; here its stores are done.
+  auto stored = [&]() __attribute__((always_inline)) { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); };
+  auto await = [&](const uint32_t* count, uint32_t need) {
+    if (tid == 0) while (team_load(count) < need) __builtin_amdgcn_s_sleep(2);
+    asm volatile("" ::: "memory");
     __syncthreads();
-    // problems that have a place together, phase, problem, member: every problem counted with as many members as the largest has
-    int x = __builtin_amdgcn_readfirstlane(ticket);
-    const int first = x / (ta.slots * 4 * ta.most) * ta.slots, together = min(ta.slots, problems - first);
-    x -= first * 4 * ta.most;
-    if (together <= 0 || x >= together * 4 * ta.most) return;          // the last ones may be fewer
-    const int phase = x / (together * ta.most);
-    x -= phase * together * ta.most;
-    const int at = first + x / ta.most, member = x % ta.most, problem = problem_at(at), chunks = members_of(problem);
-    if (member >= chunks) { __syncthreads(); continue; }
-    uint32_t* const done = ta.done + (int64_t)at * 4;
-    uint32_t* const bad = ta.done + (int64_t)ta.problems * 4 + problem;
-    {
-      const bool place = phase == 0 && at >= ta.slots;
-      const uint32_t need = place ? (uint32_t)members_of(problem_at(at - ta.slots)) : (uint32_t)chunks;
-      const uint32_t* of = phase > 0 ? done + phase - 1 : done - (int64_t)ta.slots * 4 + 3;
-      if (tid == 0) {
-        if (place || phase > 0) while (team_load(of) < need) __builtin_amdgcn_s_sleep(4);
-        __threadfence();
-      }
+  };
+  // the next number that stands for half a member that there is
+  auto take_number = [&](int to) {
+    for (;;) {
+      const int x = (int)__hip_atomic_fetch_add(ta.ctl + kTeamTicket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const TeamTaskAt t = tasks.at(x);
+      const int problem = t.at < 0 || whole ? t.at : (int)sh.list[t.at], halves = t.at < 0 ? 0 : halves_of(problem);
+      if (t.at < 0 || t.first < halves) { sh.task[to] = {t, problem, halves}; return; }
     }
-    __syncthreads();
+  };
+  if (tid == 0) take_number(0);
+  __syncthreads();
+  for (int turn = 0;; turn ^= 1) {
+    auto uniform = [](int x) __attribute__((always_inline)) { return __builtin_amdgcn_readfirstlane(x); };
+    const int at = uniform(sh.task[turn].at.at);
+    if (at < 0) return;
+    const int phase = uniform(sh.task[turn].at.phase), first = uniform(sh.task[turn].at.first), problem = uniform(sh.task[turn].problem);
+    const int halves = uniform(sh.task[turn].halves), chunks = halves >> 1, last = min(uniform(sh.task[turn].at.last), halves);
+    uint32_t* const done = ta.done + (int64_t)at * kTeamCounters;
+    uint32_t* const flags = ta.done + (int64_t)problem * kTeamCounters + kTeamFlags;
     const int seq = problem / a.LH, lz = problem - seq * a.LH;
+    const int layer = divide(lz, a.Hkv, a.inv_heads), head = lz - layer * a.Hkv;
+    uint32_t* const lines = ta.lines + (int64_t)(at % ta.slots) * pairs * most * 32;               // [pair][half member][32], weights in the first one's place
+    uint32_t* const refs = reinterpret_cast<uint32_t*>(a.lse) + ((int64_t)lz * a.n_seqs + seq) * a.lrows;
+    const uint16_t* const qb = a.q + (int64_t)layer * a.q_sl + (int64_t)seq * a.q_ss + (int64_t)(head * a.G) * a.q_sh + grp * 8;
     TeamTask t;
     t.lz = lz; t.seq = seq; t.chunks = chunks;
     t.tok0 = a.cu_seqlens[seq]; t.n = a.cu_seqlens[seq + 1] - t.tok0 - a.key_trim;
-    const int tiles = (t.n + 15) >> 4, each = tiles / chunks, more = tiles - each * chunks;
-    t.tile0 = member * each + min(member, more); t.tiles = each + (member < more ? 1 : 0);
-    const TeamShare own = team_share(t, wave);
-    uint32_t* const lines = ta.lines + (int64_t)(at % ta.slots) * pairs * ta.most * 32;            // [pair][member][32]
-    uint32_t* const refs = reinterpret_cast<uint32_t*>(a.lse) + ((int64_t)lz * a.n_seqs + seq) * a.lrows;
+    const unsigned char* const kb = a.k + ((int64_t)layer * a.kv_sl + (int64_t)head * a.kv_sh + (int64_t)t.tok0 * a.kv_st) * ESZ + grp * 8 * ESZ;
+    bool ahead = false;                                // the next number is taken
 
-    bool redo = phase == 0 ? whole : true;
-    if (phase == 2 && whole) redo = (__builtin_amdgcn_readfirstlane(team_load(bad)) & kTeamRedo) != 0;
-    if (redo) for (int r = tid; r < pairs * 32; r += 512) ref[r] = __builtin_bit_cast(float, team_load(refs + (r < a.R ? r : 0)));
-    if (phase == 3 || (phase == 1 && whole)) {
-      // totals of the rows over the members, in the team kernel's order; a wave has every eighth pair
-      for (int p = wave; p < pairs; p += 8) {
+    // One phase of half members [first, last).  ready(): waits for what the phase needs beside keys and rows.
+    auto pass = [&](auto phase_c, auto ready) __attribute__((always_inline)) {
+      constexpr int KIND = decltype(phase_c)::value;
+      u32x4 kf[NT][KS], st[KS];
+      auto fetch_keys = [&](int half) __attribute__((always_inline)) {
+        const int tiles = (t.n + 15) >> 4, each = tiles / chunks, more = tiles - each * chunks, member = half >> 1;
+        t.tile0 = member * each + min(member, more); t.tiles = each + (member < more ? 1 : 0);
+        const TeamShare own = team_share(t, (half & 1) * NW + wave);
+#pragma unroll
+        for (int i = 0; i < NT; ++i) {
+          const unsigned char* from = kb + (int64_t)min(own.key0 + i * 16 + l16, t.n - 1) * a.kv_st * ESZ;
+#pragma unroll
+          for (int ks = 0; ks < KS; ++ks) kf[i][ks] = to_bf16x8(*reinterpret_cast<const stage_t*>(from + ks * 32 * ESZ));
+        }
+        return own;
+      };
+      auto fetch_rows = [&](int chunk) __attribute__((always_inline)) {        // rows past the end are the first one
+        const int row = (chunk * kAhead + wave) * 16 + l16, r = row < a.R ? row : 0, g = row_group(r, a.inv_w);
+        const uint16_t* from = qb + (int64_t)g * a.q_sh + (int64_t)(r - g * a.W) * a.q_st;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) st[ks] = *reinterpret_cast<const u32x4*>(from + ks * 32);
+      };
+      auto leave_rows = [&](int buf) __attribute__((always_inline)) {
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) sh.q[buf][wave][ks][lane] = st[ks];
+      };
+      TeamShare next = fetch_keys(first);
+      fetch_rows(0);
+      if (tid == 0) take_number(turn ^ 1);
+      ahead = true;
+      ready();
+      if constexpr (KIND != kTeamLargest)
+        for (int r = tid; r < pairs * 32; r += 64 * NW) {
+          sh.ref[32 + r] = __builtin_bit_cast(float, team_load(refs + (r < a.R ? r : 0)));
+          if constexpr (KIND == kTeamMasses) sh.weight[32 + r] = __builtin_bit_cast(float, team_load(lines + (int64_t)(r >> 5) * most * 32 + (r & 31)));
+        }
+      const int chunks_of_rows = (2 * pairs + kAhead - 1) / kAhead;
+#pragma unroll 1
+      for (int half = first; half < last; ++half) {
+        const TeamShare own = next;
+        leave_rows(0);
+        f32x4 pad;                                     // added to the logits of the wave's last tile: -inf in places without a key
+#pragma unroll
+        for (int v = 0; v < 4; ++v) pad[v] = own.tiles < NT || own.key0 + (NT - 1) * 16 + 4 * grp + v >= t.n ? -INFINITY : 0.f;
+        f32x4 mass[NT], s[2][NT];
+#pragma unroll
+        for (int i = 0; i < NT; ++i) { mass[i] = zero; s[1][i] = f32x4{-INFINITY, -INFINITY, -INFINITY, -INFINITY}; }
+        auto flush = [&](int split) __attribute__((always_inline)) {
+          float* u = a.uraw + ((int64_t)split * a.LH + lz) * a.T + t.tok0;
+#pragma unroll
+          for (int i = 0; i < NT; ++i) {
+            const float m = mass_of_rows(mass[i], l16);
+            const int key = own.key0 + i * 16 + 4 * grp + (l16 & 3);
+            if (l16 >> 2 == i && i < own.tiles && key < t.n) u[key] = m * a.inv_g;     // the lane counts: they differ in the order of the sum
+            mass[i] = zero;
+          }
+        };
+        float of_even = 0.f;
+        // the logits of one block of rows (row: this lane's): row sums, largest logits or masses
+        auto take = [&](f32x4 (&x)[NT], int row, auto odd_c) __attribute__((always_inline)) {
+          constexpr bool ODD = decltype(odd_c)::value;
+          float of = 0.f;
+          if constexpr (KIND == kTeamLargest) {
+            of = x[0][0];
+#pragma unroll
+            for (int i = 0; i < NT; ++i)
+#pragma unroll
+              for (int v = 0; v < 4; ++v) of = fmaxf(of, x[i][v]);
+          } else {
+            const float rf = sh.ref[32 + row], w = KIND == kTeamMasses ? sh.weight[32 + row] : 0.f;
+#pragma unroll
+            for (int i = 0; i < NT; ++i)
+#pragma unroll
+              for (int v = 0; v < 4; ++v) {
+                const float e = __builtin_amdgcn_exp2f(__builtin_fmaf(x[i][v], c, -rf));
+                if constexpr (KIND == kTeamMasses) mass[i][v] = __builtin_fmaf(e, w, mass[i][v]);
+                else if (i == 0 && v == 0) of = e;
+                else of += e;
+              }
+          }
+          if constexpr (KIND != kTeamMasses) {
+            if constexpr (!ODD) {
+              of_even = of;
+            } else {                                   // both blocks: lanes below 32 take the even one
+              float p, q, lo, hi;
+              swap_halves(of_even, of, p, q);
+              if constexpr (KIND == kTeamLargest) { p = fmaxf(p, q); swap_rows(p, p, lo, hi); lo = fmaxf(lo, hi); }
+              else { swap_rows(p + q, p + q, lo, hi); lo = lo + hi; }
+              sh.part[1 + (row >> 5)][wave][(hf << 4) + l16] = lo;
+            }
+          }
+        };
+        u32x4 qf[KS];
+        auto form = [&](f32x4 (&to)[NT], const u32x4 (*from)[64]) __attribute__((always_inline)) {       // and the rows of the next block
+#pragma unroll
+          for (int i = 0; i < NT; ++i) {
+            to[i] = i == NT - 1 ? pad : zero;
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) to[i] = once_mma(kf[i][ks], qf[ks], to[i]);
+          }
+#pragma unroll
+          for (int ks = 0; ks < KS; ++ks) qf[ks] = from[ks][lane];
+        };
+#pragma unroll 1
+        for (int chunk = 0; chunk < chunks_of_rows; ++chunk) {
+          __syncthreads();
+          const int buf = chunk & 1, p0 = chunk * (kAhead / 2), p1 = min(p0 + kAhead / 2, pairs);
+          fetch_rows(chunk + 1 < chunks_of_rows ? chunk + 1 : 0);        // the last time: for the next half member
+#pragma unroll
+          for (int ks = 0; ks < KS; ++ks) qf[ks] = sh.q[buf][0][ks][lane];
+#pragma unroll 1
+          for (int p = p0; p < p1; ++p) {
+            const int b = 2 * (p - p0);
+            form(s[0], sh.q[buf][b + 1]);
+            take(s[1], (p - 1) * 32 + 16 + l16, std::true_type{});
+            if constexpr (KIND == kTeamMasses)
+              if (a.row_splits > 1 && p > 0 && p % a.nb == 0) flush(p / a.nb - 1);
+            form(s[1], sh.q[buf][b + 2 < kAhead ? b + 2 : 0]);     // past the last block: not used
+            take(s[0], p * 32 + l16, std::false_type{});
+          }
+          if (chunk + 1 < chunks_of_rows) leave_rows(buf ^ 1);
+        }
+        if (half + 1 < last) next = fetch_keys(half + 1);
+        take(s[1], (pairs - 1) * 32 + 16 + l16, std::true_type{});
+        if constexpr (KIND == kTeamMasses) flush((pairs - 1) / a.nb);
+        __syncthreads();
+        if constexpr (KIND != kTeamMasses) {
+          for (int r = tid; r < pairs * 32; r += 64 * NW) {
+            const float (&part)[NW][32] = sh.part[1 + (r >> 5)];
+            const int i = r & 31;
+            const float x = KIND == kTeamLargest ? fmaxf(fmaxf(part[0][i], part[1][i]), fmaxf(part[2][i], part[3][i])) * c : (part[0][i] + part[1][i]) + (part[2][i] + part[3][i]);
+            team_store(lines + ((int64_t)(r >> 5) * most + half) * 32 + i, __builtin_bit_cast(uint32_t, x));
+          }
+        }
+      }
+    };
+    // The references of the problem's rows become their largest logits.
+    auto refer = [&]() __attribute__((always_inline)) {
+      for (int r = tid; r < a.R; r += 64 * NW) {
+        float m = __builtin_bit_cast(float, team_load(refs + r));
+#pragma unroll 8
+        for (int h = 0; h < halves; ++h) m = fmaxf(m, __builtin_bit_cast(float, team_load(lines + ((int64_t)(r >> 5) * most + h) * 32 + (r & 31))));
+        team_store(refs + r, __builtin_bit_cast(uint32_t, m));
+      }
+      stored();
+      __syncthreads();
+    };
+    // Weights of all rows of the problem from the sums of its members, in the team kernel's order; a wave has every fourth pair.  True if a row is out of range.
+    auto weigh = [&]() __attribute__((always_inline)) {
+      if (tid == 0) sh.out = 0;
+      __syncthreads();
+      for (int p = wave; p < pairs; p += NW) {
         float total = 0.f;                             // ((0 + 1) + (2 + 3)) + ((4 + 5) + (6 + 7)) of the waves' shares
 #pragma unroll 1
         for (int half = 0; half < 8; half += 4) {
@@ -754,8 +927,9 @@ __global__ __launch_bounds__(512, 2) void score_team_again_kernel(TeamKernelArgs
 #pragma unroll
               for (int i = 0; i < PL / 2; ++i) {
                 const int m = (w + j) * PL + hf + 2 * i;
-                const float v = __builtin_bit_cast(float, team_load(lines + ((int64_t)p * ta.most + min(m, chunks - 1)) * 32 + l32));
-                x[i] = m < chunks ? v : 0.f;
+                const uint32_t* of = lines + ((int64_t)p * most + 2 * min(m, chunks - 1)) * 32 + l32;
+                const float v = __builtin_bit_cast(float, team_load(of)) + __builtin_bit_cast(float, team_load(of + 32));
+                x[i] = m < chunks ? __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, v) & 0x7FFFFFFFu) : 0.f;
               }
 #pragma unroll
               for (int n = PL / 4; n > 0; n /= 2)
@@ -771,110 +945,66 @@ __global__ __launch_bounds__(512, 2) void score_team_again_kernel(TeamKernelArgs
         }
         const bool there = p * 32 + l32 < a.R;
         const float r0 = __builtin_amdgcn_rcpf(total);
-        weight[p * 32 + l32] = there ? __builtin_fmaf(__builtin_fmaf(-total, r0, 1.0f), r0, r0) : 0.f;
-        if (there && !(total <= 1.0e30f)) any = 1;
+        const float w = there ? __builtin_fmaf(__builtin_fmaf(-total, r0, 1.0f), r0, r0) : 0.f;
+        team_store(lines + (int64_t)p * most * 32 + l32, __builtin_bit_cast(uint32_t, w));
+        if (there && !(total <= 1.0e30f)) sh.out = 1;
       }
-    }
-    __syncthreads();
-    if (phase == 1 && whole) {                         // all members find the same
-      redo = __builtin_amdgcn_readfirstlane(any) != 0;
-      if (tid == 0 && redo) __hip_atomic_fetch_or(bad, kTeamRedo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    if (redo) {
-      const int layer = divide(lz, a.Hkv, a.inv_heads), head = lz - layer * a.Hkv;
-      const unsigned char* kb = a.k + ((int64_t)layer * a.kv_sl + (int64_t)head * a.kv_sh + (int64_t)t.tok0 * a.kv_st) * ESZ + grp * 8 * ESZ;
-      const uint16_t* qb = a.q + (int64_t)layer * a.q_sl + (int64_t)seq * a.q_ss + (int64_t)(head * a.G) * a.q_sh + grp * 8;
-      u32x4 kf[NT][KS];
-#pragma unroll
-      for (int i = 0; i < NT; ++i) {
-        const unsigned char* from = kb + (int64_t)min(own.key0 + i * 16 + l16, t.n - 1) * a.kv_st * ESZ;
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) kf[i][ks] = to_bf16x8(*reinterpret_cast<const stage_t*>(from + ks * 32 * ESZ));
-      }
-      f32x4 mass[NT];
-#pragma unroll
-      for (int i = 0; i < NT; ++i) mass[i] = zero;
-      auto take_rows = [&](u32x4* to, int block) __attribute__((always_inline)) {      // rows past the end are the first one
-        const int row = block * 16 + l16, r = row < a.R ? row : 0, g = row_group(r, a.inv_w);
-        const uint16_t* from = qb + (int64_t)g * a.q_sh + (int64_t)(r - g * a.W) * a.q_st;
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) to[ks] = *reinterpret_cast<const u32x4*>(from + ks * 32);
-      };
-      u32x4 qf[2][KS];
-      take_rows(qf[0], 0);
-      take_rows(qf[1], 1);
-      for (int p = 0; p < pairs; ++p) {
-        float sum_of[2] = {0.f, 0.f};
-#pragma unroll
-        for (int b = 0; b < 2; ++b) {
-          const int row = p * 32 + b * 16 + l16;
-          f32x4 s[NT];
-#pragma unroll
-          for (int i = 0; i < NT; ++i) {
-            s[i] = zero;
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks) s[i] = once_mma(kf[i][ks], qf[b][ks], s[i]);
-          }
-          if (p + 1 < pairs) take_rows(qf[b], p * 2 + b + 2);
-#pragma unroll
-          for (int v = 0; v < 4; ++v)
-            if (own.tiles < NT || own.key0 + (NT - 1) * 16 + 4 * grp + v >= t.n) s[NT - 1][v] = -INFINITY;
-          if (phase == 1) {                            // the largest logits: of floats, as integers in the order of their sign
-            float m = -INFINITY;
-#pragma unroll
-            for (int i = 0; i < NT; ++i)
-#pragma unroll
-              for (int v = 0; v < 4; ++v) m = fmaxf(m, s[i][v]);
-            m = row_max4(m) * c;
-            if (lane < 16 && row < a.R) {
-              if (m >= 0.f) __hip_atomic_fetch_max(reinterpret_cast<int*>(refs + row), __builtin_bit_cast(int, m), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-              else if (m < 0.f) __hip_atomic_fetch_min(refs + row, __builtin_bit_cast(uint32_t, m), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            }
-            continue;
-          }
-          const float rf = ref[row], w = phase == 3 ? weight[row] : 0.f;
-          float sum = 0.f;
-#pragma unroll
-          for (int i = 0; i < NT; ++i)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-              const float x = __builtin_amdgcn_exp2f(__builtin_fmaf(s[i][v], c, -rf));
-              if (i == 0 && v == 0) sum = x; else sum += x;
-              mass[i][v] = __builtin_fmaf(x, w, mass[i][v]);
-            }
-          sum_of[b] = sum;
+      stored();
+      __syncthreads();
+      return __builtin_amdgcn_readfirstlane(sh.out) != 0;
+    };
+    // Counts the task; true for who has counted the last one of the problem's.
+    auto count = [&](uint32_t* of, uint32_t all) __attribute__((always_inline)) {
+      stored();
+      __syncthreads();
+      if (tid == 0) sh.last = __hip_atomic_fetch_add(of, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1 == all;
+      __syncthreads();
+      return __builtin_amdgcn_readfirstlane(sh.last) != 0;
+    };
+    auto far_out = [&]() { return (__builtin_amdgcn_readfirstlane((int)team_load(flags)) & (int)kTeamRedo) != 0; };
+
+    // the place of a problem's sums is free when the problem that had it has its masses
+    auto place = [&]() { if (at >= ta.slots) await(done - (int64_t)ta.slots * kTeamCounters + kTeamMassesDone, (uint32_t)tasks.tasks_of(halves_of(problem_at(at - ta.slots)), kTeamMasses)); };
+    auto leave_word = [&](uint32_t* word) { if (tid == 0) team_store(word, 1); };
+
+    if (phase == kTeamSums) {
+      pass(std::integral_constant<int, kTeamSums>{}, place);
+      if (count(done + kTeamSumsDone, (uint32_t)tasks.tasks_of(halves, phase))) {
+        const bool redo = weigh();
+        if (tid == 0 && redo) {
+          __hip_atomic_fetch_or(flags, kTeamRedo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          stored();
         }
-        if (phase == 0 || phase == 2) {
-          float x, y, lo, hi;
-          swap_halves(sum_of[0], sum_of[1], x, y);
-          swap_rows(x + y, x + y, lo, hi);
-          sums[p][wave][(hf << 4) + l16] = lo + hi;
-        } else if (phase == 3 && (p + 1 == pairs || (a.row_splits > 1 && (p + 1) % a.nb == 0))) {
-          float* u = a.uraw + ((int64_t)(p / a.nb) * a.LH + lz) * a.T + t.tok0;
-#pragma unroll
-          for (int i = 0; i < NT; ++i) {
-            const float m = mass_of_rows(mass[i], l16);
-            const int key = own.key0 + i * 16 + 4 * grp + (l16 & 3);
-            if (l16 >> 2 == i && i < own.tiles && key < t.n) u[key] = m * a.inv_g;     // the lane counts: they differ in the order of the sum
-            mass[i] = zero;
+        leave_word(done + kTeamWeighed);
+      }
+    } else if (phase == kTeamMasses) {
+      pass(std::integral_constant<int, kTeamMasses>{}, [&]() {
+        if (whole) await(done + kTeamWeighed, 1);
+        if (!whole || far_out()) await(done + kTeamWeighedAgain, 1);
+      });
+      count(done + kTeamMassesDone, 0);
+    } else {
+      if (whole) await(done + kTeamWeighed, 1);
+      if (!whole || far_out()) {
+        if (phase == kTeamLargest) {
+          pass(std::integral_constant<int, kTeamLargest>{}, [&]() { if (!whole) place(); });
+          if (count(done + kTeamLargestDone, (uint32_t)tasks.tasks_of(halves, phase))) {
+            refer();
+            leave_word(done + kTeamReferred);
+          }
+        } else {
+          pass(std::integral_constant<int, kTeamSumsAgain>{}, [&]() { await(done + kTeamReferred, 1); });
+          if (count(done + kTeamSumsAgainDone, (uint32_t)tasks.tasks_of(halves, phase))) {
+            weigh();
+            leave_word(done + kTeamWeighedAgain);
           }
         }
       }
-      if (phase == 0 || phase == 2) {
-        __syncthreads();
-        for (int r = tid; r < pairs * 32; r += 512) {
-          const float (&part)[8][32] = sums[r >> 5];
-          const int i = r & 31;
-          const float s = ((part[0][i] + part[1][i]) + (part[2][i] + part[3][i])) + ((part[4][i] + part[5][i]) + (part[6][i] + part[7][i]));
-          team_store(lines + ((int64_t)(r >> 5) * ta.most + member) * 32 + i, __builtin_bit_cast(uint32_t, s) & 0x7FFFFFFFu);
-        }
-      }
     }
-    __threadfence();
-    __syncthreads();
-    if (tid == 0) __hip_atomic_fetch_add(done + phase, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-    // Not only for `ticket`: without a barrier here, what the first thread does at the end and at the start of a turn becomes one branch,
+    // Not only for the next task: without a barrier here, what the first thread does at the end and at the start of a turn becomes one branch,
     // and the other lanes of its wave go round without it.
+    __syncthreads();
+    if (!ahead && tid == 0) take_number(turn ^ 1);
     __syncthreads();
   }
 }
@@ -889,7 +1019,7 @@ __global__ __launch_bounds__(256) void score_team_prepare_kernel(ScoreArgs a, Te
   if (at < 64) ta.ctl[at] = at == kTeamAbsent && ta.apart ? 1 : 0;
   u32x4* lines = reinterpret_cast<u32x4*>(ta.lines);
   for (int64_t i = at; i < (int64_t)ta.line_pairs * ta.members * 8; i += all) lines[i] = u32x4{kTeamEmpty, kTeamEmpty, kTeamEmpty, kTeamEmpty};
-  for (int64_t i = at; i < (int64_t)ta.problems * 5; i += all) ta.done[i] = 0;
+  for (int64_t i = at; i < (int64_t)ta.problems * kTeamCounters; i += all) ta.done[i] = 0;
   const int p = blockIdx.y, lz = p / a.n_seqs, seq = p - lz * a.n_seqs;
   const int tok0 = a.cu_seqlens[seq], n = a.cu_seqlens[seq + 1] - tok0 - a.key_trim;
   const int block = blockIdx.x * 4 + (tid >> 6);
@@ -946,7 +1076,7 @@ int launch_team(const Plan& pl, const ScoreArgs& a, char* ws, hipStream_t stream
     constexpr int ML = decltype(ml)::value;
     if (!ta.apart) score_team_kernel<D, NT, K8, ML><<<grid, block, 0, stream>>>(args);
     if (hipError_t e = hipGetLastError()) return (int)e;
-    score_team_again_kernel<D, NT, K8, ML><<<dim3(kTeamMembers), block, 0, stream>>>(args);
+    score_team_again_kernel<D, NT, K8, ML><<<dim3(2 * kTeamMembers), dim3(256), 0, stream>>>(args);
     return (int)hipGetLastError();
   });
 }
