@@ -174,9 +174,10 @@ int codecomp_score_route(const codecomp_params* params, int32_t* route, int32_t*
 /* Host-only: *members = workgroups of the largest team where codecomp_score gives the TWO_PASSES requests of these parameters to teams
  * (all of them or none), else 0.  A team holds all keys of a request and takes its softmax rows in step: every logit is formed once, but
  * the members wait for one another, so the launch needs as many compute units (256 at most) to itself.  A device with fewer takes two
- * passes.  Where other work on the device (a call on another stream, say) keeps members from starting, the waits end after 0.1 ms, and
- * a kernel that waits for nobody does the work: the same bits, in a few times the time.  Programs that run calls beside other work set
- * CODECOMP_VARIANT_NO_TEAMS: such calls take two passes. */
+ * passes.  Where other work on the device keeps members from starting, a wait ends after 0.05 ms, whoever runs stops with its problem at
+ * the latest, and a kernel that waits for nobody does the work: the same bits.  Beside copies, or a kernel that holds compute units, such
+ * a call takes 1.3 to 2.1 times as long as by two passes, one of 0.1 ms up to 3.5 times; beside another call like it, or matrix products, it
+ * is faster than by two passes as it is alone.  Programs that run calls beside such work set CODECOMP_VARIANT_NO_TEAMS. */
 int codecomp_score_teams(const codecomp_params* params, int32_t* members);
 
 /* scores[l][h][j] = pooled_u[l][h][j] + lambda * prior[j], where u is the window attention mass

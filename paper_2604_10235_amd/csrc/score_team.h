@@ -8,7 +8,8 @@
 //
 // Waiting for one another needs all workgroups of the launch on the device at once, which no launch promises: other streams and
 // processes may hold compute units.  So every wait is bounded.  If a sum does not arrive in time, or a logit outruns its row's reference
-// (the row's largest logit among 16 of its keys) by 69 nats, a word in the workspace says so, and the launch behind this one
+// (the row's largest logit among 16 of its keys) by 69 nats, a word in the workspace says so (workgroups that see that a sum was missing
+// leave at their start or with their problem), and the launch behind this one
 // (score_team_again_kernel, which otherwise ends at once) does the same work, or that of the problems concerned, with the same
 // arithmetic, bit for bit, without any wait for a workgroup that might not run: it hands out its tasks in an order in which a task
 // only waits for tasks handed out before it.
@@ -46,12 +47,13 @@ struct TeamArgs {
   int problems, slots, most;   // problems; how many of them have a place for their sums at a time there; members of the largest team
   int pairs;                   // of row blocks in a problem
   int members, ring, line_pairs, steps;
-  int apart;                   // 1: score_team_again_kernel does it all
+  int apart;                   // 1: kTeamAbsent is set from the start, so that score_team_again_kernel does it all
   uint32_t step[kTeamSteps + 1];
   uint32_t entry[kTeamEntries][2];
 };
-// Longest wait for a sum, in 10 ns.  Members that run answer within some us; what this bounds is the time lost where some do not.
-constexpr int64_t kTeamWait = 10000;
+// Longest wait for a sum, in 10 ns.  Members that run answer within some us; what this bounds is the time lost where some do not.  A round of
+// the most rows takes 48 us: a call that starts beside the last round of another one still waits for its compute units.
+constexpr int64_t kTeamWait = 5000;
 
 // One member's part of one problem.
 struct TeamTask {
@@ -88,7 +90,7 @@ struct Team {
     float ref[3][32];            // references of the rows of three pairs
     uint16_t row[kTeamRows + 64];          // where the query rows begin, in pieces of 16 bytes
     uint32_t summed[NW], ready[NW];        // pairs whose row sums a wave has left; ... whose team sums, and next query rows
-    uint32_t quit;               // a wave has waited in vain
+    uint32_t quit, absent;       // a wave has waited in vain; control word kTeamAbsent, as seen last
     u32x4 k[NW][KP - DIRECT][64];          // the next problem's keys, 64 bytes of 16 keys a piece; last, the others are reached by offsets
   };
   static_assert(sizeof(Shared) <= 160 * 1024, "local memory");
@@ -242,6 +244,13 @@ __global__ __launch_bounds__(512, 2) void score_team_kernel(TeamKernelArgs args)
   }
   if (tid < 8) sh.summed[tid] = sh.ready[tid] = 0;
   if (tid == 0) sh.quit = 0;
+  // Where a wait has failed, the work so far counts for nothing, and who goes on only keeps the kernel behind from its own: workgroups that
+  // start then leave at once, the others when their problem is through.
+  auto look_for_absent = [&]() __attribute__((always_inline)) {
+    if (wave == 0)
+      asm volatile("s_mov_b32 m0, %0\n\ts_mov_b64 exec, 1\n\tglobal_load_lds_dword %1, %2 sc1\n\ts_mov_b64 exec, -1"
+                   ::"s"(lds_address(&sh.absent)), "v"(0), "s"(team_args()->t.ctl + kTeamAbsent) : "memory", "m0");
+  };
   for (int i = tid; i < ML * 32; i += 512) (&sh.poll[0][0])[i] = 0;
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
   keys = keys_of(cur);
@@ -251,6 +260,7 @@ __global__ __launch_bounds__(512, 2) void score_team_kernel(TeamKernelArgs args)
   fetch(row_at, 1, 1);
   row_at = sh.row[64 + row_in] * 16u + piece_at;
   for (int u = 0; u < UNITS; ++u) stage(u);
+  look_for_absent();
 
   u32x4 kf[NT][KS], qf[KS];
   f32x4 e[DB][NT], mass[NT];
@@ -277,6 +287,9 @@ __global__ __launch_bounds__(512, 2) void score_team_kernel(TeamKernelArgs args)
   };
   find_pad();
   asm volatile("s_waitcnt vmcnt(0)\n\ts_barrier" ::: "memory");
+  typedef volatile __attribute__((address_space(3))) uint32_t* word_t;
+  const word_t quit = (word_t)&sh.quit, absent = (word_t)&sh.absent;
+  if (__builtin_amdgcn_readfirstlane(*absent) != 0) return;
 #pragma unroll
   for (int t = 0; t < NT; ++t) take_tile(t);
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
@@ -385,9 +398,9 @@ __global__ __launch_bounds__(512, 2) void score_team_kernel(TeamKernelArgs args)
       while (any_missing()) {
         if (!patient || wall_clock64() - t0 > kTeamWait) {
           patient = false;
-          if (lane == 0) {
+          if (lane == 0 && *quit == 0) {               // one wave says so: stores to one word take their turns, 10 .. 20 ns each
             team_store(team_args()->t.ctl + kTeamAbsent, 1);
-            *(volatile __attribute__((address_space(3))) uint32_t*)&sh.quit = 1;
+            *quit = 1;
           }
           break;
         }
@@ -572,7 +585,7 @@ __global__ __launch_bounds__(512, 2) void score_team_kernel(TeamKernelArgs args)
   auto turn = [&]() __attribute__((always_inline)) {
     if (over) return;
     if (q == cur_start + pairs && cur.valid) {         // the next problem, or none: then only the waiting exponentials are left
-      if (__builtin_amdgcn_readfirstlane(*(volatile __attribute__((address_space(3))) uint32_t*)&sh.quit) != 0) {
+      if (__builtin_amdgcn_readfirstlane(*quit | *absent) != 0) {
         summed[wave] = ready[wave] = 0x7FFFFFFF;      // no wave waits for this one any more
         over = true;
         return;
@@ -594,6 +607,7 @@ __global__ __launch_bounds__(512, 2) void score_team_kernel(TeamKernelArgs args)
     }
     if (q == rows_at && more) {                        // the rows sent for are the next problem's
       more = nxt.valid != 0;
+      look_for_absent();                               // there when this pair's sums are, and looked at where the next problem begins
       if (more) rows = team_rows(team_args(), nxt);    // else: what is sent for, to keep the count, is not used
       fpair = 0;
       row_from = reinterpret_cast<const uint16_t (*)[32]>(&sh.row[0]);
@@ -1074,7 +1088,7 @@ int launch_team(const Plan& pl, const ScoreArgs& a, char* ws, hipStream_t stream
   const dim3 grid(ta.members), block(512);
   return with_members<K8>(s.most, [&](auto ml) {
     constexpr int ML = decltype(ml)::value;
-    if (!ta.apart) score_team_kernel<D, NT, K8, ML><<<grid, block, 0, stream>>>(args);
+    score_team_kernel<D, NT, K8, ML><<<grid, block, 0, stream>>>(args);
     if (hipError_t e = hipGetLastError()) return (int)e;
     score_team_again_kernel<D, NT, K8, ML><<<dim3(2 * kTeamMembers), dim3(256), 0, stream>>>(args);
     return (int)hipGetLastError();

@@ -189,6 +189,30 @@ def test_side_by_side():
             assert torch.equal(p.scores, x)
 
 
+# Beside copies, whose workgroups hold every compute unit in turn: members are missing more often than not.
+@pytest.mark.gpu
+@pytest.mark.parametrize("lens,layers", [([20011], 8), ([5000, 2000, 12345], 6)])
+def test_beside_copies(lens, layers):
+    import torch
+    p = Made(lens, (28, 4), 64, layers)
+    want = p.score()
+    x = torch.zeros(1 << 27, device="cuda")
+    y = torch.empty_like(x)
+    params, got = p.make(), [torch.empty_like(want) for _ in range(6)]
+    assert b.codecomp_score_teams(params) > 0
+    copies, calls = torch.cuda.Stream(), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(copies):
+        for _ in range(20):
+            y.copy_(x)
+    with torch.cuda.stream(calls):
+        for out in got:
+            b.codecomp_score(p.q, p.k, p.prior, params, out, p.ws)
+    torch.cuda.synchronize()
+    for out in got:
+        assert torch.equal(out.view(torch.int32), want.view(torch.int32))
+
+
 @pytest.mark.gpu
 def test_replayed_in_a_graph():
     import torch
