@@ -162,8 +162,9 @@ int codecomp_score_layout(const codecomp_params* params, int32_t* row_splits, in
                           int32_t* waves, uint32_t* wave_desc);
 
 /* Host-only: which kernels codecomp_score takes for these parameters: route[r] (array of n_seqs) per request, one of
- *   TWO_PASSES: more keys than a workgroup holds: row statistics, then attention mass (requests without a key for the softmax among
- *               them: nothing to do), or both in one pass by teams of workgroups: see codecomp_score_teams;
+ *   TWO_PASSES: more keys than a workgroup holds, or too few such short requests beside longer ones: row statistics, then attention mass
+ *               (requests without a key for the softmax among them: nothing to do), or both in one pass by teams of workgroups: see
+ *               codecomp_score_teams;
  *   ONE_PASS  : a workgroup holds all keys of the request, every logit is formed once; its softmax rows are cut into row_chunks
  *               chunks, of which a workgroup takes chunks_in_turn one after the other;
  *   FEW_ROWS  : a workgroup holds all logits of the request.
@@ -172,7 +173,7 @@ enum { CODECOMP_ROUTE_TWO_PASSES = 0, CODECOMP_ROUTE_ONE_PASS = 1, CODECOMP_ROUT
 int codecomp_score_route(const codecomp_params* params, int32_t* route, int32_t* row_chunks, int32_t* chunks_in_turn);
 
 /* Host-only: *members = workgroups of the largest team where codecomp_score gives the TWO_PASSES requests of these parameters to teams
- * (all of them or none), else 0.  A team holds all keys of a request and takes its softmax rows in step: every logit is formed once, but
+ * (all of them or none; a request of up to 512 keys is a team of one), else 0.  A team holds all keys of a request and takes its softmax rows in step: every logit is formed once, but
  * the members wait for one another, so the launch needs as many compute units (256 at most) to itself.  A device with fewer takes two
  * passes.  Where other work on the device keeps members from starting, a wait ends after 0.05 ms, whoever runs stops with its problem at
  * the latest, and a kernel that waits for nobody does the work: the same bits.  Beside copies, or a kernel that holds compute units, such

@@ -69,7 +69,7 @@ static bool rows_quicker(int blocks, int d, bool fp8, int64_t problems, int64_t 
   return rows < passes;
 }
 
-// Are the teams quicker than the two passes, for requests that are all beyond one workgroup?  Estimates in us, without what both need:
+// Are the teams quicker than the two passes, where none of the requests takes a route of its own?  Estimates in us, without what both need:
 // a round takes its start and a time per pair of row blocks, however few of the 256 workgroups are in it; the passes take a time per key
 // and pair, and one per key.  Measured, scores, 4 KV heads of 7 query heads, window 64 (448 rows), passes -> teams: 28 x 32K keys 873 ->
 // 689 us (8-bit keys 815 -> 660), 28 x 20011 581 -> 449, 4 x 20011 96 -> 85, 16 x 8192 150 -> 120, 4 x 8192 58 -> 49, sixteen of 8K ..
@@ -82,8 +82,10 @@ static bool teams_quicker(int rounds, int pairs, int most, bool fp8, float keys)
   return teams < passes;
 }
 
-// Rounds of teams for the requests beyond one workgroup: a request takes as many members as its keys need, all problems the same time
-// (they have the same rows), so a round is filled with teams, the largest first, and repeated while they last.
+// Rounds of teams for calls whose requests all take the two passes otherwise: a request takes as many members as its keys need (one up to
+// 512 keys), all problems the same time (they have the same rows), so a round is filled with teams, the largest first, and repeated while
+// they last.  Scores with teams of one among them, passes -> teams, 448 rows: 6 layers of 32768 and 500 keys 189 -> 165 us (8-bit keys 183 ->
+// 165), 28 layers of 5000 and eight times 500 310 -> 241 (266 -> 222).
 static void schedule_teams(const codecomp_params* p, const Plan& pl, int64_t room, TeamSchedule* ts) {
   constexpr int nt = kTeamTiles;
   ts->steps = 0;
@@ -93,7 +95,7 @@ static void schedule_teams(const codecomp_params* p, const Plan& pl, int64_t roo
   int64_t keys = 0;
   for (int r = 0; r < pl.n_seqs; ++r) {
     const int n = p->cu_seqlens_host[r + 1] - p->cu_seqlens_host[r] - pl.key_trim;
-    if (n <= pl.once_keys) return;
+    if (n <= 0) return;                                // nothing to do for it: left to the passes, which see to that
     keys += n;
     const int tiles = (n + 15) / 16, chunks = (tiles + 8 * nt - 1) / (8 * nt);
     // waves hold nt tiles or one less, the last wave of the last member nt: only a wave's tile nt - 1 may have places without a key

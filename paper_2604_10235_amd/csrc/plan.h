@@ -136,7 +136,7 @@ struct Plan {
   int once_rows, once_chunks;            // query rows of a chunk, chunks
   int once_group;            // chunks that one workgroup takes in turn
   int mass_parts;            // arrays of raw attention mass that add up: row splits, or chunks where every request takes one pass
-  TeamSchedule team;         // requests beyond one workgroup, in one pass
+  TeamSchedule team;         // all requests in one pass by teams of workgroups, where they would take two passes otherwise
   int grid_override;         // > 0: the caller fixed the number of workgroups of the score passes
   int lead_tiles;            // empty positions before each request's tiles in the sequence below: the cost of starting a segment
   int tiles_per_problem;     // sum over requests of (lead_tiles + ceil(N_r / kTileKeys)): positions of one (layer, head)

@@ -1,4 +1,4 @@
-"""Requests beyond one workgroup whose logits are formed once, by teams of workgroups that wait for one another: against the oracle and
+"""Requests whose logits are formed once by teams of workgroups that wait for one another: against the oracle and
 against the two passes, which calls with a given number of workgroups take; and that what happens when a team can not do its work
 (logits out of range, members kept from starting) gives the same bits."""
 import numpy as np
@@ -40,6 +40,38 @@ def test_which_calls_are_given_to_teams():
     # rows far apart: the kernel's table of them counts pieces of 16 bytes, in 16 bits (6 heads and 63 tokens away)
     far = dict(q_stride_head=136, q_stride_seq=64 * 8400, q_stride_layer=64 * 8400)
     assert members([32768], q_stride_tok=8 * 1038, **far) == 64 and members([32768], q_stride_tok=8 * 1039, **far) == 0
+
+
+# Short requests beside longer ones, too few to be taken apart: teams of one where a member is full enough (385 to 512 keys).
+ONE_MEMBER = [([32768, 500], 6), ([9000, 385, 512, 400], 12)]
+
+
+def test_which_short_requests_are_teams_of_one():
+    def members(lens, layers, **over):
+        cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+        p = b.make_params(n_layers=layers, n_q_heads=28, n_kv_heads=4, head_dim=128, window=64, pool_kernel=7, prior_weight=1.0, cu_seqlens_host=cu,
+                          cu_budgets_host=np.arange(len(lens) + 1, dtype=np.int32) * 64, cu_seqlens_dev=0x1000, cu_budgets_dev=0x2000, **over)
+        route = b.codecomp_score_route(p)[0]
+        return b.codecomp_score_teams(p), (route == b.ROUTE_TWO_PASSES).all()
+    for lens, layers in ONE_MEMBER:
+        for kv in (b.KV_BF16, b.KV_FP8_E4M3):
+            assert members(lens, layers, kv_dtype=kv) == (-(-max(lens) // 512), True)
+    assert members([9000, 384, 512, 400], 12) == (0, True)                 # 24 tiles: waves with fewer than three
+    assert members([9000, 576, 576], 12, score_variant=8) == (18, True) and members([9000, 576, 576, 64], 12, score_variant=8) == (0, True)      # one without a key
+    assert members([9000, 500] + [500] * 40, 12) == (0, False)             # enough of them: each in a workgroup by itself
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("lens,layers", ONE_MEMBER)
+@pytest.mark.parametrize("kv", ["bf16", "fp8"])
+def test_teams_of_one(lens, layers, kv):
+    w = problem(lens, layers=layers)
+    data = inputs(w, kv)
+    one, two = (scores(w, data, wgs).scores.cpu().numpy() for wgs in (0, 256))
+    np.testing.assert_allclose(one, two, rtol=TWO_WAYS, atol=1e-30)
+    q, k, _, prior = data
+    pu.assert_scores_close(one[-1:], orc.score_packed(q[-1:], k[-1:], prior, w.cu_seqlens(), pool_kernel=w.pool_kernel, prior_weight=w.prior_weight,
+                                                       k_format="fp8_e4m3" if kv == "fp8" else "bf16"))
 
 
 # A program whose calls share the device refuses teams, and nothing else: what one workgroup or a few rows take stays where it is.
