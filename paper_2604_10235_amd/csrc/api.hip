@@ -71,11 +71,16 @@ static bool rows_quicker(int blocks, int d, bool fp8, int64_t problems, int64_t 
 
 // Are the teams quicker than the two passes, where none of the requests takes a route of its own?  Estimates in us, without what both need:
 // a round takes its start and a time per pair of row blocks, however few of the 256 workgroups are in it; the passes take a time per key
-// and pair, and one per key.  Measured, scores, 4 KV heads of 7 query heads, window 64 (448 rows), passes -> teams: 28 x 32K keys 873 ->
-// 689 us (8-bit keys 815 -> 660), 28 x 20011 581 -> 449, 4 x 20011 96 -> 85, 16 x 8192 150 -> 120, 4 x 8192 58 -> 49, sixteen of 8K ..
-// 48K 549 -> 477; 896 rows: 28 x 32K 1648 -> 1187, 28 x 5000 276 -> 237, 8 x 64K 948 -> 761; 8 KV heads, 256 rows: 8 x 64K 639 -> 563,
-// 28 x 16K 558 -> 472; 224 rows: 4 x 32K 89 -> 73.  Not taken, passes / teams: 1 x 8192 32 / 42, 1 x 16384 42 / 42, 2 x 20000 700 rows
-// 86 / 88 (rounds that are nearly empty), 8 x 49152 398 / 398 (192 of 256 workgroups in a round), 28 x 50000 224 rows 803 / 848.
+// and pair, and one per key.  Measured, scores, both sides in turn in runs of 6 ms, 4 KV heads of 7 query heads, window 64 (448 rows),
+// passes -> teams: 28 x 32K keys 890 -> 686 us (8-bit keys 826 -> 681), 28 x 20011 552 -> 466, 4 x 20011 89 -> 83, 16 x 8192 135 -> 104, 4 x 8192
+// 53 -> 41, sixteen of 8K .. 48K 469 -> 409; 896 rows: 28 x 32K 1646 -> 1229, 28 x 5000 262 -> 229, 8 x 64K 954 -> 782; 8 KV heads, 256 rows: 8 x
+// 64K 644 -> 550, 28 x 16K 574 -> 446; 224 rows: 4 x 32K 82 -> 69.  At the line: 224 rows 8 x 24000 112 -> 105; 4 KV heads of 4, 256 rows: 1 x 32K 39
+// -> 34, 16 x 12000 124 -> 112.  Not taken, passes / teams: 1 x 8192 28 / 39, 1 x 16384 37 / 39, 2 x 20000 700 rows 79 / 82 (rounds that are nearly
+// empty), 8 x 49152 402 / 403 (192 of 256 workgroups in a round), 28 x 50000 224 rows 824 / 801.
+// The times are on the safe side: of 430 calls drawn over these ranges (1 to 32 layers, 1 to 16 requests, both key types) the rule takes 204,
+// none of which gains less than 3 %, and leaves 84 that would gain more than 5, most of them of few rows or with 8-bit keys.  That pays for
+// what it leaves out: places are emptied at 1.4 us a MB (up to 8 MB where lengths differ), 8-bit keys always take the kernel for 128 members
+// (1.30 us a pair), and in calls one by one on an idle device, its clocks down, teams lose 3 to 7 % more than passes (8 x 24000 112 / 113).
 static bool teams_quicker(int rounds, int pairs, int most, bool fp8, float keys) {
   const float teams = 4.0f + (float)rounds * (5.1f + (most <= 64 ? 1.27f : 1.35f) * (float)pairs);
   const float passes = keys / (256.0f * 512.0f) * (4.5f + 1.85f * (float)pairs) * (fp8 ? 0.93f : 1.0f);
@@ -344,7 +349,7 @@ int make_plan(const codecomp_params* p, Plan* pl) {
   pl->ws_bytes = off;
   pl->team.steps = 0;
   if (own_rules && !(pl->variant & CODECOMP_VARIANT_NO_TEAMS) && !once && !pl->rows_at_once && pl->R >= 192 && pl->R <= kTeamRows && pl->d == 128 &&
-      (once_short + once_long) == 0 && LH64 * pl->n_seqs <= 65535 &&
+      LH64 * pl->n_seqs <= 65535 &&
       (int64_t)max_n * pl->kv_st * (pl->kv_fp8 ? 1 : 2) <= 0xFFFFFFFFll - 4096 &&
       ((int64_t)(pl->G - 1) * pl->q_sh + (int64_t)(pl->W - 1) * pl->q_st) / 8 <= 0xFFFF)
     schedule_teams(p, *pl, (int64_t)(pl->off_lse - pl->off_stats), &pl->team);

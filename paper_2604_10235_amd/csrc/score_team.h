@@ -21,8 +21,8 @@
 // 64 of keys, which leaves 4 tiles of 16 keys to a wave and one workgroup to a compute unit.  A round costs 5 us beyond its pairs (the two
 // passes: 4.5): half of it while the next problem's keys are on their way to LDS, the rest where all waves take them up at once.
 // Workgroups wait for counts in LDS, not at barriers: with a barrier in each block the slowest wave of every block was waited for.
-// Measured, scores of 28 layers, 4 KV heads of 7 query heads, window 64, 32K keys: two passes 873 us, teams 689; 1 layer 54 and 44; window
-// 128 1648 and 1187; 8-bit keys 815 and 660.  Error against 64 bits 7e-8 (2-norm), by two passes 3.4e-7.
+// Measured, scores of 28 layers, 4 KV heads of 7 query heads, window 64, 32K keys: two passes 890 us, teams 686; window 128 1646 and 1229;
+// 8-bit keys 826 and 681.  Error against 64 bits 7e-8 (2-norm), by two passes 3.4e-7.
 #pragma once
 #include "score_once.h"
 #include "team_tasks.h"
@@ -73,6 +73,7 @@ __device__ __forceinline__ TeamRows team_rows(Args x, const TeamTask& t) {
 
 template <int D, int NT, bool K8, int ML>
 struct Team {
+  static_assert(D == 128, "what lies in LDS, and the order of MFMAs and exponentials, are laid out for head_dim 128");
   static constexpr int KS = D / 32;                    // MFMA k-steps
   static constexpr int NW = 8;
   static constexpr int DB = 6;                         // blocks of 16 rows whose exponentials are kept: what the registers hold
@@ -80,7 +81,7 @@ struct Team {
   static constexpr int PER = KS / (K8 ? 2 : 1);        // 16-byte pieces per lane of a tile of keys
   static constexpr int KP = NT * PER;                  // ... of a wave's keys
   // Pieces of the next problem's keys that find no room in LDS beside the rest.  They are loaded when the problem begins.
-  static constexpr int DIRECT = !K8 && D == 128 ? 2 : 0;
+  static constexpr int DIRECT = K8 ? 0 : 2;
   static_assert(kTeamRing >= DB + 2, "a place is used again only when all have read it");
   struct Shared {
     u32x4 q[3][2][KS][64];       // query rows of three pairs of blocks, fragment order
@@ -206,24 +207,23 @@ __global__ __launch_bounds__(512, 2) void score_team_kernel(TeamKernelArgs args)
     return Keys{x->a.k + ((int64_t)layer * x->a.kv_sl + (int64_t)head * x->a.kv_sh + (int64_t)t.tok0 * x->a.kv_st) * ESZ, team_share(t, wave).key0, t.n - 1};
   };
   const uint32_t key_bytes = (uint32_t)args.a.kv_st * ESZ;
-  // Pieces are sent for two by two (one by one where a tile has one): they share the lane's offset.
-  constexpr int UNIT = PER > 1 ? 2 : 1, UNITS = STAGED / UNIT;
+  // Pieces are sent for two by two: they share the lane's offset.
+  constexpr int UNIT = 2, UNITS = STAGED / UNIT;
   auto key_at = [&](int i) __attribute__((always_inline)) {            // of piece i, less what is the same in all lanes
     const uint32_t key = (uint32_t)min(keys.key0 + i / PER * 16 + l16, keys.last);
     return key * key_bytes + (uint32_t)(grp * 16);
   };
   auto stage = [&](int u) __attribute__((always_inline)) {             // unit u of this wave's keys
     // A unit is a cache line of each key, so that the pairs ask alike of memory (with a half of both lines at a time, every second pair
-    // asked for everything: 8 x 64K keys, 256 rows 544 us, now 526); but of a tile that is not all in LDS the first half of both lines is
+    // asked for everything: 8 x 64K keys, 256 rows 562 us, now 537); but of a tile that is not all in LDS the first half of both lines is
     // there, and what is loaded when the problem begins is found in the cache.
     const int i = u * UNIT;
     const bool parted = PER == 4 && STAGED % PER != 0 && i >= STAGED / PER * PER;
     const int apart = parted ? 128 : 64;
-    const unsigned char* from = keys.from + (PER == 4 ? (u & 1) * (parted ? 64 : 128) : UNIT == 2 ? 0 : (i & (PER - 1)) * 64);
+    const unsigned char* from = keys.from + (PER == 4 ? (u & 1) * (parted ? 64 : 128) : 0);
     const uint32_t at = key_at(i), to = k_to + (uint32_t)i * 1024u;
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(to), "v"(at), "s"(from) : "memory", "m0");
-    if constexpr (UNIT == 2)
-      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(to + 1024u), "v"(at), "s"(from + apart) : "memory", "m0");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(to + 1024u), "v"(at), "s"(from + apart) : "memory", "m0");
   };
   const uint32_t q_to = lds_address(&sh.q[0][0][0][0]) + (uint32_t)wave * 1024u;
   const uint32_t ref_to = lds_address(&sh.ref[0][0]);
@@ -234,8 +234,7 @@ __global__ __launch_bounds__(512, 2) void score_team_kernel(TeamKernelArgs args)
     if (wave == 7)                                     // first, so that the wait below counts no more for this wave than for the others
       asm volatile("s_mov_b32 m0, %0\n\ts_bfm_b64 exec, 32, 0\n\tglobal_load_lds_dword %1, %2\n\ts_mov_b64 exec, -1"
                    ::"s"(ref_to + slot * 128u), "v"(lane * 4), "s"(rows.ref + pair * 32) : "memory", "m0");
-    if (D == 128 || wave < 2 * KS)
-      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(q_to + slot * (2 * KS * 1024u)), "v"(row_at), "s"(rows.q) : "memory", "m0");
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(q_to + slot * (2 * KS * 1024u)), "v"(row_at), "s"(rows.q) : "memory", "m0");
   };
 
   for (int r = tid; r < pairs * 32; r += 512) {        // rows past the end read the first one
@@ -546,7 +545,7 @@ __global__ __launch_bounds__(512, 2) void score_team_kernel(TeamKernelArgs args)
             continue;
           }
 #pragma unroll
-          for (int x = 0; x < (KS == 2 ? 4 : m == 1 ? 2 : 1); ++x) {
+          for (int x = 0; x < (m == 1 ? 2 : 1); ++x) {
             __builtin_amdgcn_sched_group_barrier(0x002, 1, 0);
             __builtin_amdgcn_sched_group_barrier(0x400, 1, 0);
             if (m > 1 || x > 0) __builtin_amdgcn_sched_group_barrier(0x002, 1, 0);
