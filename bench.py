@@ -69,23 +69,33 @@ def two_pass_share(w, params, binding) -> float:
     return sum(n for n, r in zip(w.seqlens, route) if r == binding.ROUTE_TWO_PASSES) / w.total_tokens
 
 
+def formed_twice(w, params, binding, stage_ms: dict) -> float:
+    """Share of the logits that this device formed twice.  Teams of workgroups need a compute unit for each member; where they do not fit
+    the library takes two passes.  With teams the row statistics launch nothing: their time is that between two events."""
+    teams = binding.codecomp_score_teams(params) > 0 and stage_ms["score_row_stats"] < 0.1 * stage_ms["score_mass"]
+    return 0.0 if teams else two_pass_share(w, params, binding)
+
+
 def binding_roofline(flops_pass: float, logits_pass: float, twice: float, ab: dict, k_bytes: int, ms_per_step: float, peaks):
-    """Floors of one step of the two-pass design (the logits are formed twice, or the share `twice` of them: row
-    normalisers, then column sums) at the published peaks and, when measured, at what this GPU sustained in this run.
-    hbm_one_read is the method's own traffic (K once); hbm_two_reads adds K's second read.  issue_mix is the measured
-    instruction mix of the passes without memory (MFMA and softmax VALU work compete for issue slots).  frac = largest
-    floor / time per step."""
+    """Floors of one step at the published peaks and, when measured, at what this GPU sustained in this run.  The share `twice` of
+    the logits is formed twice (row normalisers, then column sums), the others once; the names of the floors say which: one_pass,
+    two_passes, or mixed_passes where it is a part of them.  hbm_one_read is the method's own traffic (K once); hbm_two_reads (where
+    there are any) adds K's second read.  issue_mix is the measured instruction mix of the passes without memory (MFMA and softmax VALU
+    work compete for issue slots).  frac = largest floor / time per step."""
+    passes = "one_pass" if twice == 0.0 else "two_passes" if twice == 1.0 else "mixed_passes"
+
     def floors(mfma_tflops, exp_per_s, hbm_gbs, mix_logits_per_s=None):
-        f = {"mfma_two_passes": (1 + twice) * flops_pass / (mfma_tflops * 1e12) * 1e3,
-             "exp_two_passes": (1 + twice) * logits_pass / exp_per_s * 1e3,
-             "hbm_one_read": ab["total"] / (hbm_gbs * 1e9) * 1e3,
-             "hbm_two_reads": (ab["total"] + twice * k_bytes) / (hbm_gbs * 1e9) * 1e3}
+        f = {f"mfma_{passes}": (1 + twice) * flops_pass / (mfma_tflops * 1e12) * 1e3,
+             f"exp_{passes}": (1 + twice) * logits_pass / exp_per_s * 1e3,
+             "hbm_one_read": ab["total"] / (hbm_gbs * 1e9) * 1e3}
+        if twice > 0.0:
+            f["hbm_two_reads"] = (ab["total"] + twice * k_bytes) / (hbm_gbs * 1e9) * 1e3
         if mix_logits_per_s:
-            f["issue_mix_two_passes"] = (1 + twice) * logits_pass / mix_logits_per_s * 1e3
+            f[f"issue_mix_{passes}"] = (1 + twice) * logits_pass / mix_logits_per_s * 1e3
         return f
 
     def pack(f):
-        binding = max((k for k in f if k != "hbm_one_read"), key=lambda k: f[k])
+        binding = max((k for k in f if k != "hbm_one_read" or "hbm_two_reads" not in f), key=lambda k: f[k])
         return {"floors_ms": {k: round(v, 4) for k, v in f.items()}, "binding": binding,
                 "frac": round(f[binding] / ms_per_step, 4)}
 
@@ -268,7 +278,7 @@ def main() -> int:
 
     # dominant stage: one of the two MFMA passes; its flops = 2 * R * sum(N_r) * d per (layer, KV head), for the row statistics
     # over the requests whose logits are formed twice
-    twice = 0.0 if binding.codecomp_score_teams(prob.params) else two_pass_share(w, prob.params, binding)
+    twice = formed_twice(w, prob.params, binding, stage_ms)
     dom = max(("score_row_stats", "score_mass"), key=lambda n: stage_ms[n]) if twice > 0.0 else "score_mass"
     flops = 2.0 * w.group * w.window * T * w.head_dim * w.n_kv_heads * L
     flops_dom = flops if dom == "score_mass" else flops * twice
