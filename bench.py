@@ -71,8 +71,9 @@ def two_pass_share(w, params, binding) -> float:
 
 def formed_twice(w, params, binding, stage_ms: dict) -> float:
     """Share of the logits that this device formed twice.  Teams of workgroups need a compute unit for each member; where they do not fit
-    the library takes two passes.  With teams the row statistics launch nothing: their time is that between two events."""
-    teams = binding.codecomp_score_teams(params) > 0 and stage_ms["score_row_stats"] < 0.1 * stage_ms["score_mass"]
+    the library takes two passes.  With teams the row statistics launch nothing: their time is that between two events (up to an eighth of
+    the mass kernel's under a profiler), else they take as long as the masses."""
+    teams = binding.codecomp_score_teams(params) > 0 and stage_ms["score_row_stats"] < 0.5 * stage_ms["score_mass"]
     return 0.0 if teams else two_pass_share(w, params, binding)
 
 
