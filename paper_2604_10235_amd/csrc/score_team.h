@@ -33,8 +33,9 @@ constexpr uint32_t kTeamEmpty = 0xFFFFFFFFu;       // a sum that is not there ye
 constexpr int kTeamRing = 16;                      // pairs of row blocks whose sums have a place
 
 enum { kTeamAbsent = 0, kTeamRange = 1, kTeamTicket = 32 };        // control words: a wait has failed; rows of some problems are out of range; tasks handed out
-constexpr uint32_t kTeamOut = 1, kTeamRedo = 2;    // a problem has rows out of range, as the team kernel found; as found again
-// Counters of a problem in score_team_again_kernel: tasks of a phase that are done, weights that are there; last, what the two above say.
+constexpr uint32_t kTeamOut = 1;                   // flag of a problem: the team kernel found rows out of range
+constexpr uint32_t kTeamFine = 1, kTeamRedo = 2;   // its weights are there; it has rows out of range (found again)
+// Words of a problem in score_team_again_kernel: tasks of a phase that are done, what is there; last, kTeamOut.
 enum { kTeamSumsDone, kTeamWeighed, kTeamLargestDone, kTeamReferred, kTeamSumsAgainDone, kTeamWeighedAgain, kTeamMassesDone, kTeamFlags };
 
 __device__ __forceinline__ uint32_t team_load(const uint32_t* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
@@ -679,11 +680,11 @@ __global__ __launch_bounds__(512, 2) void score_team_kernel(TeamKernelArgs args)
 // Bound by instruction issue as the passes are, in twice the work of the team kernel: every logit is formed for the row sums and again
 // for the masses.  The query rows come through LDS, four blocks of 16 at a time, the next four on their way in registers; the MFMAs of
 // a block stand beside the exponentials of the one before.  A task is taken by half members, so that a compute unit holds two workgroups
-// of four waves, of which one works while the other waits for keys (2 us), the next number (2) and counters: 8 us of a task's 22, in which its
-// loop runs 14 (28 x 32K keys, 448 rows).  Measured, scores, by two passes / by teams / all of it by this kernel: 28 x 32K keys, 448 rows 1009
-// / 663 / 1129 us (with eight waves, rows from memory to registers, a fence and the totals of all members in each task 6239); 896 rows 1659 /
-// 1161 / 2026; 8 x 64K, 256 rows 661 / 534 / 1005; sixteen requests of 8K .. 45K 473 / 373 / 689; 4 x 20011 95 / 89 / 139.  Teams and then a row
-// of every problem out of range: 28 x 32K 2542 us (9409), 4 x 20011 321 (881).  Three workgroups a compute unit spill: 1790 instead of 1129.
+// of four waves, of which one works while the other waits for keys (2 us), the next number (2) and counters: a third of a task's 22 us, in
+// which its loop runs 14 (28 x 32K keys, 448 rows).  Measured, scores, by two passes / by teams / all of it by this kernel: 28 x 32K keys, 448
+// rows 1009 / 663 / 1104 us (with eight waves, rows from memory to registers, a fence and the totals of all members in each task 6239); 896 rows
+// 1659 / 1161 / 1990; 8 x 64K, 256 rows 661 / 534 / 957; sixteen requests of 8K .. 45K 473 / 373 / 686; 4 x 20011 95 / 89 / 140.  Teams and then a
+// row of every problem out of range: 28 x 32K 2390 us (9409), 4 x 20011 304 (881).  Three workgroups a compute unit spill: 1790.
 template <int D, int NT, bool K8, int ML>
 __global__ __launch_bounds__(256, 2) void score_team_again_kernel(TeamKernelArgs args) {
   constexpr int KS = D / 32, ESZ = K8 ? 1 : 2, PL = ML / 8, kListed = 1024, NW = 4, kAhead = NW;
@@ -699,7 +700,7 @@ __global__ __launch_bounds__(256, 2) void score_team_again_kernel(TeamKernelArgs
     float weight[32 + kTeamRows], ref[32 + kTeamRows];
     uint16_t list[kListed];
     struct { TeamTaskAt at; int problem, halves; } task[2];            // the task at hand and the next one
-    int listed, out, last;
+    int listed, out, last, redo;
   };
   __shared__ __attribute__((aligned(16))) Shared sh;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -746,15 +747,15 @@ __global__ __launch_bounds__(256, 2) void score_team_again_kernel(TeamKernelArgs
     __syncthreads();
   };
   // the next number that stands for half a member that there is
-  auto take_number = [&](int to) {
-    for (;;) {
-      const int x = (int)__hip_atomic_fetch_add(ta.ctl + kTeamTicket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  auto next_number = [&]() { return (int)__hip_atomic_fetch_add(ta.ctl + kTeamTicket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+  auto take_number = [&](int to, int x) {
+    for (;; x = next_number()) {
       const TeamTaskAt t = tasks.at(x);
       const int problem = t.at < 0 || whole ? t.at : (int)sh.list[t.at], halves = t.at < 0 ? 0 : halves_of(problem);
       if (t.at < 0 || t.first < halves) { sh.task[to] = {t, problem, halves}; return; }
     }
   };
-  if (tid == 0) take_number(0);
+  if (tid == 0) take_number(0, next_number());
   __syncthreads();
   for (int turn = 0;; turn ^= 1) {
     auto uniform = [](int x) __attribute__((always_inline)) { return __builtin_amdgcn_readfirstlane(x); };
@@ -763,7 +764,6 @@ __global__ __launch_bounds__(256, 2) void score_team_again_kernel(TeamKernelArgs
     const int phase = uniform(sh.task[turn].at.phase), first = uniform(sh.task[turn].at.first), problem = uniform(sh.task[turn].problem);
     const int halves = uniform(sh.task[turn].halves), chunks = halves >> 1, last = min(uniform(sh.task[turn].at.last), halves);
     uint32_t* const done = ta.done + (int64_t)at * kTeamCounters;
-    uint32_t* const flags = ta.done + (int64_t)problem * kTeamCounters + kTeamFlags;
     const int seq = problem / a.LH, lz = problem - seq * a.LH;
     const int layer = divide(lz, a.Hkv, a.inv_heads), head = lz - layer * a.Hkv;
     uint32_t* const lines = ta.lines + (int64_t)(at % ta.slots) * pairs * most * 32;               // [pair][half member][32], weights in the first one's place
@@ -801,9 +801,11 @@ __global__ __launch_bounds__(256, 2) void score_team_again_kernel(TeamKernelArgs
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) sh.q[buf][wave][ks][lane] = st[ks];
       };
+      int number = 0;
+      if (tid == 0) number = next_number();            // ahead of the loads: who waits for it does not wait for them
       TeamShare next = fetch_keys(first);
       fetch_rows(0);
-      if (tid == 0) take_number(turn ^ 1);
+      if (tid == 0) take_number(turn ^ 1, number);
       ahead = true;
       ready();
       if constexpr (KIND != kTeamLargest)
@@ -974,42 +976,50 @@ __global__ __launch_bounds__(256, 2) void score_team_again_kernel(TeamKernelArgs
       __syncthreads();
       return __builtin_amdgcn_readfirstlane(sh.last) != 0;
     };
-    auto far_out = [&]() { return (__builtin_amdgcn_readfirstlane((int)team_load(flags)) & (int)kTeamRedo) != 0; };
+    // Has the problem rows out of range?  Asked once in a task: `redo` is written again only behind the barriers at its end.
+    auto far_out = [&]() {
+      if (!whole) return true;
+      if (tid == 0) {
+        uint32_t word = team_load(done + kTeamWeighed);
+        while (word == 0) { __builtin_amdgcn_s_sleep(2); word = team_load(done + kTeamWeighed); }
+        sh.redo = word == kTeamRedo;
+      }
+      asm volatile("" ::: "memory");
+      __syncthreads();
+      return __builtin_amdgcn_readfirstlane(sh.redo) != 0;
+    };
 
     // the place of a problem's sums is free when the problem that had it has its masses
     auto place = [&]() { if (at >= ta.slots) await(done - (int64_t)ta.slots * kTeamCounters + kTeamMassesDone, (uint32_t)tasks.tasks_of(halves_of(problem_at(at - ta.slots)), kTeamMasses)); };
-    auto leave_word = [&](uint32_t* word) { if (tid == 0) team_store(word, 1); };
+    auto leave_word = [&](uint32_t* word, uint32_t what) { if (tid == 0) team_store(word, what); };
 
     if (phase == kTeamSums) {
       pass(std::integral_constant<int, kTeamSums>{}, place);
       if (count(done + kTeamSumsDone, (uint32_t)tasks.tasks_of(halves, phase))) {
-        const bool redo = weigh();
-        if (tid == 0 && redo) {
-          __hip_atomic_fetch_or(flags, kTeamRedo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          stored();
-        }
-        leave_word(done + kTeamWeighed);
+        leave_word(done + kTeamWeighed, weigh() ? kTeamRedo : kTeamFine);
       }
     } else if (phase == kTeamMasses) {
       pass(std::integral_constant<int, kTeamMasses>{}, [&]() {
-        if (whole) await(done + kTeamWeighed, 1);
-        if (!whole || far_out()) await(done + kTeamWeighedAgain, 1);
+        if (far_out()) await(done + kTeamWeighedAgain, 1);
       });
-      count(done + kTeamMassesDone, 0);
+      if (at + ta.slots < problems) {                  // somebody waits for the place
+        stored();
+        __syncthreads();
+        if (tid == 0) __hip_atomic_fetch_add(done + kTeamMassesDone, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
     } else {
-      if (whole) await(done + kTeamWeighed, 1);
-      if (!whole || far_out()) {
+      if (far_out()) {
         if (phase == kTeamLargest) {
           pass(std::integral_constant<int, kTeamLargest>{}, [&]() { if (!whole) place(); });
           if (count(done + kTeamLargestDone, (uint32_t)tasks.tasks_of(halves, phase))) {
             refer();
-            leave_word(done + kTeamReferred);
+            leave_word(done + kTeamReferred, 1);
           }
         } else {
           pass(std::integral_constant<int, kTeamSumsAgain>{}, [&]() { await(done + kTeamReferred, 1); });
           if (count(done + kTeamSumsAgainDone, (uint32_t)tasks.tasks_of(halves, phase))) {
             weigh();
-            leave_word(done + kTeamWeighedAgain);
+            leave_word(done + kTeamWeighedAgain, 1);
           }
         }
       }
@@ -1017,7 +1027,7 @@ __global__ __launch_bounds__(256, 2) void score_team_again_kernel(TeamKernelArgs
     // Not only for the next task: without a barrier here, what the first thread does at the end and at the start of a turn becomes one branch,
     // and the other lanes of its wave go round without it.
     __syncthreads();
-    if (!ahead && tid == 0) take_number(turn ^ 1);
+    if (!ahead && tid == 0) take_number(turn ^ 1, next_number());
     __syncthreads();
   }
 }
