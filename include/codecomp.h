@@ -177,7 +177,7 @@ int codecomp_score_route(const codecomp_params* params, int32_t* route, int32_t*
  * the members wait for one another, so the launch needs as many compute units (256 at most) to itself.  A device with fewer takes two
  * passes.  Where other work on the device keeps members from starting, a wait ends after 0.05 ms, whoever runs stops with its problem at
  * the latest, and a kernel that waits for nobody does the work: the same bits.  Beside copies, or a kernel that holds compute units, such
- * a call takes 1.3 to 2.1 times as long as by two passes, one of 0.1 ms up to 3.5 times; beside another call like it, or matrix products, it
+ * a call takes 1.2 to 2.1 times as long as by two passes, one of 0.1 ms up to 3.7 times; beside another call like it, or matrix products, it
  * is faster than by two passes as it is alone.  Programs that run calls beside such work set CODECOMP_VARIANT_NO_TEAMS. */
 int codecomp_score_teams(const codecomp_params* params, int32_t* members);
 
